@@ -153,8 +153,9 @@ h3d_status h3d_conv3d_bwd_filter_static(void* handle, const h3d_tensor* x, const
  *   backward-data: input plane d-1 receives a term from output plane d/2, so dy (and y, when act is not NONE)
  *     need their UPPER halo plane, never the lower one.                                  H3D_EHALO otherwise.
  * Workspace: h3d_conv3d_s2_workspace_bytes(handle, op, x, y) with x / y the input-side / output-side descriptors
- * for every op; 256-byte aligned.  The call rewrites the problem as a stride-1 convolution over the eight parity
- * sub-lattices of x and runs the stride-1 kernels; the workspace holds the rearranged tensors. */
+ * for every op; 256-byte aligned.  bf16 tensors have matrix-core kernels of their own (the workspace holds the packed
+ * filter or the partial sums); fp32 tensors, and bf16 samples beyond 32-bit byte offsets, are rewritten as a stride-1
+ * convolution over the eight parity sub-lattices of x (the workspace then holds the rearranged tensors). */
 size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y);
 h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y,
                              int act, float alpha, void* ws, size_t ws_bytes, void* stream);

@@ -5,11 +5,11 @@
 // sub-lattices of x.  With x'[(par,ci)][q] = x[ci][2q+par] (par = (pd,ph,pw) in {0,1}^3), per axis
 //     k = 0 reads parity 1 at q = p-1,   k = 1 reads parity 0 at q = p,   k = 2 reads parity 1 at q = p,
 // so y = W' (*) x' with a stride-1 3x3x3 filter W' over 8 Cin channels whose taps at shift +1 (and the
-// parity/shift pairs that no k maps to) are zero.  The stride-1 kernels of this library (matrix cores for
-// bf16) then run all three passes; the zero padding of the stride-1 call at q = -1 is exactly the zero
-// padding of x at index -1.  The price is that 27 of the 216 (parity, tap) products per input channel are
-// non-zero; the gain is the matrix-core kernels instead of a scalar gather for a layer that is a small
-// part of the network's work.
+// parity/shift pairs that no k maps to) are zero.  The stride-1 kernels of this library then run all three
+// passes; the zero padding of the stride-1 call at q = -1 is exactly the zero padding of x at index -1.  The
+// price is that 27 of the 216 (parity, tap) products per input channel are non-zero.  This is the route of
+// fp32 tensors and of bf16 samples beyond 32-bit offsets; other bf16 tensors go to conv_s2_mfma.hip
+// (64 -> 128 channels on 64^3, three passes: 111 us there, 818 us this way).
 //
 // Small element-wise kernels here: the parity split of x, its inverse for dx, the masked copy of dy into
 // a slab with both halo planes, the filter expansion and the extraction of dw from dW'.
@@ -18,6 +18,15 @@
 #include "common.h"
 
 namespace h3d {
+
+// conv_s2_mfma.hip: bf16 tensors whose samples 32-bit byte offsets reach
+bool s2_mfma_supported(const h3d_tensor* x, const h3d_tensor* y);
+bool s2_mask_fits(const h3d_tensor* m);
+size_t s2_mfma_ws_bytes(int op, const h3d_tensor* x, const h3d_tensor* y);
+h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, float slope, void* ws, hipStream_t s);
+h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor* y, const void* w, h3d_tensor* dx, float slope, void* ws, hipStream_t s);
+h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tensor* dy, const h3d_tensor* y, float* dw, float* db, float slope,
+                              void* ws, hipStream_t s);
 
 static constexpr int S2_THREADS = 256;
 
@@ -181,8 +190,7 @@ static void launch_expand(const void* w, void* we, int cin, int cout, hipStream_
 
 using namespace h3d;
 
-extern "C" size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y) {
-  if (!handle || !x || !y || x->c < 0 || y->c < 0) return 0;
+static size_t s2_general_ws_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y) {
   h3d_tensor xc = *x, yc = *y;
   xc.data = yc.data = nullptr;
   const S2Plan p = s2_plan(&xc, &yc);
@@ -198,6 +206,18 @@ extern "C" size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_
   }
 }
 
+extern "C" size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y) {
+  if (!handle || !x || !y || x->c < 0 || y->c < 0) return 0;
+  if (op != H3D_OP_FWD && op != H3D_OP_BWD_DATA && op != H3D_OP_BWD_FILTER) return 0;
+  return s2_mfma_supported(x, y) ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
+}
+
+// which route a backward call takes, and the workspace it needs there
+static bool s2_direct(const h3d_tensor* x, const h3d_tensor* dy, const h3d_tensor* y) { return s2_mfma_supported(x, dy) && (!y || s2_mask_fits(y)); }
+static size_t s2_need(void* handle, bool direct, int op, const h3d_tensor* x, const h3d_tensor* y) {
+  return direct ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
+}
+
 extern "C" h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, int act,
                                         float alpha, void* ws, size_t ws_bytes, void* stream) {
   if (!handle) return H3D_EINVAL;
@@ -207,6 +227,7 @@ extern "C" h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const
   if (y->d > 0 && x->d_offset > 0 && x->halo_lo < 1) return fail(handle, H3D_EHALO, "conv3d_s2_fwd: x must store its lower halo plane");
   if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_FWD, x, y)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_fwd: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_fwd: workspace must be 256-byte aligned");
+  if (s2_mfma_supported(x, y)) return s2_mfma_fwd(handle, x, w, bias, y, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(x, y);
   char* base = (char*)ws;
   p.xs.data = base;
@@ -234,8 +255,10 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_data(void* handle, const h3d_tensor* dy,
     if (!same_shard(y, dy) || y->c != dy->c) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_data: y and dy shapes differ");
     if (upper && y->halo_hi < 1) return fail(handle, H3D_EHALO, "conv3d_s2_bwd_data: y must store its upper halo plane");
   }
-  if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_DATA, dx, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_data: workspace too small");
+  const bool direct = s2_direct(dx, dy, y);
+  if (!ws || ws_bytes < s2_need(handle, direct, H3D_OP_BWD_DATA, dx, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_data: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_data: workspace must be 256-byte aligned");
+  if (direct) return s2_mfma_bwd_data(handle, dy, y, w, dx, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(dx, dy);
   char* base = (char*)ws;
   p.gs.data = base;
@@ -279,8 +302,10 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x
     H3D_TRY(check_tensor_packed(handle, y, "y"));
     if (!same_shard(y, dy) || y->c != dy->c) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_filter: y and dy shapes differ");
   }
-  if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_FILTER, x, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_filter: workspace too small");
+  const bool direct = s2_direct(x, dy, y);
+  if (!ws || ws_bytes < s2_need(handle, direct, H3D_OP_BWD_FILTER, x, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_filter: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_filter: workspace must be 256-byte aligned");
+  if (direct) return s2_mfma_bwd_filter(handle, x, dy, y, dw, db, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(x, dy);
   char* base = (char*)ws;
   p.xs.data = base;

@@ -1,0 +1,806 @@
+// Stride-2 3x3x3 convolution of bf16 tensors on the matrix cores, all three passes, straight from the caller's tensors
+// (y[p] = sum_k w[k] x~[2p+k-1]).  Per axis an even fine position 2c meets tap k = 1 of coarse position c, an odd one 2c+1
+// taps k = 2 of c and k = 0 of c+1, so 27 of the 8 x 27 (parity, shift) products exist.  The rewriting as a stride-1
+// convolution over the eight parity sub-lattices (conv_s2.hip, still the route of fp32 tensors) executes all 216 of them and
+// moves both tensors through memory three times; these kernels execute the 27.
+//
+// 64 -> 128 channels on 64^3 (14.5 GFlop and 42 MB a pass: 6 us of matrix cores, 6 us of memory), all three passes of a masked
+// layer: 818 us by the rewriting, 111 us here (kernels 32 forward, 35 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
+// At that size what bounds them is the serial chain of a workgroup (fetch a tile, transpose it into LDS, multiply): there are
+// one to two workgroups per CU, and every one lives for two to eight stages.
+#include <algorithm>
+
+#include "common.h"
+
+namespace h3d {
+
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+constexpr int S2_OOB = (int)0x80000000;   // byte offset beyond every buffer: such a lane reads zeros, its store is dropped
+
+struct S2Args {
+  Geo x, y, m;                      // fine side, coarse side (y or dy), saved output (mask)
+  int cin, cout;
+  int nchunk;                       // 16-channel chunks of the contraction (forward: of cin, padded to 2; backward-data: of cout)
+  int tiles_w, tiles_h, ntiles;
+  float slope;
+  int vec;                          // result rows are 4-byte aligned pairs
+  // backward-filter
+  int segs, bands, nstrips, strips_per_chunk, nchunks, cogroups, cigroups;
+};
+
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t s2_rsrc(const void* base, uint32_t bytes) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
+  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
+}
+
+// 8 elements of a row of `w` from column c >= 0 on; `off` = element offset of the ROW in the sample, `span` = elements of the
+// sample (>= 8).  One 16-byte buffer load without a branch (a branch around each load makes the compiler wait for every one of
+// them where the paths meet: backward-data 55 -> 48 us, backward-filter 52 -> 46 at the size above).
+//   V16: w % 8 == 0, c % 8 == 0 and 16-byte aligned rows: a group is inside the row or outside as a whole.
+//   else: the load may start at any 2-byte address and run over the end of the row into the next one, never past the sample;
+//   fix8 then drops what does not belong to the row.
+template <bool V16>
+__device__ __forceinline__ uint4 row8(__amdgpu_buffer_rsrc_t rs, int off, int c, int w, int span, bool ok) {
+  const int f = V16 ? off + c : min(off + c, span - 8);
+  const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, ok && c < w ? 2 * f : S2_OOB, 0, 0);
+  return uint4{t.x, t.y, t.z, t.w};
+}
+template <bool V16>
+__device__ __forceinline__ uint4 fix8(uint4 v, int off, int c, int w, int span) {
+  if (V16) return v;
+  const int s = off + c - min(off + c, span - 8);      // elements the load was moved forward by (the end of the sample only)
+  if (__builtin_amdgcn_ballot_w64(s > 0)) {
+    if (s & 4) v = uint4{v.z, v.w, 0u, 0u};
+    if (s & 2) v = uint4{v.y, v.z, v.w, 0u};
+    if (s & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  }
+  const int k = w - c;                                 // elements that belong to the row
+  v.x &= k >= 2 ? 0xffffffffu : k == 1 ? 0xffffu : 0u;
+  v.y &= k >= 4 ? 0xffffffffu : k == 3 ? 0xffffu : 0u;
+  v.z &= k >= 6 ? 0xffffffffu : k == 5 ? 0xffffu : 0u;
+  v.w &= k >= 8 ? 0xffffffffu : k == 7 ? 0xffffu : 0u;
+  return v;
+}
+__device__ __forceinline__ uint32_t row1(__amdgpu_buffer_rsrc_t rs, int off, int c, int w, bool ok) {
+  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, ok && c >= 0 && c < w ? 2 * (off + c) : S2_OOB, 0, 0);
+}
+
+// g = dy where the saved output is > 0, else dy * slope, rounded to bf16; two elements
+__device__ __forceinline__ uint32_t s2_mask2(uint32_t v, uint32_t m, float slope) {
+  float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
+  if (!(__uint_as_float(m << 16) > 0.f)) v0 *= slope;
+  if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
+  return pack_bf16x2(v0, v1);
+}
+__device__ __forceinline__ uint4 s2_mask8(uint4 v, uint4 m, float slope) {
+  return uint4{s2_mask2(v.x, m.x, slope), s2_mask2(v.y, m.y, slope), s2_mask2(v.z, m.z, slope), s2_mask2(v.w, m.w, slope)};
+}
+
+// v[e] = 8 consecutive columns of channel e; result: four (all eight) channels of column col
+__device__ __forceinline__ uint2 column_half(const uint4* v, int col) {
+  uint32_t d[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) d[e] = (col >> 1) == 0 ? v[e].x : (col >> 1) == 1 ? v[e].y : (col >> 1) == 2 ? v[e].z : v[e].w;
+  const uint32_t sel = (col & 1) ? 0x07060302u : 0x05040100u;
+  return uint2{__builtin_amdgcn_perm(d[1], d[0], sel), __builtin_amdgcn_perm(d[3], d[2], sel)};
+}
+__device__ __forceinline__ uint4 column_unit(const uint4 (&v)[8], int col) {
+  const uint2 lo = column_half(v, col), hi = column_half(v + 4, col);
+  return uint4{lo.x, lo.y, hi.x, hi.y};
+}
+
+__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
+  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+}
+// row of the accumulator block that register r of this lane holds
+__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r / 4) + 4 * (lane >> 5) + (r % 4); }
+
+// wp [block][chunk][tap][lane][8]: forward: block row = output channel, contraction = input channel; transposed (backward-data)
+// the other way round.  Channels beyond the tensor's are zero.
+__global__ void __launch_bounds__(256) s2_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
+                                                      int transposed, int nchunk, int64_t total) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= total) return;
+  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
+  int64_t r = i >> 9;
+  const int tap = (int)(r % 27); r /= 27;
+  const int chunk = (int)(r % nchunk), blk = (int)(r / nchunk);
+  const int row = blk * 32 + (lane & 31), k = chunk * 16 + (lane >> 5) * 8 + e;
+  const int co = transposed ? k : row, ci = transposed ? row : k;
+  wp[i] = (co < cout && ci < cin) ? w[((int64_t)co * cin + ci) * 27 + tap] : (bf16_t)0;
+}
+
+// tile index of a workgroup: the workgroups of one XCD (linear index mod 8) take a contiguous run, so that neighbouring tiles,
+// which share halo rows, meet in one L2
+__device__ __forceinline__ int xcd_tile(int i, int n) {
+  const int per = (n + 7) / 8, t = (i & 7) * per + (i >> 3);
+  return t;      // may be >= n: such a workgroup has nothing to do
+}
+
+// ---------------------------------------------------------------------------------------------------------- forward
+// A workgroup owns 4 rows x 32 columns of one output plane and up to 128 output channels.  Per stage of 32 input channels the
+// 3 x 9 x 65 input patch is transposed into LDS (16-byte units of 8 channels); even and odd columns lie apart, so that the
+// columns 2q + kw - 1 of 32 neighbouring outputs are 32 neighbouring units for every kw.  The contraction is split over the
+// wavefronts: two of them take the two 16-channel halves of a stage each (a volume of 32^3 outputs has 256 tiles: with the
+// channels in one wavefront half of the SIMDs would idle), and add their accumulators through LDS at the end, in order.
+//   NCO = 2: two wavefront pairs take 64 channels each (CB = 2 blocks of 32) and all four rows;
+//   NCO = 1: at most 64 output channels (CB = 1: 32): the pairs take two rows each.
+// Weight fragments come from L2 in packed order, one (kd,kw) step ahead.
+constexpr int SF_PITCH = 66, SF_ROWS = 9, SF_CIG = 3 * SF_ROWS * SF_PITCH, SF_UNITS = 4 * SF_CIG;   // row: 33 odd columns (from 2 w0 - 1), 32 even ones
+constexpr size_t SF_LDS = (size_t)SF_UNITS * 16;
+
+template <int NCO, int CB, bool V16>
+__global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict__ x, const uint4* __restrict__ wp, const float* __restrict__ bias,
+                                                        bf16_t* __restrict__ y, S2Args a) {
+  constexpr int R = NCO == 2 ? 4 : 2, T = CB * R;
+  extern __shared__ uint4 lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int khalf = wave & 1, pair = wave >> 1;
+  int t = xcd_tile(blockIdx.x, a.ntiles);
+  if (t >= a.ntiles) return;
+  const int w0 = (t % a.tiles_w) * 32; t /= a.tiles_w;
+  const int h0 = (t % a.tiles_h) * 4; t /= a.tiles_h;
+  const int z = t % a.y.d, n = t / a.y.d;
+  const int W = a.x.w, H = a.x.h;
+  const int ncoblk = (a.cout + 31) / 32;
+  const int blk0 = ((int)blockIdx.y * NCO + (NCO == 2 ? pair : 0)) * CB;
+  const bf16_t* xs = x + (int64_t)n * a.x.nstride;
+  const __amdgpu_buffer_rsrc_t rs = s2_rsrc(xs, (uint32_t)a.x.nstride * 2);
+  const int cstride = (int)a.x.cstride, plane = (int)a.x.plane;
+
+  // ---- staging plan: 4 x 27 rows of 8 column groups, and the one odd column in front of them
+  constexpr int NITEM = 4 * 27 * 8, NR = (NITEM + 255) / 256;
+  int off[NR], meta[NR];                  // element offset of the row (channel group included); cig | ok << 8 | unit << 9
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int item = tid + 256 * r;
+    const int cg = item & 7;
+    int q = item >> 3;
+    const int row = q % SF_ROWS; q /= SF_ROWS;
+    const int dz = q % 3, cig = q / 3;
+    const int p = 2 * z + dz - 1, h = 2 * h0 + row - 1;
+    const bool ok = item < NITEM && a.x.doff + p >= 0 && h >= 0 && h < H;
+    off[r] = cig * 8 * cstride + (p + a.x.hlo) * plane + h * W;
+    meta[r] = cig | (ok ? 256 : 0) | ((cig * SF_CIG + (dz * SF_ROWS + row) * SF_PITCH + 4 * cg) << 9);
+  }
+  int loff, lmeta;
+  {
+    int q = tid;
+    const int row = q % SF_ROWS; q /= SF_ROWS;
+    const int dz = q % 3, cig = q / 3;
+    const int p = 2 * z + dz - 1, h = 2 * h0 + row - 1;
+    const bool ok = tid < 4 * 27 && a.x.doff + p >= 0 && h >= 0 && h < H;
+    loff = cig * 8 * cstride + (p + a.x.hlo) * plane + h * W;
+    lmeta = cig | (ok ? 256 : 0) | ((cig * SF_CIG + (dz * SF_ROWS + row) * SF_PITCH) << 9);
+  }
+  uint4 v[NR][8];
+  uint32_t lv[8];
+  auto load_stage = [&](int st) {
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      const int c0 = st * 32 + e;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        const bool ok = (meta[r] & 256) && c0 + 8 * (meta[r] & 7) < a.cin;
+        v[r][e] = row8<V16>(rs, off[r] + c0 * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)a.x.nstride, ok);
+      }
+      lv[e] = row1(rs, loff + c0 * cstride, 2 * w0 - 1, W, (lmeta & 256) && c0 + 8 * (lmeta & 7) < a.cin);
+    }
+  };
+  auto store_stage = [&](int st) {
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      if (tid + 256 * r >= NITEM) continue;
+#pragma unroll
+      for (int e = 0; e < 8; ++e)
+        v[r][e] = fix8<V16>(v[r][e], off[r] + (st * 32 + e) * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)a.x.nstride);
+      uint4* dst = lds + (meta[r] >> 9);
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        dst[33 + k] = column_unit(v[r], 2 * k);
+        dst[1 + k] = column_unit(v[r], 2 * k + 1);
+      }
+    }
+    if (tid < 4 * 27)
+      lds[lmeta >> 9] = uint4{lv[0] | (lv[1] << 16), lv[2] | (lv[3] << 16), lv[4] | (lv[5] << 16), lv[6] | (lv[7] << 16)};
+  };
+
+  f32x16 acc[CB][R];
+#pragma unroll
+  for (int c = 0; c < CB; ++c)
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) acc[c][r][i] = 0.f;
+
+  const uint4* wbase[CB];
+#pragma unroll
+  for (int c = 0; c < CB; ++c) wbase[c] = wp + (int64_t)min(blk0 + c, ncoblk - 1) * a.nchunk * 27 * 64 + lane;
+  const uint4* bbase = lds + (2 * khalf + (lane >> 5)) * SF_CIG + (NCO == 2 ? 0 : pair * 2 * R) * SF_PITCH + (lane & 31);
+
+  const int nst = a.nchunk / 2;
+  load_stage(0);
+  for (int st = 0; st < nst; ++st) {
+    if (st) __syncthreads();
+    store_stage(st);
+    __syncthreads();
+    uint4 A[2][3][CB], B[2][2 * R + 1];
+    const int64_t wchunk = (int64_t)(2 * st + khalf) * 27 * 64;
+    auto load_a = [&](int step) {
+#pragma unroll
+      for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+        for (int c = 0; c < CB; ++c) A[step & 1][kh][c] = wbase[c][wchunk + ((step / 3) * 9 + kh * 3 + step % 3) * 64];
+    };
+    auto load_b = [&](int step) {
+      const int kw = step % 3;
+#pragma unroll
+      for (int r = 0; r < 2 * R + 1; ++r) B[step & 1][r] = bbase[((step / 3) * SF_ROWS + r) * SF_PITCH + (kw == 1 ? 33 : kw / 2)];
+    };
+    load_a(0);
+    load_b(0);
+#pragma unroll
+    for (int step = 0; step < 9; ++step) {
+      if (step + 1 < 9) {
+        load_a(step + 1);
+        load_b(step + 1);
+      }
+      // requests return in order: the next stage's rows are asked for behind the last weight fragments of this one
+      if (step == 7 && st + 1 < nst) load_stage(st + 1);
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int kh = 0; kh < 3; ++kh)
+#pragma unroll
+          for (int c = 0; c < CB; ++c) acc[c][r] = mfma32(A[step & 1][kh][c], B[step & 1][2 * r + kh], acc[c][r]);
+    }
+  }
+
+  // ---- the two channel halves exchange half of their accumulators and finish the other half
+  __syncthreads();
+  float4* xch = reinterpret_cast<float4*>(lds);
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (khalf == k) continue;               // what wavefront half k keeps goes out from the other one
+#pragma unroll
+    for (int i = 0; i < T / 2; ++i) {
+      const int ti = k * (T / 2) + i;
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        xch[((wave * (T / 2) + i) * 4 + q) * 64 + lane] = float4{acc[ti / R][ti % R][4 * q], acc[ti / R][ti % R][4 * q + 1], acc[ti / R][ti % R][4 * q + 2], acc[ti / R][ti % R][4 * q + 3]};
+    }
+  }
+  __syncthreads();
+  bf16_t* ys = y + (int64_t)n * a.y.nstride;
+  const __amdgpu_buffer_rsrc_t ro = s2_rsrc(ys, (uint32_t)a.y.nstride * 2);
+  const int ycs = (int)a.y.cstride, W2 = a.y.w, H2 = a.y.h, j = lane & 31;
+  const bool odd = lane & 1;
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    if (khalf != k) continue;
+#pragma unroll
+    for (int i = 0; i < T / 2; ++i) {
+      const int ti = k * (T / 2) + i, cb = ti / R, r = ti % R;
+      if (blk0 + cb >= ncoblk) continue;
+      float f[16];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float4 o = xch[(((wave ^ 1) * (T / 2) + i) * 4 + q) * 64 + lane];
+        const float ov[4] = {o.x, o.y, o.z, o.w};
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int co = (blk0 + cb) * 32 + acc_row(4 * q + e, lane);
+          const float mine = acc[cb][r][4 * q + e];
+          float s = (k == 0 ? mine + ov[e] : ov[e] + mine) + ((bias && co < a.cout) ? bias[co] : 0.f);
+          if (!(s > 0.f)) s *= a.slope;
+          f[4 * q + e] = s;
+        }
+      }
+      const int h = h0 + (NCO == 2 ? 0 : pair * R) + r;
+      const int base = (z + a.y.hlo) * (int)a.y.plane + h * W2;
+      if (a.vec) {      // neighbouring lanes swap one value, so that a lane stores two neighbouring voxels of one channel
+        const int w = w0 + j - (odd ? 1 : 0);
+        const bool in = h < H2 && w < W2;
+#pragma unroll
+        for (int q = 0; q < 16; q += 2) {
+          const int co = (blk0 + cb) * 32 + acc_row(q, lane) + (odd ? 1 : 0);
+          const float give = odd ? f[q] : f[q + 1];
+          const float got = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(give), 0xB1, 0xF, 0xF, true));
+          const uint32_t pk = odd ? pack_bf16x2(got, f[q + 1]) : pack_bf16x2(f[q], got);
+          __builtin_amdgcn_raw_buffer_store_b32(pk, ro, in && co < a.cout ? 2 * (co * ycs + base + w) : S2_OOB, 0, 0);
+        }
+      } else {
+        const int w = w0 + j;
+        const bool in = h < H2 && w < W2;
+#pragma unroll
+        for (int q = 0; q < 16; ++q) {
+          const int co = (blk0 + cb) * 32 + acc_row(q, lane);
+          __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(f[q]), ro, in && co < a.cout ? 2 * (co * ycs + base + w) : S2_OOB, 0, 0);
+        }
+      }
+    }
+  }
+}
+
+// ------------------------------------------------------------------------------------------------------ backward-data
+// A workgroup of 8 wavefronts owns 8 coarse rows x 32 coarse columns of one coarse plane, i.e. 2 x 16 x 64 voxels of dx, and 32
+// input channels; a wavefront one coarse row, with one accumulator block for each of the eight parities (128 registers).  Per
+// chunk of 16 output channels the 2 x 9 x 33 patch of g = dy act'(y) and the chunk's 27 weight fragments (27 KB) pass through
+// LDS (two buffers): the eight fragments of g at the shifts {0,1}^3 feed 27 products.  The two W parities of a lane are
+// neighbouring voxels and leave as one dword.
+constexpr int SD_PITCH = 34, SD_ROWS = 9, SD_CIG = 2 * SD_ROWS * SD_PITCH, SD_W = 27 * 64, SD_BUF = SD_W + 2 * SD_CIG;
+constexpr size_t SD_LDS = (size_t)2 * SD_BUF * 16;
+
+template <bool MASKED, bool V16>
+__global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ m, const uint4* __restrict__ wp,
+                                                          bf16_t* __restrict__ dx, S2Args a) {
+  extern __shared__ uint4 lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  int t = xcd_tile(blockIdx.x, a.ntiles);
+  if (t >= a.ntiles) return;
+  const int w0 = (t % a.tiles_w) * 32; t /= a.tiles_w;
+  const int h0 = (t % a.tiles_h) * 8; t /= a.tiles_h;
+  const int z = t % a.y.d, n = t / a.y.d;
+  const int ci0 = blockIdx.y * 32;
+  const int W2 = a.y.w, H2 = a.y.h;
+  const bf16_t* ys = dy + (int64_t)n * a.y.nstride;
+  const __amdgpu_buffer_rsrc_t rs = s2_rsrc(ys, (uint32_t)a.y.nstride * 2);
+  const int cstride = (int)a.y.cstride;
+
+  // ---- staging plan: threads 0..287 take 8 columns of 4 channels, 288..359 the column behind the tile (with all 8 channels of a
+  //      unit in one thread three wavefronts do the masking while five wait: 48 against 35 us at the size above)
+  const bool full = tid < 288, tail = tid >= 288 && tid < 360;
+  const int cg = full ? tid & 3 : 4;
+  int q = full ? tid >> 2 : tid - 288;
+  const int row = q % SD_ROWS; q /= SD_ROWS;
+  const int pl = q % 2, cq = q / 2;
+  const bool ok0 = (full || tail) && h0 + row < H2 && a.y.doff + z + pl < a.y.dglob;
+  const int off = cq * 4 * cstride + (z + pl + a.y.hlo) * (int)a.y.plane + (h0 + row) * W2;
+  const int col = w0 + 8 * cg;
+  const __amdgpu_buffer_rsrc_t rm = s2_rsrc(MASKED ? m + (int64_t)n * a.m.nstride : ys, (uint32_t)a.m.nstride * 2);
+  const int mcs = (int)a.m.cstride, moff = cq * 4 * mcs + (z + pl + a.m.hlo) * (int)a.m.plane + (h0 + row) * W2;
+  const int unit = SD_W + (cq >> 1) * SD_CIG + (pl * SD_ROWS + row) * SD_PITCH + 8 * cg;
+  uint4 v[4], mv[4], wv0, wv1, wv2, wv3;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) v[e] = mv[e] = uint4{0u, 0u, 0u, 0u};
+  const uint4* wsrc = wp + (int64_t)blockIdx.y * a.nchunk * SD_W;
+  auto load_chunk = [&](int c) {
+    const uint4* wc = wsrc + (int64_t)c * SD_W + tid;
+    wv0 = wc[0];
+    wv1 = wc[512];
+    wv2 = wc[1024];
+    wv3 = wc[min(1536, SD_W - 1 - tid)];
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const bool ok = ok0 && c * 16 + cq * 4 + e < a.cout;
+      if (full) {
+        v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)a.y.nstride, ok);
+        if (MASKED) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)a.m.nstride, ok);
+      } else if (tail) {
+        v[e].x = row1(rs, off + (c * 16 + e) * cstride, col, W2, ok);
+        if (MASKED) mv[e].x = row1(rm, moff + (c * 16 + e) * mcs, col, W2, ok);
+      }
+    }
+  };
+  auto store_chunk = [&](int c) {
+    uint4* dst = lds + (c & 1) * SD_BUF;
+    dst[tid] = wv0;
+    dst[tid + 512] = wv1;
+    dst[tid + 1024] = wv2;
+    if (tid + 1536 < SD_W) dst[tid + 1536] = wv3;
+    uint2* half = reinterpret_cast<uint2*>(dst + unit) + (cq & 1);
+    if (full) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)a.y.nstride);
+        if (MASKED) v[e] = s2_mask8(v[e], fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)a.m.nstride), a.slope);
+      }
+#pragma unroll
+      for (int k = 0; k < 8; ++k) half[2 * k] = column_half(v, k);
+    } else if (tail) {
+      uint32_t s[4];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) s[e] = MASKED ? s2_mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
+      *half = uint2{s[0] | (s[1] << 16), s[2] | (s[3] << 16)};
+    }
+  };
+
+  f32x16 acc[8];                  // parity (pd, ph, pw)
+#pragma unroll
+  for (int p = 0; p < 8; ++p)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[p][i] = 0.f;
+
+  load_chunk(0);
+  store_chunk(0);
+  for (int c = 0; c < a.nchunk; ++c) {
+    __syncthreads();
+    if (c + 1 < a.nchunk) load_chunk(c + 1);
+    const uint4* wl = lds + (c & 1) * SD_BUF + lane;
+    const uint4* bl = lds + (c & 1) * SD_BUF + SD_W + (lane >> 5) * SD_CIG + wave * SD_PITCH + (lane & 31);
+#pragma unroll
+    for (int od = 0; od < 2; ++od)
+#pragma unroll
+      for (int oh = 0; oh < 2; ++oh) {
+        const uint4 b0 = bl[(od * SD_ROWS + oh) * SD_PITCH], b1 = bl[(od * SD_ROWS + oh) * SD_PITCH + 1];
+#pragma unroll
+        for (int pd = od; pd < 2; ++pd)
+#pragma unroll
+          for (int ph = oh; ph < 2; ++ph) {
+            const int kd = od ? 0 : 1 + pd, kh = oh ? 0 : 1 + ph, tap = kd * 9 + kh * 3;
+            acc[pd * 4 + ph * 2] = mfma32(wl[(tap + 1) * 64], b0, acc[pd * 4 + ph * 2]);
+            acc[pd * 4 + ph * 2 + 1] = mfma32(wl[(tap + 2) * 64], b0, acc[pd * 4 + ph * 2 + 1]);
+            acc[pd * 4 + ph * 2 + 1] = mfma32(wl[tap * 64], b1, acc[pd * 4 + ph * 2 + 1]);
+          }
+      }
+    if (c + 1 < a.nchunk) store_chunk(c + 1);
+  }
+
+  bf16_t* xs = dx + (int64_t)n * a.x.nstride;
+  const __amdgpu_buffer_rsrc_t ro = s2_rsrc(xs, (uint32_t)a.x.nstride * 2);
+  const int W = a.x.w, H = a.x.h, ch = h0 + wave, w = 2 * (w0 + (lane & 31));
+#pragma unroll
+  for (int pd = 0; pd < 2; ++pd)
+#pragma unroll
+    for (int ph = 0; ph < 2; ++ph) {
+      const int h = 2 * ch + ph;
+      const int base = (2 * z + pd + a.x.hlo) * (int)a.x.plane + h * W + w;
+      const bool in = h < H && w < W;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const int ci = ci0 + acc_row(i, lane);
+        const int vo = in && ci < a.cin ? 2 * (ci * (int)a.x.cstride + base) : S2_OOB;
+        const uint32_t pk = pack_bf16x2(acc[pd * 4 + ph * 2][i], acc[pd * 4 + ph * 2 + 1][i]);
+        if (a.vec) {
+          __builtin_amdgcn_raw_buffer_store_b32(pk, ro, vo, 0, 0);
+        } else {
+          __builtin_amdgcn_raw_buffer_store_b16((short)(pk & 0xffffu), ro, vo, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((short)(pk >> 16), ro, w + 1 < W ? vo == S2_OOB ? S2_OOB : vo + 2 : S2_OOB, 0, 0);
+        }
+      }
+    }
+}
+
+// ---------------------------------------------------------------------------------------------------- backward-filter
+// Contraction over coarse voxels with both operands in NCDHW: rows = 32 output channels (A = g, 8 consecutive columns a lane),
+// columns = 32 input channels (B = x at every second column: the even and the odd elements of 16 consecutive ones, taken apart
+// with v_perm; even columns are tap kw = 1, odd ones kw = 2, and against g shifted by one column kw = 0), K = 16 coarse columns.
+// The tap plane kd is a grid dimension (27 accumulator blocks do not fit); a workgroup's four wavefronts hold the 9 (kh,kw)
+// blocks of 2 x 2 channel blocks (144 registers) and walk down the rows of a strip (32 coarse columns x SB_BAND rows of one
+// plane): fine row 2h is kh = 1 of g row h, fine row 2h + 1 is kh = 2 of it and kh = 0 of row h + 1, which stays in registers
+// for the next step, so x and g are read once.  Rows pass through LDS (two buffers, one barrier a step); row pitches of 9 and 5
+// units keep the 16-byte reads of neighbouring channels on different banks.
+// Partial sums [chunk][27][co][ci] per chunk of strips, added in chunk order: identical bits on every run.
+constexpr int SB_BAND = 16, SB_XP = 9, SB_GP = 5, SB_X = 2 * 64 * SB_XP, SB_BUF = SB_X + 64 * SB_GP;
+
+template <bool MASKED, bool V16>
+__global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ m,
+                                                               float* __restrict__ part, float* __restrict__ part_db, S2Args a) {
+  __shared__ uint4 lds[2 * SB_BUF];
+  __shared__ float dbl[256];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int cog = blockIdx.y / a.cigroups, cig = blockIdx.y % a.cigroups, kd = blockIdx.z, chunk = blockIdx.x;
+  const int W = a.x.w, H = a.x.h, W2 = a.y.w, H2 = a.y.h;
+  const bool want_db = kd == 1 && cig == 0;
+
+  const int g_co = cog * 64 + (tid >> 2), g_piece = tid & 3;
+  const int x_piece = tid & 7, x_ci = cig * 64 + (tid >> 3);
+  int strip = chunk * a.strips_per_chunk;
+  const int strip_end = min(strip + a.strips_per_chunk, a.nstrips);
+
+  // position of the step whose rows are being FETCHED
+  int n = 0, z = 0, w0 = 0, h = 0, hend = 0;
+  bool xrow_ok = false;
+  __amdgpu_buffer_rsrc_t rx = s2_rsrc(x, 0), rg = s2_rsrc(dy, 0), rm = rg;
+  auto open_strip = [&]() {
+    int t = strip;
+    const int band = t % a.bands; t /= a.bands;
+    w0 = (t % a.segs) * 32; t /= a.segs;
+    z = t % a.y.d; n = t / a.y.d;
+    h = band * SB_BAND - 1;                       // first step of a strip: only g row h + 1 is fetched
+    hend = min((band + 1) * SB_BAND, H2);
+    rx = s2_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)a.x.nstride * 2);
+    rg = s2_rsrc(dy + (int64_t)n * a.y.nstride, (uint32_t)a.y.nstride * 2);
+    if (MASKED) rm = s2_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
+    const int p = 2 * z + kd - 1;
+    xrow_ok = a.x.doff + p >= 0;
+  };
+
+  uint4 xv[4], gv, mv;
+  uint32_t ge = 0, me = 0;
+  bool count_db = false;
+  int xo = 0, go = 0, mo = 0, xc = 0, gc = 0;       // where the fetched groups lie: element offsets of their rows, columns
+  auto fetch = [&](bool first) {
+    xo = x_ci * (int)a.x.cstride + (2 * z + kd - 1 + a.x.hlo) * (int)a.x.plane + 2 * h * W;
+    xc = 2 * w0 + 8 * x_piece;
+    gc = w0 + 8 * g_piece;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const int ci = x_ci + 32 * (i & 1), row = 2 * h + (i >> 1);
+      xv[i] = row8<V16>(rx, xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)a.x.nstride, !first && xrow_ok && ci < a.cin && row < H);
+    }
+    const bool gok = g_co < a.cout && h + 1 < H2;
+    go = g_co * (int)a.y.cstride + (z + a.y.hlo) * (int)a.y.plane + (h + 1) * W2;
+    gv = row8<V16>(rg, go, gc, W2, (int)a.y.nstride, gok);
+    ge = row1(rg, go, w0 + 32, W2, gok && g_piece == 3);
+    if (MASKED) {
+      mo = g_co * (int)a.m.cstride + (z + a.m.hlo) * (int)a.m.plane + (h + 1) * W2;
+      mv = row8<V16>(rm, mo, gc, W2, (int)a.m.nstride, gok);
+      me = row1(rm, mo, w0 + 32, W2, gok && g_piece == 3);
+    }
+    count_db = h + 1 < hend;
+  };
+  float dbsum = 0.f;
+  auto put = [&](int buf) {
+    uint4* dst = lds + buf * SB_BUF;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      dst[((i >> 1) * 64 + (tid >> 3) + 32 * (i & 1)) * SB_XP + x_piece] =
+          fix8<V16>(xv[i], xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)a.x.nstride);
+    uint4 g = fix8<V16>(gv, go, gc, W2, (int)a.y.nstride);
+    uint32_t e = ge;
+    if (MASKED) {
+      g = s2_mask8(g, fix8<V16>(mv, mo, gc, W2, (int)a.m.nstride), a.slope);
+      e = s2_mask2(e, me, a.slope) & 0xffffu;
+    }
+    dst[SB_X + (tid >> 2) * SB_GP + g_piece] = g;
+    if (g_piece == 3) *reinterpret_cast<uint32_t*>(dst + SB_X + (tid >> 2) * SB_GP + 4) = e;
+    if (want_db && count_db) {
+      const uint32_t d[4] = {g.x, g.y, g.z, g.w};
+#pragma unroll
+      for (int k = 0; k < 4; ++k) dbsum += __uint_as_float(d[k] << 16) + __uint_as_float(d[k] & 0xffff0000u);
+    }
+  };
+
+  f32x16 acc[9];
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
+  uint4 G[2], Gs[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) G[k] = Gs[k] = uint4{0u, 0u, 0u, 0u};
+
+  const int cow = wave >> 1, ciw = wave & 1, lc = lane & 31, half = lane >> 5;
+  bool live = strip < strip_end;
+  bool first = true, cur_first = true;
+  if (live) {
+    open_strip();
+    fetch(true);
+    put(0);
+  }
+  int buf = 0;
+  while (live) {
+    __syncthreads();
+    cur_first = first;
+    // next step
+    bool more = true;
+    if (h + 1 < hend) {
+      ++h;
+      first = false;
+    } else if (++strip < strip_end) {
+      open_strip();
+      first = true;
+    } else {
+      more = false;
+    }
+    if (more) fetch(first);
+    const uint4* xl = lds + buf * SB_BUF + (ciw * 32 + lc) * SB_XP;
+    const uint4* gl = lds + buf * SB_BUF + SB_X + (cow * 32 + lc) * SB_GP;
+    uint4 N[2], Ns[2];
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      N[k] = gl[2 * k + half];
+      const uint32_t nx = *reinterpret_cast<const uint32_t*>(gl + 2 * k + half + 1);
+      Ns[k] = uint4{__builtin_amdgcn_alignbit(N[k].y, N[k].x, 16), __builtin_amdgcn_alignbit(N[k].z, N[k].y, 16),
+                    __builtin_amdgcn_alignbit(N[k].w, N[k].z, 16), __builtin_amdgcn_alignbit(nx, N[k].w, 16)};
+    }
+    if (!cur_first) {
+#pragma unroll
+      for (int row = 0; row < 2; ++row)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          const uint4 p0 = xl[row * 64 * SB_XP + 4 * k + 2 * half], p1 = xl[row * 64 * SB_XP + 4 * k + 2 * half + 1];
+          const uint4 E = {__builtin_amdgcn_perm(p0.y, p0.x, 0x05040100u), __builtin_amdgcn_perm(p0.w, p0.z, 0x05040100u),
+                           __builtin_amdgcn_perm(p1.y, p1.x, 0x05040100u), __builtin_amdgcn_perm(p1.w, p1.z, 0x05040100u)};
+          const uint4 O = {__builtin_amdgcn_perm(p0.y, p0.x, 0x07060302u), __builtin_amdgcn_perm(p0.w, p0.z, 0x07060302u),
+                           __builtin_amdgcn_perm(p1.y, p1.x, 0x07060302u), __builtin_amdgcn_perm(p1.w, p1.z, 0x07060302u)};
+          const int kh = row == 0 ? 1 : 2;
+          acc[kh * 3 + 1] = mfma32(G[k], E, acc[kh * 3 + 1]);
+          acc[kh * 3 + 2] = mfma32(G[k], O, acc[kh * 3 + 2]);
+          acc[kh * 3] = mfma32(Gs[k], O, acc[kh * 3]);
+          if (row == 1) {
+            acc[1] = mfma32(N[k], E, acc[1]);
+            acc[2] = mfma32(N[k], O, acc[2]);
+            acc[0] = mfma32(Ns[k], O, acc[0]);
+          }
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < 2; ++k) {
+      G[k] = N[k];
+      Gs[k] = Ns[k];
+    }
+    if (more) put(buf ^ 1);
+    buf ^= 1;
+    live = more;
+  }
+
+  const int cop = a.cogroups * 64, cip = a.cigroups * 64;
+  float* pp = part + (((int64_t)chunk * 27 + kd * 9) * cop + cog * 64 + cow * 32) * cip + cig * 64 + ciw * 32 + lc;
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) pp[((int64_t)t * cop + acc_row(i, lane)) * cip] = acc[t][i];
+  if (want_db) {
+    dbl[tid] = dbsum;
+    __syncthreads();
+    if (tid < 64) part_db[(int64_t)chunk * cop + cog * 64 + tid] = (dbl[4 * tid] + dbl[4 * tid + 1]) + (dbl[4 * tid + 2] + dbl[4 * tid + 3]);
+  }
+}
+
+// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight)
+__global__ void __launch_bounds__(256) s2_reduce_kernel(const float* __restrict__ part, const float* __restrict__ part_db, float* __restrict__ dw,
+                                                        float* __restrict__ db, int cin, int cout, int cip, int cop, int nchunks) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t nw = (int64_t)27 * cout * cin;
+  const float* src;
+  float* dst;
+  int64_t stride;
+  if (i < nw) {
+    const int ci = (int)(i % cin), co = (int)(i / cin % cout), tap = (int)(i / cin / cout);
+    src = part + ((int64_t)tap * cop + co) * cip + ci;
+    dst = dw + ((int64_t)co * cin + ci) * 27 + tap;
+    stride = (int64_t)27 * cop * cip;
+  } else if (db && i < nw + cout) {
+    src = part_db + (i - nw);
+    dst = db + (i - nw);
+    stride = cop;
+  } else {
+    return;
+  }
+  float s = 0.f;
+  int c = 0;
+  for (; c + 8 <= nchunks; c += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+  }
+  for (; c < nchunks; ++c) s += src[c * stride];
+  *dst = s;
+}
+
+// ------------------------------------------------------------------------------------------------------------- host
+// Byte offsets inside a sample are 32-bit (channels are counted up to the next multiple of 64).
+static bool s2_offsets_fit(const h3d_tensor* t, int bits) { return cdiv(t->c, 64) * 64 * make_geo(t).cstride < ((int64_t)1 << bits) && sample_span(t) >= 8; }
+// x: fine side, y: coarse side.  A saved output may store more halo planes than the gradient it belongs to: its own test
+// (s2_mask_fits) leaves it four times the room, and what does not pass it takes the general route.
+bool s2_mask_fits(const h3d_tensor* m) { return s2_offsets_fit(m, 30); }
+bool s2_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
+  if (x->dtype != H3D_BF16) return false;
+  if (x->n < 1 || x->c < 1 || y->c < 1 || y->d < 1 || x->h < 1 || x->w < 1) return false;
+  if (!s2_offsets_fit(x, 30) || !s2_offsets_fit(y, 28)) return false;
+  return (int64_t)x->n * y->d * cdiv(y->h, 4) * cdiv(y->w, 32) < ((int64_t)1 << 28) && cdiv(x->c, 64) * cdiv(y->c, 64) <= 65535;
+}
+
+struct S2BfPlan { int segs, bands, nstrips, per, nchunks, cogroups, cigroups; };
+// chunks: two workgroups per CU (256 CUs).  A step is shorter than the latency of the rows it prefetches, so a second workgroup
+// pays although it doubles the partial sums: one per CU 46 us (+ 7 for the reduction), two 33 (+ 10) at the size above.
+static S2BfPlan s2_bf_plan(const h3d_tensor* x, const h3d_tensor* y) {
+  S2BfPlan p;
+  p.cogroups = (int)cdiv(y->c, 64); p.cigroups = (int)cdiv(x->c, 64);
+  p.segs = (int)cdiv(y->w, 32); p.bands = (int)cdiv(y->h, SB_BAND);
+  p.nstrips = x->n * y->d * p.segs * p.bands;
+  const int64_t groups = (int64_t)3 * p.cogroups * p.cigroups;
+  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(p.nstrips, 512 / groups));
+  p.per = (int)cdiv(p.nstrips, want);
+  p.nchunks = (int)cdiv(p.nstrips, p.per);
+  return p;
+}
+
+static inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
+static size_t s2_wp_bytes(int rows, int contraction, int step) { return up256((size_t)cdiv(rows, 32) * cdiv(contraction, step) * (step / 16) * 27 * 1024); }
+
+size_t s2_mfma_ws_bytes(int op, const h3d_tensor* x, const h3d_tensor* y) {
+  if (op == H3D_OP_FWD) return s2_wp_bytes(y->c, x->c, 32);
+  if (op == H3D_OP_BWD_DATA) return s2_wp_bytes(x->c, y->c, 16);
+  const S2BfPlan p = s2_bf_plan(x, y);
+  return up256((size_t)p.nchunks * 27 * p.cogroups * p.cigroups * 4096 * sizeof(float)) + up256((size_t)p.nchunks * p.cogroups * 64 * sizeof(float));
+}
+
+static S2Args s2_args(const h3d_tensor* x, const h3d_tensor* y, const h3d_tensor* m, float slope) {
+  S2Args a;
+  memset(&a, 0, sizeof(a));
+  a.x = make_geo(x); a.y = make_geo(y); a.m = m ? make_geo(m) : a.y;
+  a.cin = x->c; a.cout = y->c; a.slope = slope;
+  return a;
+}
+static bool rows16(const h3d_tensor* t) { return t->w % 8 == 0 && (uintptr_t)t->data % 16 == 0; }
+static void s2_pack(const void* w, void* wp, int cin, int cout, bool transposed, int nchunk, hipStream_t s) {
+  const int64_t total = cdiv(transposed ? cin : cout, 32) * nchunk * 27 * 512;
+  hipLaunchKernelGGL(s2_pack_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, transposed ? 1 : 0, nchunk, total);
+}
+static unsigned xcd_grid(int n) { return (unsigned)(cdiv(n, 8) * 8); }
+template <typename K>
+static h3d_status s2_lds(void* handle, K kern, size_t bytes) {
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+    return fail(handle, H3D_EHIP, "conv3d_s2: cannot raise the dynamic LDS limit to %zu bytes", bytes);
+  return H3D_OK;
+}
+
+template <int NCO, int CB, bool V16>
+static h3d_status s2_launch_fwd(void* handle, const h3d_tensor* x, const uint4* wp, const float* bias, h3d_tensor* y, const S2Args& a, hipStream_t s) {
+  static const h3d_status ready = s2_lds(handle, s2_fwd_kernel<NCO, CB, V16>, SF_LDS);
+  H3D_TRY(ready);
+  hipLaunchKernelGGL((s2_fwd_kernel<NCO, CB, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(y->c, 32 * NCO * CB)), dim3(256), SF_LDS, s,
+                     (const bf16_t*)x->data, wp, bias, (bf16_t*)y->data, a);
+  note_kernel(handle, "s2_fwd_kernel<%d,%d,%d>", NCO, CB, (int)V16);
+  return launch_status(handle, "conv3d_s2_fwd");
+}
+
+h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, float slope, void* ws, hipStream_t s) {
+  S2Args a = s2_args(x, y, nullptr, slope);
+  a.nchunk = 2 * (int)cdiv(x->c, 32);
+  a.tiles_w = (int)cdiv(y->w, 32); a.tiles_h = (int)cdiv(y->h, 4);
+  a.ntiles = y->n * y->d * a.tiles_h * a.tiles_w;
+  a.vec = y->w % 2 == 0 && (uintptr_t)y->data % 4 == 0;
+  s2_pack(w, ws, x->c, y->c, false, a.nchunk, s);
+  const uint4* wp = (const uint4*)ws;
+  const bool v16 = rows16(x);
+  if (y->c > 64) return v16 ? s2_launch_fwd<2, 2, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<2, 2, false>(handle, x, wp, bias, y, a, s);
+  if (y->c > 32) return v16 ? s2_launch_fwd<1, 2, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<1, 2, false>(handle, x, wp, bias, y, a, s);
+  return v16 ? s2_launch_fwd<1, 1, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<1, 1, false>(handle, x, wp, bias, y, a, s);
+}
+
+template <bool MASKED, bool V16>
+static h3d_status s2_launch_bd(void* handle, const h3d_tensor* dy, const h3d_tensor* m, const uint4* wp, h3d_tensor* dx, const S2Args& a, hipStream_t s) {
+  static const h3d_status ready = s2_lds(handle, s2_bwd_data_kernel<MASKED, V16>, SD_LDS);
+  H3D_TRY(ready);
+  hipLaunchKernelGGL((s2_bwd_data_kernel<MASKED, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(dx->c, 32)), dim3(512), SD_LDS, s,
+                     (const bf16_t*)dy->data, (const bf16_t*)(m ? m->data : nullptr), wp, (bf16_t*)dx->data, a);
+  note_kernel(handle, "s2_bwd_data_kernel<%d,%d>", (int)MASKED, (int)V16);
+  return launch_status(handle, "conv3d_s2_bwd_data");
+}
+
+h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor* y, const void* w, h3d_tensor* dx, float slope, void* ws, hipStream_t s) {
+  S2Args a = s2_args(dx, dy, y, slope);
+  a.nchunk = (int)cdiv(dy->c, 16);
+  a.tiles_w = (int)cdiv(dy->w, 32); a.tiles_h = (int)cdiv(dy->h, 8);
+  a.ntiles = dy->n * dy->d * a.tiles_h * a.tiles_w;
+  a.vec = dx->w % 2 == 0 && (uintptr_t)dx->data % 4 == 0;
+  s2_pack(w, ws, dx->c, dy->c, true, a.nchunk, s);
+  const uint4* wp = (const uint4*)ws;
+  const bool v16 = rows16(dy) && (!y || rows16(y));
+  if (y) return v16 ? s2_launch_bd<true, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<true, false>(handle, dy, y, wp, dx, a, s);
+  return v16 ? s2_launch_bd<false, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<false, false>(handle, dy, y, wp, dx, a, s);
+}
+
+h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tensor* dy, const h3d_tensor* y, float* dw, float* db, float slope,
+                              void* ws, hipStream_t s) {
+  S2Args a = s2_args(x, dy, y, slope);
+  const S2BfPlan p = s2_bf_plan(x, dy);
+  a.segs = p.segs; a.bands = p.bands; a.nstrips = p.nstrips; a.strips_per_chunk = p.per; a.nchunks = p.nchunks;
+  a.cogroups = p.cogroups; a.cigroups = p.cigroups;
+  float* part = (float*)ws;
+  const int cop = p.cogroups * 64, cip = p.cigroups * 64;
+  float* part_db = (float*)((char*)ws + up256((size_t)p.nchunks * 27 * cop * cip * sizeof(float)));
+  const bool v16 = rows16(x) && rows16(dy) && (!y || rows16(y));
+  const dim3 grid((unsigned)p.nchunks, (unsigned)(p.cogroups * p.cigroups), 3);
+#define S2_BF(M, V) hipLaunchKernelGGL((s2_bwd_filter_kernel<M, V>), grid, dim3(256), 0, s, (const bf16_t*)x->data, (const bf16_t*)dy->data, \
+                                       (const bf16_t*)(y ? y->data : nullptr), part, part_db, a)
+  if (y) { if (v16) S2_BF(true, true); else S2_BF(true, false); }
+  else { if (v16) S2_BF(false, true); else S2_BF(false, false); }
+#undef S2_BF
+  note_kernel(handle, "s2_bwd_filter_kernel<%d,%d>", y ? 1 : 0, (int)v16);
+  const int64_t total = (int64_t)27 * dy->c * x->c + dy->c;
+  hipLaunchKernelGGL(s2_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const float*)part, (const float*)part_db, dw, db, x->c, dy->c,
+                     cip, cop, p.nchunks);
+  return launch_status(handle, "conv3d_s2_bwd_filter");
+}
+
+}  // namespace h3d

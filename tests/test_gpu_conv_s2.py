@@ -163,3 +163,35 @@ def test_stride2_empty_shard():
     h3d.conv3d_s2_bwd_filter(x, y, None, dw, None)
     torch.cuda.synchronize()
     assert float(dw.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("act", [orc.ACT_NONE, orc.ACT_LEAKY])
+@pytest.mark.parametrize("shape", [
+    (1, 33, 70, 4, 18, 70),      # 35 coarse columns: a second column tile of three; one channel / six channels past a block
+    (2, 16, 40, 2, 10, 144),     # aligned rows (16-byte loads), three column tiles, the middle form of the forward kernel
+    (1, 70, 130, 2, 6, 16),      # a second group of output channels, a third 32-channel stage of one partial half
+    (1, 5, 24, 4, 70, 34),       # 35 coarse rows: three bands of the filter gradient, nine row tiles
+    (3, 17, 65, 2, 3, 15),       # odd extents: rows that start at odd addresses, a group that ends past the last row
+])
+def test_stride2_bf16_tile_edges(shape, act):
+    """The edges of the direct kernels' tiles, channel blocks and row groups, against the oracle (the bars of the tests above)."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    w, bias = _weights(Ci, Co, "bf16", 340)
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    xo, xg = slab_pair(synth.flat("normal", SEED, 341, (N, Ci, D, H, W)), "bf16")
+    yo = orc.conv3d_s2_fwd(xo, w, bias, act, 0.01)
+    yg = h3d.conv3d_s2_fwd(xg, wd, bd, dev_like(yo, "bf16"), act, 0.01)
+    assert h3d.h3d_last_kernel().startswith("s2_fwd_kernel")
+    close(from_dev(yg.t), yo.a, TOL["bf16"])
+    so, sg = slab_pair(synth.flat("normal", SEED, 342, yo.a.shape), "bf16")
+    dyo, dyg = slab_pair(synth.flat("normal", SEED, 343, yo.a.shape), "bf16")
+    dxo = orc.conv3d_s2_bwd_data(dyo, so, w, xo, act, 0.01)
+    dxg = h3d.conv3d_s2_bwd_data(dyg, sg, wd, dev_like(dxo, "bf16"), act, 0.01)
+    close(from_dev(dxg.t), dxo.a, TOL["bf16"])
+    dwo, dbo = orc.conv3d_s2_bwd_filter(xo, dyo, so, act, 0.01)
+    dw, db = torch.empty((Co, Ci, 3, 3, 3), device="cuda"), torch.empty((Co,), device="cuda")
+    h3d.conv3d_s2_bwd_filter(xg, dyg, sg, dw, db, act, 0.01)
+    close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
+    close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
