@@ -40,7 +40,7 @@ h3d_status conv3d_fwd_c4(void* handle, const h3d_tensor* in, const void* w, cons
                          void* ws, size_t ws_bytes, hipStream_t stream);
 // conv_mfma.hip
 bool mfma_fwd_supported(const h3d_tensor* in, const h3d_tensor* out);
-size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out);
+size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bool backward_data);
 h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, const float* bias,
                        h3d_tensor* out, bool transpose, float out_slope, float mask_slope, void* ws, size_t ws_bytes,
                        hipStream_t stream);
@@ -76,7 +76,7 @@ extern "C" size_t h3d_conv3d_workspace_bytes(void* handle, int op, const h3d_ten
       [[fallthrough]];
     case H3D_OP_BWD_DATA:  // x: dz (input of the correlation), z: dx
       b = std::max(b, direct_fwd_ws_bytes(x->c, z->c));
-      if (mfma_fwd_supported(x, z)) b = std::max(b, mfma_fwd_ws_bytes(x, z));
+      if (mfma_fwd_supported(x, z)) b = std::max(b, mfma_fwd_ws_bytes(x, z, op == H3D_OP_BWD_DATA));
       if (f32_mfma_fwd_supported(x, z)) b = std::max(b, f32_mfma_fwd_ws_bytes(x->c, z->c));
       break;
     case H3D_OP_BWD_FILTER:  // x: activations, z: dz

@@ -23,7 +23,7 @@
 #include <algorithm>
 #include <type_traits>
 
-#include "common.h"
+#include "prep.h"
 
 namespace h3d {
 
@@ -425,7 +425,8 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
 // Instantiated: <1, 1> and <1, 1, 2> (at most 32 output channels, or small volumes) and <1, 2>.
 // RSP = 2 (for layers with a single block of output channels): eight wavefronts as well, the two of a plane taking
 // four rows of the tile each (64 accumulators, 6 row fragments per step).
-template <int CB, int WCB, int RSP = 1>
+// RAGGED: output rows of odd length (the input is then a prepared copy): a row's last voxel is stored on its own.
+template <int CB, int WCB, int RSP = 1, bool RAGGED = false>
 __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const bf16_t* __restrict__ in, const uint4* __restrict__ wp,
                                                                      const float* __restrict__ bias, bf16_t* __restrict__ out, MfmaArgs a) {
   static_assert(WCB * RSP <= 2, "at most eight wavefronts");
@@ -443,7 +444,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   const int tid = threadIdx.x, lane = tid & 63, wd = (tid >> 6) & 3;      // plane of the tile
   const int wcb = WCB == 2 ? tid >> 8 : 0, rh = RSP == 2 ? tid >> 8 : 0;   // channel-block group, row half
   const int co_blk0 = (blockIdx.y * WCB + wcb) * CB;
-  const int W = a.in.w, H = a.in.h;
+  const int W = a.in.w, H = a.in.h, WO = a.out.w;     // a prepared input has padded rows: W = WO rounded up
 
   int lds_unit[ROUNDS], item_meta[ROUNDS];     // meta: pair | hy << 8 | dz << 16 | valid << 24
 #pragma unroll
@@ -652,8 +653,8 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
     const bool odd = lane & 1;
     const uint32_t sel = odd ? 0x03020706u : 0x05040100u;
     const int cs2 = 2 * (int)a.out.cstride;
-    const int vbase = (row_ch + (odd ? 1 : 0)) * cs2 + 2 * (ps * (int)a.out.plane + h0 * W + w0 + j - (odd ? 1 : 0));
-    const bool w_ok = w0 + j - (odd ? 1 : 0) < W;
+    const int vbase = (row_ch + (odd ? 1 : 0)) * cs2 + 2 * (ps * (int)a.out.plane + h0 * WO + w0 + j - (odd ? 1 : 0));
+    const bool w_ok = w0 + j - (odd ? 1 : 0) < WO;
     const bool act = a.out_slope != 1.f;        // wave-uniform
     const float slope = a.out_slope;
     const float inf = __builtin_inff();
@@ -677,12 +678,18 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
           const uint32_t own = pack_bf16x2(v0, v1);
           const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
           uint32_t pk = __builtin_amdgcn_perm(nb, own, sel);
-          int o = (w_ok && h0 + b < H) ? vbase + 2 * b * W : BUF_OOB;
+          int o = (w_ok && h0 + b < H) ? vbase + 2 * b * WO : BUF_OOB;
           if (!WHOLE) {
             pk = inside ? pk : 0u;
             o = ch_ok ? o : BUF_OOB;
           }
-          __builtin_amdgcn_raw_buffer_store_b32(pk, rs_out, o, soff, 0);
+          if (RAGGED) {
+            const bool second = w0 + j + (odd ? 0 : 1) < WO;
+            __builtin_amdgcn_raw_buffer_store_b16((short)(pk & 0xffffu), rs_out, o, soff, 0);
+            __builtin_amdgcn_raw_buffer_store_b16((short)(pk >> 16), rs_out, second && o != BUF_OOB ? o + 2 : BUF_OOB, soff, 0);
+          } else {
+            __builtin_amdgcn_raw_buffer_store_b32(pk, rs_out, o, soff, 0);
+          }
         }
       }
     };
@@ -848,7 +855,7 @@ __global__ void __launch_bounds__(256) add_bf16_kernel(bf16_t* __restrict__ dst,
   }
 }
 
-size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out) {
+static size_t mfma_base_ws_bytes(const h3d_tensor* in, const h3d_tensor* out) {
   size_t b = mfma_wp_bytes(in, out);
   if (thin_two_pass_shape(in, out, nullptr, nullptr)) b = std::max(b, thin_two_pass_ws_bytes(out));
   const int s = mfma_splits(in, out);
@@ -891,9 +898,11 @@ static bool wide_shape(const MfmaArgs& a) {
   return a.out.w > 16 && a.out.ds >= 3 && a.out.h >= 4 && a.csplit == 1;
 }
 
-template <int CB, int WCB = 1, int RSP = 1>
+template <int CB, int WCB = 1, int RSP = 1, bool RAGGED = false>
 static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, const float* bias, bf16_t* out, MfmaArgs a, int n,
                               hipStream_t stream) {
+  if constexpr (!RAGGED)
+    if (a.out.w & 1) return launch_wide<CB, WCB, RSP, true>(handle, in, wp, bias, out, a, n, stream);
   constexpr size_t lds_bytes = (size_t)2 * 2 * 6 * 10 * 36 * 16 + WCB * CB * 64 * 16;     // two stage buffers + the bias fragments
   a.tiles_w = (int)cdiv(a.out.w, 32);
   a.tiles_h = (int)cdiv(a.out.h, 8);
@@ -904,7 +913,7 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
   a.ntiles = (int)ntiles;
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   const int64_t gx = std::min<int64_t>(ntiles, std::max<int64_t>(1, num_cu / gy));
-  auto kern = conv3d_mfma_wide_kernel<CB, WCB, RSP>;
+  auto kern = conv3d_mfma_wide_kernel<CB, WCB, RSP, RAGGED>;
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
@@ -916,6 +925,74 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
   else if (RSP == 1) note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d>", CB, WCB);
   else note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d,%d>", CB, WCB, RSP);
   return launch_status(handle, "conv3d_mfma_wide");
+}
+
+// ---- prepared input (prep.h): the wide kernel takes neither a fused mask nor rows of odd length.  Where it takes the shape
+// otherwise, the input is copied, masked and padded, slab by slab, and the wide kernel runs on the copy: same products, same order,
+// same bits as the general kernel.  The copy is bounded; without the workspace for it the general kernel runs.
+// Backward-data of masked layers, before -> after: 64->64 on 4 x 64^3 345 -> 265 us, 128->128 on 2 x 40x100x100 1140 -> 830,
+// 24->48 on 2 x 22x50x54 52 -> 36; rows of odd length, 64->64 on 64x128x127: forward 402 -> 267, backward-data 416 -> 261.
+// The budget: 64 MiB leaves slabs too small for the two-block form at 64 channels (267 -> 308 us on the last one).
+constexpr int64_t PREP_FWD_BUDGET = (int64_t)160 << 20;
+
+static bool wide_dims(const h3d_tensor* in, const h3d_tensor* out) {
+  return out->w > 16 && out->halo_lo + out->d + out->halo_hi >= 3 && out->h >= 4 && (out->c > 32 || in->c > 8);
+}
+static int64_t prep_plane_bytes(const h3d_tensor* in) { return (int64_t)in->c * in->h * prep_w(in->w) * 2; }
+// workspace for the copies behind the packed weights; 0: no prepared form
+static size_t prep_fwd_bytes(const h3d_tensor* in, const h3d_tensor* out) {
+  if (in->n < 1 || !wide_dims(in, out)) return 0;
+  PrepTiling t;
+  if (!prep_tiling(in->n, out->halo_lo + out->d + out->halo_hi, prep_plane_bytes(in), 2, PREP_FWD_BUDGET, &t)) return 0;
+  return prep_align((size_t)t.nn * (t.np + 2) * prep_plane_bytes(in));
+}
+
+// backward-data may come with a mask, which is not known here; forward needs the copy for rows of odd length only
+size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bool backward_data) {
+  size_t b = mfma_base_ws_bytes(in, out);
+  if (backward_data || in->w % 2) b = std::max(b, mfma_wp_bytes(in, out) + prep_fwd_bytes(in, out));
+  return b;
+}
+
+static h3d_status wide_conv(void* handle, const bf16_t* ip, const uint4* wq, const float* bias, bf16_t* op, const MfmaArgs& a, int n,
+                            hipStream_t stream) {
+  const int64_t ntiles = (int64_t)n * cdiv(a.out.ds, 4) * cdiv(a.out.h, 8) * cdiv(a.out.w, 32);
+  const int num_cu = static_cast<Handle*>(handle)->num_cu;
+  if (a.cout_k > 32) {
+    // few tiles (a small volume): one channel block per workgroup doubles the workgroups, same sums in the same order
+    if (ntiles * cdiv(a.ncoblk, 2) * 4 < (int64_t)num_cu * 3) return launch_wide<1, 1>(handle, ip, wq, bias, op, a, n, stream);
+    return launch_wide<1, 2>(handle, ip, wq, bias, op, a, n, stream);
+  }
+  // one block of output channels: with short channel loops (at most 32 input channels) or few tiles the eight-wavefront
+  // form that splits the rows of a plane measured faster (32->16 on 4 x 64^3 0.068 -> 0.062 ms, 32->1 on the U-Net
+  // shard 0.239 -> 0.222), with four chunks and many tiles slower (64->32 on the U-Net shard 0.480 -> 0.490)
+  if (a.nchunks <= 2 || ntiles < 2 * num_cu) return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, n, stream);
+  return launch_wide<1, 1>(handle, ip, wq, bias, op, a, n, stream);
+}
+
+// the weights are packed at the start of the workspace already
+static h3d_status prep_conv(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const float* bias, h3d_tensor* out, MfmaArgs a,
+                            float mask_slope, void* ws, hipStream_t stream) {
+  const int planes = out->halo_lo + out->d + out->halo_hi, w8 = prep_w(in->w);
+  PrepTiling t;
+  if (!prep_tiling(in->n, planes, prep_plane_bytes(in), 2, PREP_FWD_BUDGET, &t)) return H3D_OK;     // (nothing to compute)
+  bf16_t* copy = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out));
+  const Geo gi = make_geo(in), go = make_geo(out);
+  for (int i = 0; i < t.count(); ++i) {
+    const PrepSlab b = t.at(i);
+    const int a0 = b.p0 - out->halo_lo, a1 = a0 + b.np;             // output planes, interior-relative
+    // input planes of the slab that lie inside the volume (all of them are stored)
+    const int lo = (int)std::max<int64_t>(a0 - 1, -gi.doff), hi = (int)std::min<int64_t>(a1 + 1, gi.dglob - gi.doff);
+    const int np = std::max(hi - lo, 0);
+    const PrepJob j = prep_job(in, mask, mask_slope, b.n0, b.nn, lo, np, copy);
+    H3D_TRY(prep_launch(handle, j, nullptr, stream));
+    MfmaArgs s = a;
+    s.in.n = b.nn; s.in.d = b.np; s.in.w = w8; s.in.doff = gi.doff + a0; s.in.hlo = a0 - lo; s.in.ds = np; s.in.hhi = np - b.np - s.in.hlo;
+    s.in.plane = (int64_t)in->h * w8; s.in.cstride = s.in.plane * np; s.in.nstride = s.in.cstride * in->c;
+    s.out.n = b.nn; s.out.d = s.out.ds = b.np; s.out.hlo = s.out.hhi = 0; s.out.doff = go.doff + a0;
+    H3D_TRY(wide_conv(handle, copy, (const uint4*)ws, bias, (bf16_t*)out->data + b.n0 * go.nstride + (int64_t)b.p0 * go.plane, s, b.nn, stream));
+  }
+  return H3D_OK;
 }
 
 template <bool MASKED, bool VEC>
@@ -949,7 +1026,7 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   wp_dims(a.cin_k, a.cout_k, &a.nchunks, &a.ncoblk);
   a.out_slope = out_slope; a.mask_slope = mask_slope;
   if ((int64_t)out->n * a.out.ds * out->h * out->w == 0) return H3D_OK;
-  if (!ws || ws_bytes < mfma_fwd_ws_bytes(in, out)) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
+  if (!ws || ws_bytes < mfma_base_ws_bytes(in, out)) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
   if ((uintptr_t)ws % 16) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace must be 16-byte aligned");
   // a handful of output channels from at most 16 input channels: the tap-row-folding kernel
   if (!mask && conv3d_thin_supported(in, out)) return conv3d_thin(handle, in, w, bias, out, transpose, out_slope, ws, stream);
@@ -981,24 +1058,10 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   a.chunks_per_split = (int)cdiv(a.nchunks, a.csplit);
   a.part = a.csplit > 1 ? reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out)) : nullptr;
   h3d_status st;
-  if (!mask && vec && wide_shape(a)) {
-    if (a.cout_k > 32) {
-      // few tiles (a small volume): one channel block per workgroup doubles the workgroups, same sums in the same order
-      const int64_t ntiles = (int64_t)out->n * cdiv(a.out.ds, 4) * cdiv(a.out.h, 8) * cdiv(a.out.w, 32);
-      const int num_cu = static_cast<Handle*>(handle)->num_cu;
-      if (ntiles * cdiv(a.ncoblk, 2) * 4 < (int64_t)num_cu * 3) return launch_wide<1, 1>(handle, ip, wq, bias, op, a, out->n, stream);
-      return launch_wide<1, 2>(handle, ip, wq, bias, op, a, out->n, stream);
-    }
-    if (a.cin_k > 8) {      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
-      // one block of output channels: with short channel loops (at most 32 input channels) or few tiles the eight-wavefront
-      // form that splits the rows of a plane measured faster (32->16 on 4 x 64^3 0.068 -> 0.062 ms, 32->1 on the U-Net
-      // shard 0.239 -> 0.222), with four chunks and many tiles slower (64->32 on the U-Net shard 0.480 -> 0.490)
-      const int64_t ntiles = (int64_t)out->n * cdiv(a.out.ds, 4) * cdiv(a.out.h, 8) * cdiv(a.out.w, 32);
-      if (a.nchunks <= 2 || ntiles < 2 * static_cast<Handle*>(handle)->num_cu)
-        return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, out->n, stream);
-      return launch_wide<1, 1>(handle, ip, wq, bias, op, a, out->n, stream);
-    }
-  }
+  if (!mask && vec && wide_shape(a) && (a.cout_k > 32 || a.cin_k > 8))      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
+    return wide_conv(handle, ip, wq, bias, op, a, out->n, stream);
+  if (const size_t copies = prep_fwd_bytes(in, out); copies && (uintptr_t)out->data % 4 == 0 && ws_bytes >= mfma_wp_bytes(in, out) + copies)
+    return prep_conv(handle, in, mask, bias, out, a, mask_slope, ws, stream);
   if (mask) st = vec ? pick_variant<true, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)
                      : pick_variant<true, false>(handle, ip, mp, wq, bias, op, a, out->n, stream);
   else st = vec ? pick_variant<false, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)

@@ -1,0 +1,83 @@
+// The copy kernel behind prepared operands (prep.h).
+#include "prep.h"
+
+#include <algorithm>
+
+namespace h3d {
+
+// HBM: 2 B read (4 with a mask) and 2 B written per element.  A thread owns one 16-byte unit of the copy.  Source rows may start
+// at any 2-byte address (unaligned 16-byte loads); the last unit of a ragged row is loaded so that it ends with the row, and
+// shifted.
+__device__ __forceinline__ uint4 prep_load(const bf16_t* row, int col, int w) {
+  const int back = max(col + 8 - w, 0);          // 0 except in the last unit of a ragged row; w >= 8
+  uint4 v;
+  __builtin_memcpy(&v, row + col - back, 16);
+  if (back & 4) v = uint4{v.z, v.w, 0u, 0u};
+  if (back & 2) v = uint4{v.y, v.z, v.w, 0u};
+  if (back & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  return v;
+}
+__device__ __forceinline__ uint32_t prep_mask2(uint32_t v, uint32_t m, float slope) {
+  float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
+  if (!(__uint_as_float(m << 16) > 0.f)) v0 *= slope;
+  if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
+  return pack_bf16x2(v0, v1);
+}
+__device__ __forceinline__ void prep_unit(const PrepJob& a, int64_t i) {
+  if (i >= a.units) return;
+  const int wu = a.w8 / 8;
+  int64_t t = i;
+  const int u = (int)(t % wu); t /= wu;
+  const int h = (int)(t % a.s.h); t /= a.s.h;
+  const int p = (int)(t % a.np); t /= a.np;
+  const int c = (int)(t % a.s.c);
+  const int n = (int)(t / a.s.c) + a.n0;
+  const int col = 8 * u;
+  uint4 v = prep_load(a.src + n * a.s.nstride + c * a.s.cstride + (int64_t)(a.p0 + p + a.s.hlo) * a.s.plane + (int64_t)h * a.s.w, col, a.s.w);
+  if (a.msk) {
+    const uint4 m = prep_load(a.msk + n * a.m.nstride + c * a.m.cstride + (int64_t)(a.p0 + p + a.m.hlo) * a.m.plane + (int64_t)h * a.m.w, col, a.m.w);
+    v = uint4{prep_mask2(v.x, m.x, a.slope), prep_mask2(v.y, m.y, a.slope), prep_mask2(v.z, m.z, a.slope), prep_mask2(v.w, m.w, a.slope)};
+  }
+  reinterpret_cast<uint4*>(a.dst)[i] = v;
+}
+
+__global__ void __launch_bounds__(256) prep_kernel(PrepJob a, PrepJob b, int64_t blocks_a) {
+  const int64_t blk = blockIdx.x;
+  if (blk < blocks_a) prep_unit(a, blk * 256 + threadIdx.x);
+  else prep_unit(b, (blk - blocks_a) * 256 + threadIdx.x);
+}
+
+PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst) {
+  PrepJob j;
+  j.src = (const bf16_t*)t->data; j.msk = mask ? (const bf16_t*)mask->data : nullptr; j.dst = (bf16_t*)dst;
+  j.s = make_geo(t); j.m = mask ? make_geo(mask) : j.s;
+  j.n0 = n0; j.nn = nn; j.p0 = p0; j.np = np; j.w8 = prep_w(t->w); j.slope = slope;
+  j.units = (int64_t)nn * t->c * np * t->h * (j.w8 / 8);
+  return j;
+}
+
+h3d_status prep_launch(void* handle, const PrepJob& a, const PrepJob* b, hipStream_t stream) {
+  const int64_t ba = cdiv(a.units, 256), bb = b ? cdiv(b->units, 256) : 0;
+  if (ba + bb == 0) return H3D_OK;
+  if (ba + bb >= ((int64_t)1 << 31)) return fail(handle, H3D_EINVAL, "operand copy: too many blocks");
+  hipLaunchKernelGGL(prep_kernel, dim3((unsigned)(ba + bb)), dim3(256), 0, stream, a, b ? *b : a, ba);
+  return hipGetLastError() == hipSuccess ? H3D_OK : fail(handle, H3D_EHIP, "operand copy: launch failed");
+}
+
+bool prep_tiling(int n, int planes, int64_t plane_bytes, int extra, int64_t budget, PrepTiling* t) {
+  if (n < 1 || planes < 1 || plane_bytes < 1) return false;
+  const int64_t sample = (int64_t)(planes + extra) * plane_bytes;
+  if (sample <= budget) {
+    *t = {n, planes, (int)std::min<int64_t>(n, budget / sample), planes};
+    return true;
+  }
+  int64_t np = budget / plane_bytes - extra;
+  if (np < 1) return false;
+  np = std::min<int64_t>(np, planes);
+  const int64_t even = cdiv(planes, cdiv(planes, np));       // slabs of one size, and whole tiles of the kernels that own four planes
+  np = cdiv(even, 4) * 4 <= np ? cdiv(even, 4) * 4 : even;
+  *t = {n, planes, 1, (int)np};
+  return true;
+}
+
+}  // namespace h3d

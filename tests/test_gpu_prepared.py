@@ -1,0 +1,106 @@
+"""Convolution passes that copy an operand first (rows padded to whole 16-byte units, the activation's derivative multiplied
+in) and run the aligned, unmasked kernels on the copy: small shapes against the oracle, and large ones, which go in several
+slabs, against the general kernels that the same calls take when the workspace has no room for the copies."""
+import numpy as np
+import pytest
+
+import oracle as orc
+import synth
+from helpers import TOL, close, dev_like, elem_masked_bf, from_dev, quantize, slab_pair, to_dev
+
+pytestmark = pytest.mark.gpu
+SEED = synth.BASE_SEED
+
+
+class Short:
+    """A workspace one byte short of what the query asks for: the calls then take the general kernels."""
+
+    def get(self, nbytes):
+        import ctypes
+        import torch
+        self.buf = torch.empty(int(nbytes), dtype=torch.uint8, device="cuda")
+        return ctypes.c_void_p(self.buf.data_ptr()), int(nbytes) - 1
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("shape", [
+    # N, Cin, Cout, D, H, W, (halo, shard), general forward?
+    (2, 12, 40, 5, 6, 33, 0),     # odd rows, a second 32-column tile of one column, channels past a block on both sides
+    (1, 33, 9, 4, 5, 47, 1),      # interior shard with halos
+    (1, 16, 32, 3, 4, 17, 0),     # the fewest planes, rows and columns the wide kernel takes
+    (2, 40, 48, 4, 9, 38, 2),     # even rows of 19 pairs, last shard: no plane above
+    (1, 4, 16, 4, 17, 35, 0),     # a first layer's filter gradient with ragged rows
+])
+def test_prepared_operands_against_the_oracle(shape, masked):
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, ci, co, D, H, W, where = shape
+    halo = 1 if where else 0
+    off, dg = (0, D) if not where else (D, 3 * D) if where == 1 else (2 * D, 3 * D)
+    act = orc.ACT_LEAKY if masked else orc.ACT_NONE
+    b = np.sqrt(3.0 / (27 * ci))
+    w = quantize(synth.flat("uniform", SEED, 800, (co, ci, 3, 3, 3), -b, b), "bf16")
+    bias = synth.round_f32(synth.flat("uniform", SEED, 801, (co,), -0.1, 0.1)).astype(np.float64)
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    hal = (halo, 0 if where == 2 else halo)
+    planes = D + sum(hal)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 802, (N, ci, planes, H, W)), "bf16", hal, off, dg)
+    zo = orc.conv3d_fwd(xo, w, bias, act=orc.ACT_LEAKY, alpha=0.01)
+    close(from_dev(h3d.conv3d_fwd(xg, wd, bd, dev_like(zo, "bf16"), h3d.ACT_LEAKY, 0.01).t), zo.a, TOL["bf16"])
+    go, gg = slab_pair(synth.flat("normal", SEED, 803, (N, co, planes, H, W)), "bf16", hal, off, dg)
+    so, sg = slab_pair(synth.flat("normal", SEED, 804, (N, co, planes, H, W)), "bf16", hal, off, dg)
+    if not masked:
+        so = sg = None
+    dxo = orc.conv3d_bwd_data(go, so, w, act=act, alpha=0.01)
+    dxg = dev_like(dxo, "bf16")
+    dxg.t.fill_(777.0)
+    close(from_dev(h3d.conv3d_bwd_data(gg, sg, wd, dxg, act, 0.01).t), dxo.a, TOL["bf16"])
+    dwo, dbo = orc.conv3d_bwd_filter(xo, go, so, act=act, alpha=0.01)
+    dw, db = torch.full((co, ci, 3, 3, 3), 777.0, device="cuda"), torch.full((co,), 777.0, device="cuda")
+    h3d.conv3d_bwd_filter(xg, gg, sg, dw, db, act, 0.01)
+    close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
+    close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
+    dws, dbs = torch.empty_like(dw), torch.empty_like(db)
+    h3d.conv3d_bwd_filter_static(xg, gg, sg, dws, dbs, act, 0.01)
+    assert torch.equal(dw, dws) and torch.equal(db, dbs)
+
+
+@pytest.mark.parametrize("case", [
+    # N, Cin, Cout, D, H, W, masked, view of a taller slab
+    (1, 64, 64, 70, 128, 127, True, False),      # planes of one sample in several slabs, odd rows
+    (5, 64, 64, 40, 64, 64, True, False),        # whole samples in several slabs, x aligned (read in place), g masked
+    (3, 48, 40, 36, 70, 90, False, True),        # plane-run views, ragged rows
+])
+def test_slabs_of_prepared_operands_equal_the_general_kernels(case):
+    """Backward-data: same products in the same order, so the same bits.  Backward-filter: fp32 sums of the same products in
+    another order: 10^6 terms of random sign, 2^-24 each relative to a partial sum of their root-sum-square: 1e-5 of an
+    element's scale leaves an order of magnitude."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, ci, co, D, H, W, masked, view = case
+    g = torch.Generator(device="cuda")
+    g.manual_seed(5)
+    rnd = lambda c: torch.randn((N, c, D + 4, H, W), generator=g, device="cuda").to(torch.bfloat16)
+    whole = lambda t: h3d.Slab(t, 2, 2, D, 3 * D)
+    cut = (lambda t: whole(t).planes(1, D - 1, 1, 1)) if view else whole
+    x, dz, z = cut(rnd(ci)), cut(rnd(co)), cut(rnd(co)) if masked else None
+    w = torch.randn((co, ci, 3, 3, 3), generator=g, device="cuda").to(torch.bfloat16)
+    act = h3d.ACT_LEAKY if masked else h3d.ACT_NONE
+    res = []
+    for ws in (h3d.Workspace(), Short()):
+        dx = h3d.Slab(torch.full((N, ci, x.d, H, W), 3.0, device="cuda", dtype=torch.bfloat16), 0, 0, x.d_offset, x.d_global)
+        y = h3d.Slab(torch.full((N, co, x.d, H, W), 3.0, device="cuda", dtype=torch.bfloat16), 0, 0, x.d_offset, x.d_global)
+        dw, db = torch.empty(w.shape, device="cuda"), torch.empty(co, device="cuda")
+        h3d.conv3d_fwd(x, w, None, y, h3d.ACT_LEAKY, 0.01, ws)
+        h3d.conv3d_bwd_data(dz, z, w, dx, act, 0.01, ws)
+        kd = h3d.h3d_last_kernel()
+        h3d.conv3d_bwd_filter(x, dz, z, dw, db, act, 0.01, ws)
+        res.append((dx.t, dw, db, y.t, kd, h3d.h3d_last_kernel()))
+    (dx0, dw0, db0, y0, kd0, kf0), (dx1, dw1, db1, y1, kd1, kf1) = res
+    assert kf0 != kf1                                    # two kernels have run
+    if masked or W % 2:
+        assert kd0 != kd1
+    assert torch.equal(dx0, dx1) and torch.equal(y0, y1)
+    rms = float(dw1.square().mean().sqrt())
+    assert float((dw0 - dw1).abs().max()) <= 1e-5 * max(rms, float(dw1.abs().max()))
+    assert float((db0 - db1).abs().max()) <= 1e-5 * float(db1.abs().max().clamp_min(rms))
