@@ -115,6 +115,12 @@ __device__ __forceinline__ void lds_dma16(h3d_i32x4 rs, uint32_t lds_byte_addr, 
                :: "s"(lds_byte_addr), "v"(voff), "s"(rs) : "memory", "m0");
 }
 
+// the same with a scalar byte offset on top (not part of the range check: the per-lane offset alone decides)
+__device__ __forceinline__ void lds_dma16_row(h3d_i32x4 rs, uint32_t lds_byte_addr, int voff, int soff) {
+  asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, %3 offen lds"
+               :: "s"(lds_byte_addr), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
+}
+
 template <typename T> struct dtype_of;
 template <> struct dtype_of<float> { static constexpr int value = H3D_F32; };
 template <> struct dtype_of<bf16_t> { static constexpr int value = H3D_BF16; };

@@ -10,14 +10,13 @@
 // one to two workgroups per CU, and every one lives for two to eight stages.
 #include <algorithm>
 
-#include "common.h"
+#include "rowload.h"
 
 namespace h3d {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
-constexpr int S2_OOB = (int)0x80000000;   // byte offset beyond every buffer: such a lane reads zeros, its store is dropped
+// taps_reduce.hip: dw and db from partial sums [chunk][tap][cop][cip] and [chunk][cop], in chunk order
+void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
+                 hipStream_t s);
 
 struct S2Args {
   Geo x, y, m;                      // fine side, coarse side (y or dy), saved output (mask)
@@ -30,44 +29,6 @@ struct S2Args {
   int segs, bands, nstrips, strips_per_chunk, nchunks, cogroups, cigroups;
 };
 
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t s2_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
-
-// 8 elements of a row of `w` from column c >= 0 on; `off` = element offset of the ROW in the sample, `span` = elements of the
-// sample (>= 8).  One 16-byte buffer load without a branch (a branch around each load makes the compiler wait for every one of
-// them where the paths meet: backward-data 55 -> 48 us, backward-filter 52 -> 46 at the size above).
-//   V16: w % 8 == 0, c % 8 == 0 and 16-byte aligned rows: a group is inside the row or outside as a whole.
-//   else: the load may start at any 2-byte address and run over the end of the row into the next one, never past the sample;
-//   fix8 then drops what does not belong to the row.
-template <bool V16>
-__device__ __forceinline__ uint4 row8(__amdgpu_buffer_rsrc_t rs, int off, int c, int w, int span, bool ok) {
-  const int f = V16 ? off + c : min(off + c, span - 8);
-  const u32x4 t = __builtin_amdgcn_raw_buffer_load_b128(rs, ok && c < w ? 2 * f : S2_OOB, 0, 0);
-  return uint4{t.x, t.y, t.z, t.w};
-}
-template <bool V16>
-__device__ __forceinline__ uint4 fix8(uint4 v, int off, int c, int w, int span) {
-  if (V16) return v;
-  const int s = off + c - min(off + c, span - 8);      // elements the load was moved forward by (the end of the sample only)
-  if (__builtin_amdgcn_ballot_w64(s > 0)) {
-    if (s & 4) v = uint4{v.z, v.w, 0u, 0u};
-    if (s & 2) v = uint4{v.y, v.z, v.w, 0u};
-    if (s & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
-  }
-  const int k = w - c;                                 // elements that belong to the row
-  v.x &= k >= 2 ? 0xffffffffu : k == 1 ? 0xffffu : 0u;
-  v.y &= k >= 4 ? 0xffffffffu : k == 3 ? 0xffffu : 0u;
-  v.z &= k >= 6 ? 0xffffffffu : k == 5 ? 0xffffu : 0u;
-  v.w &= k >= 8 ? 0xffffffffu : k == 7 ? 0xffffu : 0u;
-  return v;
-}
-__device__ __forceinline__ uint32_t row1(__amdgpu_buffer_rsrc_t rs, int off, int c, int w, bool ok) {
-  return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, ok && c >= 0 && c < w ? 2 * (off + c) : S2_OOB, 0, 0);
-}
-
 // g = dy where the saved output is > 0, else dy * slope, rounded to bf16; two elements
 __device__ __forceinline__ uint32_t s2_mask2(uint32_t v, uint32_t m, float slope) {
   float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
@@ -79,28 +40,9 @@ __device__ __forceinline__ uint4 s2_mask8(uint4 v, uint4 m, float slope) {
   return uint4{s2_mask2(v.x, m.x, slope), s2_mask2(v.y, m.y, slope), s2_mask2(v.z, m.z, slope), s2_mask2(v.w, m.w, slope)};
 }
 
-// v[e] = 8 consecutive columns of channel e; result: four (all eight) channels of column col
-__device__ __forceinline__ uint2 column_half(const uint4* v, int col) {
-  uint32_t d[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e) d[e] = (col >> 1) == 0 ? v[e].x : (col >> 1) == 1 ? v[e].y : (col >> 1) == 2 ? v[e].z : v[e].w;
-  const uint32_t sel = (col & 1) ? 0x07060302u : 0x05040100u;
-  return uint2{__builtin_amdgcn_perm(d[1], d[0], sel), __builtin_amdgcn_perm(d[3], d[2], sel)};
-}
-__device__ __forceinline__ uint4 column_unit(const uint4 (&v)[8], int col) {
-  const uint2 lo = column_half(v, col), hi = column_half(v + 4, col);
-  return uint4{lo.x, lo.y, hi.x, hi.y};
-}
-
-__device__ __forceinline__ f32x16 mfma32(uint4 a, uint4 b, f32x16 c) {
-  return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
-}
-// row of the accumulator block that register r of this lane holds
-__device__ __forceinline__ int acc_row(int r, int lane) { return 8 * (r / 4) + 4 * (lane >> 5) + (r % 4); }
-
 // wp [block][chunk][tap][lane][8]: forward: block row = output channel, contraction = input channel; transposed (backward-data)
 // the other way round.  Channels beyond the tensor's are zero.
-__global__ void __launch_bounds__(256) s2_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
+static __global__ void __launch_bounds__(256) s2_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
                                                       int transposed, int nchunk, int64_t total) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= total) return;
@@ -148,7 +90,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
   const int ncoblk = (a.cout + 31) / 32;
   const int blk0 = ((int)blockIdx.y * NCO + (NCO == 2 ? pair : 0)) * CB;
   const bf16_t* xs = x + (int64_t)n * a.x.nstride;
-  const __amdgpu_buffer_rsrc_t rs = s2_rsrc(xs, (uint32_t)a.x.nstride * 2);
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(xs, (uint32_t)a.x.nstride * 2);
   const int cstride = (int)a.x.cstride, plane = (int)a.x.plane;
 
   // ---- staging plan: 4 x 27 rows of 8 column groups, and the one odd column in front of them
@@ -275,7 +217,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
   }
   __syncthreads();
   bf16_t* ys = y + (int64_t)n * a.y.nstride;
-  const __amdgpu_buffer_rsrc_t ro = s2_rsrc(ys, (uint32_t)a.y.nstride * 2);
+  const __amdgpu_buffer_rsrc_t ro = row_rsrc(ys, (uint32_t)a.y.nstride * 2);
   const int ycs = (int)a.y.cstride, W2 = a.y.w, H2 = a.y.h, j = lane & 31;
   const bool odd = lane & 1;
 #pragma unroll
@@ -310,7 +252,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
           const float give = odd ? f[q] : f[q + 1];
           const float got = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(give), 0xB1, 0xF, 0xF, true));
           const uint32_t pk = odd ? pack_bf16x2(got, f[q + 1]) : pack_bf16x2(f[q], got);
-          __builtin_amdgcn_raw_buffer_store_b32(pk, ro, in && co < a.cout ? 2 * (co * ycs + base + w) : S2_OOB, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b32(pk, ro, in && co < a.cout ? 2 * (co * ycs + base + w) : ROW_OOB, 0, 0);
         }
       } else {
         const int w = w0 + j;
@@ -318,7 +260,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
 #pragma unroll
         for (int q = 0; q < 16; ++q) {
           const int co = (blk0 + cb) * 32 + acc_row(q, lane);
-          __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(f[q]), ro, in && co < a.cout ? 2 * (co * ycs + base + w) : S2_OOB, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(f[q]), ro, in && co < a.cout ? 2 * (co * ycs + base + w) : ROW_OOB, 0, 0);
         }
       }
     }
@@ -347,7 +289,7 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
   const int ci0 = blockIdx.y * 32;
   const int W2 = a.y.w, H2 = a.y.h;
   const bf16_t* ys = dy + (int64_t)n * a.y.nstride;
-  const __amdgpu_buffer_rsrc_t rs = s2_rsrc(ys, (uint32_t)a.y.nstride * 2);
+  const __amdgpu_buffer_rsrc_t rs = row_rsrc(ys, (uint32_t)a.y.nstride * 2);
   const int cstride = (int)a.y.cstride;
 
   // ---- staging plan: threads 0..287 take 8 columns of 4 channels, 288..359 the column behind the tile (with all 8 channels of a
@@ -360,7 +302,7 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
   const bool ok0 = (full || tail) && h0 + row < H2 && a.y.doff + z + pl < a.y.dglob;
   const int off = cq * 4 * cstride + (z + pl + a.y.hlo) * (int)a.y.plane + (h0 + row) * W2;
   const int col = w0 + 8 * cg;
-  const __amdgpu_buffer_rsrc_t rm = s2_rsrc(MASKED ? m + (int64_t)n * a.m.nstride : ys, (uint32_t)a.m.nstride * 2);
+  const __amdgpu_buffer_rsrc_t rm = row_rsrc(MASKED ? m + (int64_t)n * a.m.nstride : ys, (uint32_t)a.m.nstride * 2);
   const int mcs = (int)a.m.cstride, moff = cq * 4 * mcs + (z + pl + a.m.hlo) * (int)a.m.plane + (h0 + row) * W2;
   const int unit = SD_W + (cq >> 1) * SD_CIG + (pl * SD_ROWS + row) * SD_PITCH + 8 * cg;
   uint4 v[4], mv[4], wv0, wv1, wv2, wv3;
@@ -440,7 +382,7 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
   }
 
   bf16_t* xs = dx + (int64_t)n * a.x.nstride;
-  const __amdgpu_buffer_rsrc_t ro = s2_rsrc(xs, (uint32_t)a.x.nstride * 2);
+  const __amdgpu_buffer_rsrc_t ro = row_rsrc(xs, (uint32_t)a.x.nstride * 2);
   const int W = a.x.w, H = a.x.h, ch = h0 + wave, w = 2 * (w0 + (lane & 31));
 #pragma unroll
   for (int pd = 0; pd < 2; ++pd)
@@ -452,13 +394,13 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int ci = ci0 + acc_row(i, lane);
-        const int vo = in && ci < a.cin ? 2 * (ci * (int)a.x.cstride + base) : S2_OOB;
+        const int vo = in && ci < a.cin ? 2 * (ci * (int)a.x.cstride + base) : ROW_OOB;
         const uint32_t pk = pack_bf16x2(acc[pd * 4 + ph * 2][i], acc[pd * 4 + ph * 2 + 1][i]);
         if (a.vec) {
           __builtin_amdgcn_raw_buffer_store_b32(pk, ro, vo, 0, 0);
         } else {
           __builtin_amdgcn_raw_buffer_store_b16((short)(pk & 0xffffu), ro, vo, 0, 0);
-          __builtin_amdgcn_raw_buffer_store_b16((short)(pk >> 16), ro, w + 1 < W ? vo == S2_OOB ? S2_OOB : vo + 2 : S2_OOB, 0, 0);
+          __builtin_amdgcn_raw_buffer_store_b16((short)(pk >> 16), ro, w + 1 < W ? vo == ROW_OOB ? ROW_OOB : vo + 2 : ROW_OOB, 0, 0);
         }
       }
     }
@@ -494,7 +436,7 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
   // position of the step whose rows are being FETCHED
   int n = 0, z = 0, w0 = 0, h = 0, hend = 0;
   bool xrow_ok = false;
-  __amdgpu_buffer_rsrc_t rx = s2_rsrc(x, 0), rg = s2_rsrc(dy, 0), rm = rg;
+  __amdgpu_buffer_rsrc_t rx = row_rsrc(x, 0), rg = row_rsrc(dy, 0), rm = rg;
   auto open_strip = [&]() {
     int t = strip;
     const int band = t % a.bands; t /= a.bands;
@@ -502,9 +444,9 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
     z = t % a.y.d; n = t / a.y.d;
     h = band * SB_BAND - 1;                       // first step of a strip: only g row h + 1 is fetched
     hend = min((band + 1) * SB_BAND, H2);
-    rx = s2_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)a.x.nstride * 2);
-    rg = s2_rsrc(dy + (int64_t)n * a.y.nstride, (uint32_t)a.y.nstride * 2);
-    if (MASKED) rm = s2_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
+    rx = row_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)a.x.nstride * 2);
+    rg = row_rsrc(dy + (int64_t)n * a.y.nstride, (uint32_t)a.y.nstride * 2);
+    if (MASKED) rm = row_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
     const int p = 2 * z + kd - 1;
     xrow_ok = a.x.doff + p >= 0;
   };
@@ -642,39 +584,6 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
   }
 }
 
-// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight)
-__global__ void __launch_bounds__(256) s2_reduce_kernel(const float* __restrict__ part, const float* __restrict__ part_db, float* __restrict__ dw,
-                                                        float* __restrict__ db, int cin, int cout, int cip, int cop, int nchunks) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t nw = (int64_t)27 * cout * cin;
-  const float* src;
-  float* dst;
-  int64_t stride;
-  if (i < nw) {
-    const int ci = (int)(i % cin), co = (int)(i / cin % cout), tap = (int)(i / cin / cout);
-    src = part + ((int64_t)tap * cop + co) * cip + ci;
-    dst = dw + ((int64_t)co * cin + ci) * 27 + tap;
-    stride = (int64_t)27 * cop * cip;
-  } else if (db && i < nw + cout) {
-    src = part_db + (i - nw);
-    dst = db + (i - nw);
-    stride = cop;
-  } else {
-    return;
-  }
-  float s = 0.f;
-  int c = 0;
-  for (; c + 8 <= nchunks; c += 8) {
-    float v[8];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
-#pragma unroll
-    for (int k = 0; k < 8; ++k) s += v[k];
-  }
-  for (; c < nchunks; ++c) s += src[c * stride];
-  *dst = s;
-}
-
 // ------------------------------------------------------------------------------------------------------------- host
 // Byte offsets inside a sample are 32-bit (channels are counted up to the next multiple of 64).
 static bool s2_offsets_fit(const h3d_tensor* t, int bits) { return cdiv(t->c, 64) * 64 * make_geo(t).cstride < ((int64_t)1 << bits) && sample_span(t) >= 8; }
@@ -797,9 +706,7 @@ h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tenso
   else { if (v16) S2_BF(false, true); else S2_BF(false, false); }
 #undef S2_BF
   note_kernel(handle, "s2_bwd_filter_kernel<%d,%d>", y ? 1 : 0, (int)v16);
-  const int64_t total = (int64_t)27 * dy->c * x->c + dy->c;
-  hipLaunchKernelGGL(s2_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const float*)part, (const float*)part_db, dw, db, x->c, dy->c,
-                     cip, cop, p.nchunks);
+  taps_reduce(part, part_db, dw, db, 27, x->c, dy->c, cip, cop, p.nchunks, s);
   return launch_status(handle, "conv3d_s2_bwd_filter");
 }
 

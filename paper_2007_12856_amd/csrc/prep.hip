@@ -9,7 +9,13 @@ namespace h3d {
 // at any 2-byte address (unaligned 16-byte loads); the last unit of a ragged row is loaded so that it ends with the row, and
 // shifted.
 __device__ __forceinline__ uint4 prep_load(const bf16_t* row, int col, int w) {
-  const int back = max(col + 8 - w, 0);          // 0 except in the last unit of a ragged row; w >= 8
+  if (w < 8) {                                   // (col is 0)
+    uint32_t e[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) e[i] = i < w ? (uint32_t)row[i] : 0u;
+    return uint4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+  }
+  const int back = max(col + 8 - w, 0);          // 0 except in the last unit of a ragged row
   uint4 v;
   __builtin_memcpy(&v, row + col - back, 16);
   if (back & 4) v = uint4{v.z, v.w, 0u, 0u};

@@ -1,0 +1,46 @@
+// Second stage of the filter gradients whose partial sums are stored [chunk][tap][co][ci] (rows of input channels, padded to the
+// kernels' channel blocks: a wavefront's accumulator registers leave as whole lines).
+#include "common.h"
+
+namespace h3d {
+
+// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight)
+__global__ void __launch_bounds__(256) taps_reduce_kernel(const float* __restrict__ part, const float* __restrict__ part_db, float* __restrict__ dw,
+                                                        float* __restrict__ db, int taps, int cin, int cout, int cip, int cop, int nchunks) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const int64_t nw = (int64_t)taps * cout * cin;
+  const float* src;
+  float* dst;
+  int64_t stride;
+  if (i < nw) {
+    const int ci = (int)(i % cin), co = (int)(i / cin % cout), tap = (int)(i / cin / cout);
+    src = part + ((int64_t)tap * cop + co) * cip + ci;
+    dst = dw + ((int64_t)co * cin + ci) * taps + tap;
+    stride = (int64_t)taps * cop * cip;
+  } else if (db && i < nw + cout) {
+    src = part_db + (i - nw);
+    dst = db + (i - nw);
+    stride = cop;
+  } else {
+    return;
+  }
+  float s = 0.f;
+  int c = 0;
+  for (; c + 8 <= nchunks; c += 8) {
+    float v[8];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
+#pragma unroll
+    for (int k = 0; k < 8; ++k) s += v[k];
+  }
+  for (; c < nchunks; ++c) s += src[c * stride];
+  *dst = s;
+}
+
+void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
+                 hipStream_t s) {
+  const int64_t total = (int64_t)taps * cout * cin + cout;
+  hipLaunchKernelGGL(taps_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, part, part_db, dw, db, taps, cin, cout, cip, cop, nchunks);
+}
+
+}  // namespace h3d

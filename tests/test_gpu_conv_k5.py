@@ -231,3 +231,38 @@ def test_k5_empty_shard():
     h3d.conv3d_k5_bwd_filter(x, z, None, dw, db)
     torch.cuda.synchronize()
     assert float(dw.abs().max()) == 0.0 and float(db.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("act", [orc.ACT_NONE, orc.ACT_LEAKY])
+@pytest.mark.parametrize("shape,shift", [
+    ((1, 3, 5, 64, 33, 33), 0),      # enough tiles for the 32-row form of the convolution kernel, one row and one column past a tile
+    ((2, 20, 40, 6, 3, 72), 0),      # columns of three rows: a wavefront group's run spans many, the second segment is 8 wide
+    ((1, 9, 33, 3, 40, 24), 1),      # whole 16-byte rows at an odd address
+    ((1, 33, 9, 3, 19, 45), 3),      # ragged rows at an odd address
+])
+def test_k5_bf16_kernel_edges(shape, shift, act):
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    print("k5 edges", shape, shift, act, flush=True)
+
+    def moved(s):      # the same values `shift` elements into a larger allocation
+        flat = torch.empty(s.t.numel() + 16, dtype=s.t.dtype, device="cuda")[shift:shift + s.t.numel()]
+        return h3d.Slab(flat.view(s.t.shape).copy_(s.t), s.halo_lo, s.halo_hi, s.d_offset, s.d_global)
+
+    w, bias = _weights(Ci, Co, "bf16", 540)
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    xo, xg = slab_pair(synth.flat("normal", SEED, 541, (N, Ci, D, H, W)), "bf16")
+    zo = orc.convk_fwd(xo, w, bias, act, 0.01)
+    zg = h3d.conv3d_k5_fwd(moved(xg), wd, bd, moved(dev_like(zo, "bf16")), act, 0.01)
+    close(from_dev(zg.t), zo.a, TOL["bf16"])
+    so, sg = slab_pair(synth.flat("normal", SEED, 542, zo.a.shape), "bf16")
+    go, gg = slab_pair(synth.flat("normal", SEED, 543, zo.a.shape), "bf16")
+    dxo = orc.convk_bwd_data(go, so, w, act, 0.01)
+    dxg = h3d.conv3d_k5_bwd_data(moved(gg), moved(sg), wd, moved(dev_like(dxo, "bf16")), act, 0.01)
+    close(from_dev(dxg.t), dxo.a, TOL["bf16"])
+    dwo, dbo = orc.convk_bwd_filter(5, xo, go, so, act, 0.01)
+    dw, db = torch.empty((Co, Ci, 5, 5, 5), device="cuda"), torch.empty((Co,), device="cuda")
+    h3d.conv3d_k5_bwd_filter(moved(xg), moved(gg), moved(sg), dw, db, act, 0.01)
+    close(from_dev(dw), dwo, 2e-4)
+    close(from_dev(db), dbo, 2e-4)
