@@ -19,7 +19,13 @@ struct BnArgs {
   int64_t run;         // d * h * w
 };
 
-template <typename T, int V> struct alignas(V * sizeof(T)) BnPack { T v[V]; };
+// 16 bytes of a run, at any element's address
+template <typename T> struct BnPack { T v[16 / sizeof(T)]; };
+template <typename T> __device__ __forceinline__ BnPack<T> bn_load(const T* p) {
+  BnPack<T> r;
+  __builtin_memcpy(&r, p, 16);
+  return r;
+}
 
 // block-wide sum of two values in a fixed order: lanes by butterfly, wavefronts in index order
 __device__ __forceinline__ void bn_block_sum2(float& a, float& b) {
@@ -46,50 +52,40 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
   const T* xp = x + n * a.x.nstride + c * a.x.cstride + (int64_t)a.x.hlo * a.x.plane;
   const T* gp = MODE == 1 ? dy + n * a.y.nstride + c * a.y.cstride + (int64_t)a.y.hlo * a.y.plane : nullptr;
   const float mu = MODE == 1 ? mean[c] : 0.f, is = MODE == 1 ? invstd[c] : 0.f;
-  float s0 = 0.f, s1 = 0.f;
-  const bool vec = (uintptr_t)xp % 16 == 0 && (MODE == 0 || (uintptr_t)gp % 16 == 0);
-  if (vec) {
-    // four 16-byte loads in flight per thread and tensor
-    constexpr int UN = 4;
-    for (int64_t eb = e0 + (int64_t)threadIdx.x * V; eb < e1; eb += (int64_t)256 * V * UN) {
-      BnPack<T, V> px[UN], pg[MODE == 1 ? UN : 1];
+  // UN 16-byte loads in flight per thread and tensor, none behind a branch, each with a pair of accumulators of its own.  Bound by
+  // memory: 4 x 16 x 128^3 bf16, statistics 57 us (4.7 TB/s; 63 before), backward sums 109 (4.9; 113 before), each behind a pass that
+  // leaves 268 MB of results on their way to memory.
+  constexpr int UN = MODE == 0 ? 8 : 4;
+  constexpr int64_t STEP = (int64_t)256 * V * UN;
+  float s0 = 0.f, s1 = 0.f, t0[UN], t1[UN];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int64_t e = eb + (int64_t)u * 256 * V;
-        if (e + V <= e1) {
-          px[u] = *reinterpret_cast<const BnPack<T, V>*>(xp + e);
-          if (MODE == 1) pg[u] = *reinterpret_cast<const BnPack<T, V>*>(gp + e);
-        }
-      }
+  for (int u = 0; u < UN; ++u) t0[u] = t1[u] = 0.f;
+  int64_t eb = e0;
+  for (; eb + STEP <= e1; eb += STEP) {
+    BnPack<T> px[UN], pg[UN];
 #pragma unroll
-      for (int u = 0; u < UN; ++u) {
-        const int64_t e = eb + (int64_t)u * 256 * V;
-        if (e + V <= e1) {
-          if (MODE == 0) {
-#pragma unroll
-            for (int i = 0; i < V; ++i) { const float v = ld(&px[u].v[i]); s0 += v; s1 = fmaf(v, v, s1); }
-          } else {
-#pragma unroll
-            for (int i = 0; i < V; ++i) { const float g = ld(&pg[u].v[i]); s0 += g; s1 = fmaf(g, (ld(&px[u].v[i]) - mu) * is, s1); }
-          }
-        }
-      }
+    for (int u = 0; u < UN; ++u) {
+      const int64_t e = eb + ((int64_t)u * 256 + threadIdx.x) * V;
+      px[u] = bn_load(xp + e);
+      if (MODE == 1) pg[u] = bn_load(gp + e);
     }
-    // the segment's ragged tail (fewer than V elements): thread 0
-    const int64_t tail = e0 + (e1 - e0) / V * V;
-    if (threadIdx.x == 0)
-      for (int64_t e = tail; e < e1; ++e) {
-        const float v = ld(xp + e);
-        if (MODE == 0) { s0 += v; s1 = fmaf(v, v, s1); }
-        else { const float g = ld(gp + e); s0 += g; s1 = fmaf(g, (v - mu) * is, s1); }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+#pragma unroll
+      for (int i = 0; i < V; ++i) {
+        const float v = ld(&px[u].v[i]);
+        if (MODE == 0) { t0[u] += v; t1[u] = fmaf(v, v, t1[u]); }
+        else { const float g = ld(&pg[u].v[i]); t0[u] += g; t1[u] = fmaf(g, (v - mu) * is, t1[u]); }
       }
-  } else {
-    for (int64_t e = e0 + threadIdx.x; e < e1; e += 256) {
-      const float v = ld(xp + e);
-      if (MODE == 0) { s0 += v; s1 = fmaf(v, v, s1); }
-      else { const float g = ld(gp + e); s0 += g; s1 = fmaf(g, (v - mu) * is, s1); }
-    }
   }
+  // the rest of the segment, element by element
+  for (int64_t e = eb + threadIdx.x; e < e1; e += 256) {
+    const float v = ld(xp + e);
+    if (MODE == 0) { s0 += v; s1 = fmaf(v, v, s1); }
+    else { const float g = ld(gp + e); s0 += g; s1 = fmaf(g, (v - mu) * is, s1); }
+  }
+#pragma unroll
+  for (int u = 0; u < UN; ++u) { s0 += t0[u]; s1 += t1[u]; }
   bn_block_sum2(s0, s1);
   if (threadIdx.x == 0) {
     float* o = part + (((int64_t)c * gridDim.z + n) * a.segs + seg) * 2;
@@ -97,72 +93,77 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
   }
 }
 
-__global__ void bn_reduce_kernel(const float* __restrict__ part, float* __restrict__ out0, float* __restrict__ out1, int c, int per) {
-  const int ch = blockIdx.x * blockDim.x + threadIdx.x;
+// one wavefront a channel: lane l adds the partial sums l, l + 64, ... in order, then the lanes by butterfly (fp64)
+__global__ void __launch_bounds__(256) bn_reduce_kernel(const float* __restrict__ part, float* __restrict__ out0, float* __restrict__ out1, int c, int per) {
+  const int ch = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
   if (ch >= c) return;
   double s0 = 0.0, s1 = 0.0;
   const float* p = part + (int64_t)ch * per * 2;
-  for (int i = 0; i < per; ++i) { s0 += p[2 * i]; s1 += p[2 * i + 1]; }
-  out0[ch] = (float)s0; out1[ch] = (float)s1;
+  for (int i = lane; i < per; i += 64) { s0 += p[2 * i]; s1 += p[2 * i + 1]; }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) { s0 += __shfl_xor(s0, off, 64); s1 += __shfl_xor(s1, off, 64); }
+  if (lane == 0) { out0[ch] = (float)s0; out1[ch] = (float)s1; }
 }
 
-// y = x * sc[c] + sh[c] (forward), or dx = dy * k1[c] + x * k2[c] + k3[c] (backward): coefficient tables in `coef`
-// coef: [c][4] = {a, b, c, unused};  out = in0 * a + in1 * b + c   (in1 unused when b == 0 and TWO == false)
+// per-channel parameters of the affine passes (the arrays hold one value a channel; gamma / beta may be null)
+struct BnCoef {
+  const float *mean, *invstd, *gamma, *beta, *sum_dy, *sum_dy_xhat;
+  float inv_count;
+};
+// out = in0 * ka + kc (forward: y = gamma (x - mean) invstd + beta), or in0 * ka + in1 * kb + kc (backward:
+// dx = k1 (dy - m1 - (x - mean) invstd m2), in0 = dy, in1 = x).  Every block works its channel's factors out itself (two launches
+// of 5 us less a layer).  The blocks walk the tensor backwards: the reduction in front of an affine pass walked it forwards, and
+// the planes it read last are still in the last-level cache (394 -> 387 us for the five passes on 4 x 16 x 128^3 bf16; with the
+// results written past the cache as well, 346; 406 before).
 template <typename T, bool TWO>
 __global__ void __launch_bounds__(256) bn_apply_kernel(const T* __restrict__ in0, const T* __restrict__ in1, T* __restrict__ out,
-                                                       const float* __restrict__ coef, Geo g0, Geo g1, Geo go, int64_t run) {
-  constexpr int V = 16 / sizeof(T);
-  const int c = blockIdx.y, n = blockIdx.z;
-  const float ka = coef[4 * c], kb = coef[4 * c + 1], kc = coef[4 * c + 2];
+                                                       BnCoef q, Geo g0, Geo g1, Geo go, int64_t run, bool past_cache) {
+  constexpr int V = 16 / sizeof(T), UN = 4;
+  const int c = gridDim.y - 1 - blockIdx.y, n = gridDim.z - 1 - blockIdx.z, bx = gridDim.x - 1 - blockIdx.x;
+  const float k1 = (q.gamma ? q.gamma[c] : 1.f) * q.invstd[c];
+  float ka = k1, kb = 0.f, kc;
+  if (TWO) {
+    const float m1 = q.sum_dy[c] * q.inv_count, m2 = q.sum_dy_xhat[c] * q.inv_count;
+    kb = -k1 * q.invstd[c] * m2;
+    kc = k1 * (q.mean[c] * q.invstd[c] * m2 - m1);
+  } else {
+    kc = (q.beta ? q.beta[c] : 0.f) - q.mean[c] * k1;
+  }
   const T* p0 = in0 + n * g0.nstride + c * g0.cstride + (int64_t)g0.hlo * g0.plane;
   const T* p1 = TWO ? in1 + n * g1.nstride + c * g1.cstride + (int64_t)g1.hlo * g1.plane : nullptr;
   T* po = out + n * go.nstride + c * go.cstride + (int64_t)go.hlo * go.plane;
-  const bool vec = (uintptr_t)p0 % 16 == 0 && (uintptr_t)po % 16 == 0 && (!TWO || (uintptr_t)p1 % 16 == 0);
-  const int64_t stride = (int64_t)gridDim.x * 256;
-  if (vec) {
-    const int64_t nv = run / V;
-    for (int64_t u = (int64_t)blockIdx.x * 256 + threadIdx.x; u < nv; u += stride) {
-      const BnPack<T, V> a = *reinterpret_cast<const BnPack<T, V>*>(p0 + u * V);
-      BnPack<T, V> b, o;
-      if (TWO) b = *reinterpret_cast<const BnPack<T, V>*>(p1 + u * V);
+  constexpr int64_t STEP = (int64_t)256 * V * UN;
+  const int64_t stride = (int64_t)gridDim.x * STEP;
+  int64_t eb = (int64_t)bx * STEP;
+  for (; eb + STEP <= run; eb += stride) {
+    BnPack<T> a[UN], b[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t e = eb + ((int64_t)u * 256 + threadIdx.x) * V;
+      a[u] = bn_load(p0 + e);
+      if (TWO) b[u] = bn_load(p1 + e);
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      BnPack<T> o;
 #pragma unroll
       for (int i = 0; i < V; ++i) {
-        float r = fmaf(ld(&a.v[i]), ka, kc);
-        if (TWO) r = fmaf(ld(&b.v[i]), kb, r);
+        float r = fmaf(ld(&a[u].v[i]), ka, kc);
+        if (TWO) r = fmaf(ld(&b[u].v[i]), kb, r);
         st(&o.v[i], r);
       }
-      *reinterpret_cast<BnPack<T, V>*>(po + u * V) = o;
-    }
-    for (int64_t e = nv * V + (int64_t)blockIdx.x * 256 + threadIdx.x; e < run; e += stride) {
-      float r = fmaf(ld(p0 + e), ka, kc);
-      if (TWO) r = fmaf(ld(p1 + e), kb, r);
-      st(po + e, r);
-    }
-  } else {
-    for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < run; e += stride) {
-      float r = fmaf(ld(p0 + e), ka, kc);
-      if (TWO) r = fmaf(ld(p1 + e), kb, r);
-      st(po + e, r);
+      store16(po + eb + ((int64_t)u * 256 + threadIdx.x) * V, &o, past_cache);
     }
   }
+  // the last, partial step of the run, element by element (at most one block has one)
+  if (eb < run)
+    for (int64_t e = eb + threadIdx.x; e < run; e += 256) {
+      float r = fmaf(ld(p0 + e), ka, kc);
+      if (TWO) r = fmaf(ld(p1 + e), kb, r);
+      st(po + e, r);
+    }
 }
 
-// coefficient tables from the per-channel parameters
-__global__ void bn_coef_fwd_kernel(const float* mean, const float* invstd, const float* gamma, const float* beta, float* coef, int c) {
-  const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-  if (ch >= c) return;
-  const float a = (gamma ? gamma[ch] : 1.f) * invstd[ch];
-  coef[4 * ch] = a; coef[4 * ch + 1] = 0.f; coef[4 * ch + 2] = (beta ? beta[ch] : 0.f) - mean[ch] * a; coef[4 * ch + 3] = 0.f;
-}
-__global__ void bn_coef_bwd_kernel(const float* mean, const float* invstd, const float* gamma, const float* sum_dy,
-                                   const float* sum_dy_xhat, float inv_count, float* coef, int c) {
-  const int ch = blockIdx.x * blockDim.x + threadIdx.x;
-  if (ch >= c) return;
-  const float k1 = (gamma ? gamma[ch] : 1.f) * invstd[ch];
-  const float m1 = sum_dy[ch] * inv_count, m2 = sum_dy_xhat[ch] * inv_count;
-  // dx = k1 * (dy - m1 - (x - mean) * invstd * m2)
-  coef[4 * ch] = k1; coef[4 * ch + 1] = -k1 * invstd[ch] * m2; coef[4 * ch + 2] = k1 * (mean[ch] * invstd[ch] * m2 - m1); coef[4 * ch + 3] = 0.f;
-}
 __global__ void bn_finalize_kernel(const float* s, const float* sq, double inv_count, float eps, float* mean, float* invstd, int c) {
   const int ch = blockIdx.x * blockDim.x + threadIdx.x;
   if (ch >= c) return;
@@ -191,8 +192,7 @@ BnArgs bn_args(const h3d_tensor* x, const h3d_tensor* y) {
 size_t bn_ws(const h3d_tensor* x) {
   const int64_t run = (int64_t)x->d * x->h * x->w;
   const int64_t segs = std::max<int64_t>(1, cdiv(run, BN_SEG));
-  // partial sums [c][n * segs][2] and, behind them, the coefficient table [c][4]
-  return (size_t)(((int64_t)x->c * x->n * segs * 2 + (int64_t)x->c * 4) * sizeof(float) + 255) & ~(size_t)255;
+  return (size_t)((int64_t)x->c * x->n * segs * 2 * sizeof(float) + 255) & ~(size_t)255;      // partial sums [c][n * segs][2]
 }
 
 template <typename T, int MODE>
@@ -203,30 +203,26 @@ h3d_status bn_sums(void* handle, const h3d_tensor* x, const h3d_tensor* dy, cons
   if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn: workspace too small");
   const BnArgs a = bn_args(x, dy);
   if ((int64_t)x->n * a.run == 0) {
-    hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 64)), dim3(64), 0, s, (const float*)ws, o0, o1, x->c, 0);
+    hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 4)), dim3(256), 0, s, (const float*)ws, o0, o1, x->c, 0);
     return launch_status(handle, "bn_sums");
   }
   hipLaunchKernelGGL((bn_partial_kernel<T, MODE>), dim3((unsigned)a.segs, (unsigned)x->c, (unsigned)x->n), dim3(256), 0, s,
                      (const T*)x->data, dy ? (const T*)dy->data : nullptr, mean, invstd, (float*)ws, a);
-  hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 64)), dim3(64), 0, s, (const float*)ws, o0, o1, x->c, x->n * a.segs);
+  hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 4)), dim3(256), 0, s, (const float*)ws, o0, o1, x->c, x->n * a.segs);
   return launch_status(handle, "bn_sums");
 }
 
 template <typename T, bool TWO>
-h3d_status bn_apply(void* handle, const h3d_tensor* in0, const h3d_tensor* in1, h3d_tensor* out, const float* coef, hipStream_t s) {
+h3d_status bn_apply(void* handle, const h3d_tensor* in0, const h3d_tensor* in1, h3d_tensor* out, const BnCoef& q, hipStream_t s) {
   const int64_t run = (int64_t)in0->d * in0->h * in0->w;
   if ((int64_t)in0->n * in0->c * run == 0) return H3D_OK;
   const Geo g0 = make_geo(in0), g1 = in1 ? make_geo(in1) : g0, go = make_geo(out);
-  const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(run, 256 * 8 * 4), 1024));
+  const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(run, 256 * (16 / (int64_t)sizeof(T)) * 4), 1024));
   hipLaunchKernelGGL((bn_apply_kernel<T, TWO>), dim3(gx, (unsigned)in0->c, (unsigned)in0->n), dim3(256), 0, s, (const T*)in0->data,
-                     in1 ? (const T*)in1->data : nullptr, (T*)out->data, coef, g0, g1, go, run);
+                     in1 ? (const T*)in1->data : nullptr, (T*)out->data, q, g0, g1, go, run,
+                     (int64_t)in0->n * in0->c * run * (int64_t)sizeof(T) >= STREAM_PAST_CACHE_BYTES && run % (16 / sizeof(T)) == 0 && (uintptr_t)out->data % 16 == 0 &&
+                         go.plane * go.hlo % (16 / sizeof(T)) == 0 && go.cstride % (16 / sizeof(T)) == 0);
   return launch_status(handle, "bn_apply");
-}
-
-float* bn_coef_ptr(void* ws, const h3d_tensor* x) {
-  const int64_t run = (int64_t)x->d * x->h * x->w;
-  const int64_t segs = std::max<int64_t>(1, cdiv(run, BN_SEG));
-  return (float*)ws + (int64_t)x->c * x->n * segs * 2;
 }
 
 }  // namespace
@@ -267,10 +263,9 @@ extern "C" h3d_status h3d_bn_fwd(void* handle, const h3d_tensor* x, const float*
   if (x->c == 0) return H3D_OK;
   if (!mean || !invstd) return fail(handle, H3D_EINVAL, "bn_fwd: NULL statistics");
   if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn_fwd: workspace too small");
-  float* coef = bn_coef_ptr(ws, x);
+  const BnCoef q{mean, invstd, gamma, beta, nullptr, nullptr, 0.f};
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(bn_coef_fwd_kernel, dim3((unsigned)cdiv(x->c, 64)), dim3(64), 0, s, mean, invstd, gamma, beta, coef, x->c);
-  return x->dtype == H3D_F32 ? bn_apply<float, false>(handle, x, nullptr, y, coef, s) : bn_apply<bf16_t, false>(handle, x, nullptr, y, coef, s);
+  return x->dtype == H3D_F32 ? bn_apply<float, false>(handle, x, nullptr, y, q, s) : bn_apply<bf16_t, false>(handle, x, nullptr, y, q, s);
 }
 
 extern "C" h3d_status h3d_bn_bwd_stats(void* handle, const h3d_tensor* dy, const h3d_tensor* x, const float* mean,
@@ -298,9 +293,7 @@ extern "C" h3d_status h3d_bn_bwd(void* handle, const h3d_tensor* dy, const h3d_t
   if (x->c == 0) return H3D_OK;
   if (!mean || !invstd || !sum_dy || !sum_dy_xhat) return fail(handle, H3D_EINVAL, "bn_bwd: NULL pointer");
   if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn_bwd: workspace too small");
-  float* coef = bn_coef_ptr(ws, x);
+  const BnCoef q{mean, invstd, gamma, nullptr, sum_dy, sum_dy_xhat, (float)(1.0 / (double)count)};
   hipStream_t s = (hipStream_t)stream;
-  hipLaunchKernelGGL(bn_coef_bwd_kernel, dim3((unsigned)cdiv(x->c, 64)), dim3(64), 0, s, mean, invstd, gamma, sum_dy, sum_dy_xhat,
-                     (float)(1.0 / (double)count), coef, x->c);
-  return x->dtype == H3D_F32 ? bn_apply<float, true>(handle, dy, x, dx, coef, s) : bn_apply<bf16_t, true>(handle, dy, x, dx, coef, s);
+  return x->dtype == H3D_F32 ? bn_apply<float, true>(handle, dy, x, dx, q, s) : bn_apply<bf16_t, true>(handle, dy, x, dx, q, s);
 }

@@ -121,6 +121,20 @@ __device__ __forceinline__ void lds_dma16_row(h3d_i32x4 rs, uint32_t lds_byte_ad
                :: "s"(lds_byte_addr), "v"(voff), "s"(rs), "s"(soff) : "memory", "m0");
 }
 
+// ---- stores of streaming passes ---------------------------------------------------------------------------------------
+// A result larger than the last-level cache can keep for its reader goes past it (non-temporal): written through the cache, its
+// dirty lines are evicted in the way of the following pass's reads.  Batch normalisation of 4 x 16 x 128^3 bf16, five passes:
+// 387 -> 346 us; a result of 2 x 16 x 128^3 (134 MB) 188 -> 169; smaller ones stay in the 256 MB cache for whoever reads them next.
+// A wavefront's store has to cover whole lines (pool_bwd_mask_kernel).
+constexpr int64_t STREAM_PAST_CACHE_BYTES = (int64_t)1 << 27;
+typedef unsigned int h3d_u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void store16(void* p, const void* v, bool past_cache) {
+  h3d_u32x4 t;
+  __builtin_memcpy(&t, v, 16);
+  if (past_cache) __builtin_nontemporal_store(t, reinterpret_cast<h3d_u32x4*>(p));
+  else __builtin_memcpy(p, &t, 16);
+}
+
 template <typename T> struct dtype_of;
 template <> struct dtype_of<float> { static constexpr int value = H3D_F32; };
 template <> struct dtype_of<bf16_t> { static constexpr int value = H3D_BF16; };

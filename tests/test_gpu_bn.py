@@ -85,3 +85,42 @@ def test_bn_rejects_mismatched_shards_and_small_workspace():
         h3d.bn_fwd(xg, m, m, None, None, yg)
     with pytest.raises(h3d.H3DError):
         h3d._check(h3d.lib().h3d_bn_stats(h3d.handle(), __import__("ctypes").byref(xg.desc()), h3d._ptr(m), h3d._ptr(m), None, 0, None))
+
+
+@pytest.mark.parametrize("shape", [
+    (2, 3, 5, 7, 9),             # a run of 315 elements: less than one step of a block, channels at odd addresses
+    (1, 2, 16, 24, 43),          # 16512 = two whole steps of the affine pass and a rest, one segment of the sums
+    (1, 1, 33, 64, 64),          # 135168 elements: a second segment of 4096
+    (1, 17, 64, 256, 256),       # 143 MB: written past the cache
+])
+def test_bn_steps_and_tails(shape):
+    """Edges of the blocks' steps and segments against float64; the sums to 1e-5 of the sum of magnitudes (fp32 partial sums of at most
+    2^17 terms), the affine results to half a unit of the eighth bit."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, C, D, H, W = shape
+    g = torch.Generator(device="cuda")
+    g.manual_seed(11)
+    x = torch.randn(shape, generator=g, device="cuda").mul_(0.7).add_(0.3).to(torch.bfloat16)
+    dy = torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    vec = lambda: torch.empty(C, device="cuda")
+    s, sq, mean, inv, sdy, sdx = (vec() for _ in range(6))
+    gamma, beta = torch.rand(C, generator=g, device="cuda") + 0.5, torch.rand(C, generator=g, device="cuda")
+    ws, xs, dys = h3d.Workspace(), h3d.Slab(x), h3d.Slab(dy)
+    y, dx = h3d.Slab(torch.full_like(x, 7.0)), h3d.Slab(torch.full_like(x, 7.0))
+    count = N * D * H * W
+    h3d.bn_stats(xs, s, sq, ws)
+    h3d.bn_finalize(s, sq, count, 1e-5, mean, inv)
+    h3d.bn_fwd(xs, mean, inv, gamma, beta, y, ws)
+    h3d.bn_bwd_stats(dys, xs, mean, inv, sdy, sdx, ws)
+    h3d.bn_bwd(dys, xs, mean, inv, gamma, sdy, sdx, count, dx, ws)
+    per = lambda v: v.double().view(1, -1, 1, 1, 1)
+    ax = (0, 2, 3, 4)
+    X, G = x.double(), dy.double()
+    xhat = (X - per(mean)) * per(inv)
+    for got, want in ((s, X), (sq, X * X), (sdy, G), (sdx, G * xhat)):
+        assert float(((got.double() - want.sum(ax)).abs() / want.abs().sum(ax)).max()) <= 1e-5
+    ref_y = per(gamma) * xhat + per(beta)
+    ref_dx = per(gamma * inv) * (G - per(sdy / count) - xhat * per(sdx / count))
+    for got, ref in ((y.t, ref_y), (dx.t, ref_dx)):
+        assert float(((got.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-5
