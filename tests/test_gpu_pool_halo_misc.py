@@ -408,3 +408,25 @@ def test_deconv_writes_and_reads_channel_views():
     assert torch.equal(dw1, dw2) and torch.equal(db1, db2)
     dwo, dbo = orc.deconv2_bwd_filter(xo, orc.Slab(from_dev(dupc.t), 0, 0, 4, 16))
     close(from_dev(dw1), dwo, 2e-4, "deconv dw from a view")
+
+
+@pytest.mark.parametrize("cin,cout,shape", [(24, 40, (13, 96, 136)), (40, 70, (7, 100, 128))])
+def test_deconv_past_the_cache_equals_its_samples(cin, cout, shape):
+    """From 128 MiB of fine tensor the bf16 kernels store and load it past the last-level cache: a call of two samples of about
+    100 MB each takes that form, one of a single sample does not, and a voxel's sum is the same one, so the bits are the same."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    d, h, w = shape
+    gen = torch.Generator(device="cuda").manual_seed(cin)
+    rand = lambda *s: torch.randn(s, device="cuda", generator=gen).bfloat16()
+    x, wt, bias = rand(2, cin, d, h, w), rand(cin, cout, 2, 2, 2), torch.randn(cout, device="cuda", generator=gen)
+    dy = rand(2, cout, 2 * d, 2 * h, 2 * w)
+    assert dy.numel() * 2 >= 1 << 27 > dy[:1].numel() * 2
+    y, dx = torch.full_like(dy, float("nan")), torch.full_like(x, float("nan"))
+    h3d.deconv2_fwd(h3d.Slab(x), wt, bias, h3d.Slab(y))
+    h3d.deconv2_bwd_data(h3d.Slab(dy), wt, h3d.Slab(dx))
+    for n in range(2):
+        y1, dx1 = torch.empty_like(dy[:1]), torch.empty_like(x[:1])
+        h3d.deconv2_fwd(h3d.Slab(x[n:n + 1]), wt, bias, h3d.Slab(y1))
+        h3d.deconv2_bwd_data(h3d.Slab(dy[n:n + 1]), wt, h3d.Slab(dx1))
+        assert torch.equal(y[n:n + 1], y1) and torch.equal(dx[n:n + 1], dx1)
