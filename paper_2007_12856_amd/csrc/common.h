@@ -45,6 +45,10 @@ inline Geo make_geo(const h3d_tensor* t) {
   return g;
 }
 
+// elements from a sample's first stored one to behind its last: what a wide load may touch.  A view's nstride is its parent's and reaches
+// past the parent's end when the view does not start at channel 0.
+__host__ __device__ inline int64_t stored_span(const Geo& g) { return (g.c - 1) * g.cstride + g.ds * g.plane; }
+
 inline bool is_packed(const h3d_tensor* t) { return t->c_stride == 0 && t->n_stride == 0; }
 // elements spanned by one sample (all channels), with the tensor's real strides
 inline int64_t sample_span(const h3d_tensor* t) {

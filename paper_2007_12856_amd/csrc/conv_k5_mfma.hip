@@ -87,7 +87,7 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
     wv3 = ws[min(1536, T::WU - 1 - tid)];
     // descriptor of the chunk's channels: byte offsets inside 16 channels are 32-bit whatever the sample's size
     const int64_t base = (int64_t)c * 16 * cstride;
-    const int span = (int)min(a.in.nstride - base, (int64_t)16 * cstride);
+    const int span = (int)min(stored_span(a.in) - base, (int64_t)16 * cstride);
     const __amdgpu_buffer_rsrc_t rs = row_rsrc(is + base, (uint32_t)span * 2);
     const int o = off + (pp + a.in.hlo) * (int)a.in.plane;
 #pragma unroll
@@ -102,7 +102,7 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
     lds[tid + 1536 < T::WU ? buf * T::BUF + 2 * T::CIG + tid + 1536 : T::TRASH + lane] = wv3;
   };
   auto store_rows = [&](int c, int pp, int buf) {
-    const int span = (int)min(a.in.nstride - (int64_t)c * 16 * cstride, (int64_t)16 * cstride);
+    const int span = (int)min(stored_span(a.in) - (int64_t)c * 16 * cstride, (int64_t)16 * cstride);
     const int o = off + (pp + a.in.hlo) * (int)a.in.plane;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = fix8<V16>(v[e], o + e * cstride, col, W, span);
@@ -418,10 +418,10 @@ __global__ void __launch_bounds__(320 * KF_GROUPS) k5_bwf_rows_kernel(const bf16
 }
 
 // ----------------------------------------------------------------------------------------------------------------- host
-// byte offsets inside a block of 32 channels are 32-bit
+// byte offsets inside a block of 32 channels are 32-bit; a block may be one channel, and a 16-byte load has to fit it
 bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z) {
   return x->dtype == H3D_BF16 && make_geo(x).cstride < ((int64_t)1 << 25) && make_geo(z).cstride < ((int64_t)1 << 25) &&
-         sample_span(x) >= 8 && sample_span(z) >= 8 && (int64_t)z->n * z->d * z->h * cdiv(z->w, 32) < ((int64_t)1 << 28);
+         make_geo(x).plane >= 8 && make_geo(z).plane >= 8 && (int64_t)z->n * z->d * z->h * cdiv(z->w, 32) < ((int64_t)1 << 28);
 }
 size_t k5_mfma_wp_bytes(int rows, int contraction) { return (size_t)cdiv(rows, 32) * cdiv(contraction, 16) * 125 * 1024; }
 

@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
 #pragma unroll
       for (int r = 0; r < NR; ++r) {
         const bool ok = (meta[r] & 256) && c0 + 8 * (meta[r] & 7) < a.cin;
-        v[r][e] = row8<V16>(rs, off[r] + c0 * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)a.x.nstride, ok);
+        v[r][e] = row8<V16>(rs, off[r] + c0 * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)stored_span(a.x), ok);
       }
       lv[e] = row1(rs, loff + c0 * cstride, 2 * w0 - 1, W, (lmeta & 256) && c0 + 8 * (lmeta & 7) < a.cin);
     }
@@ -138,7 +138,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
       if (tid + 256 * r >= NITEM) continue;
 #pragma unroll
       for (int e = 0; e < 8; ++e)
-        v[r][e] = fix8<V16>(v[r][e], off[r] + (st * 32 + e) * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)a.x.nstride);
+        v[r][e] = fix8<V16>(v[r][e], off[r] + (st * 32 + e) * cstride, 2 * w0 + 8 * ((tid + 256 * r) & 7), W, (int)stored_span(a.x));
       uint4* dst = lds + (meta[r] >> 9);
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
@@ -319,8 +319,8 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
     for (int e = 0; e < 4; ++e) {
       const bool ok = ok0 && c * 16 + cq * 4 + e < a.cout;
       if (full) {
-        v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)a.y.nstride, ok);
-        if (MASKED) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)a.m.nstride, ok);
+        v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y), ok);
+        if (MASKED) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m), ok);
       } else if (tail) {
         v[e].x = row1(rs, off + (c * 16 + e) * cstride, col, W2, ok);
         if (MASKED) mv[e].x = row1(rm, moff + (c * 16 + e) * mcs, col, W2, ok);
@@ -337,8 +337,8 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
     if (full) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)a.y.nstride);
-        if (MASKED) v[e] = s2_mask8(v[e], fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)a.m.nstride), a.slope);
+        v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y));
+        if (MASKED) v[e] = s2_mask8(v[e], fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)), a.slope);
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) half[2 * k] = column_half(v, k);
@@ -462,15 +462,15 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
       const int ci = x_ci + 32 * (i & 1), row = 2 * h + (i >> 1);
-      xv[i] = row8<V16>(rx, xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)a.x.nstride, !first && xrow_ok && ci < a.cin && row < H);
+      xv[i] = row8<V16>(rx, xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)stored_span(a.x), !first && xrow_ok && ci < a.cin && row < H);
     }
     const bool gok = g_co < a.cout && h + 1 < H2;
     go = g_co * (int)a.y.cstride + (z + a.y.hlo) * (int)a.y.plane + (h + 1) * W2;
-    gv = row8<V16>(rg, go, gc, W2, (int)a.y.nstride, gok);
+    gv = row8<V16>(rg, go, gc, W2, (int)stored_span(a.y), gok);
     ge = row1(rg, go, w0 + 32, W2, gok && g_piece == 3);
     if (MASKED) {
       mo = g_co * (int)a.m.cstride + (z + a.m.hlo) * (int)a.m.plane + (h + 1) * W2;
-      mv = row8<V16>(rm, mo, gc, W2, (int)a.m.nstride, gok);
+      mv = row8<V16>(rm, mo, gc, W2, (int)stored_span(a.m), gok);
       me = row1(rm, mo, w0 + 32, W2, gok && g_piece == 3);
     }
     count_db = h + 1 < hend;
@@ -481,11 +481,11 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       dst[((i >> 1) * 64 + (tid >> 3) + 32 * (i & 1)) * SB_XP + x_piece] =
-          fix8<V16>(xv[i], xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)a.x.nstride);
-    uint4 g = fix8<V16>(gv, go, gc, W2, (int)a.y.nstride);
+          fix8<V16>(xv[i], xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)stored_span(a.x));
+    uint4 g = fix8<V16>(gv, go, gc, W2, (int)stored_span(a.y));
     uint32_t e = ge;
     if (MASKED) {
-      g = s2_mask8(g, fix8<V16>(mv, mo, gc, W2, (int)a.m.nstride), a.slope);
+      g = s2_mask8(g, fix8<V16>(mv, mo, gc, W2, (int)stored_span(a.m)), a.slope);
       e = s2_mask2(e, me, a.slope) & 0xffffu;
     }
     dst[SB_X + (tid >> 2) * SB_GP + g_piece] = g;
@@ -586,7 +586,7 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
 
 // ------------------------------------------------------------------------------------------------------------- host
 // Byte offsets inside a sample are 32-bit (channels are counted up to the next multiple of 64).
-static bool s2_offsets_fit(const h3d_tensor* t, int bits) { return cdiv(t->c, 64) * 64 * make_geo(t).cstride < ((int64_t)1 << bits) && sample_span(t) >= 8; }
+static bool s2_offsets_fit(const h3d_tensor* t, int bits) { return cdiv(t->c, 64) * 64 * make_geo(t).cstride < ((int64_t)1 << bits) && stored_span(make_geo(t)) >= 8; }
 // x: fine side, y: coarse side.  A saved output may store more halo planes than the gradient it belongs to: its own test
 // (s2_mask_fits) leaves it four times the room, and what does not pass it takes the general route.
 bool s2_mask_fits(const h3d_tensor* m) { return s2_offsets_fit(m, 30); }

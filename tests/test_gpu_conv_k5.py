@@ -7,7 +7,7 @@ import pytest
 
 import oracle as orc
 import synth
-from helpers import TOL, cut, dev_like, from_dev, quantize, close, rel_l2, slab_pair, to_dev
+from helpers import TOL, cut, dev_like, elem_masked_bf, from_dev, quantize, close, rel_l2, slab_pair, to_dev
 
 pytestmark = pytest.mark.gpu
 SEED = synth.BASE_SEED
@@ -239,6 +239,8 @@ def test_k5_empty_shard():
     ((2, 20, 40, 6, 3, 72), 0),      # columns of three rows: a wavefront group's run spans many, the second segment is 8 wide
     ((1, 9, 33, 3, 40, 24), 1),      # whole 16-byte rows at an odd address
     ((1, 33, 9, 3, 19, 45), 3),      # ragged rows at an odd address
+    ((1, 17, 33, 2, 2, 3), 0),       # a block of one channel with planes shorter than a 16-byte load
+    ((1, 17, 33, 1, 2, 5), 1),       # and one that a load just fits
 ])
 def test_k5_bf16_kernel_edges(shape, shift, act):
     import torch
@@ -264,5 +266,7 @@ def test_k5_bf16_kernel_edges(shape, shift, act):
     dwo, dbo = orc.convk_bwd_filter(5, xo, go, so, act, 0.01)
     dw, db = torch.empty((Co, Ci, 5, 5, 5), device="cuda"), torch.empty((Co,), device="cuda")
     h3d.conv3d_k5_bwd_filter(moved(xg), moved(gg), moved(sg), dw, db, act, 0.01)
-    close(from_dev(dw), dwo, 2e-4)
-    close(from_dev(db), dbo, 2e-4)
+    # a masked gradient is rounded to bf16 once (2^-9 an element): sums over a dozen voxels, as in the smallest shape, show it
+    elem = elem_masked_bf("bf16") if act != orc.ACT_NONE and D * H * W < 64 else None
+    close(from_dev(dw), dwo, 2e-4, elem=elem)
+    close(from_dev(db), dbo, 2e-4, elem=elem)
