@@ -17,13 +17,11 @@
 // kernel adds the chunks in order, so the result is reproducible.
 #include <algorithm>
 
-#include "common.h"
+#include "rowload.h"
 
 namespace h3d {
 
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 namespace {
 
@@ -50,8 +48,12 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t db_rsrc(const void* base, uint
 // global -> LDS copy issued so that the compiler does not wait for it before later LDS reads (common.h)
 __device__ __forceinline__ void db_dma16(h3d_i32x4 rs, uint4* lds_dst, int voff) { lds_dma16(rs, lds_addr_of(lds_dst), voff); }
 
-template <int MRB>
-__global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
+// V16: rows of whole aligned 16-byte pieces, x copied straight into LDS.  Otherwise (any width and alignment) x passes through
+// registers on its way, fetched a tile ahead, and both operands are cut at the end of the row: what lies behind it belongs to the
+// next row and may be infinite.  The direct kernel, which such widths had to take, gives a lane one voxel and reads dy once per
+// input channel: 128 -> 64 channels from 64x256x248 11650 -> 215 us, 64 -> 32 from 32x192x196 706 -> 46.
+template <int MRB, bool V16>
+__global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 8 ? 4 : 2) deconv_bf_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                                      float* __restrict__ part, DbfArgs a) {
   constexpr int CI_WG = 16 * MRB;
   constexpr int XPAD = (CI_WG * DB_PCI + 63) / 64 * 64;
@@ -97,6 +99,27 @@ __global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf1
         db_dma16(rs, lds + buf * XPAD + 64 * (wave + DB_NW * i), ok ? 2 * (t0 + ci * (int)a.x.cstride + row * Wc + u8) : DB_OOB);
     }
   };
+  // the same through registers: piece i of a thread is channel (tid + 512 i) / 16, row and unit from the low bits of tid
+  constexpr int XR = V16 ? 1 : CI_WG * 4 * DB_R / (64 * DB_NW);
+  uint4 xv[XR];
+  const int xr_row = (tid >> 2) & 3, xr_u = tid & 3;
+  const int xspan = (int)stored_span(a.x), yspan = (int)stored_span(a.y);
+  auto fetch_x = [&](int n, int d, int h0, int w0) {
+    const __amdgpu_buffer_rsrc_t rs = row_rsrc(x + n * a.x.nstride, (uint32_t)xspan * 2);
+    const int o = (d + a.x.hlo) * (int)a.x.plane + (h0 + xr_row) * Wc;
+#pragma unroll
+    for (int i = 0; i < XR; ++i) {
+      const int ci = ci0 + (tid >> 4) + 32 * i;
+      xv[i] = row8<false>(rs, o + ci * (int)a.x.cstride, w0 + 8 * xr_u, Wc, xspan, ci < a.cin && h0 + xr_row < Hc);
+    }
+  };
+  auto store_x = [&](int d, int h0, int w0, int buf) {
+    const int o = (d + a.x.hlo) * (int)a.x.plane + (h0 + xr_row) * Wc;
+#pragma unroll
+    for (int i = 0; i < XR; ++i)
+      lds[buf * XPAD + ((tid >> 4) + 32 * i) * DB_PCI + 4 * xr_row + xr_u] =
+          fix8<false>(xv[i], o + (ci0 + (tid >> 4) + 32 * i) * (int)a.x.cstride, w0 + 8 * xr_u, Wc, xspan);
+  };
 
   f32x4 acc[MRB];
   f32x4 accdb = {0.f, 0.f, 0.f, 0.f};
@@ -117,15 +140,29 @@ __global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf1
     d = r % Dc;
     n = r / Dc;
   }
-  if (t_begin < t_end) load_x(n, d, th * DB_R, tw * 32, 0);
+  if (t_begin < t_end) {
+    if constexpr (V16) {
+      load_x(n, d, th * DB_R, tw * 32, 0);
+    } else {
+      fetch_x(n, d, th * DB_R, tw * 32);
+      store_x(d, th * DB_R, tw * 32, 0);
+    }
+  }
   int buf = 0;
   const char* a_base = reinterpret_cast<const char*>(lds) + 16 * (lc * DB_PCI + lg);
   for (int tile = t_begin; tile < t_end; ++tile) {
     const int h0 = th * DB_R, w0 = tw * 32;
     // ---- this tile's dy fragments: 32 contiguous bytes per lane and row, straight from global memory
-    const __amdgpu_buffer_rsrc_t rs_y = db_rsrc(dy + n * a.y.nstride, (uint32_t)a.y.nstride * 2);
+    const __amdgpu_buffer_rsrc_t rs_y = db_rsrc(dy + n * a.y.nstride, (uint32_t)(V16 ? a.y.nstride : yspan) * 2);
     u32x4 braw[DB_R][2];
-    {
+    const int yrow = co * (int)a.y.cstride + (2 * d + ta + a.y.hlo) * (int)a.y.plane + (2 * h0 + tb) * Wf, yc = 2 * (w0 + 8 * lg);
+    if constexpr (!V16) {
+#pragma unroll
+      for (int r = 0; r < DB_R; ++r)
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          braw[r][k] = __builtin_bit_cast(u32x4, row8<false>(rs_y, yrow + 2 * r * Wf, yc + 8 * k, Wf, yspan, col_ok && h0 + r < Hc));
+    } else {
       const int yb = co * (int)a.y.cstride + (2 * d + ta + a.y.hlo) * (int)a.y.plane + (2 * h0 + tb) * Wf + 2 * (w0 + 8 * lg);
 #pragma unroll
       for (int r = 0; r < DB_R; ++r) {
@@ -136,13 +173,16 @@ __global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf1
       }
     }
     // the x tile of this step has landed (issued one step ago); everyone is done with the other buffer
-    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DB_R) : "memory");
+    if constexpr (V16) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DB_R) : "memory");
     __syncthreads();
     int tw2 = tw + 1, th2 = th, d2 = d, n2 = n;
     if (tw2 == a.tiles_w) { tw2 = 0; ++th2; }
     if (th2 == a.tiles_h) { th2 = 0; ++d2; }
     if (d2 == Dc) { d2 = 0; ++n2; }
-    if (tile + 1 < t_end) load_x(n2, d2, th2 * DB_R, tw2 * 32, buf ^ 1);
+    if (tile + 1 < t_end) {
+      if constexpr (V16) load_x(n2, d2, th2 * DB_R, tw2 * 32, buf ^ 1);
+      else fetch_x(n2, d2, th2 * DB_R, tw2 * 32);
+    }
 
     const char* ap = a_base + 16 * XPAD * buf;
 #pragma unroll
@@ -150,6 +190,11 @@ __global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf1
       bf16x8 A[MRB];
 #pragma unroll
       for (int rb = 0; rb < MRB; ++rb) A[rb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(ap + 16 * (rb * 16 * DB_PCI + 4 * r)));
+      if constexpr (!V16) {
+#pragma unroll
+        for (int k = 0; k < 2; ++k)
+          braw[r][k] = __builtin_bit_cast(u32x4, fix8<false>(__builtin_bit_cast(uint4, braw[r][k]), yrow + 2 * r * Wf, yc + 8 * k, Wf, yspan));
+      }
       uint4 bf;
       bf.x = __builtin_amdgcn_perm(braw[r][0][1], braw[r][0][0], sel);
       bf.y = __builtin_amdgcn_perm(braw[r][0][3], braw[r][0][2], sel);
@@ -160,6 +205,8 @@ __global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf1
       for (int rb = 0; rb < MRB; ++rb) acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[rb], B, acc[rb], 0, 0, 0);
       if (do_db) accdb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, B, accdb, 0, 0, 0);
     }
+    if constexpr (!V16)
+      if (tile + 1 < t_end) store_x(d2, th2 * DB_R, tw2 * 32, buf ^ 1);      // (its readers passed this step's barrier)
     tw = tw2; th = th2; d = d2; n = n2;
     buf ^= 1;
   }
@@ -244,27 +291,44 @@ DbfPlan dbf_plan(const h3d_tensor* x, const h3d_tensor* dy) {
   return p;
 }
 
-template <int MRB>
-h3d_status dbf_launch(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, hipStream_t stream) {
+template <int MRB, bool V16>
+h3d_status dbf_launch_as(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, hipStream_t stream) {
   constexpr size_t lds_bytes = (size_t)2 * ((16 * MRB * DB_PCI + 63) / 64 * 64) * 16;
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_bf_mfma_kernel<MRB>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_bf_mfma_kernel<MRB, V16>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds_bytes) != hipSuccess)
       return fail(handle, H3D_EHIP, "deconv2_bwd_filter: cannot set the dynamic LDS size to %zu bytes", lds_bytes);
     attr_set = true;
   }
   const int64_t grid = cdiv(a.nchunks, 8) * 8 * (int64_t)(a.gco * a.gci);
   if (grid >= ((int64_t)1 << 31)) return fail(handle, H3D_EINVAL, "deconv2_bwd_filter: too many workgroups");
-  hipLaunchKernelGGL((deconv_bf_mfma_kernel<MRB>), dim3((unsigned)grid), dim3(64 * DB_NW), lds_bytes, stream, x, dy, part, a);
+  hipLaunchKernelGGL((deconv_bf_mfma_kernel<MRB, V16>), dim3((unsigned)grid), dim3(64 * DB_NW), lds_bytes, stream, x, dy, part, a);
   return H3D_OK;
+}
+template <int MRB>
+h3d_status dbf_launch(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, bool v16, hipStream_t stream) {
+  return v16 ? dbf_launch_as<MRB, true>(handle, x, dy, part, a, stream) : dbf_launch_as<MRB, false>(handle, x, dy, part, a, stream);
+}
+
+// whole aligned 16-byte pieces in every row of t
+bool rows_v16(const h3d_tensor* t) {
+  const Geo g = make_geo(t);
+  return t->w % 8 == 0 && (uintptr_t)t->data % 16 == 0 && g.cstride % 8 == 0 && g.nstride % 8 == 0;
+}
+// rows read in pieces that may run past their end: a sample holds at least one piece, and 32-bit byte offsets reach all of it
+bool rows_any(const h3d_tensor* t) {
+  const int64_t span = stored_span(make_geo(t));
+  return span >= 8 && span < ((int64_t)1 << 30);
 }
 
 }  // namespace
 
+static bool dbf_v16(const h3d_tensor* x, const h3d_tensor* dy) { return rows_v16(x) && rows_v16(dy); }
+
 bool deconv_bf_mfma_supported(const h3d_tensor* x, const h3d_tensor* dy) {
-  if (x->dtype != H3D_BF16 || x->c < 1 || dy->c < 1 || x->w % 8 != 0) return false;
-  if ((uintptr_t)x->data % 16 != 0 || (uintptr_t)dy->data % 16 != 0) return false;
+  if (x->dtype != H3D_BF16 || x->c < 1 || dy->c < 1) return false;
+  if (!dbf_v16(x, dy) && !(rows_any(x) && rows_any(dy))) return false;
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)dy->c * (dy->halo_lo + dy->d + dy->halo_hi) * dy->h * dy->w * 2;
   const int64_t ntiles = (int64_t)x->n * x->d * cdiv(x->h, DB_R) * cdiv(x->w, 32);
@@ -301,9 +365,10 @@ h3d_status deconv_bf_mfma(void* handle, const h3d_tensor* x, const h3d_tensor* d
   const bf16_t* xp = (const bf16_t*)x->data;
   const bf16_t* yp = (const bf16_t*)dy->data;
   h3d_status st;
-  if (p.mrb == 8) st = dbf_launch<8>(handle, xp, yp, (float*)ws, a, stream);
-  else if (p.mrb == 4) st = dbf_launch<4>(handle, xp, yp, (float*)ws, a, stream);
-  else st = dbf_launch<2>(handle, xp, yp, (float*)ws, a, stream);
+  const bool v16 = dbf_v16(x, dy);
+  if (p.mrb == 8) st = dbf_launch<8>(handle, xp, yp, (float*)ws, a, v16, stream);
+  else if (p.mrb == 4) st = dbf_launch<4>(handle, xp, yp, (float*)ws, a, v16, stream);
+  else st = dbf_launch<2>(handle, xp, yp, (float*)ws, a, v16, stream);
   if (st != H3D_OK) return st;
   hipLaunchKernelGGL(deconv_bf_mfma_reduce_kernel, dim3((unsigned)cdiv(nw + a.cout, 16)), dim3(256), 0, stream, (const float*)ws, dw,
                      db, nw, a.cout, a.nchunks);
@@ -325,8 +390,6 @@ h3d_status deconv_bf_mfma(void* handle, const h3d_tensor* x, const h3d_tensor* d
 // workgroup, as [co][ci] units with an odd pitch; every dy element is loaded exactly once.
 namespace h3d {
 namespace {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int DD_NW = 8;
 constexpr int DD_BATCH = 8;      // K-steps (pairs of output channels) whose dy loads are in flight together
@@ -541,7 +604,10 @@ __global__ void deconv_fw_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __re
 
 // STREAM (y of at least STREAM_PAST_CACHE_BYTES): written past the last-level cache (whole lines of a fine row leave at once): 128 -> 64
 // channels onto 64x256x256 (537 MB) 171 -> 138 us.
-template <int RBW, int KS, bool STREAM>
+// V16: rows of whole aligned 16-byte pieces; otherwise a piece may run into the next row (those columns are computed and dropped) but
+// not past the sample.  The direct kernel, which such widths had to take, reads x once per 8 output channels: 128 -> 64 channels onto
+// 64x256x248 1088 -> 204 us, 64 -> 32 onto 32x192x196 104 -> 29.
+template <int RBW, int KS, bool STREAM, bool V16>
 __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf16_t* __restrict__ x, const uint4* __restrict__ wp,
                                                                      const float* __restrict__ bias, bf16_t* __restrict__ y,
                                                                      DfwArgs a) {
@@ -583,15 +649,23 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
   // staging: a lane takes one (ci-group, group of 8 voxels) item of its wavefront's column block per round
   constexpr int SROUNDS = (NCIG * 4 + 63) / 64;
   u32x4 sv[SROUNDS][8];
+  const int xspan = (int)stored_span(a.x);
   auto stage_load = [&](int cb0) {
     const int cb = cb0 + wave;
     int n, d, h, w0;
     decode(cb < ncb ? cb : 0, n, d, h, w0);
-    const __amdgpu_buffer_rsrc_t rs = db_rsrc(x + n * a.x.nstride, (uint32_t)a.x.nstride * 2);
+    const __amdgpu_buffer_rsrc_t rs = db_rsrc(x + n * a.x.nstride, (uint32_t)(V16 ? a.x.nstride : xspan) * 2);
 #pragma unroll
     for (int r = 0; r < SROUNDS; ++r) {
       const int item = lane + 64 * r, cig = item >> 2, vg = item & 3;
       const int wv = w0 + 8 * vg;
+      if constexpr (!V16) {
+        const int o = cig * 8 * (int)a.x.cstride + (d + a.x.hlo) * (int)a.x.plane + h * Wc;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          sv[r][e] = __builtin_bit_cast(u32x4, row8<false>(rs, o + e * (int)a.x.cstride, wv, Wc, xspan, cb < ncb && cig < NCIG && cig * 8 + e < a.cin));
+        continue;
+      }
       const bool ok = cb < ncb && cig < NCIG && wv + 8 <= Wc;
       const int base = 2 * (cig * 8 * (int)a.x.cstride + (d + a.x.hlo) * (int)a.x.plane + h * Wc + wv);
 #pragma unroll
@@ -600,12 +674,20 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
                                                          __builtin_amdgcn_readfirstlane(2 * e * (int)a.x.cstride), 0);
     }
   };
-  auto stage_store = [&](int buf) {
+  auto stage_store = [&](int cb0, int buf) {
+    int n, d, h, w0;
+    if constexpr (!V16) decode(cb0 + wave < ncb ? cb0 + wave : 0, n, d, h, w0);
     uint4* dst0 = lds + (buf * DF_CBI + wave) * CBU;
 #pragma unroll
     for (int r = 0; r < SROUNDS; ++r) {
       const int item = lane + 64 * r, cig = item >> 2, vg = item & 3;
       if (cig >= NCIG) continue;
+      if constexpr (!V16) {
+        const int o = cig * 8 * (int)a.x.cstride + (d + a.x.hlo) * (int)a.x.plane + h * Wc;
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+          sv[r][e] = __builtin_bit_cast(u32x4, fix8<false>(__builtin_bit_cast(uint4, sv[r][e]), o + e * (int)a.x.cstride, w0 + 8 * vg, Wc, xspan));
+      }
       uint4* dst = dst0 + cig * 32 + 8 * vg;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {       // dword j of each channel = voxels 2j, 2j+1 of the group
@@ -620,7 +702,7 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
     }
   };
 
-  if (it0 < ncb) { stage_load(it0); stage_store(0); }
+  if (it0 < ncb) { stage_load(it0); stage_store(it0, 0); }
   __syncthreads();
   int buf = 0;
   for (int cb0 = it0; cb0 < ncb; cb0 += it_stride, buf ^= 1) {
@@ -664,38 +746,39 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
         }
       }
     }
-    if (more) stage_store(buf ^ 1);
+    if (more) stage_store(cb0 + it_stride, buf ^ 1);
     __syncthreads();
   }
 }
 
-template <int RBW, int KS, bool STREAM>
+template <int RBW, int KS, bool STREAM, bool V16>
 h3d_status dfw_launch_as(void* handle, const bf16_t* x, const uint4* wp, const float* bias, bf16_t* y, const DfwArgs& a,
                       hipStream_t stream) {
   constexpr size_t lds_bytes = (size_t)2 * DF_CBI * (2 * KS * 32 + 4) * 16;
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_fw_mfma_kernel<RBW, KS, STREAM>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_fw_mfma_kernel<RBW, KS, STREAM, V16>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds_bytes) != hipSuccess)
       return fail(handle, H3D_EHIP, "deconv2_fwd: cannot set the dynamic LDS size to %zu bytes", lds_bytes);
     attr_set = true;
   }
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu, cdiv(a.ncb, DF_CBI)));
-  hipLaunchKernelGGL((deconv_fw_mfma_kernel<RBW, KS, STREAM>), dim3((unsigned)grid), dim3(64 * DF_NW), lds_bytes, stream, x, wp, bias, y, a);
+  hipLaunchKernelGGL((deconv_fw_mfma_kernel<RBW, KS, STREAM, V16>), dim3((unsigned)grid), dim3(64 * DF_NW), lds_bytes, stream, x, wp, bias, y, a);
   return H3D_OK;
 }
 template <int RBW, int KS>
-h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const float* bias, bf16_t* y, const DfwArgs& a, hipStream_t stream) {
-  return fine_bytes(a.y, a.cout) >= STREAM_PAST_CACHE_BYTES ? dfw_launch_as<RBW, KS, true>(handle, x, wp, bias, y, a, stream)
-                                                            : dfw_launch_as<RBW, KS, false>(handle, x, wp, bias, y, a, stream);
+h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const float* bias, bf16_t* y, const DfwArgs& a, bool v16, hipStream_t stream) {
+  if (!v16) return dfw_launch_as<RBW, KS, false, false>(handle, x, wp, bias, y, a, stream);
+  return fine_bytes(a.y, a.cout) >= STREAM_PAST_CACHE_BYTES ? dfw_launch_as<RBW, KS, true, true>(handle, x, wp, bias, y, a, stream)
+                                                            : dfw_launch_as<RBW, KS, false, true>(handle, x, wp, bias, y, a, stream);
 }
 
 }  // namespace
 
 bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
-  if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > 64 || x->w % 8 != 0) return false;
-  if ((uintptr_t)x->data % 16 != 0 || (uintptr_t)y->data % 4 != 0) return false;
+  if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > 64 || (uintptr_t)y->data % 4 != 0) return false;
+  if (!rows_v16(x) && !rows_any(x)) return false;
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)y->c * (y->halo_lo + y->d + y->halo_hi) * y->h * y->w * 2;
   const int64_t ncb = (int64_t)x->n * x->d * x->h * cdiv(x->w, 32);
@@ -723,8 +806,9 @@ h3d_status deconv_fw_mfma(void* handle, const h3d_tensor* x, const void* w, cons
   bf16_t* yp = (bf16_t*)y->data;
   const uint4* wq = (const uint4*)ws;
   h3d_status st;
-  if (ks == 8) st = rbw == 2 ? dfw_launch<2, 8>(handle, xp, wq, bias, yp, a, stream) : dfw_launch<1, 8>(handle, xp, wq, bias, yp, a, stream);
-  else st = rbw == 2 ? dfw_launch<2, 4>(handle, xp, wq, bias, yp, a, stream) : dfw_launch<1, 4>(handle, xp, wq, bias, yp, a, stream);
+  const bool v16 = rows_v16(x);
+  if (ks == 8) st = rbw == 2 ? dfw_launch<2, 8>(handle, xp, wq, bias, yp, a, v16, stream) : dfw_launch<1, 8>(handle, xp, wq, bias, yp, a, v16, stream);
+  else st = rbw == 2 ? dfw_launch<2, 4>(handle, xp, wq, bias, yp, a, v16, stream) : dfw_launch<1, 4>(handle, xp, wq, bias, yp, a, v16, stream);
   if (st != H3D_OK) return st;
   return launch_status(handle, "deconv2_fwd_mfma");
 }

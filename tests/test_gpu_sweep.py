@@ -99,3 +99,38 @@ def test_deconv_sweep_bf16(case):
     h3d.deconv2_bwd_filter(xg, dyg, dw, db)
     close(from_dev(dw), dwo, 2e-4)
     close(from_dev(db), dbo, 2e-4)
+
+
+@pytest.mark.parametrize("case", [(0, 1, 33, 20, 2, 5, 7, 0), (1, 2, 16, 17, 1, 3, 33, 1), (2, 1, 70, 64, 3, 4, 45, 2), (3, 1, 128, 24, 1, 2, 3, 0),
+                                  (4, 1, 5, 9, 2, 1, 40, 1), (5, 3, 100, 34, 2, 9, 100, 0), (6, 1, 1, 1, 1, 2, 4, 2)])
+def test_deconv_ragged_rows_bf16(case):
+    """Rows that are no whole aligned 16-byte pieces (any width, data at an odd address), between NaNs: what a piece reads beyond its
+    row or tensor must not reach a result."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    i, N, cin, cout, d, H, W, shift = case
+    print("deconv ragged", case, flush=True)
+
+    def moved(s, even=False):
+        k = shift & ~1 if even else shift
+        flat = torch.full((s.t.numel() + 32,), float("nan"), dtype=s.t.dtype, device="cuda")[k:k + s.t.numel()]
+        return h3d.Slab(flat.view(s.t.shape).copy_(s.t), s.halo_lo, s.halo_hi, s.d_offset, s.d_global)
+
+    b = np.sqrt(3.0 / (8 * cin))
+    w = quantize(synth.flat("uniform", SEED, 5600 + i, (cin, cout, 2, 2, 2), -b, b), "bf16")
+    bias = synth.round_f32(synth.flat("uniform", SEED, 5700 + i, (cout,), -0.1, 0.1)).astype(np.float64)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 5800 + i, (N, cin, d, H, W)), "bf16")
+    xg = moved(xg)
+    yo = orc.deconv2_fwd(xo, w, bias)
+    yg = moved(dev_like(yo, "bf16"), even=True)      # (odd result addresses keep the general kernel)
+    h3d.deconv2_fwd(xg, to_dev(w, "bf16"), to_dev(bias, "f32"), yg)
+    close(from_dev(yg.t), yo.a, TOL["bf16"])
+    dyo, dyg = slab_pair(synth.flat("normal", SEED, 5900 + i, yo.a.shape), "bf16", (0, 0), yo.d_offset, yo.d_global)
+    dxo = orc.deconv2_bwd_data(dyo, w)
+    dxg = h3d.deconv2_bwd_data(moved(dyg, even=True), to_dev(w, "bf16"), moved(dev_like(dxo, "bf16")))
+    close(from_dev(dxg.t), dxo.a, TOL["bf16"])
+    dwo, dbo = orc.deconv2_bwd_filter(xo, dyo)
+    dw, db = torch.empty((cin, cout, 2, 2, 2), device="cuda"), torch.empty((cout,), device="cuda")
+    h3d.deconv2_bwd_filter(xg, moved(dyg), dw, db)
+    close(from_dev(dw), dwo, 2e-4)
+    close(from_dev(db), dbo, 2e-4)
