@@ -8,39 +8,63 @@ namespace h3d {
 
 struct ActArgs {
   Geo dz, dz2, z, g;
-  int64_t total;   // n*c*d*h*(w/VEC)
-  int wv;
+  int64_t run;     // d*h*w: a channel's interior is one run of elements in every tensor
+  int64_t units;   // pieces of 16 bytes (the last one may be shorter) in a run
+  int64_t total;   // n*c*units
   float slope;
 };
 
-template <typename T, int N>
-struct alignas(sizeof(T) * N) AVec {
-  T v[N];
-};
-
-template <typename T, int VEC, bool TWO>
-__global__ void __launch_bounds__(256) act_bwd_kernel(const T* __restrict__ dz, const T* __restrict__ dz2, const T* __restrict__ z,
-                                                      T* __restrict__ g, ActArgs a) {
-  int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
+// HBM-bound: three or four streams.  A thread takes 16 bytes of each, wherever they start: runs are cut without regard to rows, so a
+// width that is no multiple of 8 costs nothing (unaligned 16-byte accesses; one voxel a thread took 91 us for 64 channels of
+// 32x100x90 bf16, this takes 19; aligned rows of 32 x 64x256x256 137 and 137).  The last piece of a run goes element by
+// element: g may be one of the inputs, so no piece overlaps another.
+template <typename T, bool TWO>
+__global__ void __launch_bounds__(256) act_bwd_kernel(const T* dz, const T* dz2, const T* z, T* g, ActArgs a) {
+  constexpr int V = 16 / sizeof(T);
+  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (t >= a.total) return;
-  int wv = (int)(t % a.wv); t /= a.wv;
-  int h = (int)(t % a.g.h); t /= a.g.h;
-  int p = (int)(t % a.g.d); t /= a.g.d;
-  int c = (int)(t % a.g.c);
-  int n = (int)(t / a.g.c);
-  auto off = [&](const Geo& q) { return n * q.nstride + c * q.cstride + (int64_t)(p + q.hlo) * q.plane + (int64_t)h * q.w + wv * VEC; };
-  AVec<T, VEC> d = *reinterpret_cast<const AVec<T, VEC>*>(dz + off(a.dz));
-  AVec<T, VEC> m = *reinterpret_cast<const AVec<T, VEC>*>(z + off(a.z));
-  AVec<T, VEC> d2, o;
-  if (TWO) d2 = *reinterpret_cast<const AVec<T, VEC>*>(dz2 + off(a.dz2));
-#pragma unroll
-  for (int i = 0; i < VEC; ++i) {
-    float v = ld(&d.v[i]);
-    if (TWO) v += ld(&d2.v[i]);
-    if (!(ld(&m.v[i]) > 0.f)) v *= a.slope;
-    st(&o.v[i], v);
+  int64_t nc;
+  int n;
+  if (a.total >> 32) {
+    nc = t / a.units;
+    n = (int)(nc / a.g.c);
+  } else {
+    nc = (uint32_t)t / (uint32_t)a.units;
+    n = (int)((uint32_t)nc / (uint32_t)a.g.c);
   }
-  *reinterpret_cast<AVec<T, VEC>*>(g + off(a.g)) = o;
+  const int c = (int)(nc - (int64_t)n * a.g.c);
+  const int64_t e0 = (t - nc * a.units) * V;
+  auto off = [&](const Geo& q) { return n * q.nstride + c * q.cstride + q.hlo * q.plane + e0; };
+  const T *pd = dz + off(a.dz), *pz = z + off(a.z), *p2 = TWO ? dz2 + off(a.dz2) : nullptr;
+  T* po = g + off(a.g);
+  T d[V], d2[V], m[V], o[V];
+  auto product = [&](int i) {
+    float v = ld(&d[i]);
+    if (TWO) v += ld(&d2[i]);
+    if (!(ld(&m[i]) > 0.f)) v *= a.slope;
+    st(&o[i], v);
+  };
+  if (e0 + V <= a.run) {
+    __builtin_memcpy(d, pd, 16);
+    __builtin_memcpy(m, pz, 16);
+    if (TWO) __builtin_memcpy(d2, p2, 16);
+#pragma unroll
+    for (int i = 0; i < V; ++i) product(i);
+    h3d_u32x4 q;
+    __builtin_memcpy(&q, o, 16);
+    asm volatile("" : "+v"(q));      // one store: the compiler would share the last element's with the branch below
+    __builtin_memcpy(po, &q, 16);
+  } else {
+#pragma unroll
+    for (int i = 0; i < V; ++i)
+      if (e0 + i < a.run) {
+        d[i] = pd[i];
+        m[i] = pz[i];
+        if (TWO) d2[i] = p2[i];
+        product(i);
+        po[i] = o[i];
+      }
+  }
 }
 
 template <typename T>
@@ -49,23 +73,16 @@ static h3d_status act_bwd_t(void* handle, const h3d_tensor* dz, const h3d_tensor
   ActArgs a;
   a.dz = make_geo(dz); a.dz2 = dz2 ? make_geo(dz2) : a.dz; a.z = make_geo(z); a.g = make_geo(g);
   a.slope = slope;
-  constexpr int V = 16 / sizeof(T);
-  auto aligned = [&](const h3d_tensor* t) { return !t || (uintptr_t)t->data % 16 == 0; };
-  const bool vec = g->w % V == 0 && aligned(dz) && aligned(dz2) && aligned(z) && aligned(g);
-  a.wv = vec ? g->w / V : g->w;
-  a.total = (int64_t)g->n * g->c * g->d * g->h * a.wv;
+  a.run = (int64_t)g->d * g->h * g->w;
+  a.units = cdiv(a.run, 16 / (int64_t)sizeof(T));
+  a.total = (int64_t)g->n * g->c * a.units;
   if (a.total == 0) return H3D_OK;
   int64_t grid = cdiv(a.total, 256);
   if (grid >= ((int64_t)1 << 31)) return fail(handle, H3D_EINVAL, "act_bwd: too many blocks");
   const T *pd = (const T*)dz->data, *p2 = dz2 ? (const T*)dz2->data : nullptr, *pz = (const T*)z->data;
   T* pg = (T*)g->data;
-  if (vec) {
-    if (dz2) hipLaunchKernelGGL((act_bwd_kernel<T, V, true>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
-    else hipLaunchKernelGGL((act_bwd_kernel<T, V, false>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
-  } else {
-    if (dz2) hipLaunchKernelGGL((act_bwd_kernel<T, 1, true>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
-    else hipLaunchKernelGGL((act_bwd_kernel<T, 1, false>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
-  }
+  if (dz2) hipLaunchKernelGGL((act_bwd_kernel<T, true>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
+  else hipLaunchKernelGGL((act_bwd_kernel<T, false>), dim3((unsigned)grid), dim3(256), 0, s, pd, p2, pz, pg, a);
   return launch_status(handle, "act_bwd");
 }
 

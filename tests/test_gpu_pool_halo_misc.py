@@ -430,3 +430,19 @@ def test_deconv_past_the_cache_equals_its_samples(cin, cout, shape):
         h3d.deconv2_fwd(h3d.Slab(x[n:n + 1]), wt, bias, h3d.Slab(y1))
         h3d.deconv2_bwd_data(h3d.Slab(dy[n:n + 1]), wt, h3d.Slab(dx1))
         assert torch.equal(y[n:n + 1], y1) and torch.equal(dx[n:n + 1], dx1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape,shift", [((2, 3, 1, 1, 3), 0), ((1, 2, 3, 7, 13), 1), ((3, 1, 2, 3, 16), 3)])
+def test_act_bwd_in_place_at_any_address(shape, shift, dtype):
+    """Runs shorter than a 16-byte piece, with a remainder, at odd addresses, and g the same tensor as dz."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    dzo, dzg = slab_pair(synth.flat("normal", SEED, 25, shape), dtype)
+    zo, zg = slab_pair(synth.flat("normal", SEED, 26, shape), dtype)
+    go = orc.act_bwd(dzo, None, zo, orc.ACT_LEAKY, 0.01)
+    flat = torch.full((dzg.t.numel() + 16,), 7.0, dtype=dzg.t.dtype, device="cuda")
+    g = h3d.Slab(flat[shift:shift + dzg.t.numel()].view(dzg.t.shape).copy_(dzg.t))
+    h3d.act_bwd(g, None, zg, g, h3d.ACT_LEAKY, 0.01)
+    close(from_dev(g.t), go.a, (1e-6 if dtype == "f32" else 4e-3))
+    assert bool((flat[:shift] == 7.0).all()) and bool((flat[shift + dzg.t.numel():] == 7.0).all())
