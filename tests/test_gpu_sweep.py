@@ -134,3 +134,34 @@ def test_deconv_ragged_rows_bf16(case):
     h3d.deconv2_bwd_filter(xg, moved(dyg), dw, db)
     close(from_dev(dw), dwo, 2e-4)
     close(from_dev(db), dbo, 2e-4)
+
+
+@pytest.mark.parametrize("cin,cout", [(20, 40), (40, 24), (33, 72)])
+@pytest.mark.parametrize("N,D,H,W", [(1, 3, 9, 16), (1, 5, 17, 8), (24, 9, 17, 16), (48, 5, 9, 8), (16, 2, 70, 16)])
+def test_narrow_rows_by_sixteen_bytes_equal_the_general_staging(cin, cout, N, D, H, W):
+    """8 or 16 columns, at a 16-byte address (whole rows staged by 16-byte loads) and at one that is not (dwords): the products and
+    their order are the same, so the bits are.  With channels split over workgroups and without, planes in rows of tiles, halos."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    print("narrow rows", cin, cout, N, D, H, W, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(cin + W)
+    x = torch.randn((N, cin, D + 2, H, W), device="cuda", generator=gen).bfloat16()
+    w = (0.1 * torch.randn((cout, cin, 3, 3, 3), device="cuda", generator=gen)).bfloat16()
+    bias = torch.randn(cout, device="cuda", generator=gen)
+    flat = torch.full((x.numel() + 64,), float("nan"), dtype=x.dtype, device="cuda")
+    outs = []
+    for shift in (0, 2):
+        xs = flat[32 + shift:32 + shift + x.numel()].view(x.shape).copy_(x)
+        assert (xs.data_ptr() % 16 == 0) == (shift == 0)
+        y = torch.full((N, cout, D, H, W), float("nan"), dtype=x.dtype, device="cuda")
+        h3d.conv3d_fwd(h3d.Slab(xs, 1, 1, 1, D + 2), w, bias, h3d.Slab(y, 0, 0, 1, D + 2), h3d.ACT_LEAKY, 0.01)
+        outs.append(y)
+        flat.fill_(float("nan"))
+    assert torch.equal(outs[0], outs[1]) and bool(torch.isfinite(outs[0]).all())
+    # and one voxel of the last row, column and plane against its definition
+    n, d, h, v = N - 1, D - 1, H - 1, W - 1
+    patch = torch.zeros((cin, 3, 3, 3), dtype=torch.float64, device="cuda")
+    patch[:, :, :2, :2] = x[n, :, d:d + 3, h - 1:, v - 1:].double()
+    ref = (w.double() * patch).sum(dim=(1, 2, 3, 4)) + bias.double()
+    ref = torch.where(ref > 0, ref, 0.01 * ref)
+    assert float((outs[0][n, :, d, h, v].double() - ref).abs().max()) <= 2.0 ** -8 * float(ref.abs().max())
