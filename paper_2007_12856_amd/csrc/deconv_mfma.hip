@@ -778,6 +778,7 @@ h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const floa
 
 bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
   if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > 64 || (uintptr_t)y->data % 4 != 0) return false;
+  if (make_geo(y).cstride % 2 != 0 || make_geo(y).nstride % 2 != 0) return false;      // results leave as pairs in one dword
   if (!rows_v16(x) && !rows_any(x)) return false;
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)y->c * (y->halo_lo + y->d + y->halo_hi) * y->h * y->w * 2;
