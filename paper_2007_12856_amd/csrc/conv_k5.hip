@@ -318,12 +318,14 @@ Geo k5_masked(void* handle, const h3d_tensor* dz, const h3d_tensor* z, float slo
 size_t k5_copy_bytes(const h3d_tensor* dz) {
   return up256((size_t)dz->n * dz->c * (dz->halo_lo + dz->d + dz->halo_hi) * dz->h * prep_w(dz->w) * sizeof(bf16_t));
 }
-// the matrix-core route: the padded copy has to pass the test of the tensors too
-bool k5_on_mfma(const h3d_tensor* x, const h3d_tensor* z) {
+// the matrix-core route: a tensor whose padded copy the kernels read has to pass their test with padded rows.  Backward-data reads a
+// copy of z's gradient, backward-filter of that and of x (which may store more halo planes than z: either one can be the larger).
+bool k5_on_mfma(int op, const h3d_tensor* x, const h3d_tensor* z) {
   if (z->c < 1 || x->c < 1) return false;
-  h3d_tensor zp = *z;
-  zp.w = prep_w(z->w);
-  return k5_mfma_supported(x, z) && k5_mfma_supported(x, &zp);
+  h3d_tensor xp = *x, zp = *z;
+  if (op != H3D_OP_FWD) zp.w = prep_w(z->w);
+  if (op == H3D_OP_BWD_FILTER) xp.w = prep_w(x->w);
+  return k5_mfma_supported(x, z) && k5_mfma_supported(&xp, &zp);
 }
 
 bool bad_act(int act) { return act != H3D_ACT_NONE && act != H3D_ACT_RELU && act != H3D_ACT_LEAKY; }
@@ -335,7 +337,7 @@ using namespace h3d;
 
 extern "C" size_t h3d_conv3d_k5_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z) {
   if (!handle || !x || !z || x->c < 1 || z->c < 1 || x->n < 0 || x->d < 0 || x->h < 0 || x->w < 0) return 0;
-  const bool mfma = k5_on_mfma(x, z);
+  const bool mfma = k5_on_mfma(op, x, z);
   const K5Plan p = k5_plan(x, x->c, z->c, op);
   switch (op) {                  // (z is the output-side descriptor: room for its masked copy in the bf16 backward passes)
     case H3D_OP_FWD:
@@ -368,7 +370,7 @@ extern "C" h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const
   hipStream_t s = (hipStream_t)stream;
   float* wp = (float*)ws;
   const K5Args a = k5_args(x, z, nullptr, p, z->c, 1.f, act_slope(act, alpha));
-  if (k5_on_mfma(x, z)) H3D_TRY(k5_mfma_conv(handle, make_geo(x), x->data, w, x->c, z->c, false, bias, z, a.slope_out, ws, s));
+  if (k5_on_mfma(H3D_OP_FWD, x, z)) H3D_TRY(k5_mfma_conv(handle, make_geo(x), x->data, w, x->c, z->c, false, bias, z, a.slope_out, ws, s));
   else if (x->dtype == H3D_F32) { k5_launch_pack<float>(w, wp, x->c, z->c, 0, s); k5_launch_conv<float>(x, nullptr, wp, bias, z, a, s); }
   else { k5_launch_pack<bf16_t>(w, wp, x->c, z->c, 0, s); k5_launch_conv<bf16_t>(x, nullptr, wp, bias, z, a, s); }
   return launch_status(handle, "conv3d_k5_fwd");
@@ -395,7 +397,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_data(void* handle, const h3d_tensor* dz,
   hipStream_t s = (hipStream_t)stream;
   float* wp = (float*)ws;
   const K5Args a = k5_args(dz, dx, z, p, dx->c, act_slope(act, alpha), 1.f);
-  if (k5_on_mfma(dx, dz)) {
+  if (k5_on_mfma(H3D_OP_BWD_DATA, dx, dz)) {
     Geo gi = make_geo(dz);
     const void* gd = dz->data;
     if (z) {
@@ -436,7 +438,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_filter(void* handle, const h3d_tensor* x
   // the mask is read on the interior only: the planes of the saved output that exist do not limit x's window
   K5Args a = k5_args(x, dz, nullptr, p, dz->c, act_slope(act, alpha), 1.f);
   if (z) a.zg = make_geo(z);
-  if (p.tiles_total > 0 && k5_on_mfma(x, dz) && (x->w % 8 || (uintptr_t)x->data % 16 == 0)) {
+  if (p.tiles_total > 0 && k5_on_mfma(H3D_OP_BWD_FILTER, x, dz) && (x->w % 8 || (uintptr_t)x->data % 16 == 0)) {
     Geo gi = make_geo(dz), gx = make_geo(x);
     const void *gd = dz->data, *xd = x->data;
     char* copy = (char*)ws + up256(k5_mfma_bf_bytes(x, dz->c));

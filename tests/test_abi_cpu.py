@@ -41,3 +41,25 @@ def test_missing_library_fails_loudly(monkeypatch):
     monkeypatch.setattr(h3d, "LIB_PATH", "/nonexistent/libh3d.so")
     with pytest.raises(RuntimeError):
         h3d.lib()
+
+
+def _desc(h3d, n, c, d, h, w, halo=0, d_offset=None, d_global=None):
+    """A bf16 descriptor without data: what the size queries take."""
+    off = d if d_offset is None else d_offset
+    return h3d.h3d_tensor(None, h3d.BF16, n, c, d, h, w, halo, halo, off, 3 * d if d_global is None else d_global, 0, 0)
+
+
+def test_k5_filter_gradient_of_a_channel_whose_padded_copy_is_too_long():
+    """5x5x5 backward-filter of rows of 97 columns reads copies with rows of 104.  32-bit offsets reach blocks of 32 channels below 2^25
+    elements each: x as it is (33.52e6) and the padded dz (33.55e6) pass, the padded x (35.94e6, four planes taller) does not, so the
+    query must not ask for room for its copy (2.3e9 bytes); a shard of 51 planes does get it."""
+    import paper_2007_12856_amd as h3d
+    lib, handle = h3d.lib(), ctypes.cast(ctypes.create_string_buffer(4096), ctypes.c_void_p)      # (a query reads no field of the handle)
+    limit = 1 << 25
+    for d, fits in ((56, False), (51, True)):
+        x, z = _desc(h3d, 1, 32, d, 5760, 97, halo=2), _desc(h3d, 1, 32, d, 5760, 97)
+        assert (d + 4) * 5760 * 97 < limit and d * 5760 * 104 < limit and ((d + 4) * 5760 * 104 < limit) == fits
+        need = lib.h3d_conv3d_k5_workspace_bytes(handle, h3d.OP_BWD_FILTER, ctypes.byref(x), ctypes.byref(z))
+        assert (need > 2 * 32 * (d + 4) * 5760 * 104) == fits
+        # forward reads x where it lies
+        assert lib.h3d_conv3d_k5_workspace_bytes(handle, h3d.OP_FWD, ctypes.byref(x), ctypes.byref(z)) == 1 * 2 * 125 * 1024
