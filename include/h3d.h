@@ -185,8 +185,9 @@ h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x, const h3d
  * the size of dz); 256-byte aligned; H3D_EWORKSPACE if too small.
  * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation; bf16
  * tensors run on the matrix cores (backward-data and backward-filter then round g to bf16 once, as the 3x3x3 calls
- * do; the copy of x that backward-filter makes when w is no multiple of 8 is part of the workspace; whole 16-byte rows of x
- * at another address run on the vector ALU there, as do samples of fewer than 8 elements and channels of 2^25), fp32
+ * do, except that backward-filter of rows that are no multiple of 8 takes a leaky g in two parts and rounds neither; the copies
+ * that it makes of such rows are part of the workspace; whole 16-byte rows of x at another address, or of a tensor that a leaky
+ * mask applies to, run on the vector ALU there, as do samples of fewer than 8 elements and channels of 2^25), fp32
  * tensors on the vector ALU. */
 size_t h3d_conv3d_k5_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z);
 h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,

@@ -12,17 +12,19 @@
 //     to the workspace and a second kernel adds them in chunk order (two calls give identical bits).
 // bf16 tensors run on the matrix cores instead (conv_k5_mfma.hip) unless 32 channels of one exceed 32-bit byte offsets; their
 // backward passes make g = dz * act'(z) once (prep.h), with padded rows, instead of masking while staging.
+#include <algorithm>
+
 #include "prep.h"
 
 namespace h3d {
 // conv_k5_mfma.hip
 bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z);
 size_t k5_mfma_wp_bytes(int rows, int contraction);
-size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout);
+size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout, int parts);
 h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const void* w, int cin, int cout, bool transposed, const float* bias,
                         const h3d_tensor* out, float slope, void* wp, hipStream_t s);
-h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, const void* x_data, const Geo& g, const void* g_data, int cout,
-                              float* dw, float* db, void* ws, hipStream_t s);
+h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, const void* x_data, const Geo& g, const void* g_data, int64_t neg,
+                              float slope, int cout, float* dw, float* db, void* ws, hipStream_t s);
 
 namespace {
 
@@ -305,10 +307,13 @@ void k5_launch_bwf(const h3d_tensor* x, const h3d_tensor* dz, const h3d_tensor* 
                        part_db, a, p.tiles_total, p.tiles_per_chunk);
 }
 
-// g = dz * act'(z) (z null: dz) with padded rows on planes [lo, hi) of the shard, every one of them stored by both
-Geo k5_masked(void* handle, const h3d_tensor* dz, const h3d_tensor* z, float slope, int lo, int hi, void* copy, h3d_status* st, hipStream_t s) {
-  const PrepJob j = prep_job(dz, z, slope, 0, dz->n, lo, hi - lo, copy);
-  *st = prep_launch(handle, j, nullptr, s);
+// g = dz * act'(z) (z null: dz) with padded rows on planes [lo, hi) of the shard, every one of them stored by both; with `second`, what
+// lies where z is positive and, there, what lies where it is not, both without the slope
+Geo k5_masked(void* handle, const h3d_tensor* dz, const h3d_tensor* z, float slope, int lo, int hi, void* copy, void* second, h3d_status* st,
+              hipStream_t s) {
+  const PrepJob j = prep_job(dz, z, slope, 0, dz->n, lo, hi - lo, copy, second ? 1 : 0);
+  const PrepJob j2 = prep_job(dz, z, slope, 0, dz->n, lo, hi - lo, second, 2);
+  *st = prep_launch(handle, j, second ? &j2 : nullptr, s);
   Geo g = make_geo(dz);
   g.w = j.w8; g.ds = hi - lo; g.hlo = -lo; g.hhi = hi - dz->d;
   g.plane = (int64_t)g.h * g.w; g.cstride = g.plane * g.ds; g.nstride = g.cstride * g.c;
@@ -347,7 +352,9 @@ extern "C" size_t h3d_conv3d_k5_workspace_bytes(void* handle, int op, const h3d_
     case H3D_OP_BWD_FILTER:
     {
       const size_t alu = p.part_bytes + p.partdb_bytes;      // (also where x's rows are whole pieces at an odd address)
-      const size_t m = mfma ? up256(k5_mfma_bf_bytes(x, z->c)) + k5_copy_bytes(z) + (x->w % 8 ? k5_copy_bytes(x) : 0) : 0;
+      size_t m = 0;
+      if (mfma) m = up256(k5_mfma_bf_bytes(x, z->c, 1)) + k5_copy_bytes(z) + (x->w % 8 ? k5_copy_bytes(x) : 0);
+      if (mfma && x->w % 8) m = std::max(m, up256(k5_mfma_bf_bytes(x, z->c, 2)) + 2 * k5_copy_bytes(z) + k5_copy_bytes(x));
       return alu > m ? alu : m;
     }
     default:
@@ -405,7 +412,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_data(void* handle, const h3d_tensor* dz,
       const int lo = (int)(dz->d_offset < 2 ? -dz->d_offset : -2);
       const int64_t above = dz->d_global - dz->d_offset - dz->d;
       h3d_status st;
-      gi = k5_masked(handle, dz, z, a.slope_in, lo, dz->d + (int)(above < 2 ? above : 2), copy, &st, s);
+      gi = k5_masked(handle, dz, z, a.slope_in, lo, dz->d + (int)(above < 2 ? above : 2), copy, nullptr, &st, s);
       H3D_TRY(st);
       gd = copy;
     }
@@ -438,23 +445,29 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_filter(void* handle, const h3d_tensor* x
   // the mask is read on the interior only: the planes of the saved output that exist do not limit x's window
   K5Args a = k5_args(x, dz, nullptr, p, dz->c, act_slope(act, alpha), 1.f);
   if (z) a.zg = make_geo(z);
-  if (p.tiles_total > 0 && k5_on_mfma(H3D_OP_BWD_FILTER, x, dz) && (x->w % 8 || (uintptr_t)x->data % 16 == 0)) {
+  // A leaky activation's g = dz * slope does not fit bf16.  Aligned rows round it once, as the 3x3x3 calls do; where the fp32 kernel below
+  // had the shape before, the gradient comes in two parts instead, with and without the slope, each of them dz's own values:
+  // dw = x * (dz where z > 0) + slope * (x * (dz where not)).  Error of dw against 64 bits, masked 64->64 on 16x50x54: fp32 kernel 1.5e-6,
+  // rounded g 1.7e-5, two parts 3.0e-7; time 1631, 104, 175 us.  (Aligned rows with a mask at an odd address: no room for a second copy.)
+  const bool two = z && a.slope_in != 0.f && a.slope_in != 1.f && (x->w % 8 || (uintptr_t)dz->data % 16 || (uintptr_t)z->data % 16);
+  if (p.tiles_total > 0 && k5_on_mfma(H3D_OP_BWD_FILTER, x, dz) && (x->w % 8 || ((uintptr_t)x->data % 16 == 0 && !two))) {
     Geo gi = make_geo(dz), gx = make_geo(x);
     const void *gd = dz->data, *xd = x->data;
-    char* copy = (char*)ws + up256(k5_mfma_bf_bytes(x, dz->c));
+    char* copy = (char*)ws + up256(k5_mfma_bf_bytes(x, dz->c, two ? 2 : 1));
+    char* second = two ? copy + k5_copy_bytes(dz) : nullptr;
     h3d_status st;
     if (z || x->w % 8 || (uintptr_t)dz->data % 16) {
-      gi = k5_masked(handle, dz, z, a.slope_in, 0, dz->d, copy, &st, s);
+      gi = k5_masked(handle, dz, z, a.slope_in, 0, dz->d, copy, second, &st, s);
       H3D_TRY(st);
       gd = copy;
     }
     if (x->w % 8) {
-      copy += k5_copy_bytes(dz);
-      gx = k5_masked(handle, x, nullptr, 1.f, a.pmin > -2 ? a.pmin : -2, a.pmax < x->d + 2 ? a.pmax : x->d + 2, copy, &st, s);
+      copy += (two ? 2 : 1) * k5_copy_bytes(dz);
+      gx = k5_masked(handle, x, nullptr, 1.f, a.pmin > -2 ? a.pmin : -2, a.pmax < x->d + 2 ? a.pmax : x->d + 2, copy, nullptr, &st, s);
       H3D_TRY(st);
       xd = copy;
     }
-    H3D_TRY(k5_mfma_bwd_filter(handle, x, gx, xd, gi, gd, dz->c, dw, db, ws, s));
+    H3D_TRY(k5_mfma_bwd_filter(handle, x, gx, xd, gi, gd, two ? (int64_t)(k5_copy_bytes(dz) / sizeof(bf16_t)) : 0, a.slope_in, dz->c, dw, db, ws, s));
     return launch_status(handle, "conv3d_k5_bwd_filter");
   }
   const int chunks = p.chunks;

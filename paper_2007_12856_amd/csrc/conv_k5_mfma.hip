@@ -8,7 +8,7 @@
 namespace h3d {
 
 void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
-                 hipStream_t s);      // taps_reduce.hip
+                 int half, float slope, hipStream_t s);      // taps_reduce.hip
 
 struct K5MArgs {
   Geo in, out;              // staged tensor (x or g), written tensor (backward-filter: out = g)
@@ -18,7 +18,9 @@ struct K5MArgs {
   int tiles_w, tiles_h, ntiles;
   float slope;
   int vec;                  // result rows are 4-byte aligned pairs
-  int segs, chunks, cobs, cibs;       // backward-filter
+  // backward-filter.  Chunks from `half` on contract with the second part of a gradient in two parts, `neg` elements behind the first.
+  int segs, chunks, half, cobs, cibs;
+  int64_t neg;
 };
 
 // wp [block of 32 result channels][16-channel chunk][tap][lane][8]; transposed: backward-data
@@ -240,6 +242,8 @@ __global__ void __launch_bounds__(320 * KF_GROUPS) k5_bwf_rows_kernel(const bf16
   const int per_chunk = 5 * a.cobs * a.cibs, q = blockIdx.x >> 3;
   const int chunk = (int)(blockIdx.x & 7) + 8 * (q / per_chunk), kd = q % per_chunk % 5, blk = q % per_chunk / 5;
   if (chunk >= a.chunks) return;
+  const int run = chunk >= a.half ? chunk - a.half : chunk;
+  if (chunk >= a.half) g += a.neg;
   const int cob = blk / a.cibs, cib = blk % a.cibs;
   const int H = a.in.h, W = a.in.w;
   uint4* xl = lds + grp * KF_PART;
@@ -250,15 +254,15 @@ __global__ void __launch_bounds__(320 * KF_GROUPS) k5_bwf_rows_kernel(const bf16
   const int q0 = max(0, a.pmin + 2 - kd), q1 = min(a.out.d, a.pmax + 2 - kd);
   const int planes = max(q1 - q0, 0);
   const int total = a.out.n * planes * a.segs * H;
-  const int per = (total + KF_GROUPS * a.chunks - 1) / (KF_GROUPS * a.chunks);
+  const int per = (total + KF_GROUPS * a.half - 1) / (KF_GROUPS * a.half);
   // steps of a run: its rows, and four more wherever a column of rows starts (the first x rows of the window)
   auto run_steps = [&](int gi) -> int {
-    const int r0 = min(total, (chunk * KF_GROUPS + gi) * per), r1 = min(total, r0 + per);
+    const int r0 = min(total, (run * KF_GROUPS + gi) * per), r1 = min(total, r0 + per);
     return r1 > r0 ? (r1 - r0) + 4 * ((r1 - 1) / H - r0 / H + 1) : 0;
   };
   int steps = 0;
   for (int k = 0; k < KF_GROUPS; ++k) steps = max(steps, run_steps(k));
-  const int r0 = min(total, (chunk * KF_GROUPS + grp) * per), r1 = min(total, r0 + per);
+  const int r0 = min(total, (run * KF_GROUPS + grp) * per), r1 = min(total, r0 + per);
   const bool db_wave = kd == 2 && cib == 0 && kh == 2;
 
   // position of the step that is being FETCHED: g row h (from -4 on while the window fills), x row h + 2 of the window's last tap
@@ -426,14 +430,15 @@ bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z) {
 size_t k5_mfma_wp_bytes(int rows, int contraction) { return (size_t)cdiv(rows, 32) * cdiv(contraction, 16) * 125 * 1024; }
 
 // One workgroup per CU and kd (256 CUs): more chunks only add partial sums; at least 8 rows for a group of wavefronts.
-static int k5_bf_chunks(const h3d_tensor* x, int cout) {
+// A gradient in two parts has its chunks split between them.
+static int k5_bf_chunks(const h3d_tensor* x, int cout, int parts) {
   const int64_t groups = 5 * cdiv(cout, 32) * cdiv(x->c, 32);
   const int64_t rows = (int64_t)x->n * x->d * cdiv(x->w, KF_SEG) * x->h;
   const int64_t full = 32 / groups >= 1 ? 32 / groups * 8 : 256 / groups;
-  return (int)std::max<int64_t>(1, std::min<int64_t>(full, cdiv(rows, 24)));
+  return parts * (int)std::max<int64_t>(1, std::min<int64_t>(full / parts, cdiv(rows, 24)));
 }
-size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout) {
-  return (size_t)k5_bf_chunks(x, cout) * (125 * cdiv(cout, 32) * cdiv(x->c, 32) * 1024 + cdiv(cout, 32) * 32) * sizeof(float);
+size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout, int parts) {
+  return (size_t)k5_bf_chunks(x, cout, parts) * (125 * cdiv(cout, 32) * cdiv(x->c, 32) * 1024 + cdiv(cout, 32) * 32) * sizeof(float);
 }
 
 static K5MArgs k5m_args(const Geo& in, const Geo& out, int cin, int cout) {
@@ -484,12 +489,14 @@ h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const 
   return v16 ? k5_launch<4, true>(handle, in_data, wp, bias, out->data, a, out->n, s) : k5_launch<4, false>(handle, in_data, wp, bias, out->data, a, out->n, s);
 }
 
-// gx, g: x and dz or their copies, rows of the same whole number of 16-byte pieces
-h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, const void* x_data, const Geo& g, const void* g_data, int cout,
-                              float* dw, float* db, void* ws, hipStream_t s) {
+// gx, g: x and dz or their copies, rows of the same whole number of 16-byte pieces.  neg != 0: g is the first part of the gradient, the
+// second one lies `neg` elements further on and counts `slope` times.
+h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, const void* x_data, const Geo& g, const void* g_data, int64_t neg,
+                              float slope, int cout, float* dw, float* db, void* ws, hipStream_t s) {
   K5MArgs a = k5m_args(gx, g, x->c, cout);
   a.segs = (int)cdiv(gx.w, KF_SEG);
-  a.chunks = k5_bf_chunks(x, cout);
+  a.chunks = k5_bf_chunks(x, cout, neg ? 2 : 1);
+  a.half = neg ? a.chunks / 2 : a.chunks; a.neg = neg;
   a.cobs = (int)cdiv(cout, 32); a.cibs = (int)cdiv(x->c, 32);
   float* part = (float*)ws;
   float* part_db = part + (size_t)a.chunks * 125 * a.cobs * a.cibs * 1024;
@@ -498,7 +505,7 @@ h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, 
   H3D_TRY(ready);
   hipLaunchKernelGGL(k5_bwf_rows_kernel, grid, dim3(320 * KF_GROUPS), KF_LDS, s, (const bf16_t*)x_data, (const bf16_t*)g_data, part, part_db, a);
   note_kernel(handle, "k5_bwf_rows_kernel");
-  taps_reduce(part, part_db, dw, db, 125, x->c, cout, a.cibs * 32, a.cobs * 32, a.chunks, s);
+  taps_reduce(part, part_db, dw, db, 125, x->c, cout, a.cibs * 32, a.cobs * 32, a.chunks, a.half, slope, s);
   return H3D_OK;
 }
 

@@ -16,7 +16,7 @@ namespace h3d {
 
 // taps_reduce.hip: dw and db from partial sums [chunk][tap][cop][cip] and [chunk][cop], in chunk order
 void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
-                 hipStream_t s);
+                 int half, float slope, hipStream_t s);
 
 struct S2Args {
   Geo x, y, m;                      // fine side, coarse side (y or dy), saved output (mask)
@@ -706,7 +706,7 @@ h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tenso
   else { if (v16) S2_BF(false, true); else S2_BF(false, false); }
 #undef S2_BF
   note_kernel(handle, "s2_bwd_filter_kernel<%d,%d>", y ? 1 : 0, (int)v16);
-  taps_reduce(part, part_db, dw, db, 27, x->c, dy->c, cip, cop, p.nchunks, s);
+  taps_reduce(part, part_db, dw, db, 27, x->c, dy->c, cip, cop, p.nchunks, p.nchunks, 1.f, s);
   return launch_status(handle, "conv3d_s2_bwd_filter");
 }
 

@@ -16,10 +16,12 @@ struct PrepJob {
   bf16_t* dst;
   Geo s, m;
   int n0, nn, p0, np, w8;
+  int part;               // of a masked tensor: 0 all of it, times the slope where the saved output is not positive; 1 / 2 what lies where it is
+                          // positive / where it is not, as it is, and zeros elsewhere
   float slope;
   int64_t units;          // 16-byte units of dst
 };
-PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst);
+PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst, int part = 0);
 // one launch for up to two copies (b may be null)
 h3d_status prep_launch(void* handle, const PrepJob& a, const PrepJob* b, hipStream_t stream);
 

@@ -29,6 +29,11 @@ __device__ __forceinline__ uint32_t prep_mask2(uint32_t v, uint32_t m, float slo
   if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
   return pack_bf16x2(v0, v1);
 }
+// the elements whose saved output is positive (or those whose isn't), as they are
+__device__ __forceinline__ uint32_t prep_part2(uint32_t v, uint32_t m, bool positive) {
+  const bool k0 = (__uint_as_float(m << 16) > 0.f) == positive, k1 = (__uint_as_float(m & 0xffff0000u) > 0.f) == positive;
+  return v & ((k0 ? 0xffffu : 0u) | (k1 ? 0xffff0000u : 0u));
+}
 __device__ __forceinline__ void prep_unit(const PrepJob& a, int64_t i) {
   if (i >= a.units) return;
   const int wu = a.w8 / 8;
@@ -42,7 +47,9 @@ __device__ __forceinline__ void prep_unit(const PrepJob& a, int64_t i) {
   uint4 v = prep_load(a.src + n * a.s.nstride + c * a.s.cstride + (int64_t)(a.p0 + p + a.s.hlo) * a.s.plane + (int64_t)h * a.s.w, col, a.s.w);
   if (a.msk) {
     const uint4 m = prep_load(a.msk + n * a.m.nstride + c * a.m.cstride + (int64_t)(a.p0 + p + a.m.hlo) * a.m.plane + (int64_t)h * a.m.w, col, a.m.w);
-    v = uint4{prep_mask2(v.x, m.x, a.slope), prep_mask2(v.y, m.y, a.slope), prep_mask2(v.z, m.z, a.slope), prep_mask2(v.w, m.w, a.slope)};
+    const bool pos = a.part == 1;
+    v = a.part ? uint4{prep_part2(v.x, m.x, pos), prep_part2(v.y, m.y, pos), prep_part2(v.z, m.z, pos), prep_part2(v.w, m.w, pos)}
+               : uint4{prep_mask2(v.x, m.x, a.slope), prep_mask2(v.y, m.y, a.slope), prep_mask2(v.z, m.z, a.slope), prep_mask2(v.w, m.w, a.slope)};
   }
   reinterpret_cast<uint4*>(a.dst)[i] = v;
 }
@@ -53,11 +60,11 @@ __global__ void __launch_bounds__(256) prep_kernel(PrepJob a, PrepJob b, int64_t
   else prep_unit(b, (blk - blocks_a) * 256 + threadIdx.x);
 }
 
-PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst) {
+PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst, int part) {
   PrepJob j;
   j.src = (const bf16_t*)t->data; j.msk = mask ? (const bf16_t*)mask->data : nullptr; j.dst = (bf16_t*)dst;
   j.s = make_geo(t); j.m = mask ? make_geo(mask) : j.s;
-  j.n0 = n0; j.nn = nn; j.p0 = p0; j.np = np; j.w8 = prep_w(t->w); j.slope = slope;
+  j.n0 = n0; j.nn = nn; j.p0 = p0; j.np = np; j.w8 = prep_w(t->w); j.slope = slope; j.part = part;
   j.units = (int64_t)nn * t->c * np * t->h * (j.w8 / 8);
   return j;
 }

@@ -4,9 +4,9 @@
 
 namespace h3d {
 
-// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight)
+// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight), those of the chunks from `half` on times `slope`
 __global__ void __launch_bounds__(256) taps_reduce_kernel(const float* __restrict__ part, const float* __restrict__ part_db, float* __restrict__ dw,
-                                                        float* __restrict__ db, int taps, int cin, int cout, int cip, int cop, int nchunks) {
+                                                        float* __restrict__ db, int taps, int cin, int cout, int cip, int cop, int nchunks, int half, float slope) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   const int64_t nw = (int64_t)taps * cout * cin;
   const float* src;
@@ -24,23 +24,26 @@ __global__ void __launch_bounds__(256) taps_reduce_kernel(const float* __restric
   } else {
     return;
   }
-  float s = 0.f;
-  int c = 0;
-  for (; c + 8 <= nchunks; c += 8) {
-    float v[8];
+  auto sum = [&](int c, int end) {
+    float s = 0.f;
+    for (; c + 8 <= end; c += 8) {
+      float v[8];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
+      for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
 #pragma unroll
-    for (int k = 0; k < 8; ++k) s += v[k];
-  }
-  for (; c < nchunks; ++c) s += src[c * stride];
-  *dst = s;
+      for (int k = 0; k < 8; ++k) s += v[k];
+    }
+    for (; c < end; ++c) s += src[c * stride];
+    return s;
+  };
+  const float s = sum(0, half);
+  *dst = half < nchunks ? fmaf(slope, sum(half, nchunks), s) : s;
 }
 
 void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
-                 hipStream_t s) {
+                 int half, float slope, hipStream_t s) {
   const int64_t total = (int64_t)taps * cout * cin + cout;
-  hipLaunchKernelGGL(taps_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, part, part_db, dw, db, taps, cin, cout, cip, cop, nchunks);
+  hipLaunchKernelGGL(taps_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, part, part_db, dw, db, taps, cin, cout, cip, cop, nchunks, half, slope);
 }
 
 }  // namespace h3d
