@@ -195,3 +195,27 @@ def test_stride2_bf16_tile_edges(shape, act):
     h3d.conv3d_s2_bwd_filter(xg, dyg, sg, dw, db, act, 0.01)
     close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
     close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
+
+
+@pytest.mark.parametrize("shape", [(1, 32, 32, 4, 16, 64), (1, 20, 40, 4, 70, 70), (2, 16, 32, 4, 9, 33), (1, 64, 32, 2, 34, 130)])
+def test_stride2_an_infinity_reaches_only_the_taps_that_read_it(shape):
+    """bf16 backward-filter: an infinite voxel of x next to the end of a row, column or plane makes the entries of dw infinite whose sums
+    contain it and no others (the kernel's rows and columns of g beyond the volume are zeros, and zero times infinity is not)."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    gen = torch.Generator(device="cuda").manual_seed(H + W)
+    x = torch.randn((N, Ci, D, H, W), device="cuda", generator=gen).bfloat16()
+    dy = (torch.rand((N, Co, D // 2, (H + 1) // 2, (W + 1) // 2), device="cuda", generator=gen) + 0.5).bfloat16()
+    dw, db = torch.empty((Co, Ci, 3, 3, 3), device="cuda"), torch.empty((Co,), device="cuda")
+    for d, h, w in [(D - 1, H - 1, W - 1), (D - 1, H - 1, 0), (0, 0, W - 1), (1, H - 2, W - 2), (D // 2, H // 2, W // 2), (1, 31, 63)]:
+        if h >= H or w >= W:
+            continue
+        xi = x.clone()
+        xi[N - 1, 1, d, h, w] = float("inf")
+        h3d.conv3d_s2_bwd_filter(h3d.Slab(xi), h3d.Slab(dy), None, dw, db)
+        # tap k of an axis reads position q if 2 p + k - 1 = q for an output position p
+        reads = [[any(2 * p + k - 1 == q for p in range((e + 1) // 2)) for k in range(3)] for q, e in ((d, D), (h, H), (w, W))]
+        expect = torch.zeros((Co, Ci, 3, 3, 3), dtype=torch.bool)
+        expect[:, 1] = torch.tensor([[[a and b and c for c in reads[2]] for b in reads[1]] for a in reads[0]])
+        assert torch.equal(~torch.isfinite(dw).cpu(), expect), (d, h, w)
