@@ -21,7 +21,6 @@ namespace h3d {
 
 // conv_s2_mfma.hip: bf16 tensors whose samples 32-bit byte offsets reach
 bool s2_mfma_supported(const h3d_tensor* x, const h3d_tensor* y);
-bool s2_mask_fits(const h3d_tensor* m);
 size_t s2_mfma_ws_bytes(int op, const h3d_tensor* x, const h3d_tensor* y);
 h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, float slope, void* ws, hipStream_t s);
 h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor* y, const void* w, h3d_tensor* dx, float slope, void* ws, hipStream_t s);
@@ -212,12 +211,6 @@ extern "C" size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_
   return s2_mfma_supported(x, y) ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
 }
 
-// which route a backward call takes, and the workspace it needs there
-static bool s2_direct(const h3d_tensor* x, const h3d_tensor* dy, const h3d_tensor* y) { return s2_mfma_supported(x, dy) && (!y || s2_mask_fits(y)); }
-static size_t s2_need(void* handle, bool direct, int op, const h3d_tensor* x, const h3d_tensor* y) {
-  return direct ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
-}
-
 extern "C" h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, int act,
                                         float alpha, void* ws, size_t ws_bytes, void* stream) {
   if (!handle) return H3D_EINVAL;
@@ -255,10 +248,9 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_data(void* handle, const h3d_tensor* dy,
     if (!same_shard(y, dy) || y->c != dy->c) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_data: y and dy shapes differ");
     if (upper && y->halo_hi < 1) return fail(handle, H3D_EHALO, "conv3d_s2_bwd_data: y must store its upper halo plane");
   }
-  const bool direct = s2_direct(dx, dy, y);
-  if (!ws || ws_bytes < s2_need(handle, direct, H3D_OP_BWD_DATA, dx, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_data: workspace too small");
+  if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_DATA, dx, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_data: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_data: workspace must be 256-byte aligned");
-  if (direct) return s2_mfma_bwd_data(handle, dy, y, w, dx, act_slope(act, alpha), ws, (hipStream_t)stream);
+  if (s2_mfma_supported(dx, dy)) return s2_mfma_bwd_data(handle, dy, y, w, dx, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(dx, dy);
   char* base = (char*)ws;
   p.gs.data = base;
@@ -302,10 +294,9 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x
     H3D_TRY(check_tensor_packed(handle, y, "y"));
     if (!same_shard(y, dy) || y->c != dy->c) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_filter: y and dy shapes differ");
   }
-  const bool direct = s2_direct(x, dy, y);
-  if (!ws || ws_bytes < s2_need(handle, direct, H3D_OP_BWD_FILTER, x, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_filter: workspace too small");
+  if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_FILTER, x, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_filter: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_filter: workspace must be 256-byte aligned");
-  if (direct) return s2_mfma_bwd_filter(handle, x, dy, y, dw, db, act_slope(act, alpha), ws, (hipStream_t)stream);
+  if (s2_mfma_supported(x, dy)) return s2_mfma_bwd_filter(handle, x, dy, y, dw, db, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(x, dy);
   char* base = (char*)ws;
   p.xs.data = base;

@@ -40,6 +40,17 @@ __device__ __forceinline__ uint4 s2_mask8(uint4 v, uint4 m, float slope) {
   return uint4{s2_mask2(v.x, m.x, slope), s2_mask2(v.y, m.y, slope), s2_mask2(v.z, m.z, slope), s2_mask2(v.w, m.w, slope)};
 }
 
+// How a saved output is read (MASK): not at all; by row8 / row1 like the gradient; or, where it stores so many or so few elements that those do
+// not reach it (s2_mask_fits), one by one at 64-bit addresses.  That form is slow and rare, and it needs no other workspace: the size
+// query does not see the saved output.
+enum { S2_NO_MASK = 0, S2_MASK = 1, S2_FAR_MASK = 2 };
+__device__ __forceinline__ uint4 s2_far8(const bf16_t* row, int c, int w, bool ok) {
+  uint32_t e[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) e[i] = ok && c + i < w ? (uint32_t)row[c + i] : 0u;
+  return uint4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
+}
+
 // wp [block][chunk][tap][lane][8]: forward: block row = output channel, contraction = input channel; transposed (backward-data)
 // the other way round.  Channels beyond the tensor's are zero.
 static __global__ void __launch_bounds__(256) s2_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
@@ -276,7 +287,7 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
 constexpr int SD_PITCH = 34, SD_ROWS = 9, SD_CIG = 2 * SD_ROWS * SD_PITCH, SD_W = 27 * 64, SD_BUF = SD_W + 2 * SD_CIG;
 constexpr size_t SD_LDS = (size_t)2 * SD_BUF * 16;
 
-template <bool MASKED, bool V16>
+template <int MASK, bool V16>
 __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restrict__ dy, const bf16_t* __restrict__ m, const uint4* __restrict__ wp,
                                                           bf16_t* __restrict__ dx, S2Args a) {
   extern __shared__ uint4 lds[];
@@ -302,8 +313,10 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
   const bool ok0 = (full || tail) && h0 + row < H2 && a.y.doff + z + pl < a.y.dglob;
   const int off = cq * 4 * cstride + (z + pl + a.y.hlo) * (int)a.y.plane + (h0 + row) * W2;
   const int col = w0 + 8 * cg;
-  const __amdgpu_buffer_rsrc_t rm = row_rsrc(MASKED ? m + (int64_t)n * a.m.nstride : ys, (uint32_t)a.m.nstride * 2);
+  const bf16_t* ms = MASK ? m + (int64_t)n * a.m.nstride : ys;
+  const __amdgpu_buffer_rsrc_t rm = row_rsrc(ms, (uint32_t)a.m.nstride * 2);
   const int mcs = (int)a.m.cstride, moff = cq * 4 * mcs + (z + pl + a.m.hlo) * (int)a.m.plane + (h0 + row) * W2;
+  auto far_row = [&](int co) { return ms + (int64_t)co * a.m.cstride + (int64_t)(z + pl + a.m.hlo) * a.m.plane + (int64_t)(h0 + row) * W2; };
   const int unit = SD_W + (cq >> 1) * SD_CIG + (pl * SD_ROWS + row) * SD_PITCH + 8 * cg;
   uint4 v[4], mv[4], wv0, wv1, wv2, wv3;
 #pragma unroll
@@ -320,10 +333,12 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
       const bool ok = ok0 && c * 16 + cq * 4 + e < a.cout;
       if (full) {
         v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y), ok);
-        if (MASKED) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m), ok);
+        if (MASK == S2_MASK) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m), ok);
+        if (MASK == S2_FAR_MASK) mv[e] = s2_far8(far_row(c * 16 + cq * 4 + e), col, W2, ok);
       } else if (tail) {
         v[e].x = row1(rs, off + (c * 16 + e) * cstride, col, W2, ok);
-        if (MASKED) mv[e].x = row1(rm, moff + (c * 16 + e) * mcs, col, W2, ok);
+        if (MASK == S2_MASK) mv[e].x = row1(rm, moff + (c * 16 + e) * mcs, col, W2, ok);
+        if (MASK == S2_FAR_MASK) mv[e].x = s2_far8(far_row(c * 16 + cq * 4 + e), col, min(col + 1, W2), ok).x;
       }
     }
   };
@@ -338,14 +353,14 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y));
-        if (MASKED) v[e] = s2_mask8(v[e], fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)), a.slope);
+        if (MASK) v[e] = s2_mask8(v[e], MASK == S2_MASK ? fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)) : mv[e], a.slope);
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) half[2 * k] = column_half(v, k);
     } else if (tail) {
       uint32_t s[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] = MASKED ? s2_mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
+      for (int e = 0; e < 4; ++e) s[e] = MASK ? s2_mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
       *half = uint2{s[0] | (s[1] << 16), s[2] | (s[3] << 16)};
     }
   };
@@ -418,7 +433,7 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 // Partial sums [chunk][27][co][ci] per chunk of strips, added in chunk order: identical bits on every run.
 constexpr int SB_BAND = 16, SB_XP = 9, SB_GP = 5, SB_X = 2 * 64 * SB_XP, SB_BUF = SB_X + 64 * SB_GP;
 
-template <bool MASKED, bool V16>
+template <int MASK, bool V16>
 __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ m,
                                                                float* __restrict__ part, float* __restrict__ part_db, S2Args a) {
   __shared__ uint4 lds[2 * SB_BUF];
@@ -446,7 +461,7 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
     hend = min((band + 1) * SB_BAND, H2);
     rx = row_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)a.x.nstride * 2);
     rg = row_rsrc(dy + (int64_t)n * a.y.nstride, (uint32_t)a.y.nstride * 2);
-    if (MASKED) rm = row_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
+    if (MASK == S2_MASK) rm = row_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
     const int p = 2 * z + kd - 1;
     xrow_ok = a.x.doff + p >= 0;
   };
@@ -468,7 +483,12 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
     go = g_co * (int)a.y.cstride + (z + a.y.hlo) * (int)a.y.plane + (h + 1) * W2;
     gv = row8<V16>(rg, go, gc, W2, (int)stored_span(a.y), gok);
     ge = row1(rg, go, w0 + 32, W2, gok && g_piece == 3);
-    if (MASKED) {
+    if (MASK == S2_FAR_MASK) {
+      const bf16_t* row = m + (int64_t)n * a.m.nstride + (int64_t)g_co * a.m.cstride + (int64_t)(z + a.m.hlo) * a.m.plane + (int64_t)(h + 1) * W2;
+      mv = s2_far8(row, gc, W2, gok);
+      me = s2_far8(row, w0 + 32, min(w0 + 33, W2), gok && g_piece == 3).x;
+    }
+    if (MASK == S2_MASK) {
       mo = g_co * (int)a.m.cstride + (z + a.m.hlo) * (int)a.m.plane + (h + 1) * W2;
       mv = row8<V16>(rm, mo, gc, W2, (int)stored_span(a.m), gok);
       me = row1(rm, mo, w0 + 32, W2, gok && g_piece == 3);
@@ -484,8 +504,8 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
           fix8<V16>(xv[i], xo + 32 * (i & 1) * (int)a.x.cstride + (i >> 1) * W, xc, W, (int)stored_span(a.x));
     uint4 g = fix8<V16>(gv, go, gc, W2, (int)stored_span(a.y));
     uint32_t e = ge;
-    if (MASKED) {
-      g = s2_mask8(g, fix8<V16>(mv, mo, gc, W2, (int)stored_span(a.m)), a.slope);
+    if (MASK) {
+      g = s2_mask8(g, MASK == S2_MASK ? fix8<V16>(mv, mo, gc, W2, (int)stored_span(a.m)) : mv, a.slope);
       e = s2_mask2(e, me, a.slope) & 0xffffu;
     }
     dst[SB_X + (tid >> 2) * SB_GP + g_piece] = g;
@@ -603,9 +623,9 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
 // ------------------------------------------------------------------------------------------------------------- host
 // Byte offsets inside a sample are 32-bit (channels are counted up to the next multiple of 64).
 static bool s2_offsets_fit(const h3d_tensor* t, int bits) { return cdiv(t->c, 64) * 64 * make_geo(t).cstride < ((int64_t)1 << bits) && stored_span(make_geo(t)) >= 8; }
-// x: fine side, y: coarse side.  A saved output may store more halo planes than the gradient it belongs to: its own test
-// (s2_mask_fits) leaves it four times the room, and what does not pass it takes the general route.
-bool s2_mask_fits(const h3d_tensor* m) { return s2_offsets_fit(m, 30); }
+// x: fine side, y: coarse side.  A saved output may store more or fewer halo planes than the gradient it belongs to: its own test
+// (s2_mask_fits) leaves it four times the room, and one that does not pass is read by the S2_FAR_MASK form.
+static bool s2_mask_fits(const h3d_tensor* m) { return s2_offsets_fit(m, 30); }
 bool s2_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
   if (x->dtype != H3D_BF16) return false;
   if (x->n < 1 || x->c < 1 || y->c < 1 || y->d < 1 || x->h < 1 || x->w < 1) return false;
@@ -682,13 +702,13 @@ h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const f
   return v16 ? s2_launch_fwd<1, 1, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<1, 1, false>(handle, x, wp, bias, y, a, s);
 }
 
-template <bool MASKED, bool V16>
+template <int MASK, bool V16>
 static h3d_status s2_launch_bd(void* handle, const h3d_tensor* dy, const h3d_tensor* m, const uint4* wp, h3d_tensor* dx, const S2Args& a, hipStream_t s) {
-  static const h3d_status ready = s2_lds(handle, s2_bwd_data_kernel<MASKED, V16>, SD_LDS);
+  static const h3d_status ready = s2_lds(handle, s2_bwd_data_kernel<MASK, V16>, SD_LDS);
   H3D_TRY(ready);
-  hipLaunchKernelGGL((s2_bwd_data_kernel<MASKED, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(dx->c, 32)), dim3(512), SD_LDS, s,
+  hipLaunchKernelGGL((s2_bwd_data_kernel<MASK, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(dx->c, 32)), dim3(512), SD_LDS, s,
                      (const bf16_t*)dy->data, (const bf16_t*)(m ? m->data : nullptr), wp, (bf16_t*)dx->data, a);
-  note_kernel(handle, "s2_bwd_data_kernel<%d,%d>", (int)MASKED, (int)V16);
+  note_kernel(handle, "s2_bwd_data_kernel<%d,%d>", MASK, (int)V16);
   return launch_status(handle, "conv3d_s2_bwd_data");
 }
 
@@ -701,8 +721,9 @@ h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor
   s2_pack(w, ws, dx->c, dy->c, true, a.nchunk, s);
   const uint4* wp = (const uint4*)ws;
   const bool v16 = rows16(dy) && (!y || rows16(y));
-  if (y) return v16 ? s2_launch_bd<true, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<true, false>(handle, dy, y, wp, dx, a, s);
-  return v16 ? s2_launch_bd<false, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<false, false>(handle, dy, y, wp, dx, a, s);
+  if (y && !s2_mask_fits(y)) return s2_launch_bd<S2_FAR_MASK, false>(handle, dy, y, wp, dx, a, s);
+  if (y) return v16 ? s2_launch_bd<S2_MASK, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<S2_MASK, false>(handle, dy, y, wp, dx, a, s);
+  return v16 ? s2_launch_bd<S2_NO_MASK, true>(handle, dy, y, wp, dx, a, s) : s2_launch_bd<S2_NO_MASK, false>(handle, dy, y, wp, dx, a, s);
 }
 
 h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tensor* dy, const h3d_tensor* y, float* dw, float* db, float slope,
@@ -718,10 +739,12 @@ h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tenso
   const dim3 grid((unsigned)p.nchunks, (unsigned)(p.cogroups * p.cigroups), 3);
 #define S2_BF(M, V) hipLaunchKernelGGL((s2_bwd_filter_kernel<M, V>), grid, dim3(256), 0, s, (const bf16_t*)x->data, (const bf16_t*)dy->data, \
                                        (const bf16_t*)(y ? y->data : nullptr), part, part_db, a)
-  if (y) { if (v16) S2_BF(true, true); else S2_BF(true, false); }
-  else { if (v16) S2_BF(false, true); else S2_BF(false, false); }
+  const int mask = !y ? S2_NO_MASK : s2_mask_fits(y) ? S2_MASK : S2_FAR_MASK;
+  if (mask == S2_FAR_MASK) S2_BF(S2_FAR_MASK, false);
+  else if (mask == S2_MASK) { if (v16) S2_BF(S2_MASK, true); else S2_BF(S2_MASK, false); }
+  else { if (v16) S2_BF(S2_NO_MASK, true); else S2_BF(S2_NO_MASK, false); }
 #undef S2_BF
-  note_kernel(handle, "s2_bwd_filter_kernel<%d,%d>", y ? 1 : 0, (int)v16);
+  note_kernel(handle, "s2_bwd_filter_kernel<%d,%d>", mask, (int)(v16 && mask != S2_FAR_MASK));
   taps_reduce(part, part_db, dw, db, 27, x->c, dy->c, cip, cop, p.nchunks, p.nchunks, 1.f, s);
   return launch_status(handle, "conv3d_s2_bwd_filter");
 }

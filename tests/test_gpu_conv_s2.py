@@ -219,3 +219,38 @@ def test_stride2_an_infinity_reaches_only_the_taps_that_read_it(shape):
         expect = torch.zeros((Co, Ci, 3, 3, 3), dtype=torch.bool)
         expect[:, 1] = torch.tensor([[[a and b and c for c in reads[2]] for b in reads[1]] for a in reads[0]])
         assert torch.equal(~torch.isfinite(dw).cpu(), expect), (d, h, w)
+
+
+@pytest.mark.parametrize("shape,planes", [((1, 32, 1, 2, 2, 8), 0), ((2, 3, 1, 2, 2, 10), 0), ((2, 5, 1, 4, 16, 16), 1 << 18), ((1, 17, 5, 2, 6, 10), 1118482)])
+def test_stride2_saved_output_stored_unlike_the_gradient(shape, planes):
+    """bf16 backward passes whose saved output stores fewer elements a sample than a 16-byte load takes, or (behind `planes` planes of
+    halo that nobody reads) more than 32-bit offsets reach, in the workspace that the size query names: it does not see the saved output."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    print("s2 far mask", shape, planes, flush=True)
+    w, _ = _weights(Ci, Co, "bf16", 350)
+    # the upper shard of two: the lower halo planes exist, the upper ones do not
+    xo, xg = slab_pair(synth.flat("normal", SEED, 351, (N, Ci, D + 1, H, W)), "bf16", (1, 0), D, 2 * D)
+    coarse = (N, Co, D // 2, H // 2, W // 2)
+    dya = np.zeros((N, Co, D // 2 + 1) + coarse[3:])
+    dya[:, :, 1:] = synth.flat("normal", SEED, 352, coarse)
+    dyo, dyg = slab_pair(dya, "bf16", (1, 0), D // 2, D)
+    so, sg = slab_pair(synth.flat("normal", SEED, 353, coarse), "bf16", (0, 0), D // 2, D)
+    if planes:
+        tall = torch.zeros((N, Co, planes + D // 2) + coarse[3:], dtype=torch.bfloat16, device="cuda")
+        tall[:, :, planes:] = sg.t
+        sg = h3d.Slab(tall, planes, 0, D // 2, D)
+        assert 64 * tall.stride(1) >= 1 << 30      # (a workgroup's offsets reach over 64 channels)
+    else:
+        assert sg.t[0].numel() < 8 <= dyg.t[0].numel()
+    ws = h3d.Workspace()
+    dxo = orc.conv3d_s2_bwd_data(dyo, so, w, orc.Slab(xo.interior, 0, 0, D, 2 * D), orc.ACT_LEAKY, 0.01)
+    dxg = h3d.conv3d_s2_bwd_data(dyg, sg, to_dev(w, "bf16"), dev_like(dxo, "bf16"), h3d.ACT_LEAKY, 0.01, ws)
+    close(from_dev(dxg.t), dxo.a, TOL["bf16"])
+    dwo, dbo = orc.conv3d_s2_bwd_filter(xo, dyo, so, orc.ACT_LEAKY, 0.01)
+    dw, db = torch.empty((Co, Ci, 3, 3, 3), device="cuda"), torch.empty((Co,), device="cuda")
+    ws = h3d.Workspace()
+    h3d.conv3d_s2_bwd_filter(xg, dyg, sg, dw, db, h3d.ACT_LEAKY, 0.01, ws)
+    close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
+    close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
