@@ -183,12 +183,13 @@ h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x, const h3d
  * Workspace: h3d_conv3d_k5_workspace_bytes(handle, op, x, z) with x / z the input-side / output-side descriptors for
  * every op (packed copy of the filter, or the per-chunk partial sums; for bf16 backward passes also g = dz * act'(z),
  * the size of dz); 256-byte aligned; H3D_EWORKSPACE if too small.
- * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation; bf16
- * tensors run on the matrix cores (backward-data and backward-filter then round g to bf16 once, as the 3x3x3 calls
- * do, except that backward-filter of rows that are no multiple of 8 takes a leaky g in two parts and rounds neither; the copies
- * that it makes of such rows are part of the workspace; whole 16-byte rows of x at another address, or of a tensor that a leaky
- * mask applies to, run on the vector ALU there, as do samples of fewer than 8 elements and channels of 2^25), fp32
- * tensors on the vector ALU. */
+ * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation; fp32 tensors
+ * run on the vector ALU, bf16 tensors on the matrix cores, where g is rounded to bf16 once, as in the 3x3x3 calls (not by
+ * backward-filter where w is no multiple of 8: the two branches of a leaky g are summed apart there, unrounded).  bf16
+ * calls that run on the vector ALU all the same: channels of 2^25 elements and more (rows counted in multiples of 8 where a
+ * pass copies them), forward and backward-data of tensors with fewer than 8 stored elements a sample; backward-filter of
+ * planes of fewer than 8 elements, and, where w is a multiple of 8, of an x at an address that is no multiple of 16, or of a
+ * dz or z at one if the activation is leaky. */
 size_t h3d_conv3d_k5_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z);
 h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
                              int act, float alpha, void* ws, size_t ws_bytes, void* stream);

@@ -325,8 +325,10 @@ size_t k5_copy_bytes(const h3d_tensor* dz) {
 }
 // the matrix-core route: a tensor whose padded copy the kernels read has to pass their test with padded rows.  Backward-data reads a
 // copy of z's gradient, backward-filter of that and of x (which may store more halo planes than z: either one can be the larger).
+// A sample that is read where it lies has to hold one 16-byte load; backward-filter of planes that don't stays with the fp32 kernel.
 bool k5_on_mfma(int op, const h3d_tensor* x, const h3d_tensor* z) {
   if (z->c < 1 || x->c < 1) return false;
+  if (op == H3D_OP_BWD_FILTER ? make_geo(x).plane < 8 : stored_span(make_geo(op == H3D_OP_FWD ? x : z)) < 8) return false;
   h3d_tensor xp = *x, zp = *z;
   if (op != H3D_OP_FWD) zp.w = prep_w(z->w);
   if (op == H3D_OP_BWD_FILTER) xp.w = prep_w(x->w);

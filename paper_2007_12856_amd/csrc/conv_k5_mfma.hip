@@ -80,6 +80,15 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
   const int unit = cig * T::CIG + row * T::PITCH + 9 * cg - 6;
   uint4 v[8], wv0, wv1, wv2, wv3;
   const uint4* wb = wp + (int64_t)blk * a.nchunk * 125 * 64;
+  // Descriptor of the chunk's channels: byte offsets inside 16 channels are 32-bit whatever the sample's size.  A last chunk of fewer than
+  // 8 elements begins as far before its own as a 16-byte load needs.
+  auto chunk_base = [&](int c, int pp, int& o, int& span) -> int64_t {
+    const int64_t own = (int64_t)c * 16 * cstride, base = V16 ? own : min(own, stored_span(a.in) - 8);
+    const int before = (int)(own - base);
+    span = (int)min(stored_span(a.in) - base, (int64_t)16 * cstride + before);
+    o = off + before + (pp + a.in.hlo) * (int)a.in.plane;
+    return base;
+  };
   auto load_stage = [&](int c, int pp) {
     const int kd = pp - p + 2;
     const uint4* ws = wb + ((int64_t)c * 125 + kd * 25) * 64 + tid;
@@ -87,11 +96,9 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
     wv1 = ws[512];
     wv2 = ws[1024];
     wv3 = ws[min(1536, T::WU - 1 - tid)];
-    // descriptor of the chunk's channels: byte offsets inside 16 channels are 32-bit whatever the sample's size
-    const int64_t base = (int64_t)c * 16 * cstride;
-    const int span = (int)min(stored_span(a.in) - base, (int64_t)16 * cstride);
+    int o, span;
+    const int64_t base = chunk_base(c, pp, o, span);
     const __amdgpu_buffer_rsrc_t rs = row_rsrc(is + base, (uint32_t)span * 2);
-    const int o = off + (pp + a.in.hlo) * (int)a.in.plane;
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = row8<V16>(rs, o + e * cstride, col, W, span, ok && c * 16 + cig * 8 + e < a.cin);
   };
@@ -104,8 +111,8 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
     lds[tid + 1536 < T::WU ? buf * T::BUF + 2 * T::CIG + tid + 1536 : T::TRASH + lane] = wv3;
   };
   auto store_rows = [&](int c, int pp, int buf) {
-    const int span = (int)min(stored_span(a.in) - (int64_t)c * 16 * cstride, (int64_t)16 * cstride);
-    const int o = off + (pp + a.in.hlo) * (int)a.in.plane;
+    int o, span;
+    chunk_base(c, pp, o, span);
 #pragma unroll
     for (int e = 0; e < 8; ++e) v[e] = fix8<V16>(v[e], o + e * cstride, col, W, span);
     const int base = buf * T::BUF + unit;
@@ -422,10 +429,10 @@ __global__ void __launch_bounds__(320 * KF_GROUPS) k5_bwf_rows_kernel(const bf16
 }
 
 // ----------------------------------------------------------------------------------------------------------------- host
-// byte offsets inside a block of 32 channels are 32-bit; a block may be one channel, and a 16-byte load has to fit it
+// byte offsets inside a block of 32 channels are 32-bit
 bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z) {
   return x->dtype == H3D_BF16 && make_geo(x).cstride < ((int64_t)1 << 25) && make_geo(z).cstride < ((int64_t)1 << 25) &&
-         make_geo(x).plane >= 8 && make_geo(z).plane >= 8 && (int64_t)z->n * z->d * z->h * cdiv(z->w, 32) < ((int64_t)1 << 28);
+         (int64_t)z->n * z->d * z->h * cdiv(z->w, 32) < ((int64_t)1 << 28);
 }
 size_t k5_mfma_wp_bytes(int rows, int contraction) { return (size_t)cdiv(rows, 32) * cdiv(contraction, 16) * 125 * 1024; }
 

@@ -241,6 +241,9 @@ def test_k5_empty_shard():
     ((1, 33, 9, 3, 19, 45), 3),      # ragged rows at an odd address
     ((1, 17, 33, 2, 2, 3), 0),       # a block of one channel with planes shorter than a 16-byte load
     ((1, 17, 33, 1, 2, 5), 1),       # and one that a load just fits
+    ((2, 33, 17, 1, 1, 3), 1),       # a last chunk of one channel of three elements: its loads begin in the channel before
+    ((1, 2, 5, 1, 1, 4), 2),         # a sample of one load
+    ((1, 1, 7, 1, 1, 7), 0),         # and of less
 ])
 def test_k5_bf16_kernel_edges(shape, shift, act):
     import torch
@@ -257,11 +260,13 @@ def test_k5_bf16_kernel_edges(shape, shift, act):
     xo, xg = slab_pair(synth.flat("normal", SEED, 541, (N, Ci, D, H, W)), "bf16")
     zo = orc.convk_fwd(xo, w, bias, act, 0.01)
     zg = h3d.conv3d_k5_fwd(moved(xg), wd, bd, moved(dev_like(zo, "bf16")), act, 0.01)
+    assert h3d.h3d_last_kernel().startswith("k5_conv_mfma_kernel") == (Ci * D * H * W >= 8)      # (no halo here)
     close(from_dev(zg.t), zo.a, TOL["bf16"])
     so, sg = slab_pair(synth.flat("normal", SEED, 542, zo.a.shape), "bf16")
     go, gg = slab_pair(synth.flat("normal", SEED, 543, zo.a.shape), "bf16")
     dxo = orc.convk_bwd_data(go, so, w, act, 0.01)
     dxg = h3d.conv3d_k5_bwd_data(moved(gg), moved(sg), wd, moved(dev_like(dxo, "bf16")), act, 0.01)
+    assert h3d.h3d_last_kernel().startswith("k5_conv_mfma_kernel") == (Co * D * H * W >= 8)
     close(from_dev(dxg.t), dxo.a, TOL["bf16"])
     dwo, dbo = orc.convk_bwd_filter(5, xo, go, so, act, 0.01)
     dw, db = torch.empty((Co, Ci, 5, 5, 5), device="cuda"), torch.empty((Co,), device="cuda")
