@@ -12,6 +12,11 @@ namespace h3d {
 namespace {
 
 constexpr int BN_SEG = 131072;       // elements of one (sample, channel) run summed by one block
+constexpr int BN_FEW = 8;             // partial sums a channel that one thread adds
+// elements in one 16-byte piece a thread.  Runs of at most UN of them (no LONG form) load all their pieces at once, runs of at most one take
+// forms with few registers: bf16, statistics call, element by element (as the rest behind whole steps was) -> so: 64 channels of 20^3
+// 7.8 -> 4.7 us, 256 of 16^3 6.2 -> 4.4, 8 x 256 of 8^3 6.0 -> 5.1; with a single step and a rest, 16 of 33x35x37, 9.8 -> 6.7.
+template <typename T> constexpr int64_t BN_STEP = 256 * 16 / sizeof(T);
 
 struct BnArgs {
   Geo x, y;            // y: second tensor of the pass (dy, or the output)
@@ -42,7 +47,7 @@ __device__ __forceinline__ void bn_block_sum2(float& a, float& b) {
 
 // MODE 0: (sum x, sum x^2).  MODE 1: (sum dy, sum dy * (x - mean) * invstd) with y = dy.
 // part: [c][n * segs][2]
-template <typename T, int MODE>
+template <typename T, int MODE, int UN, bool LONG>
 __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x, const T* __restrict__ dy,
                                                          const float* __restrict__ mean, const float* __restrict__ invstd,
                                                          float* __restrict__ part, BnArgs a) {
@@ -55,13 +60,12 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
   // UN 16-byte loads in flight per thread and tensor, none behind a branch, each with a pair of accumulators of its own.  Bound by
   // memory: 4 x 16 x 128^3 bf16, statistics 57 us (4.7 TB/s; 63 before), backward sums 109 (4.9; 113 before), each behind a pass that
   // leaves 268 MB of results on their way to memory.
-  constexpr int UN = MODE == 0 ? 8 : 4;
   constexpr int64_t STEP = (int64_t)256 * V * UN;
   float s0 = 0.f, s1 = 0.f, t0[UN], t1[UN];
 #pragma unroll
   for (int u = 0; u < UN; ++u) t0[u] = t1[u] = 0.f;
   int64_t eb = e0;
-  for (; eb + STEP <= e1; eb += STEP) {
+  for (; LONG && eb + STEP <= e1; eb += STEP) {
     BnPack<T> px[UN], pg[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
@@ -69,6 +73,7 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
       px[u] = bn_load(xp + e);
       if (MODE == 1) pg[u] = bn_load(gp + e);
     }
+    __builtin_amdgcn_sched_barrier(0);      // (a use moved between the loads would wait for the first of them alone)
 #pragma unroll
     for (int u = 0; u < UN; ++u)
 #pragma unroll
@@ -78,8 +83,41 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
         else { const float g = ld(&pg[u].v[i]); t0[u] += g; t1[u] = fmaf(g, (v - mu) * is, t1[u]); }
       }
   }
-  // the rest of the segment, element by element
-  for (int64_t e = eb + threadIdx.x; e < e1; e += 256) {
+  auto piece = [&](const BnPack<T>& x0, const BnPack<T>& g0, float& a0, float& a1) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      const float v = ld(&x0.v[i]);
+      if (MODE == 0) { a0 += v; a1 = fmaf(v, v, a1); }
+      else { const float g = ld(&g0.v[i]); a0 += g; a1 = fmaf(g, (v - mu) * is, a1); }
+    }
+  };
+  int64_t tail = e1 - (e1 - eb) % V;
+  if (LONG) {
+    // the rest of the segment: single pieces (few registers: the loop above wants its wavefronts)
+    for (int64_t e = eb + (int64_t)threadIdx.x * V; e + V <= e1; e += (int64_t)256 * V) {
+      const BnPack<T> px = bn_load(xp + e);
+      piece(px, MODE == 1 ? bn_load(gp + e) : px, s0, s1);
+    }
+  } else if (UN == 1 && a.run <= 256) {
+    tail = eb;      // one element a thread
+  } else {
+    BnPack<T> px[UN], pg[UN];
+    bool in[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t e = eb + ((int64_t)u * 256 + threadIdx.x) * V;
+      in[u] = e + V <= e1;
+      if (in[u]) {
+        px[u] = bn_load(xp + e);
+        if (MODE == 1) pg[u] = bn_load(gp + e);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (in[u]) piece(px[u], pg[u], t0[u], t1[u]);
+  }
+  const int64_t e = tail + threadIdx.x;
+  if (e < e1) {
     const float v = ld(xp + e);
     if (MODE == 0) { s0 += v; s1 = fmaf(v, v, s1); }
     else { const float g = ld(gp + e); s0 += g; s1 = fmaf(g, (v - mu) * is, s1); }
@@ -93,16 +131,23 @@ __global__ void __launch_bounds__(256) bn_partial_kernel(const T* __restrict__ x
   }
 }
 
-// one wavefront a channel: lane l adds the partial sums l, l + 64, ... in order, then the lanes by butterfly (fp64)
+// LANES threads a channel (fp64): lane l adds the partial sums l, l + LANES, ... in order, then the lanes by butterfly
+template <int LANES>
 __global__ void __launch_bounds__(256) bn_reduce_kernel(const float* __restrict__ part, float* __restrict__ out0, float* __restrict__ out1, int c, int per) {
-  const int ch = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int ch = blockIdx.x * (256 / LANES) + threadIdx.x / LANES, lane = threadIdx.x % LANES;
   if (ch >= c) return;
   double s0 = 0.0, s1 = 0.0;
   const float* p = part + (int64_t)ch * per * 2;
-  for (int i = lane; i < per; i += 64) { s0 += p[2 * i]; s1 += p[2 * i + 1]; }
+  for (int i = lane; i < per; i += LANES) { s0 += p[2 * i]; s1 += p[2 * i + 1]; }
 #pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) { s0 += __shfl_xor(s0, off, 64); s1 += __shfl_xor(s1, off, 64); }
+  for (int off = LANES / 2; off >= 1; off >>= 1) { s0 += __shfl_xor(s0, off, 64); s1 += __shfl_xor(s1, off, 64); }
   if (lane == 0) { out0[ch] = (float)s0; out1[ch] = (float)s1; }
+}
+// One thread a channel for a few partial sums, a wavefront from there on (256 channels of 8^3 bf16, whole statistics call: one sample 4.4 us
+// and 5.0, four samples 4.9 and 5.2, eight 6.5 and 6.6, sixteen 10.6 and 9.1)
+void bn_reduce(const void* part, float* out0, float* out1, int c, int per, hipStream_t s) {
+  if (per > BN_FEW) hipLaunchKernelGGL(bn_reduce_kernel<64>, dim3((unsigned)cdiv(c, 4)), dim3(256), 0, s, (const float*)part, out0, out1, c, per);
+  else hipLaunchKernelGGL(bn_reduce_kernel<1>, dim3((unsigned)cdiv(c, 256)), dim3(256), 0, s, (const float*)part, out0, out1, c, per);
 }
 
 // per-channel parameters of the affine passes (the arrays hold one value a channel; gamma / beta may be null)
@@ -115,10 +160,10 @@ struct BnCoef {
 // of 5 us less a layer).  The blocks walk the tensor backwards: the reduction in front of an affine pass walked it forwards, and
 // the planes it read last are still in the last-level cache (394 -> 387 us for the five passes on 4 x 16 x 128^3 bf16; with the
 // results written past the cache as well, 346; 406 before).
-template <typename T, bool TWO>
+template <typename T, bool TWO, int UN, bool LONG>
 __global__ void __launch_bounds__(256) bn_apply_kernel(const T* __restrict__ in0, const T* __restrict__ in1, T* __restrict__ out,
                                                        BnCoef q, Geo g0, Geo g1, Geo go, int64_t run, bool past_cache) {
-  constexpr int V = 16 / sizeof(T), UN = 4;
+  constexpr int V = 16 / sizeof(T);
   const int c = gridDim.y - 1 - blockIdx.y, n = gridDim.z - 1 - blockIdx.z, bx = gridDim.x - 1 - blockIdx.x;
   const float k1 = (q.gamma ? q.gamma[c] : 1.f) * q.invstd[c];
   float ka = k1, kb = 0.f, kc;
@@ -135,7 +180,7 @@ __global__ void __launch_bounds__(256) bn_apply_kernel(const T* __restrict__ in0
   constexpr int64_t STEP = (int64_t)256 * V * UN;
   const int64_t stride = (int64_t)gridDim.x * STEP;
   int64_t eb = (int64_t)bx * STEP;
-  for (; eb + STEP <= run; eb += stride) {
+  for (; LONG && eb + STEP <= run; eb += stride) {
     BnPack<T> a[UN], b[UN];
 #pragma unroll
     for (int u = 0; u < UN; ++u) {
@@ -155,13 +200,48 @@ __global__ void __launch_bounds__(256) bn_apply_kernel(const T* __restrict__ in0
       store16(po + eb + ((int64_t)u * 256 + threadIdx.x) * V, &o, past_cache);
     }
   }
-  // the last, partial step of the run, element by element (at most one block has one)
-  if (eb < run)
-    for (int64_t e = eb + threadIdx.x; e < run; e += 256) {
-      float r = fmaf(ld(p0 + e), ka, kc);
-      if (TWO) r = fmaf(ld(p1 + e), kb, r);
-      st(po + e, r);
+  // the last, partial step of the run (at most one block has one): its 16-byte pieces, and fewer than V elements behind them
+  if (eb >= run) return;
+  auto piece = [&](int64_t e, const BnPack<T>& a0, const BnPack<T>& b0) {
+    BnPack<T> o;
+#pragma unroll
+    for (int i = 0; i < V; ++i) {
+      float r = fmaf(ld(&a0.v[i]), ka, kc);
+      if (TWO) r = fmaf(ld(&b0.v[i]), kb, r);
+      st(&o.v[i], r);
     }
+    store16(po + e, &o, past_cache);
+  };
+  int64_t tail = run - (run - eb) % V;
+  if (LONG) {
+    for (int64_t e = eb + (int64_t)threadIdx.x * V; e + V <= run; e += (int64_t)256 * V) {
+      const BnPack<T> a0 = bn_load(p0 + e);
+      piece(e, a0, TWO ? bn_load(p1 + e) : a0);
+    }
+  } else if (UN == 1 && run <= 256) {
+    tail = eb;
+  } else {
+    BnPack<T> a[UN], b[UN];
+    bool in[UN];
+#pragma unroll
+    for (int u = 0; u < UN; ++u) {
+      const int64_t e = eb + ((int64_t)u * 256 + threadIdx.x) * V;
+      in[u] = e + V <= run;
+      if (in[u]) {
+        a[u] = bn_load(p0 + e);
+        if (TWO) b[u] = bn_load(p1 + e);
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < UN; ++u)
+      if (in[u]) piece(eb + ((int64_t)u * 256 + threadIdx.x) * V, a[u], b[u]);
+  }
+  const int64_t e = tail + threadIdx.x;
+  if (e < run) {
+    float r = fmaf(ld(p0 + e), ka, kc);
+    if (TWO) r = fmaf(ld(p1 + e), kb, r);
+    st(po + e, r);
+  }
 }
 
 __global__ void bn_finalize_kernel(const float* s, const float* sq, double inv_count, float eps, float* mean, float* invstd, int c) {
@@ -203,12 +283,14 @@ h3d_status bn_sums(void* handle, const h3d_tensor* x, const h3d_tensor* dy, cons
   if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn: workspace too small");
   const BnArgs a = bn_args(x, dy);
   if ((int64_t)x->n * a.run == 0) {
-    hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 4)), dim3(256), 0, s, (const float*)ws, o0, o1, x->c, 0);
+    bn_reduce(ws, o0, o1, x->c, 0, s);
     return launch_status(handle, "bn_sums");
   }
-  hipLaunchKernelGGL((bn_partial_kernel<T, MODE>), dim3((unsigned)a.segs, (unsigned)x->c, (unsigned)x->n), dim3(256), 0, s,
+  constexpr int UN = MODE == 0 ? 8 : 4;
+  auto kern = a.run <= BN_STEP<T> ? bn_partial_kernel<T, MODE, 1, false> : a.run < UN * BN_STEP<T> ? bn_partial_kernel<T, MODE, UN, false> : bn_partial_kernel<T, MODE, UN, true>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)a.segs, (unsigned)x->c, (unsigned)x->n), dim3(256), 0, s,
                      (const T*)x->data, dy ? (const T*)dy->data : nullptr, mean, invstd, (float*)ws, a);
-  hipLaunchKernelGGL(bn_reduce_kernel, dim3((unsigned)cdiv(x->c, 4)), dim3(256), 0, s, (const float*)ws, o0, o1, x->c, x->n * a.segs);
+  bn_reduce(ws, o0, o1, x->c, x->n * a.segs, s);
   return launch_status(handle, "bn_sums");
 }
 
@@ -218,7 +300,8 @@ h3d_status bn_apply(void* handle, const h3d_tensor* in0, const h3d_tensor* in1, 
   if ((int64_t)in0->n * in0->c * run == 0) return H3D_OK;
   const Geo g0 = make_geo(in0), g1 = in1 ? make_geo(in1) : g0, go = make_geo(out);
   const unsigned gx = (unsigned)std::max<int64_t>(1, std::min<int64_t>(cdiv(run, 256 * (16 / (int64_t)sizeof(T)) * 4), 1024));
-  hipLaunchKernelGGL((bn_apply_kernel<T, TWO>), dim3(gx, (unsigned)in0->c, (unsigned)in0->n), dim3(256), 0, s, (const T*)in0->data,
+  auto kern = run <= BN_STEP<T> ? bn_apply_kernel<T, TWO, 1, false> : run < 4 * BN_STEP<T> ? bn_apply_kernel<T, TWO, 4, false> : bn_apply_kernel<T, TWO, 4, true>;
+  hipLaunchKernelGGL(kern, dim3(gx, (unsigned)in0->c, (unsigned)in0->n), dim3(256), 0, s, (const T*)in0->data,
                      in1 ? (const T*)in1->data : nullptr, (T*)out->data, q, g0, g1, go, run,
                      (int64_t)in0->n * in0->c * run * (int64_t)sizeof(T) >= STREAM_PAST_CACHE_BYTES && run % (16 / sizeof(T)) == 0 && (uintptr_t)out->data % 16 == 0 &&
                          go.plane * go.hlo % (16 / sizeof(T)) == 0 && go.cstride % (16 / sizeof(T)) == 0);

@@ -96,13 +96,40 @@ def test_bn_rejects_mismatched_shards_and_small_workspace():
 def test_bn_steps_and_tails(shape):
     """Edges of the blocks' steps and segments against float64; the sums to 1e-5 of the sum of magnitudes (fp32 partial sums of at most
     2^17 terms), the affine results to half a unit of the eighth bit."""
+    _bn_against_float64(shape, "bf16", 2.0 ** -8)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("shape", [
+    (9, 3, 4, 4, 4),             # 64 elements, one a thread; nine partial sums a channel
+    (1, 2, 1, 16, 16),           # 256 and 257: the last run of single elements, the first of pieces
+    (1, 2, 1, 1, 257),
+    (2, 3, 1, 32, 32),           # 1024: one piece a thread in fp32
+    (1, 2, 5, 5, 41),            # 1025
+    (2, 2, 8, 16, 16),           # 2048: one piece a thread in bf16
+    (1, 2, 3, 1, 683),           # 2049
+    (1, 1, 1, 89, 46),           # 4094, 4096: around a step of the fp32 affine pass
+    (1, 1, 4, 32, 32),
+    (1, 2, 1, 1, 8191),          # around steps of the sums in fp32 and of the bf16 affine pass
+    (1, 1, 8, 32, 32),
+    (1, 1, 3, 43, 127),          # 16383, 16384, 16385: around a step of the bf16 sums
+    (1, 1, 16, 32, 32),
+    (1, 1, 5, 29, 113),
+])
+def test_bn_short_runs(shape, dtype):
+    """Every form that the length of a run chooses, at its first and last length, against float64."""
+    _bn_against_float64(shape, dtype, 2.0 ** -8 if dtype == "bf16" else 1e-6)
+
+
+def _bn_against_float64(shape, dtype, rel):
     import torch
     import paper_2007_12856_amd as h3d
     N, C, D, H, W = shape
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
     g = torch.Generator(device="cuda")
     g.manual_seed(11)
-    x = torch.randn(shape, generator=g, device="cuda").mul_(0.7).add_(0.3).to(torch.bfloat16)
-    dy = torch.randn(shape, generator=g, device="cuda").to(torch.bfloat16)
+    x = torch.randn(shape, generator=g, device="cuda").mul_(0.7).add_(0.3).to(dt)
+    dy = torch.randn(shape, generator=g, device="cuda").to(dt)
     vec = lambda: torch.empty(C, device="cuda")
     s, sq, mean, inv, sdy, sdx = (vec() for _ in range(6))
     gamma, beta = torch.rand(C, generator=g, device="cuda") + 0.5, torch.rand(C, generator=g, device="cuda")
@@ -123,4 +150,4 @@ def test_bn_steps_and_tails(shape):
     ref_y = per(gamma) * xhat + per(beta)
     ref_dx = per(gamma * inv) * (G - per(sdy / count) - xhat * per(sdx / count))
     for got, ref in ((y.t, ref_y), (dx.t, ref_dx)):
-        assert float(((got.double() - ref).abs() - 2.0 ** -8 * ref.abs()).max()) <= 1e-5
+        assert float(((got.double() - ref).abs() - rel * ref.abs()).max()) <= 1e-5
