@@ -1329,6 +1329,22 @@ static void bf_prep_tensors(const h3d_tensor* x, const h3d_tensor* dz, const Pre
   *x_lo = lo;
 }
 
+// Masked rows of whole 16-byte units: does the copy pay against the general kernel with its fused mask?  General -> prepared, us:
+//   up to 32 output channels always: 16->16 on 16x32x32 22 -> 15, 128->32 on 16x32x32 35 -> 32, 64->32 on 64^3 229 -> 65
+//   more of them from 6 to 16: only as long as everything is small.  The rolling kernel holds one block of input channels then and reads g
+//     for half the work: 8->64 on 16x32x32 25 -> 21, 16->64 on 32^3 31 -> 31, on 4 x 32^3 39 -> 48, on 64x128x128 219 -> 350
+//   more of both: from about 1.4e8 products a tap on, counted over the general kernel's tiles, which are 32 or 64 columns wide.  Below, the
+//     rolling kernel's one round of workgroups has too few tiles to make up for their partial sums: 32->64 on 32^3 (0.7e8) 32 -> 40,
+//     64->128 on 16x32x32 (1.3e8) 35 -> 43, 40->96 on 2 x 10x30x40 (1.5e8) 54 -> 50, 24->128 on 16x48x48 (1.5e8) 55 -> 44, 128->128 on
+//     16x32x32 (2.7e8) 64 -> 55
+// For the few input channels of a first layer the general kernel is the faster one (4->16 on 4 x 128^3: 292 us against 314).
+static bool bf_mask_copy_pays(const h3d_tensor* x, const h3d_tensor* dz) {
+  if (x->c <= 4) return false;
+  if (dz->c <= 32) return true;
+  const int64_t products = (int64_t)x->n * x->d * x->h * cdiv(x->w, x->w > 32 ? 64 : 32) * (x->w > 32 ? 64 : 32) * x->c * dz->c;
+  return x->c <= 16 ? products <= (int64_t)32 << 20 : products >= (int64_t)140000000;
+}
+
 static bool bf_prep_plan(const h3d_tensor* x, const h3d_tensor* dz, BfPrep* p) {
   if (x->n < 1 || x->d < 1 || x->h < 1 || x->w < 8) return false;
   h3d_tensor whole = *x;
@@ -1336,10 +1352,9 @@ static bool bf_prep_plan(const h3d_tensor* x, const h3d_tensor* dz, BfPrep* p) {
   if (!bf_roll_shape(&whole) && !row32_bf_shape(&whole, dz)) return false;
   const int64_t row = (int64_t)x->h * prep_w(x->w) * 2;
   // Rows of whole 16-byte units: only a masked gradient is copied, in slabs of at least 24 MiB (masked 64->64 on 4 x 64^3: 425 us
-  // in 8 slabs, 875 in 16, 687 by the general kernel); for the few input channels of a first layer the general kernel with its fused
-  // mask is the faster one (4->16 on 4 x 128^3: 292 us against 314).
+  // in 8 slabs, 875 in 16, 687 by the general kernel).
   const bool whole_rows = x->w % 8 == 0;
-  if (whole_rows && x->c <= 4) return false;
+  if (whole_rows && !bf_mask_copy_pays(x, dz)) return false;
   for (int64_t mib = 64; mib >= 6; mib -= mib > 16 ? 8 : 2) {
     if (!prep_tiling(x->n, x->d, (whole_rows ? dz->c : x->c + dz->c) * row, whole_rows ? 0 : 2, mib << 20, &p->t)) return false;
     if (whole_rows && p->t.count() > 1 && mib < 24) return false;

@@ -104,3 +104,35 @@ def test_slabs_of_prepared_operands_equal_the_general_kernels(case):
     rms = float(dw1.square().mean().sqrt())
     assert float((dw0 - dw1).abs().max()) <= 1e-5 * max(rms, float(dw1.abs().max()))
     assert float((db0 - db1).abs().max()) <= 1e-5 * float(db1.abs().max().clamp_min(rms))
+
+
+@pytest.mark.parametrize("shape,copied", [
+    ((1, 24, 32, 8, 20, 32), True),         # up to 32 output channels: whatever the size
+    ((1, 24, 64, 16, 32, 32), False),       # more of both: from 1.4e8 products on
+    ((1, 64, 64, 17, 31, 64), False),
+    ((1, 64, 64, 9, 60, 40), True),         # .. counted over tiles of 64 columns
+    ((1, 16, 64, 32, 32, 32), True),        # up to 16 input channels: up to 2^25
+    ((1, 16, 64, 33, 32, 32), False),
+    ((2, 4, 48, 8, 20, 64), False),         # a first layer
+])
+def test_masked_filter_gradient_takes_the_copy_where_it_pays(shape, copied):
+    """Either side of the rule's lines, against the fp64 sum (the same products in fp32, in either kernel's order) of the rounded gradient."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, ci, co, D, H, W = shape
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x, dz, z = (torch.randn((N, c, D, H, W), generator=g, device="cuda").bfloat16() for c in (ci, co, co))
+    dw, db = torch.empty((co, ci, 3, 3, 3), device="cuda"), torch.empty(co, device="cuda")
+    h3d.conv3d_bwd_filter(h3d.Slab(x), h3d.Slab(dz), h3d.Slab(z), dw, db, h3d.ACT_LEAKY, 0.01)
+    assert ("roll" in h3d.h3d_last_kernel()) == copied, h3d.h3d_last_kernel()
+    gd = torch.where(z > 0, dz.float(), dz.float() * 0.01).bfloat16().double()
+    xp = torch.nn.functional.pad(x.double(), (1, 1, 1, 1, 1, 1))
+    ref = torch.empty_like(dw, dtype=torch.float64)
+    for a in range(3):
+        for b in range(3):
+            for c in range(3):
+                v = xp[:, :, a:a + D, b:b + H, c:c + W]
+                ref[:, :, a, b, c] = gd.transpose(0, 1).reshape(co, -1) @ v.transpose(0, 1).reshape(ci, -1).t()
+    bar = float(np.sqrt(N * D * H * W)) * 2.0 ** -23        # fp32 sum of that many products
+    close(from_dev(dw), ref.cpu().numpy(), bar, elem=8 * bar)
+    close(from_dev(db), gd.sum((0, 2, 3, 4)).cpu().numpy(), bar, elem=8 * bar)
