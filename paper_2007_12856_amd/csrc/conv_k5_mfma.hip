@@ -245,9 +245,10 @@ __global__ void __launch_bounds__(320 * KF_GROUPS) k5_bwf_rows_kernel(const bf16
   extern __shared__ uint4 lds[];
   const int tid = threadIdx.x, lane = tid & 63, lc = lane & 31, lh = lane >> 5;
   const int grp = __builtin_amdgcn_readfirstlane(tid / 320), t320 = tid % 320, kh = __builtin_amdgcn_readfirstlane(t320 >> 6);
-  // XCD (linear index mod 8) takes every eighth chunk with all its kd planes and channel blocks, which read the same rows
-  const int per_chunk = 5 * a.cobs * a.cibs, q = blockIdx.x >> 3;
-  const int chunk = (int)(blockIdx.x & 7) + 8 * (q / per_chunk), kd = q % per_chunk % 5, blk = q % per_chunk / 5;
+  // an XCD (linear index mod 8) takes an eighth of the list (chunk, channel block, kd): a chunk's kd planes and channel blocks read the
+  // same rows
+  const int per_chunk = 5 * a.cobs * a.cibs, q = (int)(blockIdx.x & 7) * (int)(gridDim.x / 8) + (int)(blockIdx.x >> 3);
+  const int chunk = q / per_chunk, kd = q % per_chunk % 5, blk = q % per_chunk / 5;
   if (chunk >= a.chunks) return;
   const int run = chunk >= a.half ? chunk - a.half : chunk;
   if (chunk >= a.half) g += a.neg;
@@ -436,12 +437,17 @@ bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z) {
 }
 size_t k5_mfma_wp_bytes(int rows, int contraction) { return (size_t)cdiv(rows, 32) * cdiv(contraction, 16) * 125 * 1024; }
 
-// One workgroup per CU and kd (256 CUs): more chunks only add partial sums; at least 8 rows for a group of wavefronts.
+// One round of workgroups (256 CUs, one each): more chunks only add partial sums; at least 8 rows for a group of wavefronts.  Chunks are
+// spread over the XCDs by the list's order, whatever their number (a chunk an XCD, as it was, left five of eight XCDs idle with three
+// chunks: masked 128->128 on 16x64x64 759 -> 284 us; 96->96 333 -> 178; with multiples of eight chunks 64->64 on 32x64x64 209 -> 154).
+// Where that leaves few and long chains of products two rounds halve them for little time: error of dw against 64 bits, 128->128 on
+// 16x64x64 (9 chains of 114 rows), 5.3e-7 -> 3.7e-7, 284 -> 296 us; on 32x96x96 1277 -> 1295 us; 64->64 on 64x128x128 1110 -> 1101.
 // A gradient in two parts has its chunks split between them.
 static int k5_bf_chunks(const h3d_tensor* x, int cout, int parts) {
   const int64_t groups = 5 * cdiv(cout, 32) * cdiv(x->c, 32);
   const int64_t rows = (int64_t)x->n * x->d * cdiv(x->w, KF_SEG) * x->h;
-  const int64_t full = 32 / groups >= 1 ? 32 / groups * 8 : 256 / groups;
+  int64_t full = std::max<int64_t>(parts, 256 / groups);
+  if (KF_GROUPS * full < 64 && rows > 96 * KF_GROUPS * full) full = std::max<int64_t>(full, 512 / groups);
   return parts * (int)std::max<int64_t>(1, std::min<int64_t>(full / parts, cdiv(rows, 24)));
 }
 size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout, int parts) {
@@ -507,7 +513,7 @@ h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, 
   a.cobs = (int)cdiv(cout, 32); a.cibs = (int)cdiv(x->c, 32);
   float* part = (float*)ws;
   float* part_db = part + (size_t)a.chunks * 125 * a.cobs * a.cibs * 1024;
-  const dim3 grid((unsigned)(cdiv(a.chunks, 8) * 8 * 5 * a.cobs * a.cibs));
+  const dim3 grid((unsigned)(cdiv((int64_t)a.chunks * 5 * a.cobs * a.cibs, 8) * 8));
   static const h3d_status ready = k5_lds(handle, k5_bwf_rows_kernel, KF_LDS);
   H3D_TRY(ready);
   hipLaunchKernelGGL(k5_bwf_rows_kernel, grid, dim3(320 * KF_GROUPS), KF_LDS, s, (const bf16_t*)x_data, (const bf16_t*)g_data, part, part_db, a);

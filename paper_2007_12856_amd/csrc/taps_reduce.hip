@@ -4,7 +4,7 @@
 
 namespace h3d {
 
-// dw[co][ci][tap] and db[co] = the partial sums in chunk order (eight loads in flight), those of the chunks from `half` on times `slope`
+// dw[co][ci][tap] and db[co] = the partial sums in a fixed order (eight loads in flight), those of the chunks from `half` on times `slope`
 __global__ void __launch_bounds__(256) taps_reduce_kernel(const float* __restrict__ part, const float* __restrict__ part_db, float* __restrict__ dw,
                                                         float* __restrict__ db, int taps, int cin, int cout, int cip, int cop, int nchunks, int half, float slope) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -25,16 +25,14 @@ __global__ void __launch_bounds__(256) taps_reduce_kernel(const float* __restric
     return;
   }
   auto sum = [&](int c, int end) {
-    float s = 0.f;
-    for (; c + 8 <= end; c += 8) {
-      float v[8];
+    float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};      // (of every eighth chunk: a chain of 170 chunks would show in db)
+    for (; c + 8 <= end; c += 8)
 #pragma unroll
-      for (int k = 0; k < 8; ++k) v[k] = src[(c + k) * stride];
+      for (int k = 0; k < 8; ++k) s[k] += src[(c + k) * stride];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) s += v[k];
-    }
-    for (; c < end; ++c) s += src[c * stride];
-    return s;
+    for (int k = 0; k < 7; ++k)
+      if (c + k < end) s[k] += src[(c + k) * stride];
+    return ((s[0] + s[1]) + (s[2] + s[3])) + ((s[4] + s[5]) + (s[6] + s[7]));
   };
   const float s = sum(0, half);
   *dst = half < nchunks ? fmaf(slope, sum(half, nchunks), s) : s;

@@ -294,3 +294,39 @@ def test_k5_ragged_masked_gradient_is_not_rounded(shape, alpha):
     bar = float(np.sqrt(N * D * H * W)) * 2.0 ** -23
     close(from_dev(dw), dwo, bar, elem=8 * bar)
     close(from_dev(db), dbo, bar, elem=8 * bar)
+
+
+@pytest.mark.parametrize("masked", [False, True])
+@pytest.mark.parametrize("shape", [(128, 128, 16, 60, 62), (100, 70, 5, 24, 40), (64, 64, 32, 64, 64), (16, 16, 8, 160, 160)])
+def test_k5_filter_gradient_sums_against_float64(shape, masked):
+    """Many channels (fewer chunks than XCDs), rows for two rounds of workgroups, few channels.  A chain holds about 400 matrix products
+    before a rounded addition takes it up; at one unit of the 24th bit each, in random directions, 20 2^-24.  (The slope
+    is a power of two, so that aligned rows, whose g is rounded to bf16, are exact as well.)"""
+    import torch
+    import paper_2007_12856_amd as h3d
+    Ci, Co, D, H, W = shape
+    print("k5 sums", shape, masked, flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn((1, Ci, D + 4, H, W), device="cuda", generator=gen).bfloat16()
+    dz = torch.randn((1, Co, D, H, W), device="cuda", generator=gen).bfloat16()
+    z = None
+    alpha = 0.25
+    if masked:
+        z = torch.randn(dz.shape, device="cuda", generator=gen).bfloat16()
+    dw, db = torch.empty((Co, Ci, 5, 5, 5), device="cuda"), torch.empty((Co,), device="cuda")
+    slab = lambda t, halo: h3d.Slab(t, halo, halo, D, 3 * D)
+    h3d.conv3d_k5_bwd_filter(slab(x, 2), slab(dz, 0), slab(z, 0) if masked else None, dw, db, h3d.ACT_LEAKY if masked else h3d.ACT_NONE, alpha)
+    assert h3d.h3d_last_kernel() == "k5_bwf_rows_kernel"
+    g = dz.double()[0]
+    if masked:
+        g = torch.where(z[0] > 0, g, alpha * g)
+    xp = torch.nn.functional.pad(x[0].double(), (2, 2, 2, 2))
+    ref = torch.empty(dw.shape, dtype=torch.float64, device="cuda")
+    gt = g.reshape(Co, -1)
+    for a in range(5):
+        for b in range(5):
+            for c in range(5):
+                ref[:, :, a, b, c] = gt @ xp[:, a:a + D, b:b + H, c:c + W].reshape(Ci, -1).t()
+    bar = 20 * 2.0 ** -24
+    assert float((dw.double() - ref).norm() / ref.norm()) <= bar
+    assert float((db.double() - gt.sum(1)).norm() / gt.sum(1).norm()) <= bar
