@@ -205,10 +205,24 @@ static size_t s2_general_ws_bytes(void* handle, int op, const h3d_tensor* x, con
   }
 }
 
+// Route of a bf16 layer (x: input side, y: output side).  The direct kernels work in blocks of 32 input channels forward and 64 x 64 in
+// backward-filter, whatever is there; the rewriting turns a first layer's few input channels into eight times as many.  us, rewriting and
+// direct:
+//   forward: 1->16 on 32x128x128 23 and 20, on 64x128x128 26 and 35, 4->16 there 43 and 37, on 128^3 57 and 66
+//   backward-filter, no mask: 1->16 on 16x32x32 16 and 17, on 32x64x64 16 and 29, on 128^3 33 and 109; 2->16 on 32x64x64 18 and 24; 3->16 on 64^3
+//     26 and 35; 4->16 on 2 x 32x96x96 37 and 47; with a mask the same within a tenth
+static bool s2_direct(int op, const h3d_tensor* x, const h3d_tensor* y) {
+  if (!s2_mfma_supported(x, y)) return false;
+  const int64_t voxels = (int64_t)x->n * x->d * x->h * x->w;
+  if (op == H3D_OP_FWD) return x->c > 4 || voxels < (x->c <= 2 ? (int64_t)3 << 18 : (int64_t)3 << 19);
+  if (op == H3D_OP_BWD_FILTER) return voxels < (int64_t)x->c * 49152 || !((x->c <= 3 && x->c * y->c <= 128) || (x->c == 4 && y->c <= 16));
+  return true;
+}
+
 extern "C" size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y) {
   if (!handle || !x || !y || x->c < 0 || y->c < 0) return 0;
   if (op != H3D_OP_FWD && op != H3D_OP_BWD_DATA && op != H3D_OP_BWD_FILTER) return 0;
-  return s2_mfma_supported(x, y) ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
+  return s2_direct(op, x, y) ? s2_mfma_ws_bytes(op, x, y) : s2_general_ws_bytes(handle, op, x, y);
 }
 
 extern "C" h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y, int act,
@@ -220,7 +234,7 @@ extern "C" h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const
   if (y->d > 0 && x->d_offset > 0 && x->halo_lo < 1) return fail(handle, H3D_EHALO, "conv3d_s2_fwd: x must store its lower halo plane");
   if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_FWD, x, y)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_fwd: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_fwd: workspace must be 256-byte aligned");
-  if (s2_mfma_supported(x, y)) return s2_mfma_fwd(handle, x, w, bias, y, act_slope(act, alpha), ws, (hipStream_t)stream);
+  if (s2_direct(H3D_OP_FWD, x, y)) return s2_mfma_fwd(handle, x, w, bias, y, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(x, y);
   char* base = (char*)ws;
   p.xs.data = base;
@@ -250,7 +264,7 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_data(void* handle, const h3d_tensor* dy,
   }
   if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_DATA, dx, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_data: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_data: workspace must be 256-byte aligned");
-  if (s2_mfma_supported(dx, dy)) return s2_mfma_bwd_data(handle, dy, y, w, dx, act_slope(act, alpha), ws, (hipStream_t)stream);
+  if (s2_direct(H3D_OP_BWD_DATA, dx, dy)) return s2_mfma_bwd_data(handle, dy, y, w, dx, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(dx, dy);
   char* base = (char*)ws;
   p.gs.data = base;
@@ -296,7 +310,7 @@ extern "C" h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x
   }
   if (!ws || ws_bytes < h3d_conv3d_s2_workspace_bytes(handle, H3D_OP_BWD_FILTER, x, dy)) return fail(handle, H3D_EWORKSPACE, "conv3d_s2_bwd_filter: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_s2_bwd_filter: workspace must be 256-byte aligned");
-  if (s2_mfma_supported(x, dy)) return s2_mfma_bwd_filter(handle, x, dy, y, dw, db, act_slope(act, alpha), ws, (hipStream_t)stream);
+  if (s2_direct(H3D_OP_BWD_FILTER, x, dy)) return s2_mfma_bwd_filter(handle, x, dy, y, dw, db, act_slope(act, alpha), ws, (hipStream_t)stream);
   S2Plan p = s2_plan(x, dy);
   char* base = (char*)ws;
   p.xs.data = base;

@@ -26,7 +26,7 @@ struct S2Args {
   float slope;
   int vec;                          // result rows are 4-byte aligned pairs
   // backward-filter
-  int segs, bands, nstrips, strips_per_chunk, nchunks, cogroups, cigroups;
+  int segs, band, bands, nstrips, strips_per_chunk, nchunks, cogroups, cigroups;
 };
 
 // g = dy where the saved output is > 0, else dy * slope, rounded to bf16; two elements
@@ -426,12 +426,12 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 // columns = 32 input channels (B = x at every second column: the even and the odd elements of 16 consecutive ones, taken apart
 // with v_perm; even columns are tap kw = 1, odd ones kw = 2, and against g shifted by one column kw = 0), K = 16 coarse columns.
 // The tap plane kd is a grid dimension (27 accumulator blocks do not fit); a workgroup's four wavefronts hold the 9 (kh,kw)
-// blocks of 2 x 2 channel blocks (144 registers) and walk down the rows of a strip (32 coarse columns x SB_BAND rows of one
+// blocks of 2 x 2 channel blocks (144 registers) and walk down the rows of a strip (32 coarse columns x a band of rows of one
 // plane): fine row 2h is kh = 1 of g row h, fine row 2h + 1 is kh = 2 of it and kh = 0 of row h + 1, which stays in registers
 // for the next step, so x and g are read once.  Rows pass through LDS (two buffers, one barrier a step); row pitches of 9 and 5
 // units keep the 16-byte reads of neighbouring channels on different banks.
 // Partial sums [chunk][27][co][ci] per chunk of strips, added in chunk order: identical bits on every run.
-constexpr int SB_BAND = 16, SB_XP = 9, SB_GP = 5, SB_X = 2 * 64 * SB_XP, SB_BUF = SB_X + 64 * SB_GP;
+constexpr int SB_XP = 9, SB_GP = 5, SB_X = 2 * 64 * SB_XP, SB_BUF = SB_X + 64 * SB_GP;
 
 template <int MASK, bool V16>
 __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy, const bf16_t* __restrict__ m,
@@ -457,8 +457,8 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
     const int band = t % a.bands; t /= a.bands;
     w0 = (t % a.segs) * 32; t /= a.segs;
     z = t % a.y.d; n = t / a.y.d;
-    h = band * SB_BAND - 1;                       // first step of a strip: only g row h + 1 is fetched
-    hend = min((band + 1) * SB_BAND, H2);
+    h = band * a.band - 1;                       // first step of a strip: only g row h + 1 is fetched
+    hend = min((band + 1) * a.band, H2);
     rx = row_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)a.x.nstride * 2);
     rg = row_rsrc(dy + (int64_t)n * a.y.nstride, (uint32_t)a.y.nstride * 2);
     if (MASK == S2_MASK) rm = row_rsrc(m + (int64_t)n * a.m.nstride, (uint32_t)a.m.nstride * 2);
@@ -633,15 +633,22 @@ bool s2_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
   return (int64_t)x->n * y->d * cdiv(y->h, 4) * cdiv(y->w, 32) < ((int64_t)1 << 28) && cdiv(x->c, 64) * cdiv(y->c, 64) <= 65535;
 }
 
-struct S2BfPlan { int segs, bands, nstrips, per, nchunks, cogroups, cigroups; };
+struct S2BfPlan { int segs, band, bands, nstrips, per, nchunks, cogroups, cigroups; };
 // chunks: two workgroups per CU (256 CUs).  A step is shorter than the latency of the rows it prefetches, so a second workgroup
 // pays although it doubles the partial sums: one per CU 46 us (+ 7 for the reduction), two 33 (+ 10) at the size above.
 static S2BfPlan s2_bf_plan(const h3d_tensor* x, const h3d_tensor* y) {
   S2BfPlan p;
   p.cogroups = (int)cdiv(y->c, 64); p.cigroups = (int)cdiv(x->c, 64);
-  p.segs = (int)cdiv(y->w, 32); p.bands = (int)cdiv(y->h, SB_BAND);
-  p.nstrips = x->n * y->d * p.segs * p.bands;
+  p.segs = (int)cdiv(y->w, 32);
   const int64_t groups = (int64_t)3 * p.cogroups * p.cigroups;
+  // Small layers: bands of 8 or 4 rows, shorter chains of steps in more workgroups.  Each band costs a step more, and its chunk 442 KB of
+  // partial sums.  us, bands of 16, 8 and 4 rows: 16->16 on 16x32x32 (24 workgroups at 16 rows) 24.8, 17.0, 14.2; 64->64 on 32^3 (48) 28.0, 23.4,
+  // 24.7; 16->8 on 32x64x64 (96) 27.1, 21.6, 23.5; 4->64 on 16x128x128 (192), 16 and 8: 31, 34.
+  for (p.band = 16;; p.band /= 2) {
+    p.bands = (int)cdiv(y->h, p.band);
+    p.nstrips = x->n * y->d * p.segs * p.bands;
+    if (p.band == 4 || p.nstrips * groups >= (p.band == 16 ? 160 : 64)) break;
+  }
   const int64_t want = std::max<int64_t>(1, std::min<int64_t>(p.nstrips, 512 / groups));
   p.per = (int)cdiv(p.nstrips, want);
   p.nchunks = (int)cdiv(p.nstrips, p.per);
@@ -730,7 +737,7 @@ h3d_status s2_mfma_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tenso
                               void* ws, hipStream_t s) {
   S2Args a = s2_args(x, dy, y, slope);
   const S2BfPlan p = s2_bf_plan(x, dy);
-  a.segs = p.segs; a.bands = p.bands; a.nstrips = p.nstrips; a.strips_per_chunk = p.per; a.nchunks = p.nchunks;
+  a.segs = p.segs; a.band = p.band; a.bands = p.bands; a.nstrips = p.nstrips; a.strips_per_chunk = p.per; a.nchunks = p.nchunks;
   a.cogroups = p.cogroups; a.cigroups = p.cigroups;
   float* part = (float*)ws;
   const int cop = p.cogroups * 64, cip = p.cigroups * 64;

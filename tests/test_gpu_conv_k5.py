@@ -297,7 +297,7 @@ def test_k5_ragged_masked_gradient_is_not_rounded(shape, alpha):
 
 
 @pytest.mark.parametrize("masked", [False, True])
-@pytest.mark.parametrize("shape", [(128, 128, 16, 60, 62), (100, 70, 5, 24, 40), (64, 64, 32, 64, 64), (16, 16, 8, 160, 160)])
+@pytest.mark.parametrize("shape", [(128, 128, 16, 60, 62), (100, 70, 5, 24, 40), (16, 16, 8, 64, 64)])
 def test_k5_filter_gradient_sums_against_float64(shape, masked):
     """Many channels (fewer chunks than XCDs), rows for two rounds of workgroups, few channels.  A chain holds about 400 matrix products
     before a rounded addition takes it up; at one unit of the 24th bit each, in random directions, 20 2^-24.  (The slope

@@ -254,3 +254,36 @@ def test_stride2_saved_output_stored_unlike_the_gradient(shape, planes):
     h3d.conv3d_s2_bwd_filter(xg, dyg, sg, dw, db, h3d.ACT_LEAKY, 0.01, ws)
     close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
     close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
+
+
+@pytest.mark.parametrize("shape,fwd,filt", [
+    # N, Cin, Cout, D, H, W; does forward / the filter gradient run on the direct kernels?
+    ((1, 1, 16, 12, 64, 62), True, True),
+    ((1, 1, 40, 12, 64, 64), True, False),
+    ((1, 1, 4, 64, 96, 128), False, False),
+    ((2, 2, 16, 16, 56, 64), True, False),
+    ((1, 3, 48, 16, 64, 160), True, True),
+    ((1, 4, 16, 8, 160, 160), True, False),
+    ((1, 4, 24, 8, 160, 160), True, True),
+    ((1, 16, 16, 16, 32, 32), True, True),      # bands of four rows
+    ((1, 16, 40, 4, 66, 64), True, True),       # bands of eight, the last of one row
+])
+def test_stride2_routes_of_few_input_channels(shape, fwd, filt):
+    """Either side of the sizes from which the rewriting is the faster route for a first layer, and the band heights of small layers."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    w, bias = _weights(Ci, Co, "bf16", 360)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 361, (N, Ci, D, H, W)), "bf16")
+    yo = orc.conv3d_s2_fwd(xo, w, bias, orc.ACT_LEAKY, 0.01)
+    yg = h3d.conv3d_s2_fwd(xg, to_dev(w, "bf16"), to_dev(bias, "f32"), dev_like(yo, "bf16"), h3d.ACT_LEAKY, 0.01)
+    assert h3d.h3d_last_kernel().startswith("s2_fwd_kernel") == fwd
+    close(from_dev(yg.t), yo.a, TOL["bf16"])
+    so, sg = slab_pair(synth.flat("normal", SEED, 362, yo.a.shape), "bf16")
+    dyo, dyg = slab_pair(synth.flat("normal", SEED, 363, yo.a.shape), "bf16")
+    dwo, dbo = orc.conv3d_s2_bwd_filter(xo, dyo, so, orc.ACT_LEAKY, 0.01)
+    dw, db = torch.empty((Co, Ci, 3, 3, 3), device="cuda"), torch.empty((Co,), device="cuda")
+    h3d.conv3d_s2_bwd_filter(xg, dyg, sg, dw, db, h3d.ACT_LEAKY, 0.01)
+    assert h3d.h3d_last_kernel().startswith("s2_bwd_filter_kernel") == filt
+    close(from_dev(dw), dwo, 2e-4, elem=elem_masked_bf("bf16"))
+    close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
