@@ -48,12 +48,8 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t db_rsrc(const void* base, uint
 // global -> LDS copy issued so that the compiler does not wait for it before later LDS reads (common.h)
 __device__ __forceinline__ void db_dma16(h3d_i32x4 rs, uint4* lds_dst, int voff) { lds_dma16(rs, lds_addr_of(lds_dst), voff); }
 
-// V16: rows of whole aligned 16-byte pieces, x copied straight into LDS.  Otherwise (any width and alignment) x passes through
-// registers on its way, fetched a tile ahead, and both operands are cut at the end of the row: what lies behind it belongs to the
-// next row and may be infinite.  The direct kernel, which such widths had to take, gives a lane one voxel and reads dy once per
-// input channel: 128 -> 64 channels from 64x256x248 11650 -> 215 us, 64 -> 32 from 32x192x196 706 -> 46.
-template <int MRB, bool V16>
-__global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 4 ? 4 : 2) deconv_bf_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
+template <int MRB>
+__global__ void __launch_bounds__(64 * DB_NW, 4) deconv_bf_mfma_kernel(const bf16_t* __restrict__ x, const bf16_t* __restrict__ dy,
                                                                      float* __restrict__ part, DbfArgs a) {
   constexpr int CI_WG = 16 * MRB;
   constexpr int XPAD = (CI_WG * DB_PCI + 63) / 64 * 64;
@@ -99,27 +95,6 @@ __global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 4 ? 4 : 2) deconv_bf_
         db_dma16(rs, lds + buf * XPAD + 64 * (wave + DB_NW * i), ok ? 2 * (t0 + ci * (int)a.x.cstride + row * Wc + u8) : DB_OOB);
     }
   };
-  // the same through registers: piece i of a thread is channel (tid + 512 i) / 16, row and unit from the low bits of tid
-  constexpr int XR = V16 ? 1 : CI_WG * 4 * DB_R / (64 * DB_NW);
-  uint4 xv[XR];
-  const int xr_row = (tid >> 2) & 3, xr_u = tid & 3;
-  const int xspan = (int)stored_span(a.x), yspan = (int)stored_span(a.y);
-  auto fetch_x = [&](int n, int d, int h0, int w0) {
-    const __amdgpu_buffer_rsrc_t rs = row_rsrc(x + n * a.x.nstride, (uint32_t)xspan * 2);
-    const int o = (d + a.x.hlo) * (int)a.x.plane + (h0 + xr_row) * Wc;
-#pragma unroll
-    for (int i = 0; i < XR; ++i) {
-      const int ci = ci0 + (tid >> 4) + 32 * i;
-      xv[i] = row8<false>(rs, o + ci * (int)a.x.cstride, w0 + 8 * xr_u, Wc, xspan, ci < a.cin && h0 + xr_row < Hc);
-    }
-  };
-  auto store_x = [&](int d, int h0, int w0, int buf) {
-    const int o = (d + a.x.hlo) * (int)a.x.plane + (h0 + xr_row) * Wc;
-#pragma unroll
-    for (int i = 0; i < XR; ++i)
-      lds[buf * XPAD + ((tid >> 4) + 32 * i) * DB_PCI + 4 * xr_row + xr_u] =
-          fix8<false>(xv[i], o + (ci0 + (tid >> 4) + 32 * i) * (int)a.x.cstride, w0 + 8 * xr_u, Wc, xspan);
-  };
 
   f32x4 acc[MRB];
   f32x4 accdb = {0.f, 0.f, 0.f, 0.f};
@@ -140,29 +115,15 @@ __global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 4 ? 4 : 2) deconv_bf_
     d = r % Dc;
     n = r / Dc;
   }
-  if (t_begin < t_end) {
-    if constexpr (V16) {
-      load_x(n, d, th * DB_R, tw * 32, 0);
-    } else {
-      fetch_x(n, d, th * DB_R, tw * 32);
-      store_x(d, th * DB_R, tw * 32, 0);
-    }
-  }
+  if (t_begin < t_end) load_x(n, d, th * DB_R, tw * 32, 0);
   int buf = 0;
   const char* a_base = reinterpret_cast<const char*>(lds) + 16 * (lc * DB_PCI + lg);
   for (int tile = t_begin; tile < t_end; ++tile) {
     const int h0 = th * DB_R, w0 = tw * 32;
     // ---- this tile's dy fragments: 32 contiguous bytes per lane and row, straight from global memory
-    const __amdgpu_buffer_rsrc_t rs_y = db_rsrc(dy + n * a.y.nstride, (uint32_t)(V16 ? a.y.nstride : yspan) * 2);
+    const __amdgpu_buffer_rsrc_t rs_y = db_rsrc(dy + n * a.y.nstride, (uint32_t)a.y.nstride * 2);
     u32x4 braw[DB_R][2];
-    const int yrow = co * (int)a.y.cstride + (2 * d + ta + a.y.hlo) * (int)a.y.plane + (2 * h0 + tb) * Wf, yc = 2 * (w0 + 8 * lg);
-    if constexpr (!V16) {
-#pragma unroll
-      for (int r = 0; r < DB_R; ++r)
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          braw[r][k] = __builtin_bit_cast(u32x4, row8<false>(rs_y, yrow + 2 * r * Wf, yc + 8 * k, Wf, yspan, col_ok && h0 + r < Hc));
-    } else {
+    {
       const int yb = co * (int)a.y.cstride + (2 * d + ta + a.y.hlo) * (int)a.y.plane + (2 * h0 + tb) * Wf + 2 * (w0 + 8 * lg);
 #pragma unroll
       for (int r = 0; r < DB_R; ++r) {
@@ -173,39 +134,20 @@ __global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 4 ? 4 : 2) deconv_bf_
       }
     }
     // the x tile of this step has landed (issued one step ago); everyone is done with the other buffer
-    if constexpr (V16) asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DB_R) : "memory");
+    asm volatile("s_waitcnt vmcnt(%0)" ::"n"(2 * DB_R) : "memory");
     __syncthreads();
     int tw2 = tw + 1, th2 = th, d2 = d, n2 = n;
     if (tw2 == a.tiles_w) { tw2 = 0; ++th2; }
     if (th2 == a.tiles_h) { th2 = 0; ++d2; }
     if (d2 == Dc) { d2 = 0; ++n2; }
-    if (tile + 1 < t_end) {
-      if constexpr (V16) load_x(n2, d2, th2 * DB_R, tw2 * 32, buf ^ 1);
-      else fetch_x(n2, d2, th2 * DB_R, tw2 * 32);
-    }
+    if (tile + 1 < t_end) load_x(n2, d2, th2 * DB_R, tw2 * 32, buf ^ 1);
 
-    // The matrix cores truncate as they add, and over a long chain that shows (db of 2^19 voxels 2e-5 off, the direct kernel 1e-7): where
-    // that kernel had the shape before, the products of a tile start from zero and a rounded addition takes them to the sum.
-    f32x4 sum[V16 ? 1 : MRB], sumdb = accdb;
-    if constexpr (!V16) {
-#pragma unroll
-      for (int rb = 0; rb < MRB; ++rb) {
-        sum[rb] = acc[rb];
-        acc[rb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-      accdb = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
     const char* ap = a_base + 16 * XPAD * buf;
 #pragma unroll
     for (int r = 0; r < DB_R; ++r) {
       bf16x8 A[MRB];
 #pragma unroll
       for (int rb = 0; rb < MRB; ++rb) A[rb] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const uint4*>(ap + 16 * (rb * 16 * DB_PCI + 4 * r)));
-      if constexpr (!V16) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k)
-          braw[r][k] = __builtin_bit_cast(u32x4, fix8<false>(__builtin_bit_cast(uint4, braw[r][k]), yrow + 2 * r * Wf, yc + 8 * k, Wf, yspan));
-      }
       uint4 bf;
       bf.x = __builtin_amdgcn_perm(braw[r][0][1], braw[r][0][0], sel);
       bf.y = __builtin_amdgcn_perm(braw[r][0][3], braw[r][0][2], sel);
@@ -216,13 +158,6 @@ __global__ void __launch_bounds__(64 * DB_NW, V16 || MRB < 4 ? 4 : 2) deconv_bf_
       for (int rb = 0; rb < MRB; ++rb) acc[rb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(A[rb], B, acc[rb], 0, 0, 0);
       if (do_db) accdb = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, B, accdb, 0, 0, 0);
     }
-    if constexpr (!V16) {
-#pragma unroll
-      for (int rb = 0; rb < MRB; ++rb) acc[rb] += sum[rb];
-      accdb += sumdb;
-    }
-    if constexpr (!V16)
-      if (tile + 1 < t_end) store_x(d2, th2 * DB_R, tw2 * 32, buf ^ 1);      // (its readers passed this step's barrier)
     tw = tw2; th = th2; d = d2; n = n2;
     buf ^= 1;
   }
@@ -307,24 +242,20 @@ DbfPlan dbf_plan(const h3d_tensor* x, const h3d_tensor* dy) {
   return p;
 }
 
-template <int MRB, bool V16>
-h3d_status dbf_launch_as(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, hipStream_t stream) {
+template <int MRB>
+h3d_status dbf_launch(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, hipStream_t stream) {
   constexpr size_t lds_bytes = (size_t)2 * ((16 * MRB * DB_PCI + 63) / 64 * 64) * 16;
   static bool attr_set = false;
   if (!attr_set) {
-    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_bf_mfma_kernel<MRB, V16>), hipFuncAttributeMaxDynamicSharedMemorySize,
+    if (hipFuncSetAttribute(reinterpret_cast<const void*>(deconv_bf_mfma_kernel<MRB>), hipFuncAttributeMaxDynamicSharedMemorySize,
                             (int)lds_bytes) != hipSuccess)
       return fail(handle, H3D_EHIP, "deconv2_bwd_filter: cannot set the dynamic LDS size to %zu bytes", lds_bytes);
     attr_set = true;
   }
   const int64_t grid = cdiv(a.nchunks, 8) * 8 * (int64_t)(a.gco * a.gci);
   if (grid >= ((int64_t)1 << 31)) return fail(handle, H3D_EINVAL, "deconv2_bwd_filter: too many workgroups");
-  hipLaunchKernelGGL((deconv_bf_mfma_kernel<MRB, V16>), dim3((unsigned)grid), dim3(64 * DB_NW), lds_bytes, stream, x, dy, part, a);
+  hipLaunchKernelGGL((deconv_bf_mfma_kernel<MRB>), dim3((unsigned)grid), dim3(64 * DB_NW), lds_bytes, stream, x, dy, part, a);
   return H3D_OK;
-}
-template <int MRB>
-h3d_status dbf_launch(void* handle, const bf16_t* x, const bf16_t* dy, float* part, const DbfArgs& a, bool v16, hipStream_t stream) {
-  return v16 ? dbf_launch_as<MRB, true>(handle, x, dy, part, a, stream) : dbf_launch_as<MRB, false>(handle, x, dy, part, a, stream);
 }
 
 // whole aligned 16-byte pieces in every row of t
@@ -340,13 +271,11 @@ bool rows_any(const h3d_tensor* t) {
 
 }  // namespace
 
-static bool dbf_v16(const h3d_tensor* x, const h3d_tensor* dy) { return rows_v16(x) && rows_v16(dy); }
-
 bool deconv_bf_mfma_supported(const h3d_tensor* x, const h3d_tensor* dy) {
   if (x->dtype != H3D_BF16 || x->c < 1 || dy->c < 1) return false;
-  // Ragged rows keep the direct kernel: the matrix cores' additions were less exact than its own (the form for them is not routed to until
-  // its error against 64 bits is measured to be no larger).
-  if (!dbf_v16(x, dy)) return false;
+  // Other rows keep the direct kernel.  (A form of this one that took them through registers, 128 -> 64 channels from 64x256x248 11650 ->
+  // 215 us, was less exact: the sum of 2^19 voxels in db 2e-5 from 64 bits, where the direct kernel's is 1e-7.)
+  if (!rows_v16(x) || !rows_v16(dy)) return false;
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)dy->c * (dy->halo_lo + dy->d + dy->halo_hi) * dy->h * dy->w * 2;
   const int64_t ntiles = (int64_t)x->n * x->d * cdiv(x->h, DB_R) * cdiv(x->w, 32);
@@ -383,10 +312,9 @@ h3d_status deconv_bf_mfma(void* handle, const h3d_tensor* x, const h3d_tensor* d
   const bf16_t* xp = (const bf16_t*)x->data;
   const bf16_t* yp = (const bf16_t*)dy->data;
   h3d_status st;
-  const bool v16 = dbf_v16(x, dy);
-  if (p.mrb == 8) st = dbf_launch<8>(handle, xp, yp, (float*)ws, a, v16, stream);
-  else if (p.mrb == 4) st = dbf_launch<4>(handle, xp, yp, (float*)ws, a, v16, stream);
-  else st = dbf_launch<2>(handle, xp, yp, (float*)ws, a, v16, stream);
+  if (p.mrb == 8) st = dbf_launch<8>(handle, xp, yp, (float*)ws, a, stream);
+  else if (p.mrb == 4) st = dbf_launch<4>(handle, xp, yp, (float*)ws, a, stream);
+  else st = dbf_launch<2>(handle, xp, yp, (float*)ws, a, stream);
   if (st != H3D_OK) return st;
   hipLaunchKernelGGL(deconv_bf_mfma_reduce_kernel, dim3((unsigned)cdiv(nw + a.cout, 16)), dim3(256), 0, stream, (const float*)ws, dw,
                      db, nw, a.cout, a.nchunks);
