@@ -916,7 +916,7 @@ static h3d_status launch_variant_as(void* handle, const bf16_t* in, const bf16_t
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.csplit), dim3(WG_THREADS), lds_bytes, stream, in, mask, wp,
                      a.csplit > 1 ? nullptr : bias, out, a);
-  note_kernel(handle, "conv3d_mfma_kernel<%d,%d,%d,%d,%d,%d,%d>", NCB, ND, TWC, (int)MASKED, (int)VEC, (int)SPLIT, (int)FLAT);
+  note_kernel(handle, "conv3d_mfma_kernel<%d,%d,%d,%d,%d,%d,%d,%d>", NCB, ND, TWC, (int)MASKED, (int)VEC, (int)SPLIT, (int)FLAT, (int)ROW16);
   if (a.csplit > 1) return hipGetLastError() == hipSuccess ? H3D_OK : fail(handle, H3D_EHIP, "conv3d_mfma: launch failed");
   return launch_status(handle, "conv3d_mfma");
 }
@@ -958,9 +958,7 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
     attr_set = true;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy), dim3(256 * WCB * RSP), lds_bytes, stream, in, wp, bias, out, a);
-  if (WCB * RSP == 1) note_kernel(handle, "conv3d_mfma_wide_kernel<%d>", CB);
-  else if (RSP == 1) note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d>", CB, WCB);
-  else note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d,%d>", CB, WCB, RSP);
+  note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d,%d,%d>", CB, WCB, RSP, (int)RAGGED);
   return launch_status(handle, "conv3d_mfma_wide");
 }
 

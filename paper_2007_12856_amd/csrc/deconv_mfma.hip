@@ -255,6 +255,7 @@ h3d_status dbf_launch(void* handle, const bf16_t* x, const bf16_t* dy, float* pa
   const int64_t grid = cdiv(a.nchunks, 8) * 8 * (int64_t)(a.gco * a.gci);
   if (grid >= ((int64_t)1 << 31)) return fail(handle, H3D_EINVAL, "deconv2_bwd_filter: too many workgroups");
   hipLaunchKernelGGL((deconv_bf_mfma_kernel<MRB>), dim3((unsigned)grid), dim3(64 * DB_NW), lds_bytes, stream, x, dy, part, a);
+  note_kernel(handle, "deconv_bf_mfma_kernel<%d>", MRB);
   return H3D_OK;
 }
 
@@ -464,6 +465,7 @@ h3d_status dbd_launch_as(void* handle, const bf16_t* dy, const bf16_t* w, bf16_t
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu, cdiv(a.ncb, DD_NW)));
   hipLaunchKernelGGL((deconv_bd_mfma_kernel<MRB, STREAM>), dim3((unsigned)grid), dim3(64 * DD_NW), lds_bytes, stream, dy, w, dx, a);
+  note_kernel(handle, "deconv_bd_mfma_kernel<%d,%d>", MRB, (int)STREAM);
   return H3D_OK;
 }
 static int64_t fine_bytes(const Geo& y, int c) { return (int64_t)y.n * c * y.d * y.plane * (int64_t)sizeof(bf16_t); }
@@ -711,6 +713,7 @@ h3d_status dfw_launch_as(void* handle, const bf16_t* x, const uint4* wp, const f
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu, cdiv(a.ncb, DF_CBI)));
   hipLaunchKernelGGL((deconv_fw_mfma_kernel<RBW, KS, STREAM, V16>), dim3((unsigned)grid), dim3(64 * DF_NW), lds_bytes, stream, x, wp, bias, y, a);
+  note_kernel(handle, "deconv_fw_mfma_kernel<%d,%d,%d,%d>", RBW, KS, (int)STREAM, (int)V16);
   return H3D_OK;
 }
 template <int RBW, int KS>

@@ -124,6 +124,8 @@ def test_deconv_ragged_rows_bf16(case):
     yo = orc.deconv2_fwd(xo, w, bias)
     yg = moved(dev_like(yo, "bf16"), even=True)      # (odd result addresses keep the general kernel)
     h3d.deconv2_fwd(xg, to_dev(w, "bf16"), to_dev(bias, "f32"), yg)
+    ragged = h3d.h3d_last_kernel().startswith("deconv_fw_mfma_kernel") and h3d.h3d_last_kernel().endswith(",0>")
+    assert ragged == (cin * d * H * W >= 8)
     close(from_dev(yg.t), yo.a, TOL["bf16"])
     dyo, dyg = slab_pair(synth.flat("normal", SEED, 5900 + i, yo.a.shape), "bf16", (0, 0), yo.d_offset, yo.d_global)
     dxo = orc.deconv2_bwd_data(dyo, w)
@@ -132,6 +134,7 @@ def test_deconv_ragged_rows_bf16(case):
     dwo, dbo = orc.deconv2_bwd_filter(xo, dyo)
     dw, db = torch.empty((cin, cout, 2, 2, 2), device="cuda"), torch.empty((cout,), device="cuda")
     h3d.deconv2_bwd_filter(xg, moved(dyg), dw, db)
+    assert not h3d.h3d_last_kernel().startswith("deconv_bf_mfma_kernel")      # (whole aligned rows only)
     close(from_dev(dw), dwo, 2e-4)
     close(from_dev(db), dbo, 2e-4)
 
@@ -155,6 +158,7 @@ def test_narrow_rows_by_sixteen_bytes_equal_the_general_staging(cin, cout, N, D,
         assert (xs.data_ptr() % 16 == 0) == (shift == 0)
         y = torch.full((N, cout, D, H, W), float("nan"), dtype=x.dtype, device="cuda")
         h3d.conv3d_fwd(h3d.Slab(xs, 1, 1, 1, D + 2), w, bias, h3d.Slab(y, 0, 0, 1, D + 2), h3d.ACT_LEAKY, 0.01)
+        assert h3d.h3d_last_kernel().startswith("conv3d_mfma_kernel<") and h3d.h3d_last_kernel().endswith(",0>" if shift else ",1>")
         outs.append(y)
         flat.fill_(float("nan"))
     assert torch.equal(outs[0], outs[1]) and bool(torch.isfinite(outs[0]).all())
