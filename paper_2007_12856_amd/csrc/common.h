@@ -68,6 +68,16 @@ h3d_status launch_status(void* handle, const char* what);   // also records `wha
 // name of the kernel that does the arithmetic of the call under way (shown by h3d_last_kernel)
 void note_kernel(void* handle, const char* fmt, ...);
 
+// raises a kernel's dynamic LDS limit once (`done`: one flag per kernel); a failure is reported and tried again by the next call
+template <typename K>
+h3d_status raise_lds_limit(void* handle, K kern, size_t bytes, bool* done) {
+  if (*done) return H3D_OK;
+  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
+    return fail(handle, H3D_EHIP, "cannot raise the dynamic LDS limit to %zu bytes", bytes);
+  *done = true;
+  return H3D_OK;
+}
+
 inline float act_slope(int act, float alpha) { return act == H3D_ACT_LEAKY ? alpha : (act == H3D_ACT_RELU ? 0.f : 1.f); }
 
 // ---- bf16 storage helpers (device) -------------------------------------------------------------

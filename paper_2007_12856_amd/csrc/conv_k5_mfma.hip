@@ -465,16 +465,10 @@ static K5MArgs k5m_args(const Geo& in, const Geo& out, int cin, int cout) {
 }
 static bool rows16(const Geo& g, const void* p) { return g.w % 8 == 0 && g.cstride % 8 == 0 && (uintptr_t)p % 16 == 0; }
 
-template <typename K>
-static h3d_status k5_lds(void* handle, K kern, size_t bytes) {
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
-    return fail(handle, H3D_EHIP, "conv3d_k5: cannot raise the dynamic LDS limit to %zu bytes", bytes);
-  return H3D_OK;
-}
 template <int RB, bool V16>
 static h3d_status k5_launch(void* handle, const void* in, const void* wp, const float* bias, void* out, K5MArgs a, int n, hipStream_t s) {
-  static const h3d_status ready = k5_lds(handle, k5_conv_mfma_kernel<RB, V16>, K5Tile<RB>::LDS);
-  H3D_TRY(ready);
+  static bool lds_set = false;
+  H3D_TRY(raise_lds_limit(handle, k5_conv_mfma_kernel<RB, V16>, K5Tile<RB>::LDS, &lds_set));
   a.tiles_w = (int)cdiv(a.out.w, 32); a.tiles_h = (int)cdiv(a.out.h, 8 * RB);
   a.ntiles = n * a.out.d * a.tiles_h * a.tiles_w;
   hipLaunchKernelGGL((k5_conv_mfma_kernel<RB, V16>), dim3((unsigned)(cdiv(a.ntiles, 8) * 8), (unsigned)cdiv(a.cout, 32)), dim3(512), K5Tile<RB>::LDS, s,
@@ -514,8 +508,8 @@ h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, 
   float* part = (float*)ws;
   float* part_db = part + (size_t)a.chunks * 125 * a.cobs * a.cibs * 1024;
   const dim3 grid((unsigned)(cdiv((int64_t)a.chunks * 5 * a.cobs * a.cibs, 8) * 8));
-  static const h3d_status ready = k5_lds(handle, k5_bwf_rows_kernel, KF_LDS);
-  H3D_TRY(ready);
+  static bool lds_set = false;
+  H3D_TRY(raise_lds_limit(handle, k5_bwf_rows_kernel, KF_LDS, &lds_set));
   hipLaunchKernelGGL(k5_bwf_rows_kernel, grid, dim3(320 * KF_GROUPS), KF_LDS, s, (const bf16_t*)x_data, (const bf16_t*)g_data, part, part_db, a);
   note_kernel(handle, "k5_bwf_rows_kernel");
   taps_reduce(part, part_db, dw, db, 125, x->c, cout, a.cibs * 32, a.cobs * 32, a.chunks, a.half, slope, s);

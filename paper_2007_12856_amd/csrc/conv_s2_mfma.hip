@@ -678,17 +678,11 @@ static void s2_pack(const void* w, void* wp, int cin, int cout, bool transposed,
   hipLaunchKernelGGL(s2_pack_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, transposed ? 1 : 0, nchunk, total);
 }
 static unsigned xcd_grid(int n) { return (unsigned)(cdiv(n, 8) * 8); }
-template <typename K>
-static h3d_status s2_lds(void* handle, K kern, size_t bytes) {
-  if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)bytes) != hipSuccess)
-    return fail(handle, H3D_EHIP, "conv3d_s2: cannot raise the dynamic LDS limit to %zu bytes", bytes);
-  return H3D_OK;
-}
 
 template <int NCO, int CB, bool V16>
 static h3d_status s2_launch_fwd(void* handle, const h3d_tensor* x, const uint4* wp, const float* bias, h3d_tensor* y, const S2Args& a, hipStream_t s) {
-  static const h3d_status ready = s2_lds(handle, s2_fwd_kernel<NCO, CB, V16>, SF_LDS);
-  H3D_TRY(ready);
+  static bool lds_set = false;
+  H3D_TRY(raise_lds_limit(handle, s2_fwd_kernel<NCO, CB, V16>, SF_LDS, &lds_set));
   hipLaunchKernelGGL((s2_fwd_kernel<NCO, CB, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(y->c, 32 * NCO * CB)), dim3(256), SF_LDS, s,
                      (const bf16_t*)x->data, wp, bias, (bf16_t*)y->data, a);
   note_kernel(handle, "s2_fwd_kernel<%d,%d,%d>", NCO, CB, (int)V16);
@@ -711,8 +705,8 @@ h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const f
 
 template <int MASK, bool V16>
 static h3d_status s2_launch_bd(void* handle, const h3d_tensor* dy, const h3d_tensor* m, const uint4* wp, h3d_tensor* dx, const S2Args& a, hipStream_t s) {
-  static const h3d_status ready = s2_lds(handle, s2_bwd_data_kernel<MASK, V16>, SD_LDS);
-  H3D_TRY(ready);
+  static bool lds_set = false;
+  H3D_TRY(raise_lds_limit(handle, s2_bwd_data_kernel<MASK, V16>, SD_LDS, &lds_set));
   hipLaunchKernelGGL((s2_bwd_data_kernel<MASK, V16>), dim3(xcd_grid(a.ntiles), (unsigned)cdiv(dx->c, 32)), dim3(512), SD_LDS, s,
                      (const bf16_t*)dy->data, (const bf16_t*)(m ? m->data : nullptr), wp, (bf16_t*)dx->data, a);
   note_kernel(handle, "s2_bwd_data_kernel<%d,%d>", MASK, (int)V16);

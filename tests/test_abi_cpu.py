@@ -63,3 +63,29 @@ def test_k5_filter_gradient_of_a_channel_whose_padded_copy_is_too_long():
         assert (need > 2 * 32 * (d + 4) * 5760 * 104) == fits
         # forward reads x where it lies
         assert lib.h3d_conv3d_k5_workspace_bytes(handle, h3d.OP_FWD, ctypes.byref(x), ctypes.byref(z)) == 1 * 2 * 125 * 1024
+
+
+def test_a_failed_kernel_setup_is_reported_to_every_handle():
+    """Without a device the dynamic LDS limit of the 5x5x5 kernel cannot be raised.  Each call says so on its own handle: the first failure
+    is not kept for the process."""
+    import subprocess
+    import sys
+    script = """
+import ctypes, sys
+sys.path.insert(0, %r)
+import paper_2007_12856_amd as h3d
+lib = h3d.lib()
+none = ctypes.c_void_p()
+assert lib.h3d_create(ctypes.byref(none)) != 0          # no device is visible to this process: nothing below can run on one
+t = lambda c: h3d.h3d_tensor(1 << 20, h3d.BF16, 1, c, 4, 16, 32, 0, 0, 0, 4, 0, 0)
+x, z = t(16), t(32)
+for attempt in range(2):
+    handle = ctypes.cast(ctypes.create_string_buffer(4096), ctypes.c_void_p)
+    need = lib.h3d_conv3d_k5_workspace_bytes(handle, h3d.OP_FWD, ctypes.byref(x), ctypes.byref(z))
+    st = lib.h3d_conv3d_k5_fwd(handle, ctypes.byref(x), ctypes.c_void_p(1 << 20), None, ctypes.byref(z), 0, 0.0, ctypes.c_void_p(1 << 20), need, None)
+    text = lib.h3d_last_error(handle)
+    assert st != 0 and b"LDS limit" in text, (attempt, st, text)
+""" % ROOT
+    env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
+    r = subprocess.run([sys.executable, "-c", script], env=env, capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stderr
