@@ -728,7 +728,13 @@ h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const floa
 bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
   if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > 64 || (uintptr_t)y->data % 4 != 0) return false;
   if (make_geo(y).cstride % 2 != 0 || make_geo(y).nstride % 2 != 0) return false;      // results leave as pairs in one dword
-  if (!rows_v16(x) && !rows_any(x)) return false;
+  // Ragged rows with few channels stay with the direct kernel, which reads x once per 8 output channels; this one pads the channels of
+  // both sides.  us, direct and here: 8->16 on 8x9x10 8.9 and 10.0, 16->16 there 12.3 and 10.0; 16->16 on 32x62x66 21 and 26, 16->32 there
+  // 33 and 26; 4->4 on 2 x 24x70x90 13 and 37.
+  if (!rows_v16(x)) {
+    if (!rows_any(x)) return false;
+    if ((int64_t)x->n * x->d * x->h * x->w < 49152 ? x->c < 16 : x->c * y->c < 512) return false;
+  }
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)y->c * (y->halo_lo + y->d + y->halo_hi) * y->h * y->w * 2;
   const int64_t ncb = (int64_t)x->n * x->d * x->h * cdiv(x->w, 32);

@@ -125,7 +125,7 @@ def test_deconv_ragged_rows_bf16(case):
     yg = moved(dev_like(yo, "bf16"), even=True)      # (odd result addresses keep the general kernel)
     h3d.deconv2_fwd(xg, to_dev(w, "bf16"), to_dev(bias, "f32"), yg)
     ragged = h3d.h3d_last_kernel().startswith("deconv_fw_mfma_kernel") and h3d.h3d_last_kernel().endswith(",0>")
-    assert ragged == (cin * d * H * W >= 8)
+    assert ragged == (cin >= 16)      # (volumes of less than 49152 voxels)
     close(from_dev(yg.t), yo.a, TOL["bf16"])
     dyo, dyg = slab_pair(synth.flat("normal", SEED, 5900 + i, yo.a.shape), "bf16", (0, 0), yo.d_offset, yo.d_global)
     dxo = orc.deconv2_bwd_data(dyo, w)
