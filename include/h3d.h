@@ -99,7 +99,13 @@ const char* h3d_last_kernel(void* handle);
  * bias: fp32 [cout] or NULL (the paper's CosmoFlow variant drops conv biases, Sec. IV).
  * act/alpha: z = y > 0 ? y : slope*y with slope = alpha (LEAKY), 0 (RELU), 1 (NONE).
  *
- * Workspace bytes needed by `op` for these shapes (0 is possible).  Returns 0 on bad arguments. */
+ * Workspace bytes needed by `op` for these shapes (0 is possible).  Returns 0 on bad arguments.
+ * x / z: the tensor that is read and the one that is written (FWD: x, z; BWD_DATA: dz, dx), or x and dz (BWD_FILTER).
+ * For bf16 layers the size has room for copies of up to 160 MiB (BWD_DATA, and FWD where w is odd) or 96 MiB (BWD_FILTER):
+ * dz with the activation's derivative multiplied in, rows padded to whole 16 bytes.  BWD_DATA does not know the activation;
+ * a caller that passes act NONE or z NULL can give it what FWD of the same two descriptors asks for.  Less room than for
+ * the copies, down to what the call needs at all (H3D_EWORKSPACE below), selects a slower kernel: in BWD_DATA and FWD with
+ * the same bits, in BWD_FILTER with the sums in another order. */
 size_t h3d_conv3d_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z);
 
 /* Forward: z[n,co,p] = act(bias[co] + sum_{ci,kd,kh,kw} w[co,ci,kd,kh,kw] * x~[n,ci,p+k-1])

@@ -300,7 +300,9 @@ def h3d_pool3d_bwd_mask(dy: Slab, mask, g: Slab, act: int, alpha: float = 0.0):
 
 def h3d_conv3d_bwd_data(dz: Slab, z: Slab | None, w, dx: Slab, act: int = ACT_NONE, alpha: float = 0.0,
                         ws: Workspace | None = None):
-    p, n = (ws or _ws).get(h3d_conv3d_workspace_bytes(OP_BWD_DATA, dz, dx))
+    # without an activation there is no masked copy to make room for: what a forward call on the same tensors needs is enough
+    linear = z is None or act == ACT_NONE
+    p, n = (ws or _ws).get(h3d_conv3d_workspace_bytes(OP_FWD if linear else OP_BWD_DATA, dz, dx))
     _check(lib().h3d_conv3d_bwd_data(handle(), ctypes.byref(dz.desc()), ctypes.byref(z.desc()) if z is not None else None,
                                      _ptr(w), ctypes.byref(dx.desc()), act, alpha, p, n, _stream()))
     return dx

@@ -89,3 +89,37 @@ for attempt in range(2):
     env = dict(os.environ, HIP_VISIBLE_DEVICES="-1", ROCR_VISIBLE_DEVICES="-1")
     r = subprocess.run([sys.executable, "-c", script], env=env, capture_output=True, text=True, timeout=120)
     assert r.returncode == 0, r.stderr
+
+
+def test_an_unmasked_data_gradient_asks_for_no_copies():
+    """64 -> 64 channels on 64 x 256 x 256: with an activation the workspace has room for a slab of the masked gradient, without one it is the
+    packed filter alone, and the wrapper asks for that."""
+    import paper_2007_12856_amd as h3d
+    lib, handle = h3d.lib(), ctypes.cast(ctypes.create_string_buffer(4096), ctypes.c_void_p)
+    dz, dx = _desc(h3d, 1, 64, 64, 256, 256, halo=1), _desc(h3d, 1, 64, 64, 256, 256)
+    packed = 64 * 64 * 27 * 2
+    need = lambda op: lib.h3d_conv3d_workspace_bytes(handle, op, ctypes.byref(dz), ctypes.byref(dx))
+    assert need(h3d.OP_BWD_DATA) > 100 << 20 and packed <= need(h3d.OP_FWD) <= 2 * packed
+
+    class Asked(Exception):
+        pass
+
+    class Slab:
+        def __init__(self, d):
+            self.d = d
+
+        def desc(self):
+            return self.d
+
+    class Workspace:
+        def get(self, nbytes):
+            raise Asked(nbytes)
+
+    saved, h3d._handle = h3d._handle, handle
+    try:
+        for z, act, op in ((None, h3d.ACT_LEAKY, h3d.OP_FWD), (Slab(dz), h3d.ACT_NONE, h3d.OP_FWD), (Slab(dz), h3d.ACT_RELU, h3d.OP_BWD_DATA)):
+            with pytest.raises(Asked) as e:
+                h3d.conv3d_bwd_data(Slab(dz), z, None, Slab(dx), act, 0.01, Workspace())
+            assert e.value.args[0] == need(op)
+    finally:
+        h3d._handle = saved
