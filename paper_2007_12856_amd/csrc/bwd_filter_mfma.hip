@@ -1358,14 +1358,14 @@ static bool bf_prep_plan(const h3d_tensor* x, const h3d_tensor* dz, BfPrep* p) {
   for (int64_t mib = 64; mib >= 6; mib -= mib > 16 ? 8 : 2) {
     if (!prep_tiling(x->n, x->d, (whole_rows ? dz->c : x->c + dz->c) * row, whole_rows ? 0 : 2, mib << 20, &p->t)) return false;
     if (whole_rows && p->t.count() > 1 && mib < 24) return false;
-    p->x_bytes = whole_rows ? 0 : prep_align((size_t)p->t.nn * x->c * (p->t.np + 2) * row);
-    p->g_bytes = prep_align((size_t)p->t.nn * dz->c * p->t.np * row);
+    p->x_bytes = whole_rows ? 0 : up256((size_t)p->t.nn * x->c * (p->t.np + 2) * row);
+    p->g_bytes = up256((size_t)p->t.nn * dz->c * p->t.np * row);
     p->part_bytes = 0;
     for (const int i : {0, p->t.count() - 1}) {          // a full slab and the last one: no other sizes occur
       h3d_tensor xc, gc;
       int lo;
       bf_prep_tensors(x, dz, p->t.at(i), &xc, &gc, &lo);
-      p->part_bytes = std::max(p->part_bytes, prep_align(bf_partial_bytes(&xc, &gc)));
+      p->part_bytes = std::max(p->part_bytes, up256(bf_partial_bytes(&xc, &gc)));
     }
     if (p->need() <= (size_t)H3D_STATIC_SCRATCH_BYTES) return true;
   }

@@ -154,6 +154,7 @@ template <> struct dtype_of<float> { static constexpr int value = H3D_F32; };
 template <> struct dtype_of<bf16_t> { static constexpr int value = H3D_BF16; };
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
+inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }      // parts of a workspace start at multiples of 256 bytes
 
 }  // namespace h3d
 

@@ -213,8 +213,6 @@ struct K5Plan {
   size_t wp_bytes, part_bytes, partdb_bytes;
 };
 
-size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 // cin / cout: channels of the input-side / output-side tensor of the layer
 K5Plan k5_plan(const h3d_tensor* t, int cin, int cout, int op) {
   K5Plan p{};

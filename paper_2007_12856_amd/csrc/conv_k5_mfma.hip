@@ -4,11 +4,9 @@
 #include <algorithm>
 
 #include "rowload.h"
+#include "taps.h"
 
 namespace h3d {
-
-void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
-                 int half, float slope, hipStream_t s);      // taps_reduce.hip
 
 struct K5MArgs {
   Geo in, out;              // staged tensor (x or g), written tensor (backward-filter: out = g)
@@ -22,20 +20,6 @@ struct K5MArgs {
   int segs, chunks, half, cobs, cibs;
   int64_t neg;
 };
-
-// wp [block of 32 result channels][16-channel chunk][tap][lane][8]; transposed: backward-data
-static __global__ void __launch_bounds__(256) k5m_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
-                                                              int transposed, int nchunk, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-  int64_t r = i >> 9;
-  const int tap = (int)(r % 125); r /= 125;
-  const int chunk = (int)(r % nchunk), blk = (int)(r / nchunk);
-  const int row = blk * 32 + (lane & 31), k = chunk * 16 + (lane >> 5) * 8 + e;
-  const int co = transposed ? k : row, ci = transposed ? row : k;
-  wp[i] = (co < cout && ci < cin) ? w[((int64_t)co * cin + ci) * 125 + (transposed ? 124 - tap : tap)] : (bf16_t)0;
-}
 
 // --------------------------------------------------------------------------------------------- forward / backward-data
 // A workgroup of 8 wavefronts owns 8 RB rows x 32 columns of one output plane and 32 output channels; a wavefront RB rows (RB
@@ -232,7 +216,7 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
 // step.  Needs rows of whole 16-byte pieces in both tensors (other widths come as padded copies).  Five wavefronts do not divide
 // over four SIMDs, so a workgroup is THREE such groups (15 wavefronts: 4, 4, 4, 3 of them on a SIMD, at most 128 registers each), each
 // with its own run of rows; their sums are added in order through LDS, so that one partial tile leaves a workgroup.
-// Partial sums [chunk][125][co][ci] (taps_reduce.hip).  32 -> 32 channels on 32 x 128 x 128, call with mask and reduction: 377 -> 181
+// Partial sums [chunk][125][co][ci] (taps.hip).  32 -> 32 channels on 32 x 128 x 128, call with mask and reduction: 377 -> 181
 // us (kernel 365 -> 155; 64 -> 64: 1007 -> 589, 0.91 PFLOP/s).  Without four of the five products 95 us remain: the wavefronts of a
 // SIMD leave the barrier together and wait for the LDS together, so reads and products of a step hardly overlap; without the copies
 // 129, so they are not it.  Two groups of wavefronts instead of three (10 of them, more registers): 168.
@@ -485,9 +469,7 @@ h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const 
   K5MArgs a = k5m_args(in, go, loopc, resc);
   a.slope = slope;
   a.vec = go.w % 2 == 0 && go.cstride % 2 == 0 && (uintptr_t)out->data % 4 == 0;
-  const int64_t total = cdiv(resc, 32) * (int64_t)a.nchunk * 125 * 512;
-  hipLaunchKernelGGL(k5m_pack_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, transposed ? 1 : 0,
-                     a.nchunk, total);
+  taps_pack<125>(w, wp, cin, cout, transposed ? TAPS_REVERSED : TAPS_FWD, a.nchunk, s);
   const bool v16 = rows16(in, in_data);
   // 32-row tiles hold more products per staged row; with fewer than one of them per CU (or low volumes) 16-row tiles occupy more CUs
   const int64_t tall = (int64_t)out->n * go.d * cdiv(go.h, 32) * cdiv(go.w, 32) * cdiv(resc, 32);

@@ -979,7 +979,7 @@ static size_t prep_fwd_bytes(const h3d_tensor* in, const h3d_tensor* out) {
   if (in->n < 1 || !wide_dims(in, out)) return 0;
   PrepTiling t;
   if (!prep_tiling(in->n, out->halo_lo + out->d + out->halo_hi, prep_plane_bytes(in), 2, PREP_FWD_BUDGET, &t)) return 0;
-  return prep_align((size_t)t.nn * (t.np + 2) * prep_plane_bytes(in));
+  return up256((size_t)t.nn * (t.np + 2) * prep_plane_bytes(in));
 }
 
 // backward-data may come with a mask, which is not known here; forward needs the copy for rows of odd length only

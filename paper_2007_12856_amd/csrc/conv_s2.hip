@@ -122,8 +122,6 @@ __global__ void __launch_bounds__(S2_THREADS) s2_extract_dw_kernel(const float* 
   dw[i] = dwe[(co * 8 * cin + par * cin + ci) * 27 + te];
 }
 
-static inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
-
 // the descriptors of the stride-1 problem
 struct S2Plan {
   h3d_tensor xs;   // x' (8 cin channels, halo 1/1)

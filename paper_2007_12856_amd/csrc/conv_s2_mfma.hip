@@ -11,12 +11,9 @@
 #include <algorithm>
 
 #include "rowload.h"
+#include "taps.h"
 
 namespace h3d {
-
-// taps_reduce.hip: dw and db from partial sums [chunk][tap][cop][cip] and [chunk][cop], in chunk order
-void taps_reduce(const float* part, const float* part_db, float* dw, float* db, int taps, int cin, int cout, int cip, int cop, int nchunks,
-                 int half, float slope, hipStream_t s);
 
 struct S2Args {
   Geo x, y, m;                      // fine side, coarse side (y or dy), saved output (mask)
@@ -29,17 +26,6 @@ struct S2Args {
   int segs, band, bands, nstrips, strips_per_chunk, nchunks, cogroups, cigroups;
 };
 
-// g = dy where the saved output is > 0, else dy * slope, rounded to bf16; two elements
-__device__ __forceinline__ uint32_t s2_mask2(uint32_t v, uint32_t m, float slope) {
-  float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
-  if (!(__uint_as_float(m << 16) > 0.f)) v0 *= slope;
-  if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
-  return pack_bf16x2(v0, v1);
-}
-__device__ __forceinline__ uint4 s2_mask8(uint4 v, uint4 m, float slope) {
-  return uint4{s2_mask2(v.x, m.x, slope), s2_mask2(v.y, m.y, slope), s2_mask2(v.z, m.z, slope), s2_mask2(v.w, m.w, slope)};
-}
-
 // How a saved output is read (MASK): not at all; by row8 / row1 like the gradient; or, where it stores so many or so few elements that those do
 // not reach it (s2_mask_fits), one by one at 64-bit addresses.  That form is slow and rare, and it needs no other workspace: the size
 // query does not see the saved output.
@@ -49,21 +35,6 @@ __device__ __forceinline__ uint4 s2_far8(const bf16_t* row, int c, int w, bool o
 #pragma unroll
   for (int i = 0; i < 8; ++i) e[i] = ok && c + i < w ? (uint32_t)row[c + i] : 0u;
   return uint4{e[0] | (e[1] << 16), e[2] | (e[3] << 16), e[4] | (e[5] << 16), e[6] | (e[7] << 16)};
-}
-
-// wp [block][chunk][tap][lane][8]: forward: block row = output channel, contraction = input channel; transposed (backward-data)
-// the other way round.  Channels beyond the tensor's are zero.
-static __global__ void __launch_bounds__(256) s2_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout,
-                                                      int transposed, int nchunk, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-  int64_t r = i >> 9;
-  const int tap = (int)(r % 27); r /= 27;
-  const int chunk = (int)(r % nchunk), blk = (int)(r / nchunk);
-  const int row = blk * 32 + (lane & 31), k = chunk * 16 + (lane >> 5) * 8 + e;
-  const int co = transposed ? k : row, ci = transposed ? row : k;
-  wp[i] = (co < cout && ci < cin) ? w[((int64_t)co * cin + ci) * 27 + tap] : (bf16_t)0;
 }
 
 // tile index of a workgroup: the workgroups of one XCD (linear index mod 8) take a contiguous run, so that neighbouring tiles,
@@ -353,14 +324,14 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y));
-        if (MASK) v[e] = s2_mask8(v[e], MASK == S2_MASK ? fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)) : mv[e], a.slope);
+        if (MASK) v[e] = mask8(v[e], MASK == S2_MASK ? fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)) : mv[e], a.slope);
       }
 #pragma unroll
       for (int k = 0; k < 8; ++k) half[2 * k] = column_half(v, k);
     } else if (tail) {
       uint32_t s[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] = MASK ? s2_mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
+      for (int e = 0; e < 4; ++e) s[e] = MASK ? mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
       *half = uint2{s[0] | (s[1] << 16), s[2] | (s[3] << 16)};
     }
   };
@@ -505,8 +476,8 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
     uint4 g = fix8<V16>(gv, go, gc, W2, (int)stored_span(a.y));
     uint32_t e = ge;
     if (MASK) {
-      g = s2_mask8(g, MASK == S2_MASK ? fix8<V16>(mv, mo, gc, W2, (int)stored_span(a.m)) : mv, a.slope);
-      e = s2_mask2(e, me, a.slope) & 0xffffu;
+      g = mask8(g, MASK == S2_MASK ? fix8<V16>(mv, mo, gc, W2, (int)stored_span(a.m)) : mv, a.slope);
+      e = mask2(e, me, a.slope) & 0xffffu;
     }
     dst[SB_X + (tid >> 2) * SB_GP + g_piece] = g;
     if (g_piece == 3) *reinterpret_cast<uint32_t*>(dst + SB_X + (tid >> 2) * SB_GP + 4) = e;
@@ -655,7 +626,6 @@ static S2BfPlan s2_bf_plan(const h3d_tensor* x, const h3d_tensor* y) {
   return p;
 }
 
-static inline size_t up256(size_t b) { return (b + 255) & ~(size_t)255; }
 static size_t s2_wp_bytes(int rows, int contraction, int step) { return up256((size_t)cdiv(rows, 32) * cdiv(contraction, step) * (step / 16) * 27 * 1024); }
 
 size_t s2_mfma_ws_bytes(int op, const h3d_tensor* x, const h3d_tensor* y) {
@@ -673,10 +643,6 @@ static S2Args s2_args(const h3d_tensor* x, const h3d_tensor* y, const h3d_tensor
   return a;
 }
 static bool rows16(const h3d_tensor* t) { return t->w % 8 == 0 && (uintptr_t)t->data % 16 == 0; }
-static void s2_pack(const void* w, void* wp, int cin, int cout, bool transposed, int nchunk, hipStream_t s) {
-  const int64_t total = cdiv(transposed ? cin : cout, 32) * nchunk * 27 * 512;
-  hipLaunchKernelGGL(s2_pack_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, transposed ? 1 : 0, nchunk, total);
-}
 static unsigned xcd_grid(int n) { return (unsigned)(cdiv(n, 8) * 8); }
 
 template <int NCO, int CB, bool V16>
@@ -695,7 +661,7 @@ h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const f
   a.tiles_w = (int)cdiv(y->w, 32); a.tiles_h = (int)cdiv(y->h, 4);
   a.ntiles = y->n * y->d * a.tiles_h * a.tiles_w;
   a.vec = y->w % 2 == 0 && (uintptr_t)y->data % 4 == 0;
-  s2_pack(w, ws, x->c, y->c, false, a.nchunk, s);
+  taps_pack<27>(w, ws, x->c, y->c, TAPS_FWD, a.nchunk, s);
   const uint4* wp = (const uint4*)ws;
   const bool v16 = rows16(x);
   if (y->c > 64) return v16 ? s2_launch_fwd<2, 2, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<2, 2, false>(handle, x, wp, bias, y, a, s);
@@ -719,7 +685,7 @@ h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor
   a.tiles_w = (int)cdiv(dy->w, 32); a.tiles_h = (int)cdiv(dy->h, 8);
   a.ntiles = dy->n * dy->d * a.tiles_h * a.tiles_w;
   a.vec = dx->w % 2 == 0 && (uintptr_t)dx->data % 4 == 0;
-  s2_pack(w, ws, dx->c, dy->c, true, a.nchunk, s);
+  taps_pack<27>(w, ws, dx->c, dy->c, TAPS_TRANSPOSED, a.nchunk, s);
   const uint4* wp = (const uint4*)ws;
   const bool v16 = rows16(dy) && (!y || rows16(y));
   if (y && !s2_mask_fits(y)) return s2_launch_bd<S2_FAR_MASK, false>(handle, dy, y, wp, dx, a, s);

@@ -39,6 +39,4 @@ struct PrepTiling {
 // even one plane fits the budget.
 bool prep_tiling(int n, int planes, int64_t plane_bytes, int extra, int64_t budget, PrepTiling* t);
 
-inline size_t prep_align(size_t b) { return (b + 255) & ~(size_t)255; }
-
 }  // namespace h3d

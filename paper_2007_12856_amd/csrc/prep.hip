@@ -1,5 +1,6 @@
 // The copy kernel behind prepared operands (prep.h).
 #include "prep.h"
+#include "rowload.h"
 
 #include <algorithm>
 
@@ -18,16 +19,7 @@ __device__ __forceinline__ uint4 prep_load(const bf16_t* row, int col, int w) {
   const int back = max(col + 8 - w, 0);          // 0 except in the last unit of a ragged row
   uint4 v;
   __builtin_memcpy(&v, row + col - back, 16);
-  if (back & 4) v = uint4{v.z, v.w, 0u, 0u};
-  if (back & 2) v = uint4{v.y, v.z, v.w, 0u};
-  if (back & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
-  return v;
-}
-__device__ __forceinline__ uint32_t prep_mask2(uint32_t v, uint32_t m, float slope) {
-  float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
-  if (!(__uint_as_float(m << 16) > 0.f)) v0 *= slope;
-  if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
-  return pack_bf16x2(v0, v1);
+  return shift8(v, back);
 }
 // the elements whose saved output is positive (or those whose isn't), as they are
 __device__ __forceinline__ uint32_t prep_part2(uint32_t v, uint32_t m, bool positive) {
@@ -49,7 +41,7 @@ __device__ __forceinline__ void prep_unit(const PrepJob& a, int64_t i) {
     const uint4 m = prep_load(a.msk + n * a.m.nstride + c * a.m.cstride + (int64_t)(a.p0 + p + a.m.hlo) * a.m.plane + (int64_t)h * a.m.w, col, a.m.w);
     const bool pos = a.part == 1;
     v = a.part ? uint4{prep_part2(v.x, m.x, pos), prep_part2(v.y, m.y, pos), prep_part2(v.z, m.z, pos), prep_part2(v.w, m.w, pos)}
-               : uint4{prep_mask2(v.x, m.x, a.slope), prep_mask2(v.y, m.y, a.slope), prep_mask2(v.z, m.z, a.slope), prep_mask2(v.w, m.w, a.slope)};
+               : mask8(v, m, a.slope);
   }
   reinterpret_cast<uint4*>(a.dst)[i] = v;
 }

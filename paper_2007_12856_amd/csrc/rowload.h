@@ -16,6 +16,24 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t row_rsrc(const void* base, uin
   return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
 }
 
+// g = v where the saved output m is > 0, else v * slope, rounded to bf16; two elements
+__device__ __forceinline__ uint32_t mask2(uint32_t v, uint32_t m, float slope) {
+  float v0 = __uint_as_float(v << 16), v1 = __uint_as_float(v & 0xffff0000u);
+  if (!(__uint_as_float(m << 16) > 0.f)) v0 *= slope;
+  if (!(__uint_as_float(m & 0xffff0000u) > 0.f)) v1 *= slope;
+  return pack_bf16x2(v0, v1);
+}
+__device__ __forceinline__ uint4 mask8(uint4 v, uint4 m, float slope) {
+  return uint4{mask2(v.x, m.x, slope), mask2(v.y, m.y, slope), mask2(v.z, m.z, slope), mask2(v.w, m.w, slope)};
+}
+// 8 elements moved down by s (0 .. 7), zeros behind them
+__device__ __forceinline__ uint4 shift8(uint4 v, int s) {
+  if (s & 4) v = uint4{v.z, v.w, 0u, 0u};
+  if (s & 2) v = uint4{v.y, v.z, v.w, 0u};
+  if (s & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
+  return v;
+}
+
 // 8 elements of a row of `w` from column c >= 0 on; `off` = element offset of the ROW in the sample, `span` = elements of the
 // sample (>= 8).  One 16-byte buffer load without a branch (a branch around each load makes the compiler wait for every one of
 // them where the paths meet: stride-2 backward-data, 64->128 on 64^3: 55 -> 48 us, backward-filter 52 -> 46).
@@ -32,11 +50,7 @@ template <bool V16>
 __device__ __forceinline__ uint4 fix8(uint4 v, int off, int c, int w, int span) {
   if (V16) return v;
   const int s = off + c - min(off + c, span - 8);      // elements the load was moved forward by (the end of the sample only)
-  if (__builtin_amdgcn_ballot_w64(s > 0)) {
-    if (s & 4) v = uint4{v.z, v.w, 0u, 0u};
-    if (s & 2) v = uint4{v.y, v.z, v.w, 0u};
-    if (s & 1) v = uint4{__builtin_amdgcn_alignbit(v.y, v.x, 16), __builtin_amdgcn_alignbit(v.z, v.y, 16), __builtin_amdgcn_alignbit(v.w, v.z, 16), v.w >> 16};
-  }
+  if (__builtin_amdgcn_ballot_w64(s > 0)) v = shift8(v, s);
   const int k = w - c;                                 // elements that belong to the row
   v.x &= k >= 2 ? 0xffffffffu : k == 1 ? 0xffffu : 0u;
   v.y &= k >= 4 ? 0xffffffffu : k == 3 ? 0xffffu : 0u;

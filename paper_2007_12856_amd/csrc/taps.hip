@@ -1,6 +1,6 @@
-// Second stage of the filter gradients whose partial sums are stored [chunk][tap][co][ci] (rows of input channels, padded to the
+// Packed filters, and the second stage of the filter gradients whose partial sums are stored [chunk][tap][co][ci] (rows of input channels, padded to the
 // kernels' channel blocks: a wavefront's accumulator registers leave as whole lines).
-#include "common.h"
+#include "taps.h"
 
 namespace h3d {
 
@@ -43,5 +43,28 @@ void taps_reduce(const float* part, const float* part_db, float* dw, float* db, 
   const int64_t total = (int64_t)taps * cout * cin + cout;
   hipLaunchKernelGGL(taps_reduce_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, part, part_db, dw, db, taps, cin, cout, cip, cop, nchunks, half, slope);
 }
+
+template <int TAPS>
+__global__ void __launch_bounds__(256) taps_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout, int form,
+                                                      int nchunk, int64_t total) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i >= total) return;
+  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
+  int64_t r = i >> 9;
+  const int tap = (int)(r % TAPS); r /= TAPS;
+  const int chunk = (int)(r % nchunk), blk = (int)(r / nchunk);
+  const int row = blk * 32 + (lane & 31), k = chunk * 16 + (lane >> 5) * 8 + e;
+  const int co = form == TAPS_FWD ? row : k, ci = form == TAPS_FWD ? k : row;
+  wp[i] = (co < cout && ci < cin) ? w[((int64_t)co * cin + ci) * TAPS + (form == TAPS_REVERSED ? TAPS - 1 - tap : tap)] : (bf16_t)0;
+}
+
+template <int TAPS>
+void taps_pack(const void* w, void* wp, int cin, int cout, int form, int nchunk, hipStream_t s) {
+  const int64_t total = cdiv(form == TAPS_FWD ? cout : cin, 32) * (int64_t)nchunk * TAPS * 512;
+  hipLaunchKernelGGL(taps_pack_kernel<TAPS>, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, form, nchunk,
+                     total);
+}
+template void taps_pack<27>(const void*, void*, int, int, int, int, hipStream_t);
+template void taps_pack<125>(const void*, void*, int, int, int, int, hipStream_t);
 
 }  // namespace h3d
