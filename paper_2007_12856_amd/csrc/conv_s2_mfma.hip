@@ -1,8 +1,8 @@
 // Stride-2 3x3x3 convolution of bf16 tensors on the matrix cores, all three passes, straight from the caller's tensors
 // (y[p] = sum_k w[k] x~[2p+k-1]).  Per axis an even fine position 2c meets tap k = 1 of coarse position c, an odd one 2c+1
 // taps k = 2 of c and k = 0 of c+1, so 27 of the 8 x 27 (parity, shift) products exist.  The rewriting as a stride-1
-// convolution over the eight parity sub-lattices (conv_s2.hip, still the route of fp32 tensors) executes all 216 of them and
-// moves both tensors through memory three times; these kernels execute the 27.
+// convolution over the eight parity sub-lattices (conv_s2.hip, still the route of fp32 tensors and large first layers) executes all 216
+// of them and moves both tensors through memory three times; these kernels execute the 27.
 //
 // 64 -> 128 channels on 64^3 (14.5 GFlop and 42 MB a pass: 6 us of matrix cores, 6 us of memory), all three passes of a masked
 // layer: 818 us by the rewriting, 111 us here (kernels 32 forward, 35 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
@@ -504,6 +504,9 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
   // call with a mask 40.2 -> 40.8 us, without 37.1 -> 37.6.)
   constexpr int CUT0 = V16 ? 3 : 0;
   uint32_t cut[2][4];
+  // a block of channels beyond the tensors' has no products and leaves no sums (three passes of 16 -> 26 channels on 16x128x104, masked:
+  // 69 -> 64 us)
+  const bool block_used = __builtin_amdgcn_readfirstlane(cog * 64 + cow * 32 < a.cout && cig * 64 + ciw * 32 < a.cin);
   bool live = strip < strip_end;
   bool first = true, cur_first = true;
   if (live) {
@@ -546,7 +549,7 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
       Ns[k] = uint4{__builtin_amdgcn_alignbit(N[k].y, N[k].x, 16), __builtin_amdgcn_alignbit(N[k].z, N[k].y, 16),
                     __builtin_amdgcn_alignbit(N[k].w, N[k].z, 16), __builtin_amdgcn_alignbit(nx, N[k].w, 16)};
     }
-    if (!cur_first) {
+    if (!cur_first && block_used) {
 #pragma unroll
       for (int row = 0; row < 2; ++row)
 #pragma unroll
@@ -580,10 +583,11 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
 
   const int cop = a.cogroups * 64, cip = a.cigroups * 64;
   float* pp = part + (((int64_t)chunk * 27 + kd * 9) * cop + cog * 64 + cow * 32) * cip + cig * 64 + ciw * 32 + lc;
+  if (block_used)
 #pragma unroll
-  for (int t = 0; t < 9; ++t)
+    for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) pp[((int64_t)t * cop + acc_row(i, lane)) * cip] = acc[t][i];
+      for (int i = 0; i < 16; ++i) pp[((int64_t)t * cop + acc_row(i, lane)) * cip] = acc[t][i];
   if (want_db) {
     dbl[tid] = dbsum;
     __syncthreads();
