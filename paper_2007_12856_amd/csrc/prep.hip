@@ -39,9 +39,12 @@ __device__ __forceinline__ void prep_unit(const PrepJob& a, int64_t i) {
   uint4 v = prep_load(a.src + n * a.s.nstride + c * a.s.cstride + (int64_t)(a.p0 + p + a.s.hlo) * a.s.plane + (int64_t)h * a.s.w, col, a.s.w);
   if (a.msk) {
     const uint4 m = prep_load(a.msk + n * a.m.nstride + c * a.m.cstride + (int64_t)(a.p0 + p + a.m.hlo) * a.m.plane + (int64_t)h * a.m.w, col, a.m.w);
-    const bool pos = a.part == 1;
-    v = a.part ? uint4{prep_part2(v.x, m.x, pos), prep_part2(v.y, m.y, pos), prep_part2(v.z, m.z, pos), prep_part2(v.w, m.w, pos)}
-               : mask8(v, m, a.slope);
+    if (a.part) {      // a branch, not a choice of values: every thread would compute both (24->48 on 2 x 22x50x54, three passes: 121 and 119 us)
+      const bool pos = a.part == 1;
+      v = uint4{prep_part2(v.x, m.x, pos), prep_part2(v.y, m.y, pos), prep_part2(v.z, m.z, pos), prep_part2(v.w, m.w, pos)};
+    } else {
+      v = mask8(v, m, a.slope);
+    }
   }
   reinterpret_cast<uint4*>(a.dst)[i] = v;
 }
