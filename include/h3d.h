@@ -160,8 +160,9 @@ h3d_status h3d_conv3d_bwd_filter_static(void* handle, const h3d_tensor* x, const
  *     need their UPPER halo plane, never the lower one.                                  H3D_EHALO otherwise.
  * Workspace: h3d_conv3d_s2_workspace_bytes(handle, op, x, y) with x / y the input-side / output-side descriptors
  * for every op; 256-byte aligned.  bf16 tensors have matrix-core kernels of their own (the workspace holds the packed
- * filter or the partial sums); fp32 tensors, and bf16 samples beyond 32-bit byte offsets, are rewritten as a stride-1
- * convolution over the eight parity sub-lattices of x (the workspace then holds the rearranged tensors). */
+ * filter or the partial sums); fp32 tensors, bf16 samples beyond 32-bit byte offsets, and forward and backward-filter of
+ * large bf16 layers with at most four input channels are rewritten as a stride-1 convolution over the eight parity
+ * sub-lattices of x (the workspace then holds the rearranged tensors). */
 size_t h3d_conv3d_s2_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* y);
 h3d_status h3d_conv3d_s2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y,
                              int act, float alpha, void* ws, size_t ws_bytes, void* stream);

@@ -216,8 +216,8 @@ __global__ void __launch_bounds__(512) k5_conv_mfma_kernel(const bf16_t* __restr
 // step.  Needs rows of whole 16-byte pieces in both tensors (other widths come as padded copies).  Five wavefronts do not divide
 // over four SIMDs, so a workgroup is THREE such groups (15 wavefronts: 4, 4, 4, 3 of them on a SIMD, at most 128 registers each), each
 // with its own run of rows; their sums are added in order through LDS, so that one partial tile leaves a workgroup.
-// Partial sums [chunk][125][co][ci] (taps.hip).  32 -> 32 channels on 32 x 128 x 128, call with mask and reduction: 377 -> 181
-// us (kernel 365 -> 155; 64 -> 64: 1007 -> 589, 0.91 PFLOP/s).  Without four of the five products 95 us remain: the wavefronts of a
+// Partial sums [chunk][125][co][ci] (taps.hip).  32 -> 32 channels on 32 x 128 x 128, call without a mask and with the reduction: 375
+// -> 165 us; a mask adds its copy (20); 64 -> 64: 1007 -> 563, 0.95 PFLOP/s.  Without four of the five products 95 us remain: the wavefronts of a
 // SIMD leave the barrier together and wait for the LDS together, so reads and products of a step hardly overlap; without the copies
 // 129, so they are not it.  Two groups of wavefronts instead of three (10 of them, more registers): 168.
 constexpr int KF_SEG = 64, KF_XP = 10, KF_X = 32 * KF_XP, KF_G = 32 * 8, KF_XS = 7, KF_GS = 3, KF_PART = KF_XS * KF_X + KF_GS * KF_G + 64;

@@ -966,7 +966,8 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
 // otherwise, the input is copied, masked and padded, slab by slab, and the wide kernel runs on the copy: same products, same order,
 // same bits as the general kernel.  The copy is bounded; without the workspace for it the general kernel runs.
 // Backward-data of masked layers, before -> after: 64->64 on 4 x 64^3 345 -> 265 us, 128->128 on 2 x 40x100x100 1140 -> 830,
-// 24->48 on 2 x 22x50x54 52 -> 36; rows of odd length, 64->64 on 64x128x127: forward 402 -> 267, backward-data 416 -> 261.
+// 24->48 on 2 x 22x50x54 52 -> 36, and down to a few tiles and channels: 16->32 on 4x8x20 30 -> 19, 4->16 on 16x32x32 23 -> 16, 1->32 on
+// 32x64x64 36 -> 26; rows of odd length, 64->64 on 64x128x127: forward 402 -> 267, backward-data 416 -> 261.
 // The budget: 64 MiB leaves slabs too small for the two-block form at 64 channels (267 -> 308 us on the last one).
 constexpr int64_t PREP_FWD_BUDGET = (int64_t)160 << 20;
 

@@ -8,7 +8,8 @@
 // parity/shift pairs that no k maps to) are zero.  The stride-1 kernels of this library then run all three
 // passes; the zero padding of the stride-1 call at q = -1 is exactly the zero padding of x at index -1.  The
 // price is that 27 of the 216 (parity, tap) products per input channel are non-zero.  This is the route of
-// fp32 tensors and of bf16 samples beyond 32-bit offsets; other bf16 tensors go to conv_s2_mfma.hip
+// fp32 tensors, of bf16 samples beyond 32-bit offsets and of large bf16 layers with few input channels (s2_direct); other bf16
+// tensors go to conv_s2_mfma.hip
 // (64 -> 128 channels on 64^3, three passes: 111 us there, 818 us this way).
 //
 // Small element-wise kernels here: the parity split of x, its inverse for dx, the masked copy of dy into

@@ -505,7 +505,7 @@ __global__ void __launch_bounds__(256, 2) s2_bwd_filter_kernel(const bf16_t* __r
   constexpr int CUT0 = V16 ? 3 : 0;
   uint32_t cut[2][4];
   // a block of channels beyond the tensors' has no products and leaves no sums (three passes of 16 -> 26 channels on 16x128x104, masked:
-  // 69 -> 64 us)
+  // 67 -> 64 us)
   const bool block_used = __builtin_amdgcn_readfirstlane(cog * 64 + cow * 32 < a.cout && cig * 64 + ciw * 32 < a.cin);
   bool live = strip < strip_end;
   bool first = true, cur_first = true;
