@@ -48,7 +48,7 @@ OTHERS = ["table1", "chain512", "k5", "split256", "bn", "layer_f32", "faces512"]
 # ----------------------------------------------------------------------------------------------- CPU baseline
 def cpu_baseline(seed):
     """The oracle, as it stands, on a bounded sample: stage 2 of the CosmoFlow-shaped stack (16->32 channels on 64^3),
-    the whole batch of four samples, all three passes (FP, BD, BF): about 10 s on the GPU machine's host cores."""
+    the whole batch of four samples, all three passes (FP, BD, BF): about 10 s on a GPU node's host cores."""
     import numpy as np
     import oracle as orc
     import synth
