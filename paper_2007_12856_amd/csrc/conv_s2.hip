@@ -208,12 +208,13 @@ static size_t s2_general_ws_bytes(void* handle, int op, const h3d_tensor* x, con
 // backward-filter, whatever is there; the rewriting turns a first layer's few input channels into eight times as many.  us, rewriting and
 // direct:
 //   forward: 1->16 on 32x128x128 23 and 20, on 64x128x128 26 and 35, 4->16 there 43 and 37, on 128^3 57 and 66
+//     one channel onto 8 or onto more than 32 earlier: 1->8 on 32x64x64 14 and 12, on 32x128x128 16 and 20; 1->64 there 22 and 26, on 32x64x64 19 and 15
 //   backward-filter, no mask: 1->16 on 16x32x32 16 and 17, on 32x64x64 16 and 29, on 128^3 33 and 109; 2->16 on 32x64x64 18 and 24; 3->16 on 64^3
 //     26 and 35; 4->16 on 2 x 32x96x96 37 and 47; with a mask the same within a tenth
 static bool s2_direct(int op, const h3d_tensor* x, const h3d_tensor* y) {
   if (!s2_mfma_supported(x, y)) return false;
   const int64_t voxels = (int64_t)x->n * x->d * x->h * x->w;
-  if (op == H3D_OP_FWD) return x->c > 4 || voxels < (x->c <= 2 ? (int64_t)3 << 18 : (int64_t)3 << 19);
+  if (op == H3D_OP_FWD) return x->c > 4 || voxels < (int64_t)3 << (x->c > 2 ? 19 : x->c == 1 && (y->c <= 8 || y->c > 32) ? 17 : 18);
   if (op == H3D_OP_BWD_FILTER) return voxels < (int64_t)x->c * 49152 || !((x->c <= 3 && x->c * y->c <= 128) || (x->c == 4 && y->c <= 16));
   return true;
 }

@@ -261,6 +261,9 @@ def test_stride2_saved_output_stored_unlike_the_gradient(shape, planes):
     ((1, 1, 16, 12, 64, 62), True, True),
     ((1, 1, 40, 12, 64, 64), True, False),
     ((1, 1, 4, 64, 96, 128), False, False),
+    ((1, 1, 8, 24, 128, 130), False, False),
+    ((1, 1, 64, 24, 128, 120), True, False),
+    ((1, 1, 64, 26, 128, 120), False, False),
     ((2, 2, 16, 16, 56, 64), True, False),
     ((1, 3, 48, 16, 64, 160), True, True),
     ((1, 4, 16, 8, 160, 160), True, False),
