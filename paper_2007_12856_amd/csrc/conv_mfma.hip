@@ -1015,7 +1015,7 @@ static h3d_status launch_variant(void* handle, const bf16_t* in, const bf16_t* m
 }
 
 static bool wide_shape(const MfmaArgs& a) {
-  return a.out.w > 16 && a.out.ds >= 3 && a.out.h >= 4 && a.csplit == 1;
+  return a.out.w > 16 && a.out.ds >= 3 && a.out.h >= 4;
 }
 
 template <int CB, int WCB = 1, int RSP = 1, bool RAGGED = false, bool SPLIT = false>
@@ -1124,7 +1124,6 @@ static h3d_status prep_conv(void* handle, const h3d_tensor* in, const h3d_tensor
     MfmaArgs s = a;
     s.in.n = b.nn; s.in.d = b.np; s.in.w = w8; s.in.doff = gi.doff + a0; s.in.hlo = a0 - lo; s.in.ds = np; s.in.hhi = np - b.np - s.in.hlo;
     s.in.plane = (int64_t)in->h * w8; s.in.cstride = s.in.plane * np; s.in.nstride = s.in.cstride * in->c;
-    if (t.count() == 1) s.csplit = wide_splits(in, out);       // (the split's sums are those of the whole tensor)
     s.out.n = b.nn; s.out.d = s.out.ds = b.np; s.out.hlo = s.out.hhi = 0; s.out.doff = go.doff + a0;
     H3D_TRY(wide_conv(handle, copy, (const uint4*)ws, bias, (bf16_t*)out->data + b.n0 * go.nstride + (int64_t)b.p0 * go.plane, s, b.nn, stream));
   }
@@ -1140,6 +1139,9 @@ static h3d_status pick_variant(void* handle, const bf16_t* in, const bf16_t* mas
   const bool flat = two_cb && a.out.ds <= 2 && a.csplit == 1;
   if (flat && wide && a.out.h >= 16) return launch_variant<2, 4, 32, MASKED, VEC, false, true>(handle, in, mask, wp, bias, out, a, n, s);
   if (flat && !wide && a.out.h >= 32) return launch_variant<2, 4, 16, MASKED, VEC, false, true>(handle, in, mask, wp, bias, out, a, n, s);
+  // a wide volume whose channels are split, without a copy of its masked or odd rows: the wide kernel's splits and sums (its partial tiles of 8 rows
+  // hold these of 4), one block of output channels in half of the wavefronts
+  if (wide && a.csplit > 1) return launch_variant<2, 4, 32, MASKED, VEC, true>(handle, in, mask, wp, bias, out, a, n, s);
   if (wide) {
     return two_cb ? launch_variant<2, 4, 32, MASKED, VEC>(handle, in, mask, wp, bias, out, a, n, s)
                   : launch_variant<1, 8, 32, MASKED, VEC>(handle, in, mask, wp, bias, out, a, n, s);
@@ -1196,14 +1198,12 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   h3d_status st;
   const size_t split_bytes = wide_split_bytes(in, out);
   if (split_bytes) {      // (wide volumes: mfma_splits is 1)
-    const int s = wide_splits(in, out);
-    a.chunks_per_split = (int)cdiv(a.nchunks, s);
+    a.csplit = wide_splits(in, out);
+    a.chunks_per_split = (int)cdiv(a.nchunks, a.csplit);
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out));
   }
-  if (!mask && vec && wide_shape(a) && (a.cout_k > 32 || a.cin_k > 8)) {      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
-    if (split_bytes) a.csplit = wide_splits(in, out);
+  if (!mask && vec && wide_shape(a) && (a.cout_k > 32 || a.cin_k > 8))      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
     return wide_conv(handle, ip, wq, bias, op, a, out->n, stream);
-  }
   if (const size_t copies = prep_fwd_bytes(in, out); copies && (uintptr_t)out->data % 4 == 0 && ws_bytes >= mfma_wp_bytes(in, out) + split_bytes + copies)
     return prep_conv(handle, in, mask, bias, out, a, mask_slope, ws, stream);
   a.pairs = vec;
@@ -1224,8 +1224,9 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   if (st != H3D_OK || a.csplit == 1) return st;
   const int64_t out_total = (int64_t)out->n * a.out.nstride;
   SplitGeo q;
-  q.nd = a.cout_k > 32 ? 4 : 8; q.twc = 16; q.rpb = 2; q.ncoblk = a.ncoblk;
-  q.tiles_w = (int)cdiv(a.out.w, 16); q.tiles_h = (int)cdiv(a.out.h, 8); q.tiles_d = (int)cdiv(a.out.ds, q.nd);
+  const bool wide = a.out.w > 16;
+  q.nd = wide || a.cout_k > 32 ? 4 : 8; q.twc = wide ? 32 : 16; q.rpb = wide ? 1 : 2; q.ncoblk = a.ncoblk;
+  q.tiles_w = (int)cdiv(a.out.w, q.twc); q.tiles_h = (int)cdiv(a.out.h, 4 * q.rpb); q.tiles_d = (int)cdiv(a.out.ds, q.nd);
   q.ntiles = out->n * q.tiles_d * q.tiles_h * q.tiles_w;
   hipLaunchKernelGGL(conv_split_reduce_kernel, dim3((unsigned)cdiv(out_total, 256)), dim3(256), 0, stream, (const float*)a.part, bias, op,
                      a.out, q, a.csplit, out_slope);
