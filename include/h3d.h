@@ -75,9 +75,11 @@ typedef struct {
    * of its first channel, n / c / d / halo_* / d_offset describe the view, the strides are the parent's.  Views are
    * accepted by the three convolution passes, h3d_act_bwd, h3d_pool3d_fwd / _bwd / _bwd_act and the h3d_deconv2_*
    * calls; every other entry point returns H3D_EUNSUPPORTED.
-   * Forward / backward-data on views that tile a slab give the whole-slab call's result bit for bit, except
-   * where the whole-slab call is small enough to take the channel-split kernel (bf16, W <= 16, fewer than 64
-   * workgroups): views are never split, so the fp32 summation order of the two differs there. */
+   * Forward / backward-data on views that tile a slab give the whole-slab call's result bit for bit, except where
+   * the slab is so small that the call sums its input channels in parts (fp32 partial sums, added in order); views
+   * never do, so the summation order of the two differs there.  Only packed results are summed in parts: whole
+   * samples (d = d_global, no halos) of few tiles, bf16 and fp32, and bf16 shards with W <= 16 of fewer than 64
+   * workgroups. */
   int64_t c_stride;
   int64_t n_stride;
 } h3d_tensor;

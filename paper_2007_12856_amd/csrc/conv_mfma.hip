@@ -857,6 +857,8 @@ static int mfma_splits(const h3d_tensor* in, const h3d_tensor* out) {
   if (wide || wgs == 0 || nchunks < 2 || !is_packed(out)) return 1;    // (only the narrow-volume variants come in a split form)
   // bytes of one split's sums: they cost a write and a read
   const int64_t part = (int64_t)out->n * cdiv(ds, nd) * cdiv(out->h, 8) * cdiv(out->w, 16) * ncoblk * nd * 4096 * 4;
+  // from 64 workgroups on whole samples only: a shard's sums are those of the views that tile it
+  if (wgs >= 64 && (out->d != out->d_global || out->halo_lo || out->halo_hi)) return 1;
   int s = (int)std::min<int64_t>(nchunks, wgs < 64 ? cdiv(256, wgs) : std::max<int64_t>(1, 256 / wgs));
   while (s > 1 && s * part > ((int64_t)(wgs < 64 ? 24 : 40) << 20)) --s;
   // from 64 workgroups on a split has to save more of a tile's 6 us a chunk than its sums and the launch that adds them take: 256->256 on

@@ -314,7 +314,7 @@ def test_conv3d_sharded_matches_oracle_and_unsharded_gpu(dtype, cin, cout):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cin,cout,W,exact", [(4, 16, 40, True), (16, 32, 32, True), (24, 8, 36, True), (64, 128, 40, True),
-                                              (64, 128, 8, False)])
+                                              (64, 128, 8, False), (256, 256, 8, True)])      # (72 workgroups)
 def test_main_halo_split_is_bit_exact(dtype, cin, cout, W, exact):
     """Sec. III-C: the planes that need no halo (main) and the two strips that do are computed by separate
     calls on plane-run views of the same buffers; together they must reproduce the whole-slab call bit for bit."""
@@ -359,6 +359,40 @@ def test_main_halo_split_is_bit_exact(dtype, cin, cout, W, exact):
     tol_w = 1e-5 if dtype == "f32" else 2e-4
     close(from_dev(dw), dwo, tol_w)
     close(from_dev(db), dbo, tol_w)
+
+
+@pytest.mark.parametrize("dtype,N,c,D,H,W", [("bf16", 2, 64, 9, 18, 32), ("f32", 2, 64, 9, 18, 32), ("bf16", 4, 256, 16, 8, 8), ("bf16", 2, 64, 9, 18, 8)])
+def test_whole_samples_are_summed_in_parts_and_views_are_not(dtype, N, c, D, H, W):
+    """Which calls may sum their channels in parts: the packed whole sample does; plane runs of it, one in a packed tensor of its own with the
+    neighbours as halos, and its channels as a range of a wider tensor do not, and these agree bit for bit."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    print("whole and views", dtype, N, c, D, H, W, flush=True)
+    g = torch.Generator(device="cuda").manual_seed(c + W)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn((N, c, D, H, W), generator=g, device="cuda").to(td)
+    w = (0.05 * torch.randn((c, c, 3, 3, 3), generator=g, device="cuda")).to(td)
+
+    def fwd(xs, zs):
+        h3d.conv3d_fwd(xs, w, None, zs, h3d.ACT_LEAKY, 0.01)
+        name = h3d.h3d_last_kernel()
+        return zs.t, "split" in name or (name.startswith("conv3d_mfma_kernel<") and name.split(",")[5] == "1")
+
+    whole, parted = fwd(h3d.Slab(x), h3d.Slab(torch.empty_like(x)))
+    assert parted
+    views = h3d.Slab(torch.empty_like(x))
+    for p0, p1 in ((1, D - 1), (0, 1), (D - 1, D)):
+        assert not fwd(h3d.Slab(x).planes(p0, p1, 1 if p0 else 0, 1 if p1 < D else 0), views.planes(p0, p1))[1]
+    wide = torch.empty((N, 2 * c, D, H, W), dtype=td, device="cuda")
+    ranged, parted = fwd(h3d.Slab(x), h3d.Slab(wide[:, c:]))
+    assert not parted and torch.equal(ranged, views.t)
+    if W > 16 or N * D * c > 8192:      # (narrow shards of fewer than 64 workgroups are summed in parts)
+        inner = x[:, :, 1:D - 1].contiguous()
+        shard, parted = fwd(h3d.Slab(x, 1, 1, 1, D), h3d.Slab(torch.empty_like(inner), 0, 0, 1, D))
+        assert not parted and torch.equal(shard, views.t[:, :, 1:D - 1])
+    # as many products summed in another order
+    bar = 2.0 ** -8 if dtype == "bf16" else 2.0 ** -23 * (27 * c) ** 0.5
+    assert float((views.t.double() - whole.double()).norm()) <= bar * float(whole.double().norm())
 
 
 # (N, Cin, Cout, D, H, W, halo, d_offset, d_global): fp32 tensors on the matrix cores.  Both instances of the forward kernel

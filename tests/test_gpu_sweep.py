@@ -280,7 +280,7 @@ def test_f32_few_tiles_with_split_channels(N, ci, co, D, H, W, split):
     close(from_dev(dxg.t), dxo.a, TOL["f32"], "dx")
 
 
-@pytest.mark.parametrize("N,ci,co,D,H,W,split", [(5, 144, 72, 8, 9, 16, True), (64, 40, 32, 1, 4, 5, False), (8, 112, 128, 9, 8, 7, True), (65, 80, 40, 4, 16, 3, False)])
+@pytest.mark.parametrize("N,ci,co,D,H,W,split", [(5, 144, 72, 8, 9, 16, True), (8, 144, 128, 8, 16, 8, True), (64, 40, 32, 1, 4, 5, False), (8, 112, 128, 9, 8, 7, True), (65, 80, 40, 4, 16, 3, False)])
 def test_narrow_volumes_split_from_64_workgroups_on(N, ci, co, D, H, W, split):
     """Narrow volumes between 64 and 256 workgroups: channels split where it pays; an uneven last split; more workgroups than 256 stay whole."""
     import torch
