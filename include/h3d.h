@@ -106,8 +106,11 @@ const char* h3d_last_kernel(void* handle);
  * For bf16 layers the size has room for copies of up to 160 MiB (BWD_DATA, and FWD where w is odd) or 96 MiB (BWD_FILTER):
  * dz with the activation's derivative multiplied in, rows padded to whole 16 bytes.  BWD_DATA does not know the activation;
  * a caller that passes act NONE or z NULL can give it what FWD of the same two descriptors asks for.  Less room than for
- * the copies, down to what the call needs at all (H3D_EWORKSPACE below), selects a slower kernel: in BWD_DATA and FWD with
- * the same bits, in BWD_FILTER with the sums in another order. */
+ * the copies selects a slower kernel: in BWD_DATA and FWD with the same bits, in BWD_FILTER with the sums in another order.
+ * FWD and BWD_DATA of small whole samples, whose channels are summed in parts (see h3d_tensor), also ask for the parts' sums;
+ * without room for those they are summed in one chain (same values to a rounding), so that what a larger volume of the same
+ * channels asks for does for a smaller one: down to the packed filter, for bf16 results with W <= 16 of fewer than 64
+ * workgroups down to their parts' sums.  H3D_EWORKSPACE below that. */
 size_t h3d_conv3d_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z);
 
 /* Forward: z[n,co,p] = act(bias[co] + sum_{ci,kd,kh,kw} w[co,ci,kd,kh,kw] * x~[n,ci,p+k-1])

@@ -355,9 +355,10 @@ h3d_status conv3d_f32_mfma(void* handle, const h3d_tensor* in, const h3d_tensor*
   const int cin_k = in->c, cout_k = out->c;
   const int cin = transpose ? cout_k : cin_k, cout = transpose ? cin_k : cout_k;
   const bool thin = cout_k <= 4;
-  const F32Plan p = f32_plan(cin_k, out);
+  F32Plan p = f32_plan(cin_k, out);
+  if (ws_bytes < p.wk_bytes + p.part_bytes) { p.nsplit = 1; p.per_split = p.ncig; p.part_bytes = 0; }      // no room for the sums: one chain
   const int cb = p.cb, nc = 16 * cb, hv = p.hv, tr = p.tr, ncog = p.ncog;
-  if (!ws || ws_bytes < p.wk_bytes + p.part_bytes) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
+  if (!ws || ws_bytes < p.wk_bytes) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
   if (mask && !fits_buf(mask)) return fail(handle, H3D_EUNSUPPORTED, "conv3d: z too large for this kernel");
   F32Args a;
   a.in = make_geo(in);

@@ -294,3 +294,39 @@ def test_narrow_volumes_split_from_64_workgroups_on(N, ci, co, D, H, W, split):
     zg = h3d.conv3d_fwd(xg, wd, bd, dev_like(zo, "bf16", float("nan")), h3d.ACT_LEAKY, 0.01)
     assert (h3d.h3d_last_kernel().split(",")[5] == "1") == split, h3d.h3d_last_kernel()
     close(from_dev(zg.t), zo.a, TOL["bf16"], "z")
+
+
+@pytest.mark.parametrize("dtype,N,ci,co,D,H,W,larger", [("bf16", 1, 100, 33, 3, 4, 17, 64), ("bf16", 1, 64, 64, 16, 32, 32, 64), ("bf16", 8, 144, 128, 8, 16, 8, 128),
+                                                        ("f32", 2, 36, 40, 5, 7, 16, 128), ("f32", 1, 70, 36, 3, 5, 33, 64)])
+def test_the_workspace_of_a_larger_volume_does_for_a_smaller_one(dtype, N, ci, co, D, H, W, larger):
+    """Calls that would sum their channels in parts, in a workspace sized by a layer of the same channels that does not: one chain of sums."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    print("larger workspace", dtype, N, ci, co, D, H, W, flush=True)
+    rng = np.random.default_rng(ci + W)
+    w = quantize(rng.uniform(-1, 1, (co, ci, 3, 3, 3)) / np.sqrt(9 * ci), dtype)
+    wd, bd = to_dev(w, dtype), to_dev(rng.uniform(-0.1, 0.1, co), "f32")
+    xo, xg = slab_pair(rng.standard_normal((N, ci, D, H, W)), dtype)
+    go, gg = slab_pair(rng.standard_normal((N, co, D, H, W)), dtype)
+    so, sg = slab_pair(rng.standard_normal((N, co, D, H, W)), dtype)
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    big = lambda c: h3d.Slab(torch.empty((N, c, larger, 64, 16 if W <= 16 else 64), dtype=td, device="cuda"))
+
+    class Sized:
+        def __init__(self, op, a, b):
+            self.n = h3d.h3d_conv3d_workspace_bytes(op, big(a), big(b))
+            self.buf = torch.full((self.n + 4096,), 171, dtype=torch.uint8, device="cuda")
+
+        def get(self, nbytes):
+            assert nbytes > self.n, "the smaller volume asks for more"
+            return self.buf.data_ptr(), self.n
+
+    zo = orc.conv3d_fwd(xo, w, from_dev(bd), act=orc.ACT_LEAKY, alpha=0.01)
+    dxo = orc.conv3d_bwd_data(go, so, w, act=orc.ACT_LEAKY, alpha=0.01)
+    for ws, ref, call in ((Sized(h3d.OP_FWD, ci, co), zo, lambda t, k: h3d.conv3d_fwd(xg, wd, bd, t, h3d.ACT_LEAKY, 0.01, k)),
+                          (Sized(h3d.OP_FWD, co, ci), dxo, lambda t, k: h3d.conv3d_bwd_data(gg, sg, wd, t, h3d.ACT_LEAKY, 0.01, k))):
+        t = dev_like(ref, dtype, float("nan"))
+        call(t, ws)
+        assert "split" not in h3d.h3d_last_kernel()
+        close(from_dev(t.t), ref.a, TOL[dtype])
+        assert bool((ws.buf[ws.n:] == 171).all())
