@@ -194,9 +194,13 @@ h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x, const h3d
  *                     (overwritten; the shard's partial gradient; deterministic: fixed chunks of tiles, added in order)
  * Workspace: h3d_conv3d_k5_workspace_bytes(handle, op, x, z) with x / z the input-side / output-side descriptors for
  * every op (packed copy of the filter, or the per-chunk partial sums; for bf16 backward passes also g = dz * act'(z),
- * the size of dz); 256-byte aligned; H3D_EWORKSPACE if too small.
- * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation; fp32 tensors
- * run on the vector ALU, bf16 tensors on the matrix cores, where g is rounded to bf16 once, as in the 3x3x3 calls (not by
+ * the size of dz; for fp32 forward and backward-data of tensors of few tiles also the sums of their input channels' parts,
+ * up to eight times the result); 256-byte aligned; H3D_EWORKSPACE if too small.  fp32 takes less as well: the sums are
+ * one chain without room for parts, and the vector ALU's kernels, for whose filter or partial sums there has to be room, take
+ * over where the matrix cores' own do not fit.
+ * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation.  fp32 tensors
+ * run on the matrix cores unless a sample exceeds 32-bit byte offsets (forward and backward-data of few tiles sum their input
+ * channels in parts, shards too: shards of different sizes agree to a rounding), bf16 tensors do too, where g is rounded to bf16 once, as in the 3x3x3 calls (not by
  * backward-filter where w is no multiple of 8: the two branches of a leaky g are summed apart there, unrounded).  bf16
  * calls that run on the vector ALU all the same: channels of 2^25 elements and more (rows counted in multiples of 8 where a
  * pass copies them), forward and backward-data of tensors with fewer than 8 stored elements a sample; backward-filter of

@@ -29,9 +29,10 @@ h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, 
 // conv_k5_f32.hip
 bool k5f_supported(const h3d_tensor* in, const h3d_tensor* out);
 size_t k5f_conv_bytes(int cin_k, const h3d_tensor* out);
+size_t k5f_filter_bytes(int cin_k, const h3d_tensor* out);
 size_t k5f_bf_bytes(const h3d_tensor* x, int cout);
 h3d_status k5f_conv(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, int cin, int cout, bool transposed, const float* bias,
-                    h3d_tensor* out, int pmin, int pmax, float slope_in, float slope_out, void* ws, hipStream_t s);
+                    h3d_tensor* out, int pmin, int pmax, float slope_in, float slope_out, void* ws, size_t ws_bytes, hipStream_t s);
 h3d_status k5f_bwd_filter(void* handle, const h3d_tensor* x, const h3d_tensor* dz, const h3d_tensor* z, float* dw, float* db, int pmin, int pmax,
                           float slope, void* ws, hipStream_t s);
 
@@ -347,6 +348,14 @@ bool k5_on_f32(const h3d_tensor* in, const h3d_tensor* out, const h3d_tensor* ma
   return k5f_supported(in, out) && (!mask || k5f_supported(mask, out));
 }
 
+// what a call is refused below.  fp32: what the vector-ALU route needs, which takes over where a workspace has no room for the matrix cores' packed
+// filter or the filter gradient's partial sums
+size_t k5_least_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z) {
+  if (x->dtype != H3D_F32) return h3d_conv3d_k5_workspace_bytes(handle, op, x, z);
+  const K5Plan p = k5_plan(x, x->c, z->c, op);
+  return op == H3D_OP_BWD_FILTER ? p.part_bytes + p.partdb_bytes : p.wp_bytes;
+}
+
 bool bad_act(int act) { return act != H3D_ACT_NONE && act != H3D_ACT_RELU && act != H3D_ACT_LEAKY; }
 
 }  // namespace
@@ -387,7 +396,7 @@ extern "C" h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const
   if (!w) return fail(handle, H3D_EINVAL, "conv3d_k5_fwd: NULL weights");
   if (bad_act(act)) return fail(handle, H3D_EINVAL, "bad activation %d", act);
   if (!k5_halo_ok(x)) return fail(handle, H3D_EHALO, "conv3d_k5_fwd: x must store two halo planes on every side that is inside the volume");
-  if (!ws || ws_bytes < h3d_conv3d_k5_workspace_bytes(handle, H3D_OP_FWD, x, z)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_fwd: workspace too small");
+  if (!ws || ws_bytes < k5_least_bytes(handle, H3D_OP_FWD, x, z)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_fwd: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_k5_fwd: workspace must be 256-byte aligned");
   const K5Plan p = k5_plan(x, x->c, z->c, H3D_OP_FWD);
   if (p.tiles_total == 0) return H3D_OK;
@@ -395,7 +404,7 @@ extern "C" h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const
   float* wp = (float*)ws;
   const K5Args a = k5_args(x, z, nullptr, p, z->c, 1.f, act_slope(act, alpha));
   if (k5_on_mfma(H3D_OP_FWD, x, z)) H3D_TRY(k5_mfma_conv(handle, make_geo(x), x->data, w, x->c, z->c, false, bias, z, a.slope_out, ws, s));
-  else if (k5_on_f32(x, z, nullptr)) H3D_TRY(k5f_conv(handle, x, nullptr, w, x->c, z->c, false, bias, z, a.pmin, a.pmax, 1.f, a.slope_out, ws, s));
+  else if (k5_on_f32(x, z, nullptr) && ws_bytes >= k5f_filter_bytes(x->c, z)) H3D_TRY(k5f_conv(handle, x, nullptr, w, x->c, z->c, false, bias, z, a.pmin, a.pmax, 1.f, a.slope_out, ws, ws_bytes, s));
   else if (x->dtype == H3D_F32) { k5_launch_pack<float>(w, wp, x->c, z->c, 0, s); k5_launch_conv<float>(x, nullptr, wp, bias, z, a, s); }
   else { k5_launch_pack<bf16_t>(w, wp, x->c, z->c, 0, s); k5_launch_conv<bf16_t>(x, nullptr, wp, bias, z, a, s); }
   return launch_status(handle, "conv3d_k5_fwd");
@@ -415,7 +424,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_data(void* handle, const h3d_tensor* dz,
     if (!same_shard(z, dz) || z->c != dz->c) return fail(handle, H3D_EINVAL, "conv3d_k5_bwd_data: z and dz shapes differ");
     if (!k5_halo_ok(z)) return fail(handle, H3D_EHALO, "conv3d_k5_bwd_data: z must store two halo planes on every side that is inside the volume");
   }
-  if (!ws || ws_bytes < h3d_conv3d_k5_workspace_bytes(handle, H3D_OP_BWD_DATA, dx, dz)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_bwd_data: workspace too small");
+  if (!ws || ws_bytes < k5_least_bytes(handle, H3D_OP_BWD_DATA, dx, dz)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_bwd_data: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_k5_bwd_data: workspace must be 256-byte aligned");
   const K5Plan p = k5_plan(dx, dx->c, dz->c, H3D_OP_BWD_DATA);
   if (p.tiles_total == 0) return H3D_OK;
@@ -436,7 +445,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_data(void* handle, const h3d_tensor* dz,
     }
     H3D_TRY(k5_mfma_conv(handle, gi, gd, w, dx->c, dz->c, true, nullptr, dx, 1.f, ws, s));
   }
-  else if (k5_on_f32(dz, dx, z)) H3D_TRY(k5f_conv(handle, dz, z, w, dx->c, dz->c, true, nullptr, dx, a.pmin, a.pmax, a.slope_in, 1.f, ws, s));
+  else if (k5_on_f32(dz, dx, z) && ws_bytes >= k5f_filter_bytes(dz->c, dx)) H3D_TRY(k5f_conv(handle, dz, z, w, dx->c, dz->c, true, nullptr, dx, a.pmin, a.pmax, a.slope_in, 1.f, ws, ws_bytes, s));
   else if (dz->dtype == H3D_F32) { k5_launch_pack<float>(w, wp, dx->c, dz->c, 1, s); k5_launch_conv<float>(dz, z, wp, nullptr, dx, a, s); }
   else { k5_launch_pack<bf16_t>(w, wp, dx->c, dz->c, 1, s); k5_launch_conv<bf16_t>(dz, z, wp, nullptr, dx, a, s); }
   return launch_status(handle, "conv3d_k5_bwd_data");
@@ -455,7 +464,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_filter(void* handle, const h3d_tensor* x
     H3D_TRY(check_tensor_packed(handle, z, "z"));
     if (!same_shard(z, dz) || z->c != dz->c) return fail(handle, H3D_EINVAL, "conv3d_k5_bwd_filter: z and dz shapes differ");
   }
-  if (!ws || ws_bytes < h3d_conv3d_k5_workspace_bytes(handle, H3D_OP_BWD_FILTER, x, dz)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_bwd_filter: workspace too small");
+  if (!ws || ws_bytes < k5_least_bytes(handle, H3D_OP_BWD_FILTER, x, dz)) return fail(handle, H3D_EWORKSPACE, "conv3d_k5_bwd_filter: workspace too small");
   if ((uintptr_t)ws & 255) return fail(handle, H3D_EINVAL, "conv3d_k5_bwd_filter: workspace must be 256-byte aligned");
   const K5Plan p = k5_plan(x, x->c, dz->c, H3D_OP_BWD_FILTER);
   hipStream_t s = (hipStream_t)stream;
@@ -489,7 +498,7 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_filter(void* handle, const h3d_tensor* x
     H3D_TRY(k5_mfma_bwd_filter(handle, x, gx, xd, gi, gd, two ? (int64_t)(k5_copy_bytes(dz) / sizeof(bf16_t)) : 0, a.slope_in, dz->c, dw, db, ws, s));
     return launch_status(handle, "conv3d_k5_bwd_filter");
   }
-  if (p.tiles_total > 0 && k5_on_f32(x, dz, z)) {
+  if (p.tiles_total > 0 && k5_on_f32(x, dz, z) && ws_bytes >= k5f_bf_bytes(x, dz->c)) {
     H3D_TRY(k5f_bwd_filter(handle, x, dz, z, dw, db, a.pmin, a.pmax, a.slope_in, ws, s));
     return launch_status(handle, "conv3d_k5_bwd_filter");
   }

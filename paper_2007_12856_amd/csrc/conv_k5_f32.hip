@@ -456,6 +456,8 @@ size_t k5f_conv_bytes(int cin_k, const h3d_tensor* out) {
   const K5FPlan p = k5f_plan(cin_k, out);
   return p.wk_bytes + p.part_bytes;
 }
+// .. without the sums of the splits: a call that has no room for those is not split (a workspace that is large enough for a larger volume)
+size_t k5f_filter_bytes(int cin_k, const h3d_tensor* out) { return k5f_plan(cin_k, out).wk_bytes; }
 size_t k5f_bf_bytes(const h3d_tensor* x, int cout) {
   const K5FBfPlan p = k5f_bf_plan(x, cout);
   return p.part_bytes + p.db_bytes;
@@ -463,8 +465,10 @@ size_t k5f_bf_bytes(const h3d_tensor* x, int cout) {
 
 // cin / cout: channels of the layer; pmin, pmax: planes of `in` (and of the mask) that are stored and inside the volume
 h3d_status k5f_conv(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, int cin, int cout, bool transposed, const float* bias,
-                    h3d_tensor* out, int pmin, int pmax, float slope_in, float slope_out, void* ws, hipStream_t s) {
-  const K5FPlan p = k5f_plan(in->c, out);
+                    h3d_tensor* out, int pmin, int pmax, float slope_in, float slope_out, void* ws, size_t ws_bytes,
+                    hipStream_t s) {
+  K5FPlan p = k5f_plan(in->c, out);
+  if (ws_bytes < p.wk_bytes + p.part_bytes) { p.nsplit = 1; p.per_split = p.ncig; p.part_bytes = 0; }
   if (p.tiles >= ((int64_t)1 << 31) || p.ncog > 65535) return fail(handle, H3D_EINVAL, "conv3d_k5: too many blocks");
   K5FArgs a;
   a.in = make_geo(in); a.mask = mask ? make_geo(mask) : a.in; a.out = make_geo(out);

@@ -388,3 +388,41 @@ def test_k5_f32_eight_row_tiles_equal_two_row_tiles():
             assert ",2," in h3d.h3d_last_kernel() and torch.equal(y1[0], y[n])
             h3d.conv3d_k5_bwd_data(h3d.Slab(x[n:n + 1].contiguous()), h3d.Slab(x.roll(1, 0)[n:n + 1].contiguous()), wt, h3d.Slab(d1), h3d.ACT_LEAKY, 0.01)
             assert ",2," in h3d.h3d_last_kernel() and torch.equal(d1[0], d[n])
+
+
+@pytest.mark.parametrize("N,ci,co,D,H,W", [(1, 96, 16, 3, 7, 16), (1, 30, 40, 2, 9, 33)])
+def test_k5_f32_in_less_workspace(N, ci, co, D, H, W):
+    """What a larger volume of the same channels asks for does (the channels are then not summed in parts), and what the vector ALU's kernels
+    need does: their packed filter (16 channels a block, every contraction channel), or the chunks' partial sums."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    print("k5 f32 workspace", N, ci, co, D, H, W, flush=True)
+    rng = np.random.default_rng(ci)
+    w = quantize(rng.uniform(-1, 1, (co, ci, 5, 5, 5)) / np.sqrt(40 * ci), "f32")
+    wd, bd = to_dev(w, "f32"), to_dev(rng.uniform(-0.1, 0.1, co), "f32")
+    xo, xg = slab_pair(rng.standard_normal((N, ci, D, H, W)), "f32")
+    go, gg = slab_pair(rng.standard_normal((N, co, D, H, W)), "f32")
+    so, sg = slab_pair(rng.standard_normal((N, co, D, H, W)), "f32")
+    big = lambda c: h3d.Slab(torch.empty((N, c, 64, 64, W), device="cuda"))
+    packed = lambda a, b: -(-(-(-a // 16) * 16 * b * 125 * 4) // 256) * 256
+    zo = orc.convk_fwd(xo, w, from_dev(bd), orc.ACT_LEAKY, 0.01)
+    dxo = orc.convk_bwd_data(go, so, w, orc.ACT_LEAKY, 0.01)
+
+    class Sized:
+        def __init__(self, n):
+            self.n, self.buf = n, torch.full((n + 4096,), 171, dtype=torch.uint8, device="cuda")
+
+        def get(self, nbytes):
+            assert nbytes > self.n
+            return self.buf.data_ptr(), self.n
+
+    for op, ref, least, call in ((h3d.OP_FWD, zo, packed(co, ci), lambda t, k: h3d.conv3d_k5_fwd(xg, wd, bd, t, h3d.ACT_LEAKY, 0.01, k)),
+                                 (h3d.OP_BWD_DATA, dxo, packed(ci, co), lambda t, k: h3d.conv3d_k5_bwd_data(gg, sg, wd, t, h3d.ACT_LEAKY, 0.01, k))):
+        for n, kernel in ((h3d.h3d_conv3d_k5_workspace_bytes(op, big(ci), big(co)), "k5f_conv"), (least, "")):
+            ws, t = Sized(n), dev_like(ref, "f32", float("nan"))
+            call(t, ws)
+            assert h3d.h3d_last_kernel().startswith(kernel)
+            close(from_dev(t.t), ref.a, TOL["f32"])
+            assert bool((ws.buf[n:] == 171).all())
+        with pytest.raises(h3d.H3DError):
+            call(dev_like(ref, "f32"), Sized(least - 256))
