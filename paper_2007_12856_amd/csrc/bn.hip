@@ -270,19 +270,20 @@ int64_t bn_seg(const h3d_tensor* x) {
   return std::min(BN_SEG_MAX, std::max<int64_t>(1, cdiv(cdiv(run, cdiv(BN_BLOCKS, rows)), BN_SEG_MIN)) * BN_SEG_MIN);
 }
 
-BnArgs bn_args(const h3d_tensor* x, const h3d_tensor* y) {
+BnArgs bn_args(const h3d_tensor* x, const h3d_tensor* y, int64_t seg) {
   BnArgs a;
   a.x = make_geo(x);
   a.y = y ? make_geo(y) : a.x;
   a.run = (int64_t)x->d * x->h * x->w;
-  a.seg = bn_seg(x);
+  a.seg = seg;
   a.segs = (int)std::max<int64_t>(1, cdiv(a.run, a.seg));
   return a;
 }
 
-size_t bn_ws(const h3d_tensor* x) {
+// partial sums of segments of `seg` elements.  The longest ones are what a call is refused below: what a larger tensor asks for does for a smaller one.
+size_t bn_ws(const h3d_tensor* x, int64_t seg) {
   const int64_t run = (int64_t)x->d * x->h * x->w;
-  const int64_t segs = std::max<int64_t>(1, cdiv(run, bn_seg(x)));
+  const int64_t segs = std::max<int64_t>(1, cdiv(run, seg));
   return (size_t)((int64_t)x->c * x->n * segs * 2 * sizeof(float) + 255) & ~(size_t)255;      // partial sums [c][n * segs][2]
 }
 
@@ -291,8 +292,9 @@ h3d_status bn_sums(void* handle, const h3d_tensor* x, const h3d_tensor* dy, cons
                    float* o1, void* ws, size_t ws_bytes, hipStream_t s) {
   if (x->c == 0) return H3D_OK;
   if (!o0 || !o1) return fail(handle, H3D_EINVAL, "bn: NULL output");
-  if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn: workspace too small");
-  const BnArgs a = bn_args(x, dy);
+  if (!ws || ws_bytes < bn_ws(x, BN_SEG_MAX)) return fail(handle, H3D_EWORKSPACE, "bn: workspace too small");
+  const int64_t seg = bn_seg(x);
+  const BnArgs a = bn_args(x, dy, ws_bytes < bn_ws(x, seg) ? BN_SEG_MAX : seg);
   if ((int64_t)x->n * a.run == 0) {
     bn_reduce(ws, o0, o1, x->c, 0, s);
     return launch_status(handle, "bn_sums");
@@ -326,7 +328,7 @@ using namespace h3d;
 
 extern "C" size_t h3d_bn_workspace_bytes(void* handle, const h3d_tensor* x) {
   if (!handle || !x) return 0;
-  return bn_ws(x);
+  return bn_ws(x, bn_seg(x));
 }
 
 extern "C" h3d_status h3d_bn_stats(void* handle, const h3d_tensor* x, float* sum, float* sqsum, void* ws, size_t ws_bytes,
@@ -356,7 +358,7 @@ extern "C" h3d_status h3d_bn_fwd(void* handle, const h3d_tensor* x, const float*
   if (!same_shard(x, y) || x->c != y->c) return fail(handle, H3D_EINVAL, "bn_fwd: x and y must agree in shape, shard and dtype");
   if (x->c == 0) return H3D_OK;
   if (!mean || !invstd) return fail(handle, H3D_EINVAL, "bn_fwd: NULL statistics");
-  if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn_fwd: workspace too small");
+  if (!ws || ws_bytes < bn_ws(x, BN_SEG_MAX)) return fail(handle, H3D_EWORKSPACE, "bn_fwd: workspace too small");
   const BnCoef q{mean, invstd, gamma, beta, nullptr, nullptr, 0.f};
   hipStream_t s = (hipStream_t)stream;
   return x->dtype == H3D_F32 ? bn_apply<float, false>(handle, x, nullptr, y, q, s) : bn_apply<bf16_t, false>(handle, x, nullptr, y, q, s);
@@ -386,7 +388,7 @@ extern "C" h3d_status h3d_bn_bwd(void* handle, const h3d_tensor* dy, const h3d_t
   if (count <= 0) return fail(handle, H3D_EINVAL, "bn_bwd: count must be positive");
   if (x->c == 0) return H3D_OK;
   if (!mean || !invstd || !sum_dy || !sum_dy_xhat) return fail(handle, H3D_EINVAL, "bn_bwd: NULL pointer");
-  if (!ws || ws_bytes < bn_ws(x)) return fail(handle, H3D_EWORKSPACE, "bn_bwd: workspace too small");
+  if (!ws || ws_bytes < bn_ws(x, BN_SEG_MAX)) return fail(handle, H3D_EWORKSPACE, "bn_bwd: workspace too small");
   const BnCoef q{mean, invstd, gamma, nullptr, sum_dy, sum_dy_xhat, (float)(1.0 / (double)count)};
   hipStream_t s = (hipStream_t)stream;
   return x->dtype == H3D_F32 ? bn_apply<float, true>(handle, dy, x, dx, q, s) : bn_apply<bf16_t, true>(handle, dy, x, dx, q, s);

@@ -163,3 +163,33 @@ def _bn_against_float64(shape, dtype, rel):
     ref_dx = per(gamma * inv) * (G - per(sdy / count) - xhat * per(sdx / count))
     for got, ref in ((y.t, ref_y), (dx.t, ref_dx)):
         assert float(((got.double() - ref).abs() - rel * ref.abs()).max()) <= 1e-5
+
+
+@pytest.mark.parametrize("shape", [(1, 32, 33, 64, 64), (1, 64, 16, 32, 32), (2, 3, 4, 4, 8)])
+def test_bn_sums_in_the_workspace_of_a_larger_tensor(shape):
+    """One partial sum for each 131072 elements of a channel's run is room enough; less is refused.  Sums to 1e-5 of the sum of magnitudes."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    n, c, d, h, w = shape
+    x = torch.randn(shape, generator=torch.Generator(device="cuda").manual_seed(3), device="cuda")
+    room = -(-(n * c * -(-d * h * w // 131072) * 8) // 256) * 256
+
+    class Sized:
+        def __init__(self, k):
+            self.k, self.buf = k, torch.full((k + 4096,), 171, dtype=torch.uint8, device="cuda")
+
+        def get(self, nbytes):
+            return self.buf.data_ptr(), self.k
+
+    s, sq = torch.full((c,), 7.0, device="cuda"), torch.full((c,), 7.0, device="cuda")
+    ws = Sized(room)
+    h3d.bn_stats(h3d.Slab(x), s, sq, ws)
+    xd = x.double()
+    assert bool(((s.double() - xd.sum((0, 2, 3, 4))).abs() <= 1e-5 * xd.abs().sum((0, 2, 3, 4))).all())
+    assert bool(((sq.double() - xd.square().sum((0, 2, 3, 4))).abs() <= 1e-5 * xd.square().sum((0, 2, 3, 4))).all())
+    y = torch.empty_like(x)
+    one = torch.ones(c, device="cuda")
+    h3d.bn_fwd(h3d.Slab(x), 0 * one, one, one, 0 * one, h3d.Slab(y), ws)
+    assert torch.equal(x, y) and bool((ws.buf[room:] == 171).all())
+    with pytest.raises(h3d.H3DError):
+        h3d.bn_stats(h3d.Slab(x), s, sq, Sized(room - 256))
