@@ -685,7 +685,10 @@ static h3d_status deconv_bwd_filter_t(void* handle, const h3d_tensor* x, const h
   a.x = make_geo(x); a.y = make_geo(dy); a.cin = x->c; a.cout = dy->c;
   a.voxels = (int64_t)x->n * x->d * x->h * x->w;
   if (a.cin == 0 || a.cout == 0) return H3D_OK;
-  if (deconv_bf_flat_supported(x, dy)) return deconv_bf_flat(handle, x, dy, dw, db, ws, ws_bytes, s);
+  // fp32 and ragged rows in a workspace that has no room for that kernel's partial sums, or an address it does not take: the direct kernel
+  if (deconv_bf_flat_supported(x, dy) &&
+      ((x->dtype == H3D_BF16 && x->w % 8 == 0) || (ws_bytes >= deconv_bf_flat_ws_bytes(x, dy) && (uintptr_t)ws % 16 == 0)))
+    return deconv_bf_flat(handle, x, dy, dw, db, ws, ws_bytes, s);
   df_plan(a.voxels, a.cin, a.cout, &a.chunk, &a.nchunks);
   int cog = (int)cdiv(a.cout, DF_COT);
   size_t need = (size_t)a.nchunks * cog * DF_COT * a.cin * 9 * 4;

@@ -330,3 +330,26 @@ def test_the_workspace_of_a_larger_volume_does_for_a_smaller_one(dtype, N, ci, c
         assert "split" not in h3d.h3d_last_kernel()
         close(from_dev(t.t), ref.a, TOL[dtype])
         assert bool((ws.buf[ws.n:] == 171).all())
+
+
+@pytest.mark.parametrize("dtype,cin,cout,d,H,W,shift,kernel", [
+    ("f32", 20, 24, 4, 16, 32, 4, "deconv2_bwd_filter"), ("bf16", 20, 24, 4, 16, 30, 4, "deconv2_bwd_filter"), ("f32", 20, 24, 4, 16, 32, 0, "deconv_bf_flat_kernel")])
+def test_deconv_filter_gradient_in_a_workspace_at_an_odd_address(dtype, cin, cout, d, H, W, shift, kernel):
+    """fp32 tensors and ragged rows in a workspace that is no multiple of 16: the direct kernel, as for one too small for the matrix cores' sums."""
+    import torch
+    import paper_2007_12856_amd as h3d
+
+    class Moved:
+        def get(self, nbytes):
+            self.buf = torch.empty(int(nbytes) + 16, dtype=torch.uint8, device="cuda")
+            return self.buf.data_ptr() + shift, int(nbytes)
+
+    rng = np.random.default_rng(cin)
+    xo, xg = slab_pair(rng.standard_normal((1, cin, d, H, W)), dtype)
+    dyo, dyg = slab_pair(rng.standard_normal((1, cout, 2 * d, 2 * H, 2 * W)), dtype)
+    dwo, dbo = orc.deconv2_bwd_filter(xo, dyo)
+    dw, db = torch.full((cin, cout, 2, 2, 2), float("nan"), device="cuda"), torch.full((cout,), float("nan"), device="cuda")
+    h3d.deconv2_bwd_filter(xg, dyg, dw, db, Moved())
+    assert h3d.h3d_last_kernel().startswith(kernel)
+    close(from_dev(dw), dwo, 2e-5)
+    close(from_dev(db), dbo, 2e-5)
