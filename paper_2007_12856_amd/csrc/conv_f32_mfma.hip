@@ -103,11 +103,13 @@ struct F32Args {
   float out_slope, mask_slope;
   int vec;                // 16-byte stores allowed
   int per_split;          // channel groups of a split (blockIdx.z)
-  int64_t split_elems;    // elements of one split's sums (0: not split)
+  int64_t split_elems;    // elements of one split's sums, which lie as the (packed) output does
   float* part;
 };
 
-template <int CB, int TR, int HV, bool MASKED, bool THIN = false>
+// SPLIT: the channel groups are dealt to blockIdx.z.  (A form of its own: as a test at run time it cost the other forms up to 17 %, 8->64 of
+// 2 x 16x52x80 44.9 -> 52 us, thin 164->4 on 8 x 18x22x66 309 -> 331.)
+template <int CB, int TR, int HV, bool MASKED, bool THIN = false, bool SPLIT = false>
 __global__ void __launch_bounds__(256, 2) conv3d_f32_mfma_kernel(const float* __restrict__ in, const float* __restrict__ mask,
                                                                  const float* __restrict__ wk, const float* __restrict__ bias,
                                                                  float* __restrict__ out, F32Args a) {
@@ -165,7 +167,7 @@ __global__ void __launch_bounds__(256, 2) conv3d_f32_mfma_kernel(const float* __
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const int co = cog * NC + cb * 16 + (lane & 15);
-    const float b = (!THIN && bias && !a.split_elems && co < a.cout) ? bias[co] : 0.f;
+    const float b = (!THIN && bias && !SPLIT && co < a.cout) ? bias[co] : 0.f;
 #pragma unroll
     for (int r = 0; r < NAR; ++r)
 #pragma unroll
@@ -177,8 +179,8 @@ __global__ void __launch_bounds__(256, 2) conv3d_f32_mfma_kernel(const float* __
   const __amdgpu_buffer_rsrc_t rs_in = f32_rsrc(in + (int64_t)n * a.in.nstride, (uint32_t)(a.in.nstride * 4));
   const __amdgpu_buffer_rsrc_t rs_mk = f32_rsrc(MASKED ? mask + (int64_t)n * a.mask.nstride : in, (uint32_t)(a.mask.nstride * 4));
 
-  const int cig1 = min(a.ncig, (int)(blockIdx.z + 1) * a.per_split);
-  for (int cig = blockIdx.z * a.per_split; cig < cig1; ++cig) {
+  const int cig1 = SPLIT ? min(a.ncig, (int)(blockIdx.z + 1) * a.per_split) : a.ncig;
+  for (int cig = SPLIT ? blockIdx.z * a.per_split : 0; cig < cig1; ++cig) {
     // ---- stage 4 input channels (tile + halo) and their weights
     float v[4][FX_PT];
 #pragma unroll
@@ -255,8 +257,7 @@ __global__ void __launch_bounds__(256, 2) conv3d_f32_mfma_kernel(const float* __
 
   // ---- epilogue: activation, zero outside the volume, 16-byte stores of 4 voxels of one channel
   if (!live) return;
-  const bool split = !THIN && a.split_elems != 0;      // (out is packed then: the sums lie as it does)
-  float* on = (split ? a.part + blockIdx.z * a.split_elems : out) + (int64_t)n * a.out.nstride + (int64_t)ps * a.out.plane;
+  float* on = (SPLIT ? a.part + blockIdx.z * a.split_elems : out) + (int64_t)n * a.out.nstride + (int64_t)ps * a.out.plane;
 #pragma unroll
   for (int cb = 0; cb < CB; ++cb) {
     const int co = cog * NC + cb * 16 + (lane & 15);
@@ -283,7 +284,7 @@ __global__ void __launch_bounds__(256, 2) conv3d_f32_mfma_kernel(const float* __
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
           float x = o[j];
-          if (!split && !(x > 0.f)) x *= a.out_slope;
+          if (!SPLIT && !(x > 0.f)) x *= a.out_slope;
           o[j] = inside ? x : 0.f;
         }
         float* p = oc + (int64_t)h * W + wc;
@@ -383,27 +384,30 @@ h3d_status conv3d_f32_mfma(void* handle, const h3d_tensor* in, const h3d_tensor*
     hipLaunchKernelGGL(pack_w_f32_mfma_kernel, dim3((unsigned)cdiv(nw, 256)), dim3(256), 0, stream, (const float*)w, (float*)ws,
                        cin, cout, transpose ? 1 : 0, a.ncig, nc, nw);
   const dim3 g((unsigned)tiles, (unsigned)ncog, (unsigned)p.nsplit);
-#define H3D_F32_LAUNCH(CBV, TRV, HVV, MK, TH)                                                                           \
-  hipLaunchKernelGGL((conv3d_f32_mfma_kernel<CBV, TRV, HVV, MK, TH>), g, dim3(256), 0, stream, (const float*)in->data,  \
-                     (const float*)(mask ? mask->data : nullptr), (const float*)ws, bias, (float*)out->data, a)
-#define H3D_F32_LAUNCH_M(CBV, TRV, HVV, TH)                                                                             \
-  do {                                                                                                                  \
-    if (mask) H3D_F32_LAUNCH(CBV, TRV, HVV, true, TH); else H3D_F32_LAUNCH(CBV, TRV, HVV, false, TH);                   \
+#define H3D_F32_LAUNCH(CBV, TRV, HVV, TH, SP)                                                                              \
+  do {                                                                                                                   \
+    if (mask)                                                                                                            \
+      hipLaunchKernelGGL((conv3d_f32_mfma_kernel<CBV, TRV, HVV, true, TH, SP>), g, dim3(256), 0, stream, (const float*)in->data, \
+                         (const float*)mask->data, (const float*)ws, bias, (float*)out->data, a);                        \
+    else                                                                                                                 \
+      hipLaunchKernelGGL((conv3d_f32_mfma_kernel<CBV, TRV, HVV, false, TH, SP>), g, dim3(256), 0, stream, (const float*)in->data, \
+                         (const float*)nullptr, (const float*)ws, bias, (float*)out->data, a);                           \
   } while (0)
 #define H3D_F32_LAUNCH_T(CBV, TH)                                                                                       \
   do {                                                                                                                  \
-    if (tr == 8 && hv == 2) H3D_F32_LAUNCH_M(CBV, 8, 2, TH);                                                            \
-    else if (tr == 8) H3D_F32_LAUNCH_M(CBV, 8, 1, TH);                                                                  \
-    else if (hv == 2) H3D_F32_LAUNCH_M(CBV, 2, 2, TH);                                                                  \
-    else H3D_F32_LAUNCH_M(CBV, 2, 1, TH);                                                                               \
+    if (tr == 8 && hv == 2) H3D_F32_LAUNCH(CBV, 8, 2, TH, false);                                                       \
+    else if (tr == 8) H3D_F32_LAUNCH(CBV, 8, 1, TH, false);                                                             \
+    else if (hv == 2 && p.nsplit > 1) H3D_F32_LAUNCH(CBV, 2, 2, TH, !TH);                                               \
+    else if (p.nsplit > 1) H3D_F32_LAUNCH(CBV, 2, 1, TH, !TH);                                                          \
+    else if (hv == 2) H3D_F32_LAUNCH(CBV, 2, 2, TH, false);                                                             \
+    else H3D_F32_LAUNCH(CBV, 2, 1, TH, false);                                                                          \
   } while (0)
-  if (thin) H3D_F32_LAUNCH_T(1, true);
+  if (thin) H3D_F32_LAUNCH_T(1, true);      // (never split)
   else if (cb == 1) H3D_F32_LAUNCH_T(1, false);
   else H3D_F32_LAUNCH_T(2, false);
   if (p.nsplit > 1)
     hipLaunchKernelGGL(conv_f32_split_kernel, dim3((unsigned)cdiv(a.split_elems, 256)), dim3(256), 0, stream, bias, (float*)out->data, a, p.nsplit);
 #undef H3D_F32_LAUNCH_T
-#undef H3D_F32_LAUNCH_M
 #undef H3D_F32_LAUNCH
   if (thin) note_kernel(handle, "conv3d_f32_mfma_kernel<thin,%d,%d>", tr, hv);
   else note_kernel(handle, "conv3d_f32_mfma_kernel<%d,%d,%d>%s", cb, tr, hv, p.nsplit > 1 ? " (split)" : "");
