@@ -436,6 +436,19 @@ struct F32BfArgs {
   float mask_slope;
 };
 
+// the last digit of r in base n, taken off it; 32-bit wherever that does (a 64-bit division is some hundred instructions, and a chunk of one tile
+// makes seven of them)
+__device__ __forceinline__ int take_digit(int64_t& r, int n) {
+  if (r >> 32) {
+    const int d = (int)(r % n);
+    r /= n;
+    return d;
+  }
+  const uint32_t v = (uint32_t)r, q = v / (uint32_t)n;
+  r = q;
+  return (int)(v - q * (uint32_t)n);
+}
+
 // What bounds it: the fp32 matrix cores (fp32: 387 us of products for 32 -> 64 channels on 32x128x128), then what a workgroup does between
 // its products.  So tiles are walked along the depth with the planes of x in a ring of four: a step brings one plane (a third of the loads and
 // LDS stores of a tile by itself) while the products of the last three run, with one barrier.
@@ -476,19 +489,21 @@ __global__ void __launch_bounds__(256, 2) bwd_filter_f32_mfma_kernel(const float
   // before them, which only bring the planes in.  Step e of the chunk loads plane q into slot e % 4 and, from a run's third step on, g of plane
   // q - 1, whose three planes of x are then there.
   const int64_t t0 = (int64_t)chunk * a.tiles_per_chunk, t1 = min(t0 + a.tiles_per_chunk, a.tiles);
-  int64_t run = t0 / D;
-  int q = (int)(t0 % D) - 1, qend = (int)min((int64_t)D, t1 - run * D), step = 0, n, h0, w0;
+  int64_t run = t0, last_run = t1 - 1;
+  int q = take_digit(run, D) - 1;
+  take_digit(last_run, D);
+  int qend = (int)min((int64_t)D, t1 - run * D), step = 0, n, h0, w0;
   int xo, go;                              // in-plane byte offsets of this thread's voxels
   auto place = [&]() {
     int64_t r = run;
-    w0 = (int)(r % a.nwg) * BT_W; r /= a.nwg;
-    h0 = (int)(r % a.nhg) * BT_R;
-    n = (int)(r / a.nhg);
+    w0 = take_digit(r, a.nwg) * BT_W;
+    h0 = take_digit(r, a.nhg) * BT_R;
+    n = (int)r;
     const int hx = h0 - 1 + xrow, wx = w0 - 1 + xcol, hg = h0 + gs / BT_W, wg = w0 + gs % BT_W;
     xo = xmine && hx >= 0 && hx < H && wx >= 0 && wx < W ? 4 * (hx * W + wx) : F32_OOB;
     go = hg < H && wg < W ? 4 * (hg * W + wg) : F32_OOB;
   };
-  const int nsteps = t0 < t1 ? (int)(t1 - t0) + 2 * (int)((t1 - 1) / D - t0 / D + 1) : 0;
+  const int nsteps = t0 < t1 ? (int)(t1 - t0) + 2 * (int)(last_run - run + 1) : 0;
   place();
   auto load_step = [&](bool ok) {
     const __amdgpu_buffer_rsrc_t rs_x = f32_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)(a.x.nstride * 4));
@@ -558,46 +573,50 @@ __global__ void __launch_bounds__(256, 2) bwd_filter_f32_mfma_kernel(const float
     store_step(2);
   }
   __syncthreads();
-  for (int e = 2; e < nsteps; ++e) {
-    const bool mul = step >= 2;
-    advance();
-    load_step(e + 1 < nsteps);
-    __builtin_amdgcn_sched_barrier(0);
-    // ---- this wavefront's row(s): CPL products for each of the 27 taps and for the bias gradient
-    if (mul) {
-      const float* xk[3];
+  // ---- this wavefront's row(s): CPL products for each of the 27 taps and for the bias gradient
+  auto multiply = [&](int e) {
+    const float* xk[3];
 #pragma unroll
-      for (int kd = 0; kd < 3; ++kd) xk[kd] = xr + ((e + 2 + kd) & 3) * XPL;      // slots of steps e - 2, e - 1, e
-      const float* ge = gr + (e & 1) * GB;
+    for (int kd = 0; kd < 3; ++kd) xk[kd] = xr + ((e + 2 + kd) & 3) * XPL;      // slots of steps e - 2, e - 1, e
+    const float* ge = gr + (e & 1) * GB;
 #pragma unroll
-      for (int rr = 0; rr < T.rw; ++rr) {
-        float g[CPL], xf[2][XW];
-        auto read_x = [&](int t9, float (&v)[XW]) {
-          const float* p = xk[t9 / 3] + (t9 % 3 + rr) * XP;
+    for (int rr = 0; rr < T.rw; ++rr) {
+      float g[CPL], xf[2][XW];
+      auto read_x = [&](int t9, float (&v)[XW]) {
+        const float* p = xk[t9 / 3] + (t9 % 3 + rr) * XP;
 #pragma unroll
-          for (int k = 0; k < CPL; k += 4) *reinterpret_cast<f32x4*>(v + k) = *reinterpret_cast<const f32x4*>(p + k);
-          *reinterpret_cast<float2*>(v + CPL) = *reinterpret_cast<const float2*>(p + CPL);
-        };
+        for (int k = 0; k < CPL; k += 4) *reinterpret_cast<f32x4*>(v + k) = *reinterpret_cast<const f32x4*>(p + k);
+        *reinterpret_cast<float2*>(v + CPL) = *reinterpret_cast<const float2*>(p + CPL);
+      };
 #pragma unroll
-        for (int k = 0; k < CPL; k += 4) *reinterpret_cast<f32x4*>(g + k) = *reinterpret_cast<const f32x4*>(ge + rr * BT_W + k);
-        read_x(0, xf[0]);
+      for (int k = 0; k < CPL; k += 4) *reinterpret_cast<f32x4*>(g + k) = *reinterpret_cast<const f32x4*>(ge + rr * BT_W + k);
+      read_x(0, xf[0]);
 #pragma unroll
-        for (int t9 = 0; t9 < 9; ++t9) {
-          if (t9 < 8) read_x(t9 + 1, xf[(t9 + 1) & 1]);
-          const float (&v)[XW] = xf[t9 & 1];
+      for (int t9 = 0; t9 < 9; ++t9) {
+        if (t9 < 8) read_x(t9 + 1, xf[(t9 + 1) & 1]);
+        const float (&v)[XW] = xf[t9 & 1];
 #pragma unroll
-          for (int j = 0; j < CPL; ++j)
+        for (int j = 0; j < CPL; ++j)
 #pragma unroll
-            for (int kw = 0; kw < 3; ++kw)
-              acc[t9 * 3 + kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j + kw], g[j], acc[t9 * 3 + kw], 0, 0, 0);
-          if (t9 < CPL) acc[27] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, g[t9], acc[27], 0, 0, 0);
-          __builtin_amdgcn_sched_barrier(0);
-        }
+          for (int kw = 0; kw < 3; ++kw)
+            acc[t9 * 3 + kw] = __builtin_amdgcn_mfma_f32_16x16x4f32(v[j + kw], g[j], acc[t9 * 3 + kw], 0, 0, 0);
+        if (t9 < CPL) acc[27] = __builtin_amdgcn_mfma_f32_16x16x4f32(1.f, g[t9], acc[27], 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
       }
     }
+  };
+  // the last step is apart: nothing is loaded, stored or waited for behind it (chunks of one tile, two rounds of workgroups: 24->8 on 18x16x192
+  // 39.5 -> 36 us), and a branch around the loads would make the others wait
+  for (int e = 2; e + 1 < nsteps; ++e) {
+    const bool mul = step >= 2;
+    advance();
+    load_step(true);
+    __builtin_amdgcn_sched_barrier(0);
+    if (mul) multiply(e);
     store_step(e + 1);
     __syncthreads();
   }
+  if (nsteps > 0) multiply(nsteps - 1);
 
   // ---- the four wavefronts' sums, added in wavefront order through LDS (the x tile's space: 28 x 1024 B x 4 <= 41 KB)
   float* red = lds_x;
