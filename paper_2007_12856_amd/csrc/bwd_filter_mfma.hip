@@ -969,123 +969,172 @@ __global__ void __launch_bounds__(64 * NW, NW == 4 ? 4 : 2) bwd_filter_roll_smal
 // consecutive outputs; G thread groups (16, or 64 when there are many chunks) each add every G-th chunk in
 // increasing order, then the G group sums are added in group order.  (dw and the bias partials share the kernel: the bias
 // partials are stored behind the dw partials.)  `add`: on top of what dw / db hold (the slabs of a prepared call, in order).
-// tap = 0: the partial tiles are laid out as dw; otherwise [27][cout][cin] with tap = cout * cin.
-__device__ __forceinline__ int64_t bfm_out(int64_t i, int tap) {
-  if (!tap) return i;
-  const uint32_t t = (uint32_t)i / (uint32_t)tap;
-  return ((uint32_t)i - t * (uint32_t)tap) * (int64_t)27 + t;
+// tap = 0: the partial tiles are laid out as dw; otherwise [27][cout][cin] with tap = cout * cin (the rolling and the many-channel kernel).  A
+// block then takes P (cout, cin) pairs of one tap, 108 bytes apart in dw.  The 27 blocks of a group of pairs follow each other on one XCD, whose L2
+// puts their lines together: dealt out in turn, every line of dw was written back in eight parts (24->48 on 2 x 22x50x54 14.3 -> 10 us, 128->64
+// on 64x256x256 15.9 -> 15; laid out as dw these took 11.2 and 13.8).  Groups of 64 pairs are dealt to the XCDs in turn; of 16 a small layer has few, so an XCD
+// takes an eighth of their blocks, whatever group that begins in (13->16 on 8 x 7x80x160 8.6 -> 7.4 us; with groups of 64 that measured 3 % worse).
+struct BfmOut {
+  int64_t i, out;      // element of a partial tile, of dw
+  bool ok;
+};
+template <bool TAP, int P>
+__device__ __forceinline__ BfmOut bfm_out(uint32_t block, int64_t e, int64_t nw, int tap) {      // e: of the block's P elements
+  if (!TAP) {
+    const int64_t i = (int64_t)block * P + e;
+    return {i, i, i < nw};
+  }
+  uint32_t unit;      // 27 * group of pairs + tap
+  if (P == 16) unit = (block & 7) * ((((uint32_t)tap + P - 1) / P * 27 + 7) / 8) + (block >> 3);
+  else unit = ((block >> 3) / 27 * 8 + (block & 7)) * 27 + (block >> 3) % 27;
+  const uint32_t t = unit % 27;
+  const int64_t pair = (int64_t)(unit / 27) * P + e;
+  return {t * (int64_t)tap + pair, pair * 27 + t, pair < tap};
+}
+static int64_t bfm_blocks(int64_t nw, int P, int tap) {
+  if (!tap) return cdiv(nw, P);
+  return P == 16 ? cdiv(cdiv(tap, P) * 27, 8) * 8 : cdiv(cdiv(tap, P), 8) * 8 * 27;
 }
 
+// the bias gradient: 16 channels a block, behind the nblk_w blocks of weights
 template <int G>
-__global__ void __launch_bounds__(16 * G) bfm_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                            float* __restrict__ db, int64_t nw, int cout, int nchunks, int add, int tap) {
-  __shared__ float red[G][17];
+__device__ __forceinline__ void bfm_reduce_bias(const float* __restrict__ part, float* __restrict__ db, int64_t nw, int cout, int nchunks, int add,
+                                                int64_t nblk_w, float (&red)[G][17]) {
   const int o = threadIdx.x & 15, cg = threadIdx.x >> 4;
-  const int64_t i = (int64_t)blockIdx.x * 16 + o;
-  const int64_t nout = nw + cout;
+  const int64_t i = ((int64_t)blockIdx.x - nblk_w) * 16 + o;
   float s = 0.f;
-  if (i < nout) {
-    const bool is_w = i < nw;
-    const float* base = is_w ? part + i : part + (int64_t)nchunks * nw + (i - nw);
-    const int64_t stride = is_w ? nw : cout;
+  if (i < cout) {
+    const float* base = part + (int64_t)nchunks * nw + i;
+    for (int c = cg; c < nchunks; c += G) s += base[(int64_t)c * cout];
+  }
+  red[cg][o] = s;
+  __syncthreads();
+  if (cg == 0 && i < cout && db) {
+    float t = red[0][o];
+#pragma unroll
+    for (int k = 1; k < G; ++k) t += red[k][o];
+    db[i] = add ? db[i] + t : t;
+  }
+}
+
+template <int G, bool TAP>
+__global__ void __launch_bounds__(16 * G) bfm_reduce_kernel(const float* __restrict__ part, float* __restrict__ dw,
+                                                            float* __restrict__ db, int64_t nw, int cout, int nchunks, int add, int tap, int64_t nblk_w) {
+  __shared__ float red[G][17];
+  if (blockIdx.x >= nblk_w) return bfm_reduce_bias<G>(part, db, nw, cout, nchunks, add, nblk_w, red);
+  const int o = threadIdx.x & 15, cg = threadIdx.x >> 4;
+  const BfmOut q = bfm_out<TAP, 16>(blockIdx.x, o, nw, tap);
+  float s = 0.f;
+  if (q.ok) {
+    const float* base = part + q.i;
     int c = cg;
     for (; c + 7 * G < nchunks; c += 8 * G) {      // eight loads in flight, added in increasing chunk order
       float v[8];
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = base[(int64_t)(c + u * G) * stride];
+      for (int u = 0; u < 8; ++u) v[u] = base[(int64_t)(c + u * G) * nw];
 #pragma unroll
       for (int u = 0; u < 8; ++u) s += v[u];
     }
-    for (; c < nchunks; c += G) s += base[(int64_t)c * stride];
+    for (; c < nchunks; c += G) s += base[(int64_t)c * nw];
   }
   red[cg][o] = s;
   __syncthreads();
-  if (cg == 0 && i < nout) {
+  if (cg == 0 && q.ok) {
     float t = red[0][o];
 #pragma unroll
     for (int k = 1; k < G; ++k) t += red[k][o];
-    const int64_t ow = bfm_out(i, tap);
-    if (i < nw) dw[ow] = add ? dw[ow] + t : t;
-    else if (db) db[i - nw] = add ? db[i - nw] + t : t;
+    dw[q.out] = add ? dw[q.out] + t : t;
   }
 }
 
 // The same sum, same order, four weights per thread (nw a multiple of 4, 16-byte-aligned partials): 16 lanes read
 // 256 contiguous bytes of a chunk row instead of 64.
+template <bool TAP>
 __global__ void __launch_bounds__(256) bfm_reduce4_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                          float* __restrict__ db, int64_t nw, int cout, int nchunks, int add, int tap) {
+                                                          float* __restrict__ db, int64_t nw, int cout, int nchunks, int add, int tap, int64_t nblk_w) {
+  if (blockIdx.x >= nblk_w) {
+    __shared__ float redb[16][17];
+    return bfm_reduce_bias<16>(part, db, nw, cout, nchunks, add, nblk_w, redb);
+  }
   __shared__ float4 red[16][17];
   const int o = threadIdx.x & 15, cg = threadIdx.x >> 4;
-  const int64_t nq = nw / 4, nblk_w = (nq + 15) / 16;
-  if ((int64_t)blockIdx.x < nblk_w) {
-    const int64_t q = (int64_t)blockIdx.x * 16 + o;
-    float4 s = {0.f, 0.f, 0.f, 0.f};
-    if (q < nq) {
-      for (int c = cg; c < nchunks; c += 16) {
-        const float4 v = reinterpret_cast<const float4*>(part + (int64_t)c * nw)[q];
-        s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
-      }
-    }
-    red[cg][o] = s;
-    __syncthreads();
-    if (cg == 0 && q < nq) {
-      float4 t = red[0][o];
-#pragma unroll
-      for (int k = 1; k < 16; ++k) { t.x += red[k][o].x; t.y += red[k][o].y; t.z += red[k][o].z; t.w += red[k][o].w; }
-      if (tap) {
-        const float v[4] = {t.x, t.y, t.z, t.w};
-#pragma unroll
-        for (int k = 0; k < 4; ++k) {
-          const int64_t ow = bfm_out(4 * q + k, tap);
-          dw[ow] = add ? dw[ow] + v[k] : v[k];
-        }
-        return;
-      }
-      if (add) {
-        const float4 old = reinterpret_cast<const float4*>(dw)[q];
-        t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w;
-      }
-      reinterpret_cast<float4*>(dw)[q] = t;
-    }
-  } else {
-    __shared__ float redb[16][17];
-    const int64_t i = ((int64_t)blockIdx.x - nblk_w) * 16 + o;
-    float s = 0.f;
-    if (i < cout) {
-      const float* base = part + (int64_t)nchunks * nw + i;
-      for (int c = cg; c < nchunks; c += 16) s += base[(int64_t)c * cout];
-    }
-    redb[cg][o] = s;
-    __syncthreads();
-    if (cg == 0 && i < cout && db) {
-      float t = redb[0][o];
-#pragma unroll
-      for (int k = 1; k < 16; ++k) t += redb[k][o];
-      db[i] = add ? db[i] + t : t;
+  const BfmOut q = bfm_out<TAP, 64>(blockIdx.x, 4 * o, nw, tap);
+  float4 s = {0.f, 0.f, 0.f, 0.f};
+  if (q.ok) {
+    for (int c = cg; c < nchunks; c += 16) {
+      const float4 v = *reinterpret_cast<const float4*>(part + (int64_t)c * nw + q.i);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
     }
   }
+  red[cg][o] = s;
+  __syncthreads();
+  if (cg != 0 || !q.ok) return;
+  float4 t = red[0][o];
+#pragma unroll
+  for (int k = 1; k < 16; ++k) { t.x += red[k][o].x; t.y += red[k][o].y; t.z += red[k][o].z; t.w += red[k][o].w; }
+  if (TAP) {
+    const float v[4] = {t.x, t.y, t.z, t.w};
+    float* d = dw + q.out;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) d[27 * k] = add ? d[27 * k] + v[k] : v[k];
+    return;
+  }
+  float4* d = reinterpret_cast<float4*>(dw + q.out);
+  if (add) {
+    const float4 old = *d;
+    t.x += old.x; t.y += old.y; t.z += old.z; t.w += old.w;
+  }
+  *d = t;
 }
 
 // Same sum for many outputs and few chunks (the late, channel-rich layers): one thread per output adds the chunks
 // in increasing order, so every chunk row is read in whole contiguous kilobytes.
+__device__ __forceinline__ float bfm_sum(const float* base, int64_t stride, int nchunks) {
+  float s = 0.f;
+  int c = 0;
+  auto add = [&](auto n) {
+    float v[n()];
+#pragma unroll
+    for (int k = 0; k < n(); ++k) v[k] = base[(int64_t)(c + k) * stride];
+#pragma unroll
+    for (int k = 0; k < n(); ++k) s += v[k];
+    c += n();
+  };
+  while (c + 8 <= nchunks) add(std::integral_constant<int, 8>());
+  if (c + 4 <= nchunks) add(std::integral_constant<int, 4>());
+  if (c + 2 <= nchunks) add(std::integral_constant<int, 2>());
+  if (c < nchunks) add(std::integral_constant<int, 1>());
+  return s;
+}
 __global__ void __launch_bounds__(256) bfm_reduce_wide_kernel(const float* __restrict__ part, float* __restrict__ dw,
-                                                              float* __restrict__ db, int64_t nw, int cout, int nchunks, int add, int tap) {
+                                                              float* __restrict__ db, int64_t nw, int cout, int nchunks, int add) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (i >= nw + cout) return;
   const bool is_w = i < nw;
-  const float* base = is_w ? part + i : part + (int64_t)nchunks * nw + (i - nw);
-  const int64_t stride = is_w ? nw : cout;
-  float s = 0.f;
-  int c = 0;
-  for (; c + 4 <= nchunks; c += 4) {
-    const float a0 = base[(int64_t)c * stride], a1 = base[(int64_t)(c + 1) * stride];
-    const float a2 = base[(int64_t)(c + 2) * stride], a3 = base[(int64_t)(c + 3) * stride];
-    s = (((s + a0) + a1) + a2) + a3;
-  }
-  for (; c < nchunks; ++c) s += base[(int64_t)c * stride];
-  const int64_t ow = bfm_out(i, tap);
-  if (is_w) dw[ow] = add ? dw[ow] + s : s;
+  const float s = is_w ? bfm_sum(part + i, nw, nchunks) : bfm_sum(part + (int64_t)nchunks * nw + (i - nw), cout, nchunks);
+  if (is_w) dw[i] = add ? dw[i] + s : s;
   else if (db) db[i - nw] = add ? db[i - nw] + s : s;
+}
+// .. of partial tiles laid out tap by tap: a block takes all 27 taps of 32 pairs, half a wavefront one tap (128 contiguous bytes of a chunk's
+// row), and turns them through LDS into 3456 contiguous bytes of dw (256->256 on 8 x 16^3 21.5 -> 13.2 us, 192->192 on 2 x 8x38x11 15.7 -> 11.4; 64 pairs a
+// block 17.5 and 13.7).
+constexpr int BFM_PAIRS = 32;
+__global__ void __launch_bounds__(28 * BFM_PAIRS) bfm_reduce_taps_kernel(const float* __restrict__ part, float* __restrict__ dw, float* __restrict__ db,
+                                                                        int64_t nw, int cout, int nchunks, int add, int tap, int64_t nblk_w) {
+  __shared__ float red[27 * BFM_PAIRS];
+  if (blockIdx.x >= nblk_w) {
+    const int64_t i = (blockIdx.x - nblk_w) * (28 * BFM_PAIRS) + threadIdx.x;
+    if (i >= cout || !db) return;
+    const float s = bfm_sum(part + (int64_t)nchunks * nw + i, cout, nchunks);
+    db[i] = add ? db[i] + s : s;
+    return;
+  }
+  const int p = threadIdx.x % BFM_PAIRS, t = threadIdx.x / BFM_PAIRS;
+  const int64_t pair0 = (int64_t)blockIdx.x * BFM_PAIRS;
+  if (t < 27 && pair0 + p < tap) red[27 * p + t] = bfm_sum(part + t * (int64_t)tap + pair0 + p, nw, nchunks);
+  __syncthreads();
+  const int64_t o = pair0 * 27 + threadIdx.x;
+  if (t < 27 && o < nw) dw[o] = add ? dw[o] + red[threadIdx.x] : red[threadIdx.x];
 }
 
 struct BfPlan {
@@ -1315,18 +1364,22 @@ static h3d_status bf_direct(void* handle, const h3d_tensor* x, const h3d_tensor*
   if (st != H3D_OK) return st;
   int64_t nw = (int64_t)a.cout * a.cin * 27;
   const int tap = by_tap ? a.cout * a.cin : 0;
-  if (nw >= 65536 && a.npart <= 16)
+  const auto reduce = [&](auto kern, int P, int threads) {
+    const int64_t nblk_w = bfm_blocks(nw, P, tap);
+    hipLaunchKernelGGL(kern, dim3((unsigned)(nblk_w + cdiv(a.cout, 16))), dim3(threads), 0, stream, (const float*)ws, dw, db, nw, a.cout, a.npart, add, tap, nblk_w);
+  };
+  if (nw >= 65536 && a.npart <= 16 && tap)
+    hipLaunchKernelGGL(bfm_reduce_taps_kernel, dim3((unsigned)(cdiv(tap, BFM_PAIRS) + cdiv(a.cout, 28 * BFM_PAIRS))), dim3(28 * BFM_PAIRS), 0, stream,
+                       (const float*)ws, dw, db, nw, a.cout, a.npart, add, tap, cdiv(tap, BFM_PAIRS));
+  else if (nw >= 65536 && a.npart <= 16)
     hipLaunchKernelGGL(bfm_reduce_wide_kernel, dim3((unsigned)cdiv(nw + a.cout, 256)), dim3(256), 0, stream, (const float*)ws, dw, db,
-                       nw, a.cout, a.npart, add, tap);
+                       nw, a.cout, a.npart, add);
   else if (nw >= 32768 && nw % 4 == 0 && (uintptr_t)ws % 16 == 0 && (uintptr_t)dw % 16 == 0)     // (few weights: more, smaller workgroups)
-    hipLaunchKernelGGL(bfm_reduce4_kernel, dim3((unsigned)(cdiv(nw / 4, 16) + cdiv(a.cout, 16))), dim3(256), 0, stream, (const float*)ws, dw,
-                       db, nw, a.cout, a.npart, add, tap);
+    tap ? reduce(bfm_reduce4_kernel<true>, 64, 256) : reduce(bfm_reduce4_kernel<false>, 64, 256);
   else if (a.npart >= 128)
-    hipLaunchKernelGGL(bfm_reduce_kernel<64>, dim3((unsigned)cdiv(nw + a.cout, 16)), dim3(1024), 0, stream, (const float*)ws, dw, db, nw,
-                       a.cout, a.npart, add, tap);
+    tap ? reduce(bfm_reduce_kernel<64, true>, 16, 1024) : reduce(bfm_reduce_kernel<64, false>, 16, 1024);
   else
-    hipLaunchKernelGGL(bfm_reduce_kernel<16>, dim3((unsigned)cdiv(nw + a.cout, 16)), dim3(256), 0, stream, (const float*)ws, dw, db, nw,
-                       a.cout, a.npart, add, tap);
+    tap ? reduce(bfm_reduce_kernel<16, true>, 16, 256) : reduce(bfm_reduce_kernel<16, false>, 16, 256);
   return launch_status(handle, "conv3d_bwd_filter_mfma");
 }
 
