@@ -60,7 +60,7 @@ struct MfmaArgs {
   // split of the input-channel chunks over blockIdx.z (small volumes with many channels would otherwise
   // occupy a handful of CUs): each split writes fp32 partial sums, a second kernel adds them in order
   int csplit, chunks_per_split;
-  int pairs;        // output rows can be stored two voxels at a time (ROW16: the input may be a prepared copy of odd or unaligned rows)
+  int pairs;        // output rows can be stored two voxels at a time (false only with a prepared input)
   float* part;      // [csplit][n][cout][stored planes][h][w], used when csplit > 1
 };
 
@@ -93,7 +93,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, ui
 // vector-memory instructions of a chunk took as long as its products), and the columns outside the volume, always the same units of
 // LDS, are cleared once.  256 -> 256 channels on 8 x 16^3 120 -> 111 us, 64 -> 64 on 32 x 8^3 34 -> 31; same products in the
 // same order.
-template <int NCB, int ND, int TWC, bool MASKED, bool VEC, bool SPLIT, bool FLAT, bool ROW16>
+// ROW = 1: from the tensor itself.  ROW = 2: from a prepared copy whose rows are longer than the result's, or onto a result whose rows cannot be
+// stored two voxels at a time (told apart at run time this cost the first form 3 to 5 %: 64->8 on 4 x 4x198x16 12.9 -> 13.6 us).
+template <int NCB, int ND, int TWC, bool MASKED, bool VEC, bool SPLIT, bool FLAT, int ROW>
 __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* __restrict__ in, const bf16_t* __restrict__ mask,
                                                                  const uint4* __restrict__ wp, const float* __restrict__ bias,
                                                                  bf16_t* __restrict__ out, MfmaArgs a) {
@@ -106,6 +108,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   constexpr int PAIRS = (TW + 4) / 2;
   constexpr int CIG_UNITS = TD2 * TH2 * P;
   constexpr int BUF_UNITS = 2 * CIG_UNITS;
+  constexpr bool ROW16 = ROW != 0;
   static_assert(!ROW16 || (TWC == 16 && VEC && !MASKED), "16-byte staging: one tile across, no mask");
   constexpr int ITEMS_ROW = ROW16 ? 2 : PAIRS;
   constexpr int NITEMS = 2 * TD2 * TH2 * ITEMS_ROW;
@@ -116,7 +119,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int cbw = wave / ND, wd = wave % ND;
   const int co_blk = blockIdx.y * NCB + cbw;
-  const int W = a.in.w, H = a.in.h, WO = a.out.w;     // a prepared input has padded rows (ROW16 only)
+  const int W = a.in.w, H = a.in.h, WO = ROW == 2 ? a.out.w : W;
 
   // ---- tile-invariant part of the staging plan: which units this thread fills
   int lds_unit[ROUNDS], item_meta[ROUNDS];   // meta: pair | hy << 8 | dz << 16 | cig << 24 (cig 2: no item)
@@ -341,7 +344,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
       return;
     }
     const __amdgpu_buffer_rsrc_t rs_out = make_rsrc(out + n * a.out.nstride, (uint32_t)a.out.nstride * 2);
-    if (VEC && (!ROW16 || a.pairs)) {
+    if (VEC && (ROW != 2 || a.pairs)) {
       // Two adjacent voxels live in adjacent lanes.  Lane pairs swap one value (DPP quad_perm [1,0,3,2])
       // so that the even lane holds both voxels of channel row r and the odd lane both voxels of row
       // r+1: every lane then stores ONE dword (two bf16) instead of two shorts.
@@ -978,7 +981,7 @@ static size_t mfma_base_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bo
   return b;
 }
 
-template <int NCB, int ND, int TWC, bool MASKED, bool VEC, bool SPLIT, bool FLAT, bool ROW16>
+template <int NCB, int ND, int TWC, bool MASKED, bool VEC, bool SPLIT, bool FLAT, int ROW>
 static h3d_status launch_variant_as(void* handle, const bf16_t* in, const bf16_t* mask, const uint4* wp, const float* bias,
                                  bf16_t* out, MfmaArgs a, int n, hipStream_t stream) {
   constexpr int RPB = 32 / TWC, TH = 4 * RPB;
@@ -995,7 +998,7 @@ static h3d_status launch_variant_as(void* handle, const bf16_t* in, const bf16_t
   // one resident workgroup per CU (LDS-limited), spread over the output-channel groups
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   int64_t gx = std::min<int64_t>(ntiles, std::max<int64_t>(1, num_cu / (gy * a.csplit)));
-  auto kern = conv3d_mfma_kernel<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, ROW16>;
+  auto kern = conv3d_mfma_kernel<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, ROW>;
   static bool attr_set = false;   // per instantiation
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
@@ -1004,7 +1007,7 @@ static h3d_status launch_variant_as(void* handle, const bf16_t* in, const bf16_t
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.csplit), dim3(WG_THREADS), lds_bytes, stream, in, mask, wp,
                      a.csplit > 1 ? nullptr : bias, out, a);
-  note_kernel(handle, "conv3d_mfma_kernel<%d,%d,%d,%d,%d,%d,%d,%d>", NCB, ND, TWC, (int)MASKED, (int)VEC, (int)SPLIT, (int)FLAT, (int)ROW16);
+  note_kernel(handle, "conv3d_mfma_kernel<%d,%d,%d,%d,%d,%d,%d,%d>", NCB, ND, TWC, (int)MASKED, (int)VEC, (int)SPLIT, (int)FLAT, ROW);
   if (a.csplit > 1) return hipGetLastError() == hipSuccess ? H3D_OK : fail(handle, H3D_EHIP, "conv3d_mfma: launch failed");
   return launch_status(handle, "conv3d_mfma");
 }
@@ -1014,9 +1017,10 @@ static h3d_status launch_variant(void* handle, const bf16_t* in, const bf16_t* m
                                  bf16_t* out, const MfmaArgs& a, int n, hipStream_t stream) {
   if constexpr (TWC == 16 && VEC && !MASKED) {
     if (a.in.w % 8 == 0 && (uintptr_t)in % 16 == 0 && a.in.cstride % 8 == 0 && a.in.nstride % 8 == 0)
-      return launch_variant_as<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, true>(handle, in, mask, wp, bias, out, a, n, stream);
+      return a.pairs && a.in.w == a.out.w ? launch_variant_as<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, 1>(handle, in, mask, wp, bias, out, a, n, stream)
+                                          : launch_variant_as<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, 2>(handle, in, mask, wp, bias, out, a, n, stream);
   }
-  return launch_variant_as<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, false>(handle, in, mask, wp, bias, out, a, n, stream);
+  return launch_variant_as<NCB, ND, TWC, MASKED, VEC, SPLIT, FLAT, 0>(handle, in, mask, wp, bias, out, a, n, stream);
 }
 
 static bool wide_shape(const MfmaArgs& a) {
