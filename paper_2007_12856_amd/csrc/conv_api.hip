@@ -17,7 +17,7 @@ h3d_status bwd_filter_direct(void* handle, const h3d_tensor* x, const h3d_tensor
                              float* db, float mask_slope, void* ws, size_t ws_bytes, hipStream_t stream);
 // conv_f32_mfma.hip
 bool f32_mfma_fwd_supported(const h3d_tensor* in, const h3d_tensor* out);
-size_t f32_mfma_fwd_ws_bytes(int cin_k, const h3d_tensor* out);
+size_t f32_mfma_fwd_ws_bytes(void* handle, int cin_k, const h3d_tensor* out);
 h3d_status conv3d_f32_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, const float* bias,
                            h3d_tensor* out, bool transpose, float out_slope, float mask_slope, void* ws, size_t ws_bytes,
                            hipStream_t stream);
@@ -40,7 +40,7 @@ h3d_status conv3d_fwd_c4(void* handle, const h3d_tensor* in, const void* w, cons
                          void* ws, size_t ws_bytes, hipStream_t stream);
 // conv_mfma.hip
 bool mfma_fwd_supported(const h3d_tensor* in, const h3d_tensor* out);
-size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bool backward_data);
+size_t mfma_fwd_ws_bytes(void* handle, const h3d_tensor* in, const h3d_tensor* out, bool backward_data);
 h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, const float* bias,
                        h3d_tensor* out, bool transpose, float out_slope, float mask_slope, void* ws, size_t ws_bytes,
                        hipStream_t stream);
@@ -76,8 +76,8 @@ extern "C" size_t h3d_conv3d_workspace_bytes(void* handle, int op, const h3d_ten
       [[fallthrough]];
     case H3D_OP_BWD_DATA:  // x: dz (input of the correlation), z: dx
       b = std::max(b, direct_fwd_ws_bytes(x->c, z->c));
-      if (mfma_fwd_supported(x, z)) b = std::max(b, mfma_fwd_ws_bytes(x, z, op == H3D_OP_BWD_DATA));
-      if (f32_mfma_fwd_supported(x, z)) b = std::max(b, f32_mfma_fwd_ws_bytes(x->c, z));
+      if (mfma_fwd_supported(x, z)) b = std::max(b, mfma_fwd_ws_bytes(handle, x, z, op == H3D_OP_BWD_DATA));
+      if (f32_mfma_fwd_supported(x, z)) b = std::max(b, f32_mfma_fwd_ws_bytes(handle, x->c, z));
       break;
     case H3D_OP_BWD_FILTER:  // x: activations, z: dz
       // the size of the one kernel family h3d_conv3d_bwd_filter gives these shapes to (same order of tests as there)

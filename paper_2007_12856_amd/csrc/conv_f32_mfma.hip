@@ -327,17 +327,17 @@ struct F32Plan {
   int cb, tr, hv, ncig, ncog, nsplit, per_split;
   size_t wk_bytes, part_bytes;
 };
-constexpr int F32_CUS = 256;      // (the workspace query names no device)
-static F32Plan f32_plan(int cin_k, const h3d_tensor* out) {
+static F32Plan f32_plan(void* handle, int cin_k, const h3d_tensor* out) {
+  const int num_cu = static_cast<Handle*>(handle)->num_cu;
   F32Plan p;
   p.cb = f32_cb(out->c); p.hv = out->w <= 16 ? 1 : 2;
   p.ncig = (int)cdiv(cin_k, 4); p.ncog = (int)cdiv(out->c, 16 * p.cb);
   const int64_t ds = out->halo_lo + out->d + out->halo_hi, planes = out->n * cdiv(ds, FT_P) * cdiv(out->w, 16 * p.hv) * p.ncog;
   // 8-row tiles unless they would leave most of the chip idle: then 2-row tiles, four times as many workgroups
-  p.tr = planes * cdiv(out->h, 8) < 2 * F32_CUS && out->h > 2 ? 2 : 8;
+  p.tr = planes * cdiv(out->h, 8) < 2 * num_cu && out->h > 2 ? 2 : 8;
   const int64_t wgs = std::max<int64_t>(1, planes * cdiv(out->h, p.tr));
   const bool whole = out->d == out->d_global && !out->halo_lo && !out->halo_hi && is_packed(out) && out->c > 4 && p.ncig > 8;
-  p.nsplit = whole && p.tr == 2 ? (int)std::max<int64_t>(1, std::min<int64_t>({4 * F32_CUS / wgs, (int64_t)p.ncig / 2, (int64_t)8})) : 1;
+  p.nsplit = whole && p.tr == 2 ? (int)std::max<int64_t>(1, std::min<int64_t>({4 * num_cu / wgs, (int64_t)p.ncig / 2, (int64_t)8})) : 1;
   p.per_split = (int)cdiv(p.ncig, p.nsplit);
   p.nsplit = (int)cdiv(p.ncig, p.per_split);
   p.wk_bytes = up256((size_t)p.ncog * p.ncig * 108 * 16 * p.cb * sizeof(float));
@@ -345,8 +345,8 @@ static F32Plan f32_plan(int cin_k, const h3d_tensor* out) {
   return p;
 }
 
-size_t f32_mfma_fwd_ws_bytes(int cin_k, const h3d_tensor* out) {
-  const F32Plan p = f32_plan(cin_k, out);
+size_t f32_mfma_fwd_ws_bytes(void* handle, int cin_k, const h3d_tensor* out) {
+  const F32Plan p = f32_plan(handle, cin_k, out);
   return p.wk_bytes + p.part_bytes;
 }
 
@@ -356,7 +356,7 @@ h3d_status conv3d_f32_mfma(void* handle, const h3d_tensor* in, const h3d_tensor*
   const int cin_k = in->c, cout_k = out->c;
   const int cin = transpose ? cout_k : cin_k, cout = transpose ? cin_k : cout_k;
   const bool thin = cout_k <= 4;
-  F32Plan p = f32_plan(cin_k, out);
+  F32Plan p = f32_plan(handle, cin_k, out);
   if (ws_bytes < p.wk_bytes + p.part_bytes) { p.nsplit = 1; p.per_split = p.ncig; p.part_bytes = 0; }      // no room for the sums: one chain
   const int cb = p.cb, nc = 16 * cb, hv = p.hv, tr = p.tr, ncog = p.ncog;
   if (!ws || ws_bytes < p.wk_bytes) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");

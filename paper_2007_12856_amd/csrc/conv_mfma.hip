@@ -852,7 +852,7 @@ __global__ void __launch_bounds__(256) conv_wide_split_reduce_kernel(const float
 
 // How many ways the input-channel chunks of a narrow volume are split: 1 unless the tiles alone would leave most CUs idle.
 // (room: of a workspace for the sums of every split; without it those of at least 64 workgroups are not split)
-static int mfma_splits(const h3d_tensor* in, const h3d_tensor* out, bool room) {
+static int mfma_splits(const h3d_tensor* in, const h3d_tensor* out, int num_cu, bool room) {
   const int nchunks = (int)cdiv(in->c, CI_CHUNK), ncoblk = (int)cdiv(out->c, 32);
   const bool wide = out->w > 16, two_cb = out->c > 32;
   const int twc = wide ? 32 : 16, ncb = two_cb ? 2 : 1, nd = 8 / ncb, th = 4 * (32 / twc);
@@ -863,7 +863,7 @@ static int mfma_splits(const h3d_tensor* in, const h3d_tensor* out, bool room) {
   const int64_t part = (int64_t)out->n * cdiv(ds, nd) * cdiv(out->h, 8) * cdiv(out->w, 16) * ncoblk * nd * 4096 * 4;
   // from 64 workgroups on whole samples only: a shard's sums are those of the views that tile it
   if (wgs >= 64 && (!room || out->d != out->d_global || out->halo_lo || out->halo_hi)) return 1;
-  int s = (int)std::min<int64_t>(nchunks, wgs < 64 ? cdiv(256, wgs) : std::max<int64_t>(1, 256 / wgs));
+  int s = (int)std::min<int64_t>(nchunks, wgs < 64 ? cdiv(256, wgs) : std::max<int64_t>(1, num_cu / wgs));
   while (s > 1 && s * part > ((int64_t)(wgs < 64 ? 24 : 40) << 20)) --s;
   // from 64 workgroups on a split has to save more of a tile's 6 us a chunk than its sums and the launch that adds them take: 256->256 on
   // 8 x 8^3 101 -> 52 us, on 2 x 16^3 100 -> 58, 128->128 on 8 x 8x16x16 53 -> 45
@@ -954,29 +954,29 @@ static bool wide_dims(const h3d_tensor* in, const h3d_tensor* out) {
 static int64_t wide_units(const h3d_tensor* out) {
   return (int64_t)out->n * cdiv(out->halo_lo + out->d + out->halo_hi, 4) * cdiv(out->h, 8) * cdiv(out->w, 32) * cdiv(out->c, 32);
 }
-static int wide_splits(const h3d_tensor* in, const h3d_tensor* out) {
+static int wide_splits(const h3d_tensor* in, const h3d_tensor* out, int num_cu) {
   const int nchunks = (int)cdiv(in->c, CI_CHUNK);
   if (nchunks < 2 || !wide_dims(in, out) || !is_packed(out) || out->d != out->d_global || out->halo_lo || out->halo_hi) return 1;
   const int64_t units = wide_units(out);
   int best = 1;
   double cost = 4.4 * nchunks;
-  for (int s = 2; s <= nchunks && s * units <= 256; ++s) {
+  for (int s = 2; s <= nchunks && s * units <= num_cu; ++s) {
     const double c = 4.4 * cdiv(nchunks, s) + 4.0 + 0.045 * (double)(s * units);
     if (cdiv(nchunks, cdiv(nchunks, s)) == s && c < cost) { cost = c; best = s; }
   }
   return best;
 }
-static size_t wide_split_bytes(const h3d_tensor* in, const h3d_tensor* out) {
-  const int s = wide_splits(in, out);
+static size_t wide_split_bytes(const h3d_tensor* in, const h3d_tensor* out, int num_cu) {
+  const int s = wide_splits(in, out, num_cu);
   return s > 1 ? (size_t)(s * wide_units(out)) * 131072 : 0;
 }
 
 // what a call needs without copies; less room, down to what is left without the splits that can be left out, is taken too (the sums are then one
 // chain): a workspace that is large enough for a larger volume, which is not split, does for this one
-static size_t mfma_base_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bool room) {
-  size_t b = mfma_wp_bytes(in, out) + (room ? wide_split_bytes(in, out) : 0);
+static size_t mfma_base_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, int num_cu, bool room) {
+  size_t b = mfma_wp_bytes(in, out) + (room ? wide_split_bytes(in, out, num_cu) : 0);
   if (thin_two_pass_shape(in, out, nullptr, nullptr)) b = std::max(b, thin_two_pass_ws_bytes(out));
-  const int s = mfma_splits(in, out, room);
+  const int s = mfma_splits(in, out, num_cu, room);
   if (s > 1) b += (size_t)s * split_part_floats(out) * sizeof(float);
   return b;
 }
@@ -1089,10 +1089,11 @@ static size_t prep_narrow_bytes(const h3d_tensor* in, const h3d_tensor* out) {
 }
 
 // backward-data may come with a mask, which is not known here; forward needs the copy for rows of odd length only
-size_t mfma_fwd_ws_bytes(const h3d_tensor* in, const h3d_tensor* out, bool backward_data) {
-  size_t b = mfma_base_ws_bytes(in, out, true);
+size_t mfma_fwd_ws_bytes(void* handle, const h3d_tensor* in, const h3d_tensor* out, bool backward_data) {
+  const int num_cu = static_cast<Handle*>(handle)->num_cu;
+  size_t b = mfma_base_ws_bytes(in, out, num_cu, true);
   if (backward_data || in->w % 2)
-    b = std::max(mfma_wp_bytes(in, out) + wide_split_bytes(in, out) + prep_fwd_bytes(in, out), b + prep_narrow_bytes(in, out));
+    b = std::max(mfma_wp_bytes(in, out) + wide_split_bytes(in, out, num_cu) + prep_fwd_bytes(in, out), b + prep_narrow_bytes(in, out));
   return b;
 }
 
@@ -1173,8 +1174,9 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   wp_dims(a.cin_k, a.cout_k, &a.nchunks, &a.ncoblk);
   a.out_slope = out_slope; a.mask_slope = mask_slope;
   if ((int64_t)out->n * a.out.ds * out->h * out->w == 0) return H3D_OK;
-  const bool room = ws_bytes >= mfma_base_ws_bytes(in, out, true);
-  if (!ws || ws_bytes < mfma_base_ws_bytes(in, out, false)) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
+  const int num_cu = static_cast<Handle*>(handle)->num_cu;
+  const bool room = ws_bytes >= mfma_base_ws_bytes(in, out, num_cu, true);
+  if (!ws || ws_bytes < mfma_base_ws_bytes(in, out, num_cu, false)) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
   if ((uintptr_t)ws % 16) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace must be 16-byte aligned");
   // a handful of output channels from at most 16 input channels: the tap-row-folding kernel
   if (!mask && conv3d_thin_supported(in, out)) return conv3d_thin(handle, in, w, bias, out, transpose, out_slope, ws, stream);
@@ -1202,13 +1204,13 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   const bf16_t* mp = mask ? (const bf16_t*)mask->data : nullptr;
   bf16_t* op = (bf16_t*)out->data;
   const uint4* wq = (const uint4*)ws;
-  a.csplit = mfma_splits(in, out, room);
+  a.csplit = mfma_splits(in, out, num_cu, room);
   a.chunks_per_split = (int)cdiv(a.nchunks, a.csplit);
   a.part = a.csplit > 1 ? reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out)) : nullptr;
   h3d_status st;
-  const size_t split_bytes = room ? wide_split_bytes(in, out) : 0;
+  const size_t split_bytes = room ? wide_split_bytes(in, out, num_cu) : 0;
   if (split_bytes) {      // (wide volumes: mfma_splits is 1)
-    a.csplit = wide_splits(in, out);
+    a.csplit = wide_splits(in, out, num_cu);
     a.chunks_per_split = (int)cdiv(a.nchunks, a.csplit);
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out));
   }
@@ -1217,9 +1219,9 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   if (const size_t copies = prep_fwd_bytes(in, out); copies && (uintptr_t)out->data % 4 == 0 && ws_bytes >= mfma_wp_bytes(in, out) + split_bytes + copies)
     return prep_conv(handle, in, mask, bias, out, a, mask_slope, ws, split_bytes, stream);
   a.pairs = vec;
-  if (const size_t copy = mask || in->w % 2 ? prep_narrow_bytes(in, out) : 0; copy && ws_bytes >= mfma_base_ws_bytes(in, out, room) + copy) {
+  if (const size_t copy = mask || in->w % 2 ? prep_narrow_bytes(in, out) : 0; copy && ws_bytes >= mfma_base_ws_bytes(in, out, num_cu, room) + copy) {
     // the planes that the output's window reaches inside the volume (all of them are stored), behind whatever else the workspace holds
-    bf16_t* dst = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + mfma_base_ws_bytes(in, out, room));
+    bf16_t* dst = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + mfma_base_ws_bytes(in, out, num_cu, room));
     const int lo = (int)std::max<int64_t>(-out->halo_lo - 1, -a.in.doff), hi = (int)std::min<int64_t>(out->d + out->halo_hi + 1, a.in.dglob - a.in.doff);
     H3D_TRY(prep_launch(handle, prep_job(in, mask, mask_slope, 0, in->n, lo, hi - lo, dst), nullptr, stream));
     a.in.w = prep_w(in->w); a.in.ds = hi - lo; a.in.hlo = -lo; a.in.hhi = hi - in->d;
