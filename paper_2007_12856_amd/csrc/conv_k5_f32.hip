@@ -15,18 +15,13 @@
 // 38x58x32 3008 and 1272, 24 -> 64 on 2 x 16x32x10 2228 and 298.
 #include <algorithm>
 
+#include "rowload.h"
 #include "taps.h"
 
 namespace h3d {
 namespace {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int OOB = (int)0x80000000;      // byte offset beyond every buffer: reads as zero
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buf_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t p = reinterpret_cast<uint64_t>(base);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)p), hi = __builtin_amdgcn_readfirstlane((uint32_t)(p >> 32));
-  return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(((uint64_t)hi << 32) | lo), 0, (int)__builtin_amdgcn_readfirstlane(bytes), 0x00020000);
-}
 // (the range check looks at voff alone)
 __device__ __forceinline__ float buf_load(__amdgpu_buffer_rsrc_t rs, int voff, uint32_t soff) {
   return __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rs, voff, (int)__builtin_amdgcn_readfirstlane(soff), 0));
@@ -79,8 +74,8 @@ __global__ void __launch_bounds__(256, 2) k5f_conv_kernel(const float* __restric
     const int s = tid + 256 * i, col = s % XC, row = s / XC % XR, q = p0 - 2 + s / XPL;
     const int hh = h0 - 2 + row, ww = w0 - 2 + col;
     const bool ok = s < SP && q >= a.pmin && q < a.pmax && hh >= 0 && hh < H && ww >= 0 && ww < W;
-    xoff[i] = ok ? 4 * (int)((q + a.in.hlo) * a.in.plane + (int64_t)hh * W + ww) : OOB;
-    if (MASKED) moff[i] = ok ? 4 * (int)((q + a.mask.hlo) * a.mask.plane + (int64_t)hh * W + ww) : OOB;
+    xoff[i] = ok ? 4 * (int)((q + a.in.hlo) * a.in.plane + (int64_t)hh * W + ww) : ROW_OOB;
+    if (MASKED) moff[i] = ok ? 4 * (int)((q + a.mask.hlo) * a.mask.plane + (int64_t)hh * W + ww) : ROW_OOB;
   }
   const int p = p0 + wave;
   const bool live = p < a.out.d;
@@ -95,8 +90,8 @@ __global__ void __launch_bounds__(256, 2) k5f_conv_kernel(const float* __restric
 #pragma unroll
       for (int hf = 0; hf < HV; ++hf) acc[cb][r][hf] = f32x4{b, b, b, b};
   }
-  const __amdgpu_buffer_rsrc_t rs_in = buf_rsrc(in + (int64_t)n * a.in.nstride, (uint32_t)(a.in.nstride * 4));
-  const __amdgpu_buffer_rsrc_t rs_mk = buf_rsrc(MASKED ? mask + (int64_t)n * a.mask.nstride : in, (uint32_t)(a.mask.nstride * 4));
+  const __amdgpu_buffer_rsrc_t rs_in = row_rsrc(in + (int64_t)n * a.in.nstride, (uint32_t)(a.in.nstride * 4));
+  const __amdgpu_buffer_rsrc_t rs_mk = row_rsrc(MASKED ? mask + (int64_t)n * a.mask.nstride : in, (uint32_t)(a.mask.nstride * 4));
   const float* xw = lds + (lane >> 4) * CS + wave * XPL + (lane & 15);
 
   const int cig1 = min(a.ncig, (int)(blockIdx.z + 1) * a.per_split);
@@ -117,8 +112,8 @@ __global__ void __launch_bounds__(256, 2) k5f_conv_kernel(const float* __restric
         const bool ok = ci < a.cin;                        // uniform
 #pragma unroll
         for (int i = 0; i < PT; ++i) {
-          v[c][i] = buf_load(rs_in, ok ? xoff[i] : OOB, 4u * ci * (uint32_t)a.in.cstride);
-          if (MASKED) m[c][i] = buf_load(rs_mk, ok ? moff[i] : OOB, 4u * ci * (uint32_t)a.mask.cstride);
+          v[c][i] = buf_load(rs_in, ok ? xoff[i] : ROW_OOB, 4u * ci * (uint32_t)a.in.cstride);
+          if (MASKED) m[c][i] = buf_load(rs_mk, ok ? moff[i] : ROW_OOB, 4u * ci * (uint32_t)a.mask.cstride);
         }
       }
 #pragma unroll
@@ -249,34 +244,34 @@ __global__ void __launch_bounds__(256, 2) k5f_bwf_kernel(const float* __restrict
     const int w0 = (int)(r % a.nwg) * BW; r /= a.nwg;
     const int h0 = (int)(r % a.nhg) * BR; r /= a.nhg;
     const int p = (int)(r % D), n = (int)(r / D), q = p + kd - 2;
-    const __amdgpu_buffer_rsrc_t rs_x = buf_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)(a.x.nstride * 4));
-    const __amdgpu_buffer_rsrc_t rs_g = buf_rsrc(dz + (int64_t)n * a.g.nstride, (uint32_t)(a.g.nstride * 4));
-    const __amdgpu_buffer_rsrc_t rs_z = buf_rsrc(MASKED ? z + (int64_t)n * a.z.nstride : dz, (uint32_t)(a.z.nstride * 4));
+    const __amdgpu_buffer_rsrc_t rs_x = row_rsrc(x + (int64_t)n * a.x.nstride, (uint32_t)(a.x.nstride * 4));
+    const __amdgpu_buffer_rsrc_t rs_g = row_rsrc(dz + (int64_t)n * a.g.nstride, (uint32_t)(a.g.nstride * 4));
+    const __amdgpu_buffer_rsrc_t rs_z = row_rsrc(MASKED ? z + (int64_t)n * a.z.nstride : dz, (uint32_t)(a.z.nstride * 4));
     const bool pok = ok && q >= a.pmin && q < a.pmax;
     const uint32_t xp = (uint32_t)max(q + a.x.hlo, 0) * (uint32_t)a.x.plane;
     auto offset = [&](int row, int col) {
       const int hh = h0 - 2 + row, ww = w0 - 2 + col;
-      return pok && hh >= 0 && hh < H && ww >= 0 && ww < W ? 4 * (hh * W + ww) : OOB;
+      return pok && hh >= 0 && hh < H && ww >= 0 && ww < W ? 4 * (hh * W + ww) : ROW_OOB;
     };
-    const int vo = xmine ? offset(xrow, xcol) : OOB;
+    const int vo = xmine ? offset(xrow, xcol) : ROW_OOB;
 #pragma unroll
-    for (int c = 0; c < 16; ++c) xv[c] = buf_load(rs_x, c < nci ? vo : OOB, 4u * ((cig * 16 + c) * (uint32_t)a.x.cstride + xp));
+    for (int c = 0; c < 16; ++c) xv[c] = buf_load(rs_x, c < nci ? vo : ROW_OOB, 4u * ((cig * 16 + c) * (uint32_t)a.x.cstride + xp));
     if (!NARROW) {
 #pragma unroll
       for (int j = 0; j < 2; ++j) {
         const int c = (tid + 256 * j) >> 5, eo = offset((tid >> 2) & 7, 32 + (tid & 3));
-        xe[j] = buf_load(rs_x, c < nci && eo != OOB ? eo + 4 * c * (int)a.x.cstride : OOB, 4u * (cig * 16 * (uint32_t)a.x.cstride + xp));
+        xe[j] = buf_load(rs_x, c < nci && eo != ROW_OOB ? eo + 4 * c * (int)a.x.cstride : ROW_OOB, 4u * (cig * 16 * (uint32_t)a.x.cstride + xp));
       }
     }
     const int hg = h0 + gs / BW, wg = w0 + gs % BW;
-    const int go = ok && hg < H && wg < W ? 4 * (hg * W + wg) : OOB;
+    const int go = ok && hg < H && wg < W ? 4 * (hg * W + wg) : ROW_OOB;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-      const int off = gc0 + j < nco ? go : OOB;
-      gv[j] = buf_load(rs_g, off == OOB ? OOB : off + 4 * gc0 * (int)a.g.cstride,
+      const int off = gc0 + j < nco ? go : ROW_OOB;
+      gv[j] = buf_load(rs_g, off == ROW_OOB ? ROW_OOB : off + 4 * gc0 * (int)a.g.cstride,
                        4u * ((cog * 16 + j) * (uint32_t)a.g.cstride + (p + a.g.hlo) * (uint32_t)a.g.plane));
       if (MASKED)      // 0 where g is 0
-        zv[j] = buf_load(rs_z, off == OOB ? OOB : off + 4 * gc0 * (int)a.z.cstride,
+        zv[j] = buf_load(rs_z, off == ROW_OOB ? ROW_OOB : off + 4 * gc0 * (int)a.z.cstride,
                          4u * ((cog * 16 + j) * (uint32_t)a.z.cstride + (p + a.z.hlo) * (uint32_t)a.z.plane));
     }
   };
