@@ -996,18 +996,29 @@ static int64_t bfm_blocks(int64_t nw, int P, int tap) {
   return P == 16 ? cdiv(cdiv(tap, P) * 27, 8) * 8 : cdiv(cdiv(tap, P), 8) * 8 * 27;
 }
 
+// every G-th chunk from cg on, in increasing order, eight loads in flight
+template <int G>
+__device__ __forceinline__ float bfm_group_sum(const float* base, int64_t stride, int cg, int nchunks) {
+  float s = 0.f;
+  int c = cg;
+  for (; c + 7 * G < nchunks; c += 8 * G) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = base[(int64_t)(c + u * G) * stride];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) s += v[u];
+  }
+  for (; c < nchunks; c += G) s += base[(int64_t)c * stride];
+  return s;
+}
+
 // the bias gradient: 16 channels a block, behind the nblk_w blocks of weights
 template <int G>
 __device__ __forceinline__ void bfm_reduce_bias(const float* __restrict__ part, float* __restrict__ db, int64_t nw, int cout, int nchunks, int add,
                                                 int64_t nblk_w, float (&red)[G][17]) {
   const int o = threadIdx.x & 15, cg = threadIdx.x >> 4;
   const int64_t i = ((int64_t)blockIdx.x - nblk_w) * 16 + o;
-  float s = 0.f;
-  if (i < cout) {
-    const float* base = part + (int64_t)nchunks * nw + i;
-    for (int c = cg; c < nchunks; c += G) s += base[(int64_t)c * cout];
-  }
-  red[cg][o] = s;
+  red[cg][o] = i < cout ? bfm_group_sum<G>(part + (int64_t)nchunks * nw + i, cout, cg, nchunks) : 0.f;
   __syncthreads();
   if (cg == 0 && i < cout && db) {
     float t = red[0][o];
@@ -1024,20 +1035,7 @@ __global__ void __launch_bounds__(16 * G) bfm_reduce_kernel(const float* __restr
   if (blockIdx.x >= nblk_w) return bfm_reduce_bias<G>(part, db, nw, cout, nchunks, add, nblk_w, red);
   const int o = threadIdx.x & 15, cg = threadIdx.x >> 4;
   const BfmOut q = bfm_out<TAP, 16>(blockIdx.x, o, nw, tap);
-  float s = 0.f;
-  if (q.ok) {
-    const float* base = part + q.i;
-    int c = cg;
-    for (; c + 7 * G < nchunks; c += 8 * G) {      // eight loads in flight, added in increasing chunk order
-      float v[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = base[(int64_t)(c + u * G) * nw];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) s += v[u];
-    }
-    for (; c < nchunks; c += G) s += base[(int64_t)c * nw];
-  }
-  red[cg][o] = s;
+  red[cg][o] = q.ok ? bfm_group_sum<G>(part + q.i, nw, cg, nchunks) : 0.f;
   __syncthreads();
   if (cg == 0 && q.ok) {
     float t = red[0][o];
