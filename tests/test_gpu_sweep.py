@@ -134,7 +134,9 @@ def test_deconv_ragged_rows_bf16(case):
     dwo, dbo = orc.deconv2_bwd_filter(xo, dyo)
     dw, db = torch.empty((cin, cout, 2, 2, 2), device="cuda"), torch.empty((cout,), device="cuda")
     h3d.deconv2_bwd_filter(xg, moved(dyg), dw, db)
-    assert not h3d.h3d_last_kernel().startswith("deconv_bf_mfma_kernel")      # (whole aligned rows only)
+    # pieces of as many voxels as divide the width, and the plane into whole units of 8 where they are the longest
+    piece = 4 if W % 4 == 0 and H * W % 8 == 0 else 2 if W % 2 == 0 else 1
+    assert h3d.h3d_last_kernel() == "deconv_bf_flat_kernel<bf16,%d,%d>" % (128 if cin > 64 else 64 if cin > 32 else 32, piece)
     close(from_dev(dw), dwo, 2e-4)
     close(from_dev(db), dbo, 2e-4)
 
