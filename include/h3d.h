@@ -198,14 +198,14 @@ h3d_status h3d_conv3d_s2_bwd_filter(void* handle, const h3d_tensor* x, const h3d
  * up to eight times the result); 256-byte aligned; H3D_EWORKSPACE if too small.  fp32 takes less as well: the sums are
  * one chain without room for parts, and the vector ALU's kernels, for whose filter or partial sums there has to be room, take
  * over where the matrix cores' own do not fit.
- * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation.  fp32 tensors
- * run on the matrix cores unless a sample exceeds 32-bit byte offsets (forward and backward-data of few tiles sum their input
- * channels in parts, shards too: shards of different sizes agree to a rounding), bf16 tensors do too, where g is rounded to bf16 once, as in the 3x3x3 calls (not by
- * backward-filter where w is no multiple of 8: the two branches of a leaky g are summed apart there, unrounded).  bf16
- * calls that run on the vector ALU all the same: channels of 2^25 elements and more (rows counted in multiples of 8 where a
- * pass copies them), forward and backward-data of tensors with fewer than 8 stored elements a sample; backward-filter of
- * planes of fewer than 8 elements, and, where w is a multiple of 8, of an x at an address that is no multiple of 16, or of a
- * dz or z at one if the activation is leaky. */
+ * More than 65535 interior planes or n * ceil(channels/16) > 65535: H3D_EUNSUPPORTED.  fp32 accumulation, on the matrix
+ * cores.  fp32 tensors: forward and backward-data of few tiles sum their input channels in parts, on shards too (shards of
+ * different sizes agree to a rounding); samples beyond 32-bit byte offsets run on the vector ALU.  bf16 tensors: g is rounded
+ * to bf16 once, as in the 3x3x3 calls (not by backward-filter where w is no multiple of 8: the two branches of a leaky g are
+ * summed apart there, unrounded).  bf16 calls that run on the vector ALU all the same: channels of 2^25 elements and more
+ * (rows counted in multiples of 8 where a pass copies them), forward and backward-data of tensors with fewer than 8 stored
+ * elements a sample; backward-filter of planes of fewer than 8 elements, and, where w is a multiple of 8, of an x at an
+ * address that is no multiple of 16, or of a dz or z at one if the activation is leaky. */
 size_t h3d_conv3d_k5_workspace_bytes(void* handle, int op, const h3d_tensor* x, const h3d_tensor* z);
 h3d_status h3d_conv3d_k5_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
                              int act, float alpha, void* ws, size_t ws_bytes, void* stream);
@@ -341,7 +341,8 @@ h3d_status h3d_mse_fwd_bwd(void* handle, const void* pred, const float* target, 
  * per-channel sum and squared sum).  The allreduce itself is the caller's.  All per-channel arrays are fp32
  * device memory of x->c entries; sums run over the INTERIOR planes of the slab only, in a fixed order (the
  * same inputs give the same bits); halo planes are neither read nor written.  Packed tensors only.
- * Workspace: h3d_bn_workspace_bytes(x) bytes for every call below that takes one. */
+ * Workspace: h3d_bn_workspace_bytes(x) bytes for every call below that takes one; what a larger tensor of the same samples
+ * and channels asks for does as well (the sums are then taken in longer runs). */
 size_t h3d_bn_workspace_bytes(void* handle, const h3d_tensor* x);
 /* sum[c] = sum of x, sqsum[c] = sum of x^2 over n, d, h, w of this shard. */
 h3d_status h3d_bn_stats(void* handle, const h3d_tensor* x, float* sum, float* sqsum, void* ws, size_t ws_bytes, void* stream);

@@ -14,7 +14,7 @@ LIB = os.path.join(HERE, "libh3d.so")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-I", INCLUDE, "-I", CSRC,
-         # packed-fp32 VALU forms are kept out of the generated code on the test machines
+         # packed-fp32 VALU forms are kept out of the generated code
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          # the LDS-copy helper names m0 in its clobber list (common.h), which clang flags as a reserved register
          "-Wno-inline-asm",
