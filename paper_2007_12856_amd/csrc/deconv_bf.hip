@@ -309,6 +309,8 @@ DbfPlan dbf_plan(const h3d_tensor* x, const h3d_tensor* dy) {
   int64_t want = std::max<int64_t>(1, (p.ci_wg == 128 ? 512 : 768) / ((int64_t)p.gco * p.gci));
   want = std::min<int64_t>(want, std::max<int64_t>(1, ((int64_t)64 << 20) / per_chunk_bytes));
   p.tiles_per_chunk = (int)std::max<int64_t>(1, cdiv(p.ntiles, want));
+  // the kernel takes two tiles a turn: an odd number from three on costs as much as the next even one
+  if (p.tiles_per_chunk > 2) p.tiles_per_chunk += p.tiles_per_chunk & 1;
   p.nchunks = (int)std::max<int64_t>(1, cdiv(p.ntiles, p.tiles_per_chunk));
   return p;
 }
