@@ -308,10 +308,14 @@ DbfPlan dbf_plan(const h3d_tensor* x, const h3d_tensor* dy) {
   const int64_t per_chunk_bytes = std::max<int64_t>(1, ((int64_t)x->c * dy->c + dy->c) * 8 * 4);
   int64_t want = std::max<int64_t>(1, (p.ci_wg == 128 ? 512 : 768) / ((int64_t)p.gco * p.gci));
   want = std::min<int64_t>(want, std::max<int64_t>(1, ((int64_t)64 << 20) / per_chunk_bytes));
-  // .. and no chunks of less than four tiles: their sums cost more than the products (us with the second stage, from one tile on and from four: 96 ->
-  // 64 channels from 64x16x16 24.2 and 18.8, 128 -> 128 from 2 x 16^3 26.6 and 21.9, 128 -> 64 from 8x16x16 13.9 and 11.6, 33 -> 20 from 2x5x7 9.6
-  // and 9.8; the calls behind gain as much again, their operands are still cached)
-  want = std::min<int64_t>(want, std::max<int64_t>(1, p.ntiles / 4));
+  // bf16: .. and no chunks of less than four tiles, six where that still gives every CU a workgroup: their sums cost more than the products, and push
+  // the operands of the calls behind out of the cache.  us of all three passes, from one tile on, four and six: 96 -> 64 channels from 64x16x16 52.7, 47.0
+  // and 47.9, 128 -> 64 from 8x16x16 42.8, 40.5 and 44.3, 64 -> 24 from 32x112x32 59.1, 59.0 and 54.6, 53 -> 128 from 2 x 16x18x32, three sets of
+  // tensors in turn, 91.7, 94.0 and 86.3.  (fp32 tiles are half as long and four times the work: 32 -> 32 from 8x16x16 48.8, 49.7 and 53.6)
+  if (x->dtype == H3D_BF16) {
+    const int64_t least = p.ntiles / 6 * (int64_t)(p.gco * p.gci) >= 256 ? 6 : 4;
+    want = std::min<int64_t>(want, std::max<int64_t>(1, p.ntiles / least));
+  }
   p.tiles_per_chunk = (int)std::max<int64_t>(1, cdiv(p.ntiles, want));
   // the kernel takes two tiles a turn: an odd number from three on costs as much as the next even one
   if (p.tiles_per_chunk > 2) p.tiles_per_chunk += p.tiles_per_chunk & 1;
