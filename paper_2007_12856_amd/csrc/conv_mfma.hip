@@ -434,14 +434,16 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
 // weight fragments and 10 row fragments for 24 * CB products: one weight fragment feeds 8 products and one row
 // fragment up to 3 * CB, against 4 and 2-3 in the kernel above, so the weight stream from L2 and the LDS reads per
 // product are both halved, and a chunk of 16 input channels is 216 * CB products per wavefront between two barriers.
-// With one wavefront per SIMD nothing hides a stall, so everything is requested ahead: weight fragments one step
-// ahead (two register sets; they do not depend on the tile, so the stream runs on across chunk and tile borders),
-// row fragments one step ahead (a register is refilled as soon as its last product has been issued), and the input
-// of the next stage in two groups of 8 channels (40 registers) that are requested in thirds at steps 0-2 and 4-6 and
-// written to the other LDS buffer at step 4 and after step 8.  Vector-memory operations return in issue order and
-// share one counter, so a wait for the weight fragments of step s + 1 also waits for the input requests issued
-// before them, i.e. up to step s - 1: the input stream has about two steps (3000 cycles) of latency to hide in, not
-// half a chunk; a third weight set would add a step but does not fit the 512 registers.
+// Nothing else hides a wavefront's stall, so everything is requested ahead: weight fragments two steps ahead (three
+// register sets; they do not depend on the tile, so the stream runs on across chunk and tile borders, and nine steps a
+// chunk let the sets take turns without a copy), row fragments RING products' worth ahead (a register is refilled as soon
+// as its last product has been issued), and the input of the next stage in two groups of 8 channels that are requested in
+// thirds at steps 0-2 and 4-6 and written to the other LDS buffer at step 4 and after step 8.  Vector-memory operations
+// return in issue order and share one counter, so a wait for the weight fragments of step s + 2 also waits for the input
+// requests issued before them, i.e. up to step s - 1: with one step between request and use (ten row fragments in flight,
+// which left no registers for a third set) the products waited for HBM.  Five row fragments are enough beside three sets:
+// 64 -> 64 on 32x128x128 98.9 -> 94.8 us, 32 -> 64 on 66x256x256 474 -> 457, 128 -> 64 on 64x256x256 1409 -> 1380, its
+// backward-data 1498 -> 1465, 64 -> 8 on 8 x 21x118x160 373 -> 357; layers of one or two chunks a tile as before; four fragments 1 % slower.
 // Measured by switching parts off (128 -> 64 channels on 64 x 256 x 256, one box): with the output stores redirected
 // into a 64 KB window that stays in the L2 the kernel takes 1.19 instead of 1.44 ms although it issues the same
 // instructions - 5 % fewer cycles and a shader clock of 2.14 instead of 1.85 GHz; cache-policy bits on the stores and a
@@ -471,6 +473,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   constexpr int NITEMS = TD2 * TH2 * PAIRS;   // (plane, row, pair of columns) items of one channel group
   constexpr int ROUNDS = (NITEMS + NT - 1) / NT;
   constexpr int NFRAG = VB + 2;
+  constexpr int RING = WCB == 2 ? 5 : NFRAG;   // row fragments in flight: as many as fit beside three sets of weights
   extern __shared__ uint4 lds[];
 
   const int tid = threadIdx.x, lane = tid & 63, wd = (tid >> 6) & 3;      // plane of the tile
@@ -607,45 +610,46 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
     }
   };
 
-  uint4 afr[2][3][CB];        // weight fragments of the current and of the next step
+  uint4 afr[3][3][CB];        // weight fragments of the current and of the next two steps (nine steps a chunk: the sets take turns across chunks)
   const int G = gridDim.x;
   int tile = (G % 8 == 0) ? (int)(blockIdx.x % 8) * (G / 8) + (int)(blockIdx.x / 8) : (int)blockIdx.x;
   if (tile >= a.ntiles) return;
   const int c_begin = SPLIT ? blockIdx.z * a.chunks_per_split : 0, c_end = SPLIT ? min(a.nchunks, c_begin + a.chunks_per_split) : a.nchunks;
 
   // One chunk: 9 steps of 24 * CB products.  c_next: the chunk whose weight stream follows this one's.  The step order
-  // is: request the next step's weight fragments, then this step's share of the next stage's input, then multiply; a
-  // row fragment register is refilled for the next step as soon as its last product has been issued.
+  // is: request the weight fragments of the step after next, then this step's share of the next stage's input, then
+  // multiply; a row fragment register is refilled as soon as its last product has been issued.
   auto compute_chunk = [&](int c, int c_next, int buf, bool more, int next_tile, bool last_chunk) {
     const uint4* base = lds + buf * BUF_UNITS + lane_unit;
-    uint4 bfr[NFRAG];
+    uint4 bfr[RING];
+    auto row = [&](int i) { return base[(i / NFRAG / 3 * TH2 + i % NFRAG) * P + i / NFRAG % 3]; };      // row fragment i of the chunk's 9 * NFRAG
 #pragma unroll
-    for (int s = 0; s < NFRAG; ++s) bfr[s] = base[s * P];
+    for (int i = 0; i < RING; ++i) bfr[i] = row(i);
     const int cn = last_chunk ? c_begin : c + 1;
 #pragma unroll
     for (int step = 0; step < 9; ++step) {
-      if (step + 1 < 9) load_a(c, step + 1, afr[(step + 1) & 1]);
-      else load_a(c_next, 0, afr[(step + 1) & 1]);
+      if (step + 2 < 9) load_a(c, step + 2, afr[(step + 2) % 3]);
+      else load_a(c_next, step + 2 - 9, afr[(step + 2) % 3]);
       if (step == 0 && last_chunk && more) plan_tile(next_tile);
       if (step < 3) load_part(cn, 0, step, more);
       if (step == 4 && more) store_half(buf ^ 1, 0);
       if (step >= 4 && step < 7) load_part(cn, 1, step - 4, more);
-      const int kd1 = (step + 1) / 3, kw1 = (step + 1) % 3;
 #pragma unroll
       for (int s = 0; s < NFRAG; ++s) {
-        const bf16x8 B = __builtin_bit_cast(bf16x8, bfr[s]);
+        const int i = step * NFRAG + s;
+        const bf16x8 B = __builtin_bit_cast(bf16x8, bfr[i % RING]);
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh) {
           const int b = s - kh;
           if (b >= 0 && b < VB) {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
-              acc[cb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[step & 1][kh][cb]), B, acc[cb][b], 0, 0, 0);
+              acc[cb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[step % 3][kh][cb]), B, acc[cb][b], 0, 0, 0);
           }
         }
-        if (step + 1 < 9) bfr[s] = base[(kd1 * TH2 + s) * P + kw1];
+        if (i + RING < 9 * NFRAG) bfr[i % RING] = row(i + RING);
       }
-      // one wavefront per SIMD: the requests, address arithmetic and LDS traffic of the step must be issued in the
+      // the requests, address arithmetic and LDS traffic of the step must be issued in the
       // shadow of its products (a product occupies the matrix pipe for 32 cycles, the wavefront can issue about seven
       // other instructions meanwhile), not in a block in front of them
 #pragma unroll
@@ -656,11 +660,6 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
       __builtin_amdgcn_sched_barrier(0);
     }
     if (more) store_half(buf ^ 1, 1);
-    // nine steps: the fragments requested at step 8 sit in set 1, the next chunk starts with set 0
-#pragma unroll
-    for (int kh = 0; kh < 3; ++kh)
-#pragma unroll
-      for (int cb = 0; cb < CB; ++cb) afr[0][kh][cb] = afr[1][kh][cb];
   };
 
   // Epilogue of a tile (CB * 128 values per lane): everything that does not depend on the value is taken out of the
@@ -760,6 +759,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   load_half(c_begin, 1, true);
   store_half(0, 1);
   load_a(c_begin, 0, afr[0]);
+  load_a(c_begin, 1, afr[1]);
   __syncthreads();
   int buf = 0;
   while (true) {
