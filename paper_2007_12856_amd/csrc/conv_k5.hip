@@ -21,6 +21,7 @@ namespace h3d {
 bool k5_mfma_supported(const h3d_tensor* x, const h3d_tensor* z);
 size_t k5_mfma_wp_bytes(int rows, int contraction);
 size_t k5_mfma_bf_bytes(const h3d_tensor* x, int cout, int parts);
+TapsPackJob k5_mfma_pack(const void* w, void* wp, int cin, int cout, bool transposed);
 h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const void* w, int cin, int cout, bool transposed, const float* bias,
                         const h3d_tensor* out, float slope, void* wp, hipStream_t s);
 h3d_status k5_mfma_bwd_filter(void* handle, const h3d_tensor* x, const Geo& gx, const void* x_data, const Geo& g, const void* g_data, int64_t neg,
@@ -318,10 +319,10 @@ void k5_launch_bwf(const h3d_tensor* x, const h3d_tensor* dz, const h3d_tensor* 
 // g = dz * act'(z) (z null: dz) with padded rows on planes [lo, hi) of the shard, every one of them stored by both; with `second`, what
 // lies where z is positive and, there, what lies where it is not, both without the slope
 Geo k5_masked(void* handle, const h3d_tensor* dz, const h3d_tensor* z, float slope, int lo, int hi, void* copy, void* second, h3d_status* st,
-              hipStream_t s) {
+              hipStream_t s, const TapsPackJob* pack = nullptr) {
   const PrepJob j = prep_job(dz, z, slope, 0, dz->n, lo, hi - lo, copy, second ? 1 : 0);
   const PrepJob j2 = prep_job(dz, z, slope, 0, dz->n, lo, hi - lo, second, 2);
-  *st = prep_launch(handle, j, second ? &j2 : nullptr, s);
+  *st = prep_launch(handle, j, second ? &j2 : nullptr, s, pack);
   Geo g = make_geo(dz);
   g.w = j.w8; g.ds = hi - lo; g.hlo = -lo; g.hhi = hi - dz->d;
   g.plane = (int64_t)g.h * g.w; g.cstride = g.plane * g.ds; g.nstride = g.cstride * g.c;
@@ -439,11 +440,12 @@ extern "C" h3d_status h3d_conv3d_k5_bwd_data(void* handle, const h3d_tensor* dz,
       const int lo = (int)(dz->d_offset < 2 ? -dz->d_offset : -2);
       const int64_t above = dz->d_global - dz->d_offset - dz->d;
       h3d_status st;
-      gi = k5_masked(handle, dz, z, a.slope_in, lo, dz->d + (int)(above < 2 ? above : 2), copy, nullptr, &st, s);
+      const TapsPackJob pack = k5_mfma_pack(w, ws, dx->c, dz->c, true);      // beside the copy
+      gi = k5_masked(handle, dz, z, a.slope_in, lo, dz->d + (int)(above < 2 ? above : 2), copy, nullptr, &st, s, &pack);
       H3D_TRY(st);
       gd = copy;
     }
-    H3D_TRY(k5_mfma_conv(handle, gi, gd, w, dx->c, dz->c, true, nullptr, dx, 1.f, ws, s));
+    H3D_TRY(k5_mfma_conv(handle, gi, gd, z ? nullptr : w, dx->c, dz->c, true, nullptr, dx, 1.f, ws, s));
   }
   else if (k5_on_f32(dz, dx, z) && ws_bytes >= k5f_filter_bytes(dz->c, dx)) H3D_TRY(k5f_conv(handle, dz, z, w, dx->c, dz->c, true, nullptr, dx, a.pmin, a.pmax, a.slope_in, 1.f, ws, ws_bytes, s));
   else if (dz->dtype == H3D_F32) { k5_launch_pack<float>(w, wp, dx->c, dz->c, 1, s); k5_launch_conv<float>(dz, z, wp, nullptr, dx, a, s); }

@@ -461,7 +461,11 @@ static h3d_status k5_launch(void* handle, const void* in, const void* wp, const 
   return hipGetLastError() == hipSuccess ? H3D_OK : fail(handle, H3D_EHIP, "conv3d_k5: launch failed");
 }
 
-// in: the staged tensor (x, or g of backward-data, whose rows may be padded: in.w >= out.w)
+TapsPackJob k5_mfma_pack(const void* w, void* wp, int cin, int cout, bool transposed) {
+  return taps_pack_job(w, wp, cin, cout, transposed ? TAPS_REVERSED : TAPS_FWD, (int)cdiv(transposed ? cout : cin, 16), 125);
+}
+
+// in: the staged tensor (x, or g of backward-data, whose rows may be padded: in.w >= out.w); w null: wp is packed already
 h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const void* w, int cin, int cout, bool transposed, const float* bias,
                         const h3d_tensor* out, float slope, void* wp, hipStream_t s) {
   const Geo go = make_geo(out);
@@ -469,7 +473,7 @@ h3d_status k5_mfma_conv(void* handle, const Geo& in, const void* in_data, const 
   K5MArgs a = k5m_args(in, go, loopc, resc);
   a.slope = slope;
   a.vec = go.w % 2 == 0 && go.cstride % 2 == 0 && (uintptr_t)out->data % 4 == 0;
-  taps_pack<125>(w, wp, cin, cout, transposed ? TAPS_REVERSED : TAPS_FWD, a.nchunk, s);
+  if (w) taps_pack(k5_mfma_pack(w, wp, cin, cout, transposed), s);
   const bool v16 = rows16(in, in_data);
   // 32-row tiles hold more products per staged row; with fewer than one of them per CU (or low volumes) 16-row tiles occupy more CUs
   const int64_t tall = (int64_t)out->n * go.d * cdiv(go.h, 32) * cdiv(go.w, 32) * cdiv(resc, 32);

@@ -11,7 +11,7 @@
 //     channels a whole volume apart, so the input tile (with its halo) is transposed on its way
 //     into LDS: 16-byte units of 8 channels, laid out [ci-group][d][h][w], read back with
 //     conflict-free ds_read_b128 at the 27 shifted offsets;
-//   * weights are pre-packed in exact fragment order ([co-block][ci-chunk][tap][lane][8]) and go
+//   * weights are pre-packed in exact fragment order ([co-block][ci-chunk][tap][lane][8], taps.h) and go
 //     global -> registers (fully coalesced 1 KB per fragment, L1/L2 resident), prefetched one
 //     (kd,kw) step ahead; they never touch LDS;
 //   * a workgroup is 8 wavefronts: NCB blocks of 32 output channels x ND depth planes; each
@@ -32,25 +32,6 @@ typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 constexpr int CI_CHUNK = 16;
 constexpr int WG_THREADS = 512;
-
-// wp: [co_blk][chunk][tap][lane][8] bf16; lane l, element e: co_k = 32*co_blk + l%32, ci_k = 16*chunk + 8*(l/32) + e
-__global__ void pack_w_mfma_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout, int transpose,
-                                   int nchunks, int ncoblk) {
-  int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  int64_t total = (int64_t)ncoblk * nchunks * 27 * 512;
-  if (i >= total) return;
-  int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-  int64_t r = i >> 9;
-  int tap = (int)(r % 27); r /= 27;
-  int chunk = (int)(r % nchunks);
-  int cb = (int)(r / nchunks);
-  int co_k = cb * 32 + (lane & 31), ci_k = chunk * CI_CHUNK + (lane >> 5) * 8 + e;
-  int cin_k = transpose ? cout : cin, cout_k = transpose ? cin : cout;
-  bf16_t v = 0;
-  if (co_k < cout_k && ci_k < cin_k)
-    v = transpose ? w[((int64_t)ci_k * cin + co_k) * 27 + (26 - tap)] : w[((int64_t)co_k * cin + ci_k) * 27 + tap];
-  wp[i] = v;
-}
 
 struct MfmaArgs {
   Geo in, mask, out;
@@ -1115,9 +1096,9 @@ static h3d_status wide_conv(void* handle, const bf16_t* ip, const uint4* wq, con
   return launch_wide<1, 1>(handle, ip, wq, bias, op, a, n, stream);
 }
 
-// the weights are packed at the start of the workspace already
+// pack: the weights, to the start of the workspace, beside the first copy
 static h3d_status prep_conv(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const float* bias, h3d_tensor* out, MfmaArgs a,
-                            float mask_slope, void* ws, size_t split_bytes, hipStream_t stream) {
+                            float mask_slope, void* ws, size_t split_bytes, const TapsPackJob& pack, hipStream_t stream) {
   const int planes = out->halo_lo + out->d + out->halo_hi, w8 = prep_w(in->w);
   PrepTiling t;
   if (!prep_tiling(in->n, planes, prep_plane_bytes(in), 2, PREP_FWD_BUDGET, &t)) return H3D_OK;     // (nothing to compute)
@@ -1130,7 +1111,7 @@ static h3d_status prep_conv(void* handle, const h3d_tensor* in, const h3d_tensor
     const int lo = (int)std::max<int64_t>(a0 - 1, -gi.doff), hi = (int)std::min<int64_t>(a1 + 1, gi.dglob - gi.doff);
     const int np = std::max(hi - lo, 0);
     const PrepJob j = prep_job(in, mask, mask_slope, b.n0, b.nn, lo, np, copy);
-    H3D_TRY(prep_launch(handle, j, nullptr, stream));
+    H3D_TRY(prep_launch(handle, j, nullptr, stream, i ? nullptr : &pack));
     MfmaArgs s = a;
     s.in.n = b.nn; s.in.d = b.np; s.in.w = w8; s.in.doff = gi.doff + a0; s.in.hlo = a0 - lo; s.in.ds = np; s.in.hhi = np - b.np - s.in.hlo;
     s.in.plane = (int64_t)in->h * w8; s.in.cstride = s.in.plane * np; s.in.nstride = s.in.cstride * in->c;
@@ -1197,9 +1178,7 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   const bool vec = (in->w % 2 == 0) && ((uintptr_t)in->data % 4 == 0) && ((uintptr_t)out->data % 4 == 0) &&
                    (!mask || (uintptr_t)mask->data % 4 == 0);
   const int cin = transpose ? a.cout_k : a.cin_k, cout = transpose ? a.cin_k : a.cout_k;
-  int64_t total = (int64_t)a.ncoblk * a.nchunks * 27 * 512;
-  hipLaunchKernelGGL(pack_w_mfma_kernel, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, stream, (const bf16_t*)w, (bf16_t*)ws, cin,
-                     cout, transpose ? 1 : 0, a.nchunks, a.ncoblk);
+  const TapsPackJob pack = taps_pack_job(w, ws, cin, cout, transpose ? TAPS_REVERSED : TAPS_FWD, a.nchunks, 27);
   const bf16_t* ip = (const bf16_t*)in->data;
   const bf16_t* mp = mask ? (const bf16_t*)mask->data : nullptr;
   bf16_t* op = (bf16_t*)out->data;
@@ -1215,24 +1194,29 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out));
   }
   if (!mask && vec && wide_shape(a) && (a.cout_k > 32 || a.cin_k > 8))      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
+  {
+    taps_pack(pack, stream);
     return wide_conv(handle, ip, wq, bias, op, a, out->n, stream);
+  }
   if (const size_t copies = prep_fwd_bytes(in, out); copies && (uintptr_t)out->data % 4 == 0 && ws_bytes >= mfma_wp_bytes(in, out) + split_bytes + copies)
-    return prep_conv(handle, in, mask, bias, out, a, mask_slope, ws, split_bytes, stream);
+    return prep_conv(handle, in, mask, bias, out, a, mask_slope, ws, split_bytes, pack, stream);
   a.pairs = vec;
   if (const size_t copy = mask || in->w % 2 ? prep_narrow_bytes(in, out) : 0; copy && ws_bytes >= mfma_base_ws_bytes(in, out, num_cu, room) + copy) {
     // the planes that the output's window reaches inside the volume (all of them are stored), behind whatever else the workspace holds
     bf16_t* dst = reinterpret_cast<bf16_t*>(static_cast<char*>(ws) + mfma_base_ws_bytes(in, out, num_cu, room));
     const int lo = (int)std::max<int64_t>(-out->halo_lo - 1, -a.in.doff), hi = (int)std::min<int64_t>(out->d + out->halo_hi + 1, a.in.dglob - a.in.doff);
-    H3D_TRY(prep_launch(handle, prep_job(in, mask, mask_slope, 0, in->n, lo, hi - lo, dst), nullptr, stream));
+    H3D_TRY(prep_launch(handle, prep_job(in, mask, mask_slope, 0, in->n, lo, hi - lo, dst), nullptr, stream, &pack));
     a.in.w = prep_w(in->w); a.in.ds = hi - lo; a.in.hlo = -lo; a.in.hhi = hi - in->d;
     a.in.plane = (int64_t)in->h * a.in.w; a.in.cstride = a.in.plane * a.in.ds; a.in.nstride = a.in.cstride * in->c;
     a.pairs = out->w % 2 == 0 && (uintptr_t)out->data % 4 == 0 && a.out.cstride % 2 == 0 && a.out.nstride % 2 == 0;
     st = pick_variant<false, true>(handle, dst, nullptr, wq, bias, op, a, out->n, stream);
+  } else {
+    taps_pack(pack, stream);
+    if (mask) st = vec ? pick_variant<true, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)
+                       : pick_variant<true, false>(handle, ip, mp, wq, bias, op, a, out->n, stream);
+    else st = vec ? pick_variant<false, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)
+                  : pick_variant<false, false>(handle, ip, mp, wq, bias, op, a, out->n, stream);
   }
-  else if (mask) st = vec ? pick_variant<true, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)
-                     : pick_variant<true, false>(handle, ip, mp, wq, bias, op, a, out->n, stream);
-  else st = vec ? pick_variant<false, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)
-                : pick_variant<false, false>(handle, ip, mp, wq, bias, op, a, out->n, stream);
   if (st != H3D_OK || a.csplit == 1) return st;
   const int64_t out_total = (int64_t)out->n * a.out.nstride;
   SplitGeo q;

@@ -665,7 +665,7 @@ h3d_status s2_mfma_fwd(void* handle, const h3d_tensor* x, const void* w, const f
   a.tiles_w = (int)cdiv(y->w, 32); a.tiles_h = (int)cdiv(y->h, 4);
   a.ntiles = y->n * y->d * a.tiles_h * a.tiles_w;
   a.vec = y->w % 2 == 0 && (uintptr_t)y->data % 4 == 0;
-  taps_pack<27>(w, ws, x->c, y->c, TAPS_FWD, a.nchunk, s);
+  taps_pack(taps_pack_job(w, ws, x->c, y->c, TAPS_FWD, a.nchunk, 27), s);
   const uint4* wp = (const uint4*)ws;
   const bool v16 = rows16(x);
   if (y->c > 64) return v16 ? s2_launch_fwd<2, 2, true>(handle, x, wp, bias, y, a, s) : s2_launch_fwd<2, 2, false>(handle, x, wp, bias, y, a, s);
@@ -689,7 +689,7 @@ h3d_status s2_mfma_bwd_data(void* handle, const h3d_tensor* dy, const h3d_tensor
   a.tiles_w = (int)cdiv(dy->w, 32); a.tiles_h = (int)cdiv(dy->h, 8);
   a.ntiles = dy->n * dy->d * a.tiles_h * a.tiles_w;
   a.vec = dx->w % 2 == 0 && (uintptr_t)dx->data % 4 == 0;
-  taps_pack<27>(w, ws, dx->c, dy->c, TAPS_TRANSPOSED, a.nchunk, s);
+  taps_pack(taps_pack_job(w, ws, dx->c, dy->c, TAPS_TRANSPOSED, a.nchunk, 27), s);
   const uint4* wp = (const uint4*)ws;
   const bool v16 = rows16(dy) && (!y || rows16(y));
   if (y && !s2_mask_fits(y)) return s2_launch_bd<S2_FAR_MASK, false>(handle, dy, y, wp, dx, a, s);

@@ -3,6 +3,7 @@
 // rows and no mask; a pass over the operand at streaming rate buys them for every other width and for fused masks.
 #pragma once
 #include "common.h"
+#include "taps.h"
 
 namespace h3d {
 
@@ -22,8 +23,8 @@ struct PrepJob {
   int64_t units;          // 16-byte units of dst
 };
 PrepJob prep_job(const h3d_tensor* t, const h3d_tensor* mask, float slope, int n0, int nn, int p0, int np, void* dst, int part = 0);
-// one launch for up to two copies (b may be null)
-h3d_status prep_launch(void* handle, const PrepJob& a, const PrepJob* b, hipStream_t stream);
+// one launch for up to two copies (b may be null) and the packed filter of the kernel behind them (or null: 27 or 125 taps)
+h3d_status prep_launch(void* handle, const PrepJob& a, const PrepJob* b, hipStream_t stream, const TapsPackJob* pack = nullptr);
 
 // Work is done in slabs whose copies fit a budget: runs of whole samples, or of planes of one sample.
 struct PrepSlab { int n0, nn, p0, np; };      // p0: index of the first output plane, counted from the caller's first one

@@ -45,26 +45,14 @@ void taps_reduce(const float* part, const float* part_db, float* dw, float* db, 
 }
 
 template <int TAPS>
-__global__ void __launch_bounds__(256) taps_pack_kernel(const bf16_t* __restrict__ w, bf16_t* __restrict__ wp, int cin, int cout, int form,
-                                                      int nchunk, int64_t total) {
-  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= total) return;
-  const int e = (int)(i & 7), lane = (int)((i >> 3) & 63);
-  int64_t r = i >> 9;
-  const int tap = (int)(r % TAPS); r /= TAPS;
-  const int chunk = (int)(r % nchunk), blk = (int)(r / nchunk);
-  const int row = blk * 32 + (lane & 31), k = chunk * 16 + (lane >> 5) * 8 + e;
-  const int co = form == TAPS_FWD ? row : k, ci = form == TAPS_FWD ? k : row;
-  wp[i] = (co < cout && ci < cin) ? w[((int64_t)co * cin + ci) * TAPS + (form == TAPS_REVERSED ? TAPS - 1 - tap : tap)] : (bf16_t)0;
+__global__ void __launch_bounds__(256) taps_pack_kernel(TapsPackJob j) {
+  taps_pack_element(j, (int64_t)blockIdx.x * 256 + threadIdx.x, TAPS);
 }
 
-template <int TAPS>
-void taps_pack(const void* w, void* wp, int cin, int cout, int form, int nchunk, hipStream_t s) {
-  const int64_t total = cdiv(form == TAPS_FWD ? cout : cin, 32) * (int64_t)nchunk * TAPS * 512;
-  hipLaunchKernelGGL(taps_pack_kernel<TAPS>, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, (const bf16_t*)w, (bf16_t*)wp, cin, cout, form, nchunk,
-                     total);
+void taps_pack(const TapsPackJob& j, hipStream_t s) {
+  const dim3 grid((unsigned)cdiv(j.total, 256));
+  if (j.taps == 27) hipLaunchKernelGGL(taps_pack_kernel<27>, grid, dim3(256), 0, s, j);
+  else hipLaunchKernelGGL(taps_pack_kernel<125>, grid, dim3(256), 0, s, j);
 }
-template void taps_pack<27>(const void*, void*, int, int, int, int, hipStream_t);
-template void taps_pack<125>(const void*, void*, int, int, int, int, hipStream_t);
 
 }  // namespace h3d
