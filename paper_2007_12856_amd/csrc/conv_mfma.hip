@@ -95,6 +95,8 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   constexpr int NITEMS = 2 * TD2 * TH2 * ITEMS_ROW;
   constexpr int ROUNDS = (NITEMS + WG_THREADS - 1) / WG_THREADS;
   constexpr int NFRAG = 3 * RPB + 3;   // distinct start rows b*RPB + kh
+  constexpr int RING = 4;              // row fragments in flight
+  constexpr int APRE = 5, PRE = MASKED ? 0 : 4;   // steps whose weights are requested before the next stage's input; by the chunk before (a masked form has no registers to spare)
   extern __shared__ uint4 lds[];
 
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -258,36 +260,36 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
     }
   };
 
-  // One chunk = 9 (kd,kw) steps of 12 MFMAs.  Vector-memory loads return in order, so a wait for a
-  // weight fragment also waits for every load issued before it.  The weight fragments of the first
-  // APRE steps are therefore requested BEFORE the (long-latency) input loads of the next stage are
-  // issued (`issue_next`), and the remaining ones only once those have had several steps to land.
-  constexpr int APRE = 5;
-  auto compute_chunk = [&](int c, int buf, auto&& issue_next) {
+  // One chunk = 9 (kd,kw) steps of 12 MFMAs.  Vector-memory loads return in order, so a wait for a weight fragment also waits for every
+  // load issued before it.  The weights of the first APRE steps are therefore requested before the (long-latency) input loads of the next
+  // stage (`issue_next`), PRE of them by the chunk before (c_next: the chunk after this one), and the others once the input has had some
+  // steps to land.  Row fragments come through a ring of four, read as the products go (two whole steps of them in registers, read
+  // in one go, left the matrix pipes to wait for LDS and no registers for weights of the next chunk), one memory or LDS
+  // instruction or two behind each product.  us, before and after: 256->256 on 8 x 16^3 106 and 98, 64->128 on 4 x 16^3 30.9 and 26.4, 128->96 on
+  // 53x48x8 52 and 43, 64->64 on 2x256x256 37.7 and 34.3, 256->256 on 8^3 28.2 and 27.6, masked 16->8 on 4 x 16x64x64 28.2 and 27.1.
+  uint4 afr[9][3];
+  auto compute_chunk = [&](int c, int c_next, int buf, auto&& issue_next) {
     const uint4* base = lds + buf * BUF_UNITS + lane_unit;
-    uint4 afr[9][3];
-    uint4 bfr[2][NFRAG];     // row fragments of the current and of the next (kd,kw) step
-    auto load_b = [&](int step, uint4 (&dst)[NFRAG]) {
-      const int kd = step / 3, kw = step % 3;
+    uint4 bfr[RING];
+    auto row = [&](int i) { return base[(i / NFRAG / 3 * TH2 + i % NFRAG) * P + i / NFRAG % 3]; };      // row fragment i of the chunk's 9 * NFRAG
 #pragma unroll
-      for (int s = 0; s < NFRAG; ++s) dst[s] = base[(kd * TH2 + s) * P + kw];
-    };
+    for (int step = PRE; step < APRE; ++step) load_a(c, step, afr[step]);
 #pragma unroll
-    for (int step = 0; step < APRE; ++step) load_a(c, step, afr[step]);
-    load_b(0, bfr[0]);
+    for (int i = 0; i < RING; ++i) bfr[i] = row(i);
     __builtin_amdgcn_sched_barrier(0);   // keep the weight requests ahead of the input loads ...
     issue_next();
     __builtin_amdgcn_sched_barrier(0);   // ... and the input loads ahead of the MFMA steps (not sunk below them)
 #pragma unroll
     for (int step = 0; step < 9; ++step) {
-      if (step + 1 < 9) load_b(step + 1, bfr[(step + 1) & 1]);     // in flight during this step's MFMAs
       if (step == APRE - 1) {
 #pragma unroll
         for (int s2 = APRE; s2 < 9; ++s2) load_a(c, s2, afr[s2]);
       }
+      if (step >= 9 - PRE) load_a(c_next, step - (9 - PRE), afr[step - (9 - PRE)]);
 #pragma unroll
       for (int s = 0; s < NFRAG; ++s) {
-        const bf16x8 B = __builtin_bit_cast(bf16x8, bfr[step & 1][s]);
+        const int i = step * NFRAG + s;
+        const bf16x8 B = __builtin_bit_cast(bf16x8, bfr[i % RING]);
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh) {
           // the block whose start row b*RPB + kh equals s
@@ -296,7 +298,14 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
             acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[step][kh]), B, acc[b], 0, 0, 0);
           }
         }
+        if (i + RING < 9 * NFRAG) bfr[i % RING] = row(i + RING);
       }
+#pragma unroll
+      for (int i = 0; i < 12; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);      // one MFMA
+        __builtin_amdgcn_sched_group_barrier(0x326, 2, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
   };
 
@@ -379,6 +388,10 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   const int c_end = SPLIT ? min(a.nchunks, c_begin + a.chunks_per_split) : a.nchunks;
   plan_tile(tile);
   load_chunk(c_begin, true);
+  if (wave_active) {
+#pragma unroll
+    for (int step = 0; step < PRE; ++step) load_a(c_begin, step, afr[step]);
+  }
   if constexpr (ROW16) {      // the units of columns -2, -1 and 16, 17 (no piece covers them) of every row, both buffers
     for (int i = tid; i < 2 * 2 * TD2 * TH2 * 4; i += WG_THREADS) lds[(i >> 2) * P + (i & 1) + ((i & 2) ? 18 : 0)] = uint4{0, 0, 0, 0};
   }
@@ -394,7 +407,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
         if (last_chunk && more) plan_tile(next_tile);
         load_chunk(last_chunk ? c_begin : c + 1, more);
       };
-      if (wave_active) compute_chunk(c, buf, issue_next);
+      if (wave_active) compute_chunk(c, last_chunk ? c_begin : c + 1, buf, issue_next);
       else issue_next();
       if (more) store_chunk(buf ^ 1);
       __syncthreads();
