@@ -943,7 +943,7 @@ __global__ void __launch_bounds__(256) add_bf16_kernel(bf16_t* __restrict__ dst,
 // 33, 256->256 on 8x32x32 85 and 46, 128->96 on 16x16x32 46 and 25, 192->64 on 6x16x34 60 and 28, 64->32 on 8x16x24 25 and 18, 64->64 on 16x32x32
 // 28 and 25.
 static bool wide_dims(const h3d_tensor* in, const h3d_tensor* out) {
-  return out->w > 16 && out->halo_lo + out->d + out->halo_hi >= 3 && out->h >= 4 && (out->c > 32 || in->c > 8);
+  return out->w > 16 && out->halo_lo + out->d + out->halo_hi >= 3 && out->h >= 4;
 }
 static int64_t wide_units(const h3d_tensor* out) {
   return (int64_t)out->n * cdiv(out->halo_lo + out->d + out->halo_hi, 4) * cdiv(out->h, 8) * cdiv(out->w, 32) * cdiv(out->c, 32);
@@ -1206,8 +1206,9 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
     a.chunks_per_split = (int)cdiv(a.nchunks, a.csplit);
     a.part = reinterpret_cast<float*>(static_cast<char*>(ws) + mfma_wp_bytes(in, out));
   }
-  if (!mask && vec && wide_shape(a) && (a.cout_k > 32 || a.cin_k > 8))      // (16 input channels = one chunk per tile: 16->32 on 4 x 64^3 0.056 ms with the kernel above, 0.043 here)
-  {
+  // Also where half of the only chunk is padding (at most 8 input and 32 output channels).  us, general kernel and here: 8->32 on 32x64x64 18.5 and 14.1,
+  // 8->16 on 64x128x128 47 and 37, on copies masked backward-data of 16->8 on 4 x 16x64x64 29.6 and 17.9, 8->8 on 9x30x41 71 and 15.6
+  if (!mask && vec && wide_shape(a)) {
     taps_pack(pack, stream);
     return wide_conv(handle, ip, wq, bias, op, a, out->n, stream);
   }

@@ -250,6 +250,37 @@ def test_conv3d_few_channels_bf16(shape):
     close(from_dev(zg.t), zo.a, TOL[dtype])
 
 
+# (N, channels in, channels out, D, H, W) of a layer whose forward and backward-data both have half a channel chunk: tiles of 4 x 8 x 32 and one
+# more or less on every side, odd rows, a channel
+@pytest.mark.parametrize("shape", [(1, 8, 8, 3, 4, 17), (2, 6, 8, 4, 8, 18), (1, 8, 5, 5, 9, 34), (1, 7, 8, 4, 7, 33), (2, 5, 7, 9, 17, 65), (1, 8, 1, 3, 16, 31)])
+def test_conv3d_wide_kernel_with_half_a_chunk(shape):
+    """At most 8 contraction and 32 result channels on a wide volume: the wide kernel, on a copy where the operand is masked or its rows are odd;
+    the same bits as the general kernel, which a result at an odd address still gets."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    w, bias = _weights(Ci, Co, "bf16", 90)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 92, (N, Ci, D, H, W)), "bf16")
+    dzo, dzg = slab_pair(synth.flat("normal", SEED, 93, (N, Co, D, H, W)), "bf16")
+    zo, zg = slab_pair(synth.flat("normal", SEED, 94, (N, Co, D, H, W)), "bf16")
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    thin = W >= 32 and W % 2 == 0
+    for name, ref, call, c in (("fwd", orc.conv3d_fwd(xo, w, bias, act=orc.ACT_LEAKY, alpha=0.01), lambda o: h3d.conv3d_fwd(xg, wd, bd, o, h3d.ACT_LEAKY, 0.01), Co),
+                               ("bwd", orc.conv3d_bwd_data(dzo, zo, w, act=orc.ACT_LEAKY, alpha=0.01), lambda o: h3d.conv3d_bwd_data(dzg, zg, wd, o, h3d.ACT_LEAKY, 0.01), Ci)):
+        n = N * c * D * H * W
+        got = []
+        for shift in (0, 1):
+            buf = torch.full((n + 2,), 3.0, dtype=torch.bfloat16, device="cuda")
+            out = h3d.Slab(buf[shift:shift + n].view(N, c, D, H, W))
+            call(out)
+            assert torch.all(buf[:shift] == 3.0) and torch.all(buf[shift + n:] == 3.0)
+            got.append(out.t.clone())
+            if not (name == "fwd" and thin):
+                assert ("wide" in h3d.h3d_last_kernel()) == (shift == 0), h3d.h3d_last_kernel()
+        close(from_dev(got[0]), ref.a, TOL["bf16"])
+        assert torch.equal(got[0], got[1])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cin,cout", [(4, 16), (3, 5), (16, 32)])
 def test_conv3d_sharded_matches_oracle_and_unsharded_gpu(dtype, cin, cout):
