@@ -450,6 +450,11 @@ F32_SHAPES = [
     (2, 20, 24, 4, 12, 8, 1, 0, 4),
     (1, 3, 6, 5, 9, 12, 0, 0, 5),
     (4, 5, 6, 16, 256, 16, 0, 0, 16),
+    # where the rows or the channels of a workgroup's tile divide evenly over the chip
+    (2, 5, 32, 16, 128, 128, 0, 0, 16),
+    (1, 5, 32, 4, 128, 128, 0, 0, 4),
+    (4, 5, 32, 16, 32, 16, 0, 0, 16),
+    (1, 9, 40, 5, 34, 40, 1, 4, 16),
 ]
 
 
