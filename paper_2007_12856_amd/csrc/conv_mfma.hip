@@ -1097,9 +1097,12 @@ static h3d_status wide_conv(void* handle, const bf16_t* ip, const uint4* wq, con
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   if (a.csplit > 1) return launch_wide<1, 1, 2, false, true>(handle, ip, wq, bias, op, a, n, stream);
   if (a.cout_k > 32) {
-    // one round of workgroups with a channel block each (a small volume): the rows of a plane over two wavefronts; same sums in the same order.
-    // Beyond that two blocks a workgroup: 64->64 on 24x48x48 28.8 us, two blocks 41; 24->48 on 2 x 22x50x54 (336 tiles and blocks) 31 against 36
-    if (ntiles * a.ncoblk <= num_cu) return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, n, stream);
+    // Two channel blocks a workgroup, or one with the rows of a plane over two wavefronts (same sums in the same order): a tile takes 0.58 to 0.64 times
+    // as long with one, so it pays where the tiles, or an odd number of blocks, divide badly over the CUs.  us, two blocks and one: 64->64
+    // on 4 x 8x134x54 (272 tiles) 81 and 75, 128->96 on 16x112x160 231 and 197, 256->96 446 and 375, 32->51 on 58x96x64 52 and 47, 64->64 on 24x48x48 41
+    // and 29; but on 32x128x128 (512 tiles) 97 and 113, 24->48 on 2 x 22x50x54 31 and 36, 22->96 on 8 x 24x64x53 170 and 172
+    auto rounds = [&](int64_t gy) { return cdiv(ntiles, std::max<int64_t>(1, num_cu / gy)); };
+    if (62 * rounds(a.ncoblk) < 100 * rounds(cdiv(a.ncoblk, 2))) return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, n, stream);
     return launch_wide<1, 2>(handle, ip, wq, bias, op, a, n, stream);
   }
   // one block of output channels: with short channel loops (at most 32 input channels) or few tiles the eight-wavefront
