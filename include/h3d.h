@@ -246,7 +246,7 @@ h3d_status h3d_pool3d_bwd_act(void* handle, const h3d_tensor* dy, const h3d_tens
 /* ---- convolution forward fused with the 2x2x2 average pooling that follows it, and the matching backward step ----
  * (Sec. III-A: operations that are "normally considered cheap" - pooling, activations - dominate once the tensors
  * are large; here the unpooled activation never has to travel to memory and back.)
- * AVERAGE pooling only (the CosmoFlow shapes; a max-pooled layer uses the separate calls).
+ * AVERAGE pooling only (the CosmoFlow shapes; a max-pooled layer uses h3d_conv3d_fwd_maxpool or the separate calls).
  * y = avgpool(act(b + W * x)): the pooled tensor of the same shard (extents and offsets half of z's, halos allowed,
  * interior written).  z describes the unpooled output; z->data == NULL means it is not stored (only where a fused
  * kernel exists: bf16, Cin <= 4, Cout <= 32, z without halos, even d and h, w a multiple of 8; otherwise
@@ -258,6 +258,11 @@ size_t h3d_act_mask_bytes(const h3d_tensor* z);                       /* 0 if w 
 h3d_status h3d_conv3d_fwd_pool(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
                                h3d_tensor* y, void* mask, int act, float alpha,
                                void* ws, size_t ws_bytes, void* stream);
+/* z = act(b + W * x) and y = maxpool(z), for every shape h3d_conv3d_fwd and h3d_pool3d_fwd accept (z and y may be views); one launch for bf16
+ * volumes wider than 16 voxels with z without halos and w a multiple of 4, the two calls one after the other otherwise.  Same bits either
+ * way; workspace as for H3D_OP_FWD. */
+h3d_status h3d_conv3d_fwd_maxpool(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
+                                  h3d_tensor* y, int act, float alpha, void* ws, size_t ws_bytes, void* stream);
 /* mask of a stored output z (what the fused call writes by itself). */
 h3d_status h3d_act_mask(void* handle, const h3d_tensor* z, void* mask, void* stream);
 /* y = avgpool(x) and, in the same pass, the mask of x (what h3d_pool3d_fwd and h3d_act_mask write one after the other):

@@ -71,6 +71,7 @@ _SIGNATURES = {
     "h3d_pool3d_fwd_mask": (ctypes.c_int, [_P, _T, _T, _P, _P]),
     "h3d_act_mask_bytes": (ctypes.c_size_t, [_T]),
     "h3d_conv3d_fwd_pool": (ctypes.c_int, [_P, _T, _P, _P, _T, _T, _P, ctypes.c_int, ctypes.c_float, _P, ctypes.c_size_t, _P]),
+    "h3d_conv3d_fwd_maxpool": (ctypes.c_int, [_P, _T, _P, _P, _T, _T, ctypes.c_int, ctypes.c_float, _P, ctypes.c_size_t, _P]),
     "h3d_act_mask": (ctypes.c_int, [_P, _T, _P, _P]),
     "h3d_pool3d_bwd_mask": (ctypes.c_int, [_P, _T, _P, _T, ctypes.c_int, ctypes.c_float, _P]),
     "h3d_halo_bytes": (ctypes.c_size_t, [_T, ctypes.c_int]),
@@ -294,6 +295,13 @@ def h3d_conv3d_fwd_pool(x: Slab, w, bias, z, y: Slab, mask, act: int = ACT_NONE,
     p, n = (ws or _ws).get(lib().h3d_conv3d_workspace_bytes(handle(), OP_FWD, xd, zd))
     _check(lib().h3d_conv3d_fwd_pool(handle(), xd, _ptr(w), _ptr(bias), zd, y.desc(),
                                      _ptr(mask), act, alpha, p, n, _stream()))
+    return y
+
+
+def h3d_conv3d_fwd_maxpool(x: Slab, w, bias, z: Slab, y: Slab, act: int = ACT_NONE, alpha: float = 0.0, ws: Workspace | None = None):
+    xd, zd = x.desc(), z.desc()
+    p, n = (ws or _ws).get(lib().h3d_conv3d_workspace_bytes(handle(), OP_FWD, xd, zd))
+    _check(lib().h3d_conv3d_fwd_maxpool(handle(), xd, _ptr(w), _ptr(bias), zd, y.desc(), act, alpha, p, n, _stream()))
     return y
 
 
@@ -579,7 +587,7 @@ pool3d_fwd, pool3d_bwd, act_bwd, pool3d_bwd_act = h3d_pool3d_fwd, h3d_pool3d_bwd
 halo_bytes, halo_pack, halo_unpack = h3d_halo_bytes, h3d_halo_pack, h3d_halo_unpack
 box_bytes, box_pack, box_unpack = h3d_box_bytes, h3d_box_pack, h3d_box_unpack
 conv3d_fwd_pool, act_mask, act_mask_bytes, pool3d_bwd_mask = h3d_conv3d_fwd_pool, h3d_act_mask, h3d_act_mask_bytes, h3d_pool3d_bwd_mask
-pool3d_fwd_mask = h3d_pool3d_fwd_mask
+pool3d_fwd_mask, conv3d_fwd_maxpool = h3d_pool3d_fwd_mask, h3d_conv3d_fwd_maxpool
 deconv2_fwd, deconv2_bwd_data, deconv2_bwd_filter = h3d_deconv2_fwd, h3d_deconv2_bwd_data, h3d_deconv2_bwd_filter
 concat_c, split_c = h3d_concat_c, h3d_split_c
 dense_fwd, dense_bwd, mse_fwd_bwd = h3d_dense_fwd, h3d_dense_bwd, h3d_mse_fwd_bwd

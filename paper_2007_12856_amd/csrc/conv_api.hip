@@ -44,6 +44,9 @@ size_t mfma_fwd_ws_bytes(void* handle, const h3d_tensor* in, const h3d_tensor* o
 h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, const float* bias,
                        h3d_tensor* out, bool transpose, float out_slope, float mask_slope, void* ws, size_t ws_bytes,
                        hipStream_t stream);
+bool wide_pool_supported(void* handle, const h3d_tensor* in, const h3d_tensor* z, const h3d_tensor* y);
+h3d_status conv3d_wide_pool(void* handle, const h3d_tensor* in, const void* w, const float* bias, h3d_tensor* z, h3d_tensor* y, float out_slope, void* ws,
+                            size_t ws_bytes, hipStream_t stream);
 bool mfma_bf_supported(const h3d_tensor* x, const h3d_tensor* dz);
 size_t mfma_bf_ws_bytes(const h3d_tensor* x, const h3d_tensor* dz);
 h3d_status bwd_filter_mfma(void* handle, const h3d_tensor* x, const h3d_tensor* dz, const h3d_tensor* z, float* dw,
@@ -136,6 +139,24 @@ extern "C" h3d_status h3d_conv3d_fwd_pool(void* handle, const h3d_tensor* x, con
   H3D_TRY(h3d_pool3d_fwd(handle, z, y, H3D_POOL_AVG, stream));
   if (mask) H3D_TRY(h3d_act_mask(handle, z, mask, stream));
   return H3D_OK;
+}
+
+extern "C" h3d_status h3d_conv3d_fwd_maxpool(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
+                                             h3d_tensor* y, int act, float alpha, void* ws, size_t ws_bytes, void* stream) {
+  if (!handle) return H3D_EINVAL;
+  H3D_TRY(check_tensor(handle, x, "x"));
+  H3D_TRY(check_tensor(handle, z, "z"));
+  H3D_TRY(check_tensor(handle, y, "y"));
+  H3D_TRY(check_act(handle, act));
+  if (!w && x->c * z->c > 0) return fail(handle, H3D_EINVAL, "conv3d_fwd_maxpool: NULL weights");
+  H3D_TRY(check_pair(handle, x, z, "conv3d_fwd_maxpool"));
+  H3D_TRY(pool_shapes_check(handle, z, y, "conv3d_fwd_maxpool"));
+  if (!c4_roll_supported(x, z) && !c4_fwd_supported(x, z) && wide_pool_supported(handle, x, z, y))
+    return conv3d_wide_pool(handle, x, w, bias, z, y, act_slope(act, alpha), ws, ws_bytes, (hipStream_t)stream);
+  // what the pooling pass would refuse is refused before anything is enqueued
+  if ((uintptr_t)z->data % (2 * elt_size(z->dtype))) return fail(handle, H3D_EUNSUPPORTED, "pool3d: data pointers must be aligned to two elements");
+  H3D_TRY(h3d_conv3d_fwd(handle, x, w, bias, z, act, alpha, ws, ws_bytes, stream));
+  return h3d_pool3d_fwd(handle, z, y, H3D_POOL_MAX, stream);
 }
 
 extern "C" h3d_status h3d_conv3d_bwd_data(void* handle, const h3d_tensor* dz, const h3d_tensor* z, const void* w,

@@ -43,6 +43,8 @@ struct MfmaArgs {
   int csplit, chunks_per_split;
   int pairs;        // output rows can be stored two voxels at a time (false only with a prepared input)
   float* part;      // [csplit][n][cout][stored planes][h][w], used when csplit > 1
+  Geo yp;           // max-pooled result (POOL)
+  bf16_t* ypool;
 };
 
 __device__ __forceinline__ uint32_t mask_pair(uint32_t v, uint32_t m, float slope) {
@@ -454,7 +456,11 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
 // four rows of the tile each (64 accumulators, 6 row fragments per step).
 // RAGGED: output rows of odd length (the input is then a prepared copy): a row's last voxel is stored on its own.
 // SPLIT: the input chunks are dealt to blockIdx.z; the accumulators leave as they are, [split][tile][channel block][plane][row * 16 + r][lane].
-template <int CB, int WCB, int RSP = 1, bool RAGGED = false, bool SPLIT = false>
+// POOL: the 2x2x2 max pooling of the result is written beside it.  A wavefront takes half of the rows of two planes, so that a window's eight voxels are
+// in one pair of lanes (12 row fragments a step instead of 10; with whole planes and an exchange through LDS the wavefronts meet between tiles,
+// and nothing hides their stores: 512 us).  us, two calls and one: 32 -> 64 on
+// 64x256x256 544 and 486, on 16x128x128 41.6 and 38.1, 16 -> 32 on 4 x 64^3 54.7 and 46.4, 32 -> 64 on 4 x 32^3 31.3 and 24.8.
+template <int CB, int WCB, int RSP = 1, bool RAGGED = false, bool SPLIT = false, bool POOL = false>
 __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const bf16_t* __restrict__ in, const uint4* __restrict__ wp,
                                                                      const float* __restrict__ bias, bf16_t* __restrict__ out, MfmaArgs a) {
   static_assert(WCB * RSP <= 2, "at most eight wavefronts");
@@ -466,12 +472,14 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   constexpr int BUF_UNITS = 2 * CIG_UNITS;
   constexpr int NITEMS = TD2 * TH2 * PAIRS;   // (plane, row, pair of columns) items of one channel group
   constexpr int ROUNDS = (NITEMS + NT - 1) / NT;
-  constexpr int NFRAG = VB + 2;
-  constexpr int RING = WCB == 2 ? 5 : NFRAG;   // row fragments in flight: as many as fit beside three sets of weights
+  constexpr int PL = POOL ? 2 : 1, VR = VB / PL;             // planes, and rows of each, of a wavefront
+  constexpr int NFRAG = PL * (VR + 2);
+  constexpr int RING = WCB == 2 ? (POOL ? 4 : 5) : NFRAG;   // row fragments in flight: as many as fit beside three sets of weights (pooling, 5: 498 us)
   extern __shared__ uint4 lds[];
 
-  const int tid = threadIdx.x, lane = tid & 63, wd = (tid >> 6) & 3;      // plane of the tile
+  const int tid = threadIdx.x, lane = tid & 63, wd = POOL ? (tid >> 6) & 2 : (tid >> 6) & 3;      // (first) plane of the tile
   const int wcb = WCB == 2 ? tid >> 8 : 0, rh = RSP == 2 ? tid >> 8 : 0;   // channel-block group, row half
+  const int row0 = POOL ? ((tid >> 6) & 1) * (TH / 2) + rh * VR : rh * VB;                  // first row of the tile
   const int co_blk0 = (blockIdx.y * WCB + wcb) * CB;
   const int W = a.in.w, H = a.in.h, WO = a.out.w;     // a prepared input has padded rows: W = WO rounded up
 
@@ -587,7 +595,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   };
   init_acc();
 
-  const int lane_unit = (lane >> 5) * CIG_UNITS + (wd * TH2 + rh * VB) * P + j + 1;
+  const int lane_unit = (lane >> 5) * CIG_UNITS + (wd * TH2 + row0) * P + j + 1;
   const int a_voff = lane * 16;
   // weight fragments of one (kd,kw) step: [kh][channel block]; a channel block beyond Cout re-reads the last valid one
   auto load_a = [&](int c, int step, uint4 (&dst)[3][CB]) {
@@ -616,7 +624,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   auto compute_chunk = [&](int c, int c_next, int buf, bool more, int next_tile, bool last_chunk) {
     const uint4* base = lds + buf * BUF_UNITS + lane_unit;
     uint4 bfr[RING];
-    auto row = [&](int i) { return base[(i / NFRAG / 3 * TH2 + i % NFRAG) * P + i / NFRAG % 3]; };      // row fragment i of the chunk's 9 * NFRAG
+    auto row = [&](int i) { return base[((i / NFRAG / 3 + i % NFRAG / (VR + 2)) * TH2 + i % NFRAG % (VR + 2)) * P + i / NFRAG % 3]; };      // row fragment i of the chunk's 9 * NFRAG
 #pragma unroll
     for (int i = 0; i < RING; ++i) bfr[i] = row(i);
     const int cn = last_chunk ? c_begin : c + 1;
@@ -634,11 +642,11 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
         const bf16x8 B = __builtin_bit_cast(bf16x8, bfr[i % RING]);
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh) {
-          const int b = s - kh;
-          if (b >= 0 && b < VB) {
+          const int b = s % (VR + 2) - kh, o = s / (VR + 2) * VR + b;
+          if (b >= 0 && b < VR) {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
-              acc[cb][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[step % 3][kh][cb]), B, acc[cb][b], 0, 0, 0);
+              acc[cb][o] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, afr[step % 3][kh][cb]), B, acc[cb][o], 0, 0, 0);
           }
         }
         if (i + RING < 9 * NFRAG) bfr[i % RING] = row(i + RING);
@@ -665,7 +673,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
     const int th = t % a.tiles_h; t /= a.tiles_h;
     const int td = t % a.tiles_d;
     const int n = t / a.tiles_d;
-    const int w0 = tw * TW, h0 = th * TH + rh * VB, ps = td * TD + wd;      // this wavefront's first row
+    const int w0 = tw * TW, h0 = th * TH + row0, ps = td * TD + wd;      // this wavefront's first row
     if (ps >= a.out.ds) return;
     if constexpr (SPLIT) {
 #pragma unroll
@@ -730,6 +738,77 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
         }
       }
     };
+    if constexpr (POOL) {
+      static_assert(CB == 1 && !RAGGED && !SPLIT, "one channel block a wavefront, whole rows");
+      if (co_blk0 >= a.ncoblk) return;
+      // two lanes that hold neighbouring voxels of a channel store both of one of two pooled rows (or, of one row, of one of two channels)
+      const __amdgpu_buffer_rsrc_t rs_y = make_rsrc(a.ypool + n * a.yp.nstride, (uint32_t)a.yp.nstride * 2);
+      const bool second = lane & 2;
+      const uint32_t sel2 = second ? 0x03020706u : 0x05040100u;
+      const int wy = w0 / 2 + (j >> 1) - (second ? 1 : 0), qy = ps / 2 + a.yp.hlo, hy = h0 / 2 + (VR == 4 && second ? 1 : 0);
+      const bool y_ok = wy < a.yp.w && hy < a.yp.h;
+      const int ybase = 2 * ((row_ch + (odd ? 1 : 0) + (VR == 2 && second ? 2 : 0)) * (int)a.yp.cstride + qy * (int)a.yp.plane + hy * a.yp.w + wy);
+      auto block = [&](auto whole_c) {
+        constexpr bool WHOLE = decltype(whole_c)::value;
+        uint32_t before = 0;
+#pragma unroll
+        for (int r = 0; r < 16; r += 2) {
+          const int co_u = co_blk0 * 32 + 8 * (r / 4) + (r % 4), co = co_u + row_ch + (odd ? 1 : 0);
+          const int soff = __builtin_amdgcn_readfirstlane(co_u * cs2);
+          uint32_t pk[VB];
+#pragma unroll
+          for (int b = 0; b < VB; ++b) {
+            float v0 = acc[0][b][r], v1 = acc[0][b][r + 1];
+            const float s0 = v0 * slope, s1 = v1 * slope;
+            asm("v_max_f32 %0, %1, %2" : "=v"(v0) : "v"(v0), "v"(s0));
+            asm("v_max_f32 %0, %1, %2" : "=v"(v1) : "v"(v1), "v"(s1));
+            const uint32_t own = pack_bf16x2(v0, v1);
+            const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
+            pk[b] = __builtin_amdgcn_perm(nb, own, sel);
+            const int o = w_ok && h0 + b % VR < H ? vbase + 2 * (b / VR * (int)a.out.plane + b % VR * WO) : BUF_OOB;
+            __builtin_amdgcn_raw_buffer_store_b32(pk[b], rs_out, WHOLE || co < a.cout_k ? o : BUF_OOB, soff, 0);
+          }
+          uint32_t best[VR / 2];
+#pragma unroll
+          for (int k = 0; k < VR / 2; ++k) {
+            const uint32_t w4[4] = {pk[2 * k], pk[2 * k + 1], pk[VR + 2 * k], pk[VR + 2 * k + 1]};
+            float e[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) e[i] = __uint_as_float((i & 1) ? w4[i / 2] & 0xffff0000u : w4[i / 2] << 16);
+            // The pooling kernel goes through a window with "if e > m": m stays where the first element is NaN or equals the maximum.  A maximum of
+            // the others does for that unless zeros of both signs follow a negative element.
+            float m;
+            asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(e[1]), "v"(e[2]), "v"(e[3]));
+            asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(m), "v"(e[4]), "v"(e[5]));
+            asm("v_max3_f32 %0, %1, %2, %3" : "=v"(m) : "v"(m), "v"(e[6]), "v"(e[7]));
+            m = m > e[0] ? m : e[0];
+            if (__builtin_expect(__builtin_amdgcn_ballot_w64(m == 0.f && e[0] < 0.f) != 0, 0)) {
+              m = e[0];
+#pragma unroll
+              for (int i = 1; i < 8; ++i) m = e[i] > m ? e[i] : m;
+            }
+            best[k] = __float_as_uint(m);
+          }
+          uint32_t own;
+          if (VR == 4) {
+            own = __builtin_amdgcn_perm(best[VR / 2 - 1], best[0], 0x07060302u);
+          } else if (r % 4 == 0) {
+            before = best[0];
+            continue;
+          } else {
+            own = __builtin_amdgcn_perm(best[0], before, 0x07060302u);
+          }
+          const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0x4E, 0xF, 0xF, true);
+          const int co_y = VR == 4 ? co_u : co_u - 2;
+          const bool ok = y_ok && (WHOLE || co_y + row_ch + (odd ? 1 : 0) + (VR == 2 && second ? 2 : 0) < a.cout_k);
+          __builtin_amdgcn_raw_buffer_store_b32(__builtin_amdgcn_perm(nb, own, sel2), rs_y, ok ? ybase : BUF_OOB,
+                                                __builtin_amdgcn_readfirstlane(2 * co_y * (int)a.yp.cstride), 0);
+        }
+      };
+      if (co_blk0 * 32 + 32 <= a.cout_k) block(std::true_type{});
+      else block(std::false_type{});
+      return;
+    }
     using T_ = std::true_type;
     using F_ = std::false_type;
 #pragma unroll
@@ -1021,10 +1100,10 @@ static bool wide_shape(const MfmaArgs& a) {
   return a.out.w > 16 && a.out.ds >= 3 && a.out.h >= 4;
 }
 
-template <int CB, int WCB = 1, int RSP = 1, bool RAGGED = false, bool SPLIT = false>
+template <int CB, int WCB = 1, int RSP = 1, bool RAGGED = false, bool SPLIT = false, bool POOL = false>
 static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, const float* bias, bf16_t* out, MfmaArgs a, int n,
                               hipStream_t stream) {
-  if constexpr (!RAGGED && !SPLIT)
+  if constexpr (!RAGGED && !SPLIT && !POOL)
     if (a.out.w & 1) return launch_wide<CB, WCB, RSP, true>(handle, in, wp, bias, out, a, n, stream);
   constexpr size_t lds_bytes = (size_t)2 * 2 * 6 * 10 * 36 * 16 + WCB * CB * 64 * 16;     // two stage buffers + the bias fragments
   a.tiles_w = (int)cdiv(a.out.w, 32);
@@ -1036,7 +1115,7 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
   a.ntiles = (int)ntiles;
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   const int64_t gx = std::min<int64_t>(ntiles, std::max<int64_t>(1, num_cu / (gy * a.csplit)));
-  auto kern = conv3d_mfma_wide_kernel<CB, WCB, RSP, RAGGED, SPLIT>;
+  auto kern = conv3d_mfma_wide_kernel<CB, WCB, RSP, RAGGED, SPLIT, POOL>;
   static bool attr_set = false;
   if (!attr_set) {
     if (hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds_bytes) != hipSuccess)
@@ -1044,7 +1123,7 @@ static h3d_status launch_wide(void* handle, const bf16_t* in, const uint4* wp, c
     attr_set = true;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)gx, (unsigned)gy, (unsigned)a.csplit), dim3(256 * WCB * RSP), lds_bytes, stream, in, wp, SPLIT ? nullptr : bias, out, a);
-  note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d,%d,%d>%s", CB, WCB, RSP, (int)RAGGED, SPLIT ? " (split)" : "");
+  note_kernel(handle, "conv3d_mfma_wide_kernel<%d,%d,%d,%d>%s", CB, WCB, RSP, (int)RAGGED, SPLIT ? " (split)" : POOL ? " (max-pooled)" : "");
   if constexpr (SPLIT) {
     const int64_t total = (int64_t)n * a.cout_k * a.out.ds * a.out.h * cdiv(a.out.w, 4);
     const int vec = a.out.w % 4 == 0 && a.out.cstride % 4 == 0 && a.out.nstride % 4 == 0 && (uintptr_t)out % 8 == 0;
@@ -1091,18 +1170,23 @@ size_t mfma_fwd_ws_bytes(void* handle, const h3d_tensor* in, const h3d_tensor* o
   return b;
 }
 
+// Two channel blocks a workgroup, or one with the rows of a plane over two wavefronts (same sums in the same order): a tile takes 0.58 to 0.64 times
+// as long with one, so it pays where the tiles, or an odd number of blocks, divide badly over the CUs.  us, two blocks and one: 64->64
+// on 4 x 8x134x54 (272 tiles) 81 and 75, 128->96 on 16x112x160 231 and 197, 256->96 446 and 375, 32->51 on 58x96x64 52 and 47, 64->64 on 24x48x48 41
+// and 29; but on 32x128x128 (512 tiles) 97 and 113, 24->48 on 2 x 22x50x54 31 and 36, 22->96 on 8 x 24x64x53 170 and 172
+static bool one_block(void* handle, int64_t ntiles, int64_t ncoblk) {
+  const int num_cu = static_cast<Handle*>(handle)->num_cu;
+  auto rounds = [&](int64_t gy) { return cdiv(ntiles, std::max<int64_t>(1, num_cu / gy)); };
+  return 62 * rounds(ncoblk) < 100 * rounds(cdiv(ncoblk, 2));
+}
+
 static h3d_status wide_conv(void* handle, const bf16_t* ip, const uint4* wq, const float* bias, bf16_t* op, const MfmaArgs& a, int n,
                             hipStream_t stream) {
   const int64_t ntiles = (int64_t)n * cdiv(a.out.ds, 4) * cdiv(a.out.h, 8) * cdiv(a.out.w, 32);
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
   if (a.csplit > 1) return launch_wide<1, 1, 2, false, true>(handle, ip, wq, bias, op, a, n, stream);
   if (a.cout_k > 32) {
-    // Two channel blocks a workgroup, or one with the rows of a plane over two wavefronts (same sums in the same order): a tile takes 0.58 to 0.64 times
-    // as long with one, so it pays where the tiles, or an odd number of blocks, divide badly over the CUs.  us, two blocks and one: 64->64
-    // on 4 x 8x134x54 (272 tiles) 81 and 75, 128->96 on 16x112x160 231 and 197, 256->96 446 and 375, 32->51 on 58x96x64 52 and 47, 64->64 on 24x48x48 41
-    // and 29; but on 32x128x128 (512 tiles) 97 and 113, 24->48 on 2 x 22x50x54 31 and 36, 22->96 on 8 x 24x64x53 170 and 172
-    auto rounds = [&](int64_t gy) { return cdiv(ntiles, std::max<int64_t>(1, num_cu / gy)); };
-    if (62 * rounds(a.ncoblk) < 100 * rounds(cdiv(a.ncoblk, 2))) return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, n, stream);
+    if (one_block(handle, ntiles, a.ncoblk)) return launch_wide<1, 1, 2>(handle, ip, wq, bias, op, a, n, stream);
     return launch_wide<1, 2>(handle, ip, wq, bias, op, a, n, stream);
   }
   // one block of output channels: with short channel loops (at most 32 input channels) or few tiles the eight-wavefront
@@ -1244,6 +1328,34 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
   hipLaunchKernelGGL(conv_split_reduce_kernel, dim3((unsigned)cdiv(out_total, 256)), dim3(256), 0, stream, (const float*)a.part, bias, op,
                      a.out, q, a.csplit, out_slope);
   return launch_status(handle, "conv3d_split_reduce");
+}
+
+// Forward and 2x2x2 max pooling in one launch, for what h3d_conv3d_fwd gives to the wide kernel unsplit and without a copy: pairs of planes, rows and
+// columns that begin with the tensor, and whole pairs of pooled voxels in a row.
+bool wide_pool_supported(void* handle, const h3d_tensor* in, const h3d_tensor* z, const h3d_tensor* y) {
+  if (!mfma_fwd_supported(in, z) || y->dtype != H3D_BF16 || conv3d_thin_supported(in, z) || !wide_dims(in, z)) return false;
+  if (z->halo_lo || z->halo_hi || z->d % 2 || z->h % 2 || z->w % 4 || !is_packed(y)) return false;
+  if ((uintptr_t)in->data % 4 || (uintptr_t)z->data % 4 || (uintptr_t)y->data % 4) return false;
+  return z->n > 0 && wide_splits(in, z, static_cast<Handle*>(handle)->num_cu) == 1;
+}
+h3d_status conv3d_wide_pool(void* handle, const h3d_tensor* in, const void* w, const float* bias, h3d_tensor* z, h3d_tensor* y, float out_slope, void* ws,
+                            size_t ws_bytes, hipStream_t stream) {
+  MfmaArgs a;
+  a.in = a.mask = make_geo(in); a.out = make_geo(z); a.yp = make_geo(y);
+  a.cin_k = in->c; a.cout_k = z->c;
+  wp_dims(a.cin_k, a.cout_k, &a.nchunks, &a.ncoblk);
+  a.out_slope = out_slope; a.mask_slope = 1.f;
+  a.csplit = 1; a.chunks_per_split = a.nchunks; a.pairs = 1; a.part = nullptr;
+  a.ypool = (bf16_t*)y->data;
+  if (!ws || ws_bytes < mfma_base_ws_bytes(in, z, static_cast<Handle*>(handle)->num_cu, false)) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace too small");
+  if ((uintptr_t)ws % 16) return fail(handle, H3D_EWORKSPACE, "conv3d: workspace must be 16-byte aligned");
+  taps_pack(taps_pack_job(w, ws, a.cin_k, a.cout_k, TAPS_FWD, a.nchunks, 27), stream);
+  const int64_t ntiles = (int64_t)z->n * cdiv(a.out.ds, 4) * cdiv(a.out.h, 8) * cdiv(a.out.w, 32);
+  const bf16_t* ip = (const bf16_t*)in->data;
+  const uint4* wq = (const uint4*)ws;
+  bf16_t* op = (bf16_t*)z->data;
+  return one_block(handle, ntiles, a.ncoblk) || a.cout_k <= 32 ? launch_wide<1, 1, 2, false, false, true>(handle, ip, wq, bias, op, a, z->n, stream)
+                                                               : launch_wide<1, 2, 1, false, false, true>(handle, ip, wq, bias, op, a, z->n, stream);
 }
 
 }  // namespace h3d

@@ -261,7 +261,7 @@ class UNetLevel:
     activation-backward passes produce g tensors whose halos are exchanged the same way."""
 
     def __init__(self, x: Slab, params: dict, dout: torch.Tensor, faces: dict):
-        from . import (ACT_RELU, FACE_D_HI, FACE_D_LO, POOL_MAX, act_bwd, concat_c, deconv2_bwd_data, deconv2_bwd_filter,
+        from . import (ACT_RELU, FACE_D_HI, FACE_D_LO, POOL_MAX, act_bwd, concat_c, conv3d_fwd_maxpool, deconv2_bwd_data, deconv2_bwd_filter,
                        deconv2_fwd, halo_unpack, split_c)
         self.ws = Workspace()
         self.x, self.P, self.faces = x, params, faces
@@ -312,8 +312,8 @@ class UNetLevel:
         W = {k: v[0] for k, v in params.items()}
         dflops = 2 * 128 * 64 * T["up"].t.numel() // 64
         op("c1_fwd", lambda: conv3d_fwd(x, *P["c1"], T["a1"], R, 0.0, ws), cflops("c1", T["a1"]), (x.t, T["a1"].t, W["c1"]))
-        op("c2_fwd", lambda: conv3d_fwd(T["a1"], *P["c2"], T["a2"], R, 0.0, ws), cflops("c2", T["a2"]), (T["a1"].t, T["a2"].t, W["c2"]))
-        op("pool_fwd", lambda: pool3d_fwd(T["a2"], T["p"], POOL_MAX), 0, (T["a2"].t, T["p"].interior))
+        op("c2_fwd_pool", lambda: conv3d_fwd_maxpool(T["a1"], *P["c2"], T["a2"], T["p"], R, 0.0, ws), cflops("c2", T["a2"]),
+           (T["a1"].t, T["a2"].t, T["p"].interior, W["c2"]))
         exchange("p", T["p"], 2)
         op("c3_fwd", lambda: conv3d_fwd(T["p"], *P["c3"], T["b1"], R, 0.0, ws), cflops("c3", T["b1"]), (T["p"].t, T["b1"].t, W["c3"]))
         op("c4_fwd", lambda: conv3d_fwd(T["b1"], *P["c4"], T["b2"], R, 0.0, ws), cflops("c4", T["b2"]), (T["b1"].t, T["b2"].t, W["c4"]))

@@ -132,3 +132,35 @@ def test_pool_fwd_with_mask_equals_the_two_separate_passes(shape, halo):
         zz = h3d.Slab(torch.zeros((1, 1, 2, 2, 8), dtype=torch.bfloat16, device="cuda"))
         h3d.pool3d_fwd_mask(zz, h3d.Slab(torch.zeros((1, 1, 1, 1, 4), dtype=torch.bfloat16, device="cuda")), m2)
     assert e.value.status == -2
+
+
+# (N, Cin, Cout, D, H, W, pooled halo, view): tiles of 4 x 8 x 32 cut by every extent, both forms (one and two channel blocks a workgroup), a block of which few
+# channels exist, several tiles a workgroup, and shapes that run as two passes (rows of an odd number of pairs, 16 columns, two planes)
+@pytest.mark.parametrize("case", [(1, 16, 32, 4, 8, 32, 0, False), (2, 24, 40, 6, 10, 36, 1, False), (1, 8, 5, 4, 4, 20, 0, True), (1, 33, 70, 10, 18, 68, 2, True),
+                                  (2, 16, 64, 36, 66, 100, 0, False), (1, 17, 33, 8, 6, 40, 1, True), (1, 16, 24, 6, 8, 34, 0, False), (1, 16, 24, 4, 8, 16, 0, True),
+                                  (1, 16, 24, 2, 8, 40, 0, False)])
+def test_conv_fwd_maxpool_equals_the_two_calls(case):
+    """z and the pooled tensor have the bits of the separate calls, infinities and NaN among the inputs; nothing else is written."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W, halo, view = case
+    g = torch.Generator(device="cuda").manual_seed(D * W + Co)
+    x = torch.randn((N, Ci, D + 2, H, W), generator=g, device="cuda").bfloat16()
+    x[0, 0, 1, 1, 3], x[0, Ci - 1, D // 2, H // 2, W - 2] = float("inf"), float("nan")
+    xs = h3d.Slab(x, 1, 1, D, 4 * D)
+    w = (torch.rand((Co, Ci, 3, 3, 3), generator=g, device="cuda") - 0.5).bfloat16()
+    b = torch.rand((Co,), generator=g, device="cuda") - 0.5
+    got = []
+    for fused in (True, False):
+        z = torch.full((N, Co + 3, D + 2, H, W) if view else (N, Co, D, H, W), 5.0, dtype=torch.bfloat16, device="cuda")
+        zs = h3d.Slab(z, 1, 1, D, 4 * D).channels(2, 2 + Co, 0, 0) if view else h3d.Slab(z, 0, 0, D, 4 * D)
+        y = torch.full((N, Co, D // 2 + 2 * halo, H // 2, W // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+        ys = h3d.Slab(y, halo, halo, D // 2, 2 * D)
+        if fused:
+            h3d.conv3d_fwd_maxpool(xs, w, b, zs, ys, h3d.ACT_RELU, 0.0)
+            assert h3d.h3d_last_kernel().endswith("(max-pooled)") == (W % 4 == 0 and W > 16 and D > 2), h3d.h3d_last_kernel()
+        else:
+            h3d.conv3d_fwd(xs, w, b, zs, h3d.ACT_RELU, 0.0)
+            h3d.pool3d_fwd(zs, ys, h3d.POOL_MAX)
+        got.append((z.view(torch.int16).clone(), y.view(torch.int16).clone()))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
