@@ -220,6 +220,7 @@ namespace h3d {
 namespace {
 
 constexpr int DF_NW = 8;
+constexpr int DF_GRP = 16;       // row blocks (of 4 output channels) of a workgroup
 constexpr int DF_CBI = 8;        // 32-voxel column blocks staged per iteration (one per wavefront)
 
 struct DfwArgs {
@@ -255,13 +256,13 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int Wc = a.x.w, Hc = a.x.h, Dc = a.x.d, Wf = a.y.w;
-  const int nrb = (8 * a.cout + 31) / 32;
+  const int nrb = (8 * a.cout + 31) / 32, rb0 = (int)blockIdx.y * DF_GRP + wave;      // a workgroup has up to 64 output channels
 
   // ---- this wavefront's weight fragments
   uint4 A[RBW][KS];
 #pragma unroll
   for (int j = 0; j < RBW; ++j) {
-    const int rb = wave + DF_NW * j;
+    const int rb = rb0 + DF_NW * j;
 #pragma unroll
     for (int s = 0; s < KS; ++s) A[j][s] = rb < nrb ? wp[((int64_t)rb * KS + s) * 64 + lane] : uint4{0, 0, 0, 0};
   }
@@ -271,7 +272,7 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
   for (int j = 0; j < RBW; ++j)
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int co = 4 * (wave + DF_NW * j) + q;
+      const int co = 4 * (rb0 + DF_NW * j) + q;
       bv[j][q] = (bias && co < a.cout) ? bias[co] : 0.f;
     }
 
@@ -371,7 +372,7 @@ __global__ void __launch_bounds__(64 * DF_NW, 2) deconv_fw_mfma_kernel(const bf1
       const int vo = wv < Wc ? 2 * ((2 * d + half + a.y.hlo) * (int)a.y.plane + 2 * h * Wf + 2 * wv) : ROW_OOB;
 #pragma unroll
       for (int j = 0; j < RBW; ++j) {
-        const int rb = wave + DF_NW * j;
+        const int rb = rb0 + DF_NW * j;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
           const int co = 4 * rb + q;
@@ -401,8 +402,9 @@ h3d_status dfw_launch_as(void* handle, const bf16_t* x, const uint4* wp, const f
     attr_set = true;
   }
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
-  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu, cdiv(a.ncb, DF_CBI)));
-  hipLaunchKernelGGL((deconv_fw_mfma_kernel<RBW, KS, STREAM, V16>), dim3((unsigned)grid), dim3(64 * DF_NW), lds_bytes, stream, x, wp, bias, y, a);
+  const int64_t groups = cdiv(a.cout, 4 * DF_GRP);      // one resident round over all of them
+  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu / groups, cdiv(a.ncb, DF_CBI)));
+  hipLaunchKernelGGL((deconv_fw_mfma_kernel<RBW, KS, STREAM, V16>), dim3((unsigned)grid, (unsigned)groups), dim3(64 * DF_NW), lds_bytes, stream, x, wp, bias, y, a);
   note_kernel(handle, "deconv_fw_mfma_kernel<%d,%d,%d,%d>", RBW, KS, (int)STREAM, (int)V16);
   return H3D_OK;
 }
@@ -418,15 +420,18 @@ h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const floa
 
 }  // namespace
 
+// Up to 1024 output channels, 64 a workgroup (each group reads x again, less than it writes).  us, direct kernel and here: 128->128 on 32x64x64 545 and 63,
+// 64->96 on 16x48x80 112 and 29, 28->102 on 4 x 26x26x84 219 and 118, 32->128 on 12x16x80 29.7 and 14.5, 24->96 on 4x8x8 14.7 and 11.7.
+constexpr int DF_COUT = 1024;
 bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
-  if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > 64 || (uintptr_t)y->data % 4 != 0) return false;
+  if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > DF_COUT || (uintptr_t)y->data % 4 != 0) return false;
   if (make_geo(y).cstride % 2 != 0 || make_geo(y).nstride % 2 != 0) return false;      // results leave as pairs in one dword
   // Ragged rows with few channels stay with the direct kernel, which reads x once per 8 output channels; this one pads the channels of
   // both sides.  us, direct and here: 8->16 on 8x9x10 8.9 and 10.0, 16->16 there 12.3 and 10.0; 16->16 on 32x62x66 21 and 26, 16->32 there
-  // 33 and 26; 4->4 on 2 x 24x70x90 13 and 37.
+  // 33 and 26; 4->4 on 2 x 24x70x90 13 and 37; 16->72 on 8x10x14 12.2 and 12.7.
   if (!rows_v16(x)) {
     if (!rows_any(x)) return false;
-    if ((int64_t)x->n * x->d * x->h * x->w < 49152 ? x->c < 16 : x->c * y->c < 512) return false;
+    if ((int64_t)x->n * x->d * x->h * x->w < 49152 ? x->c < (y->c > 64 ? 17 : 16) : x->c * y->c < 512) return false;
   }
   const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
   const int64_t ys = (int64_t)y->c * (y->halo_lo + y->d + y->halo_hi) * y->h * y->w * 2;
@@ -448,7 +453,7 @@ h3d_status deconv_fw_mfma(void* handle, const h3d_tensor* x, const void* w, cons
   a.ncb = (int64_t)x->n * x->d * x->h * a.wblks;
   if (a.ncb == 0) return H3D_OK;
   if (!ws || ws_bytes < deconv_fw_mfma_ws_bytes(x, y) || (uintptr_t)ws % 16) return fail(handle, H3D_EWORKSPACE, "deconv2_fwd: workspace too small or misaligned");
-  const int ks = a.cin > 64 ? 8 : 4, nrb = (int)cdiv(8 * (int64_t)a.cout, 32), rbw = (int)cdiv(nrb, DF_NW);
+  const int ks = a.cin > 64 ? 8 : 4, nrb = (int)cdiv(8 * (int64_t)a.cout, 32), rbw = nrb > DF_NW ? 2 : 1;
   hipLaunchKernelGGL(deconv_fw_pack_kernel, dim3((unsigned)cdiv((int64_t)nrb * ks * 512, 256)), dim3(256), 0, stream, (const bf16_t*)w,
                      (bf16_t*)ws, a.cin, a.cout, nrb, ks);
   const bf16_t* xp = (const bf16_t*)x->data;

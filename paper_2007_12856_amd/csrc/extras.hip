@@ -711,7 +711,8 @@ extern "C" size_t h3d_deconv2_workspace_bytes(void* handle, int op, const h3d_te
   size_t b = 0;
   if (op == H3D_OP_FWD) {
     b = (size_t)x->c * cdiv(y->c, DC_COT) * DC_COT * 8 * 4;
-    if (deconv_fw_mfma_supported(x, y)) b = std::max(b, deconv_fw_mfma_ws_bytes(x, y));
+    // (whatever the extents: a workspace for one volume does for another of the same channels)
+    if (x->dtype == H3D_BF16 && x->c >= 1 && x->c <= 128 && y->c >= 1 && y->c <= 1024) b = std::max(b, deconv_fw_mfma_ws_bytes(x, y));
   }
   else if (op == H3D_OP_BWD_DATA) b = (size_t)y->c * 8 * cdiv(x->c, DC_COT) * DC_COT * 4;
   else if (op == H3D_OP_BWD_FILTER) {

@@ -101,6 +101,26 @@ def test_deconv_sweep_bf16(case):
     close(from_dev(db), dbo, 2e-4)
 
 
+@pytest.mark.parametrize("N,cin,cout,d,H,W,fast", [(1, 17, 65, 2, 3, 8, True), (2, 64, 96, 1, 5, 40, True), (1, 70, 128, 2, 3, 33, True), (1, 20, 129, 3, 2, 31, True),
+                                                   (1, 9, 200, 2, 4, 16, True), (1, 16, 72, 2, 5, 14, False), (1, 130, 66, 1, 3, 8, False)])
+def test_deconv_forward_of_more_than_64_output_channels(N, cin, cout, d, H, W, fast):
+    """Groups of 64 output channels, the last one with few of them, whole and ragged rows; nothing is written around the result."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    b = np.sqrt(3.0 / (8 * cin))
+    w = quantize(synth.flat("uniform", SEED, 6000 + cout, (cin, cout, 2, 2, 2), -b, b), "bf16")
+    bias = synth.round_f32(synth.flat("uniform", SEED, 6100 + cout, (cout,), -0.1, 0.1)).astype(np.float64)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 6200 + cout, (N, cin, d, H, W)), "bf16")
+    yo = orc.deconv2_fwd(xo, w, bias)
+    n = yo.a.size
+    buf = torch.full((n + 64,), 3.0, dtype=torch.bfloat16, device="cuda")
+    y = h3d.Slab(buf[32:32 + n].view(yo.a.shape), 0, 0, yo.d_offset, yo.d_global)
+    h3d.deconv2_fwd(xg, to_dev(w, "bf16"), to_dev(bias, "f32"), y)
+    assert h3d.h3d_last_kernel().startswith("deconv_fw_mfma_kernel") == fast, h3d.h3d_last_kernel()
+    close(from_dev(y.t), yo.a, TOL["bf16"])
+    assert torch.all(buf[:32] == 3.0) and torch.all(buf[32 + n:] == 3.0)
+
+
 @pytest.mark.parametrize("case", [(0, 1, 33, 20, 2, 5, 7, 0), (1, 2, 16, 17, 1, 3, 33, 1), (2, 1, 70, 64, 3, 4, 45, 2), (3, 1, 128, 24, 1, 2, 3, 0),
                                   (4, 1, 5, 9, 2, 1, 40, 1), (5, 3, 100, 34, 2, 9, 100, 0), (6, 1, 1, 1, 1, 2, 4, 2)])
 def test_deconv_ragged_rows_bf16(case):
