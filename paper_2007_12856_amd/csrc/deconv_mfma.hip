@@ -48,11 +48,15 @@ __global__ void __launch_bounds__(64 * DD_NW, 2) deconv_bd_mfma_kernel(const bf1
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int nks = (a.cout + 1) / 2;
+  // this workgroup's channels of dx
+  const int ci0 = (int)blockIdx.y * 32 * MRB, ncin = min(a.cin - ci0, 32 * MRB);
+  const uint32_t x_bytes = (uint32_t)(a.x.nstride - ci0 * a.x.cstride) * 2;
+  dx += ci0 * a.x.cstride;
 
   // ---- W[ci][co][8] -> LDS [co][ci]; rows of a padding channel are zero (their dy operand is zero too)
   {
-    const uint4* wu = reinterpret_cast<const uint4*>(w);
-    const int total = a.cin * a.cout;
+    const uint4* wu = reinterpret_cast<const uint4*>(w) + (int64_t)ci0 * a.cout;
+    const int total = ncin * a.cout;
     for (int i = tid; i < total; i += 64 * DD_NW) {
       const int ci = i / a.cout, co = i % a.cout;
       lds[co * CP + ci] = wu[i];
@@ -127,14 +131,14 @@ __global__ void __launch_bounds__(64 * DD_NW, 2) deconv_bd_mfma_kernel(const bf1
     // (buffer stores: the lane's voxel offset plus a scalar channel offset; a store to a channel beyond Cin or a
     //  column beyond W gets an out-of-range offset and is dropped)
     {
-      const __amdgpu_buffer_rsrc_t rs_x = row_rsrc(dx + n * a.x.nstride, (uint32_t)a.x.nstride * 2);
+      const __amdgpu_buffer_rsrc_t rs_x = row_rsrc(dx + n * a.x.nstride, x_bytes);
       const int vo = wv < Wc ? 2 * (4 * half * (int)a.x.cstride + (d + a.x.hlo) * (int)a.x.plane + h * Wc + wv) : ROW_OOB;
 #pragma unroll
       for (int rb = 0; rb < MRB; ++rb)
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
           const int ci_u = rb * 32 + 8 * (i / 4) + (i % 4);      // wave-uniform part of the channel
-          const bool ch_ok = ci_u + 4 * half < a.cin;
+          const bool ch_ok = ci_u + 4 * half < ncin;
           __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(acc[rb][i]), rs_x, ch_ok ? vo : ROW_OOB,
                                                 __builtin_amdgcn_readfirstlane(2 * ci_u * (int)a.x.cstride), 0);
         }
@@ -153,29 +157,37 @@ h3d_status dbd_launch_as(void* handle, const bf16_t* dy, const bf16_t* w, bf16_t
     attr_bytes = lds_bytes;
   }
   const int num_cu = static_cast<Handle*>(handle)->num_cu;
-  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu, cdiv(a.ncb, DD_NW)));
-  hipLaunchKernelGGL((deconv_bd_mfma_kernel<MRB, STREAM>), dim3((unsigned)grid), dim3(64 * DD_NW), lds_bytes, stream, dy, w, dx, a);
+  const int64_t groups = cdiv(a.cin, 32 * MRB);
+  const int64_t grid = std::max<int64_t>(1, std::min<int64_t>(num_cu / groups, cdiv(a.ncb, DD_NW)));
+  hipLaunchKernelGGL((deconv_bd_mfma_kernel<MRB, STREAM>), dim3((unsigned)grid, (unsigned)groups), dim3(64 * DD_NW), lds_bytes, stream, dy, w, dx, a);
   note_kernel(handle, "deconv_bd_mfma_kernel<%d,%d>", MRB, (int)STREAM);
   return H3D_OK;
 }
 static int64_t fine_bytes(const Geo& y, int c) { return (int64_t)y.n * c * y.d * y.plane * (int64_t)sizeof(bf16_t); }
 template <int MRB>
 h3d_status dbd_launch(void* handle, const bf16_t* dy, const bf16_t* w, bf16_t* dx, const DbdArgs& a, size_t lds_bytes, hipStream_t stream) {
-  return fine_bytes(a.y, a.cout) >= STREAM_PAST_CACHE_BYTES ? dbd_launch_as<MRB, true>(handle, dy, w, dx, a, lds_bytes, stream)
+  // (groups of channels of dx read dy at about the same time: through the cache)
+  return a.cin <= 32 * MRB && fine_bytes(a.y, a.cout) >= STREAM_PAST_CACHE_BYTES ? dbd_launch_as<MRB, true>(handle, dy, w, dx, a, lds_bytes, stream)
                                                             : dbd_launch_as<MRB, false>(handle, dy, w, dx, a, lds_bytes, stream);
 }
 
-size_t dbd_lds_bytes(int cin, int cout) {
-  const int mrb = (int)cdiv(cin, 32);
-  return (size_t)((cout + 1) / 2 * 2) * ((32 * mrb) | 1) * 16;
+// The filter lies in LDS, 32 MRB channels of dx of it a workgroup: all blocks of 32 where up to four fit, else groups of blocks in blockIdx.y, each of which
+// reads dy.  us, direct kernel and here: 128 -> 128 channels (of dx and of dy) from 32x64x64 634 and 68 (402 MB of dy in two passes), 128 -> 96 460 and 51,
+// 96 -> 128 from 16x32x64 139 and 22, 256 -> 64 from 8x32x32 55 and 15, 200 -> 33 from 4x20x24 22 and 12.
+size_t dbd_lds_bytes(int mrb, int cout) { return (size_t)((cout + 1) / 2 * 2) * ((32 * mrb) | 1) * 16; }
+int dbd_mrb(int cin, int cout) {
+  const int64_t blocks = cdiv(cin, 32);
+  int64_t mrb = std::min<int64_t>(4, blocks);
+  while (mrb > 0 && dbd_lds_bytes((int)mrb, cout) > 160 * 1024) --mrb;
+  return mrb == 0 ? 0 : (int)cdiv(blocks, cdiv(blocks, mrb));      // groups alike
 }
 
 }  // namespace
 
 bool deconv_bd_mfma_supported(const h3d_tensor* dx, const h3d_tensor* dy, const void* w) {
-  if (dx->dtype != H3D_BF16 || dx->c < 1 || dx->c > 128 || dy->c < 1) return false;
+  if (dx->dtype != H3D_BF16 || dx->c < 1 || dx->c > 1024 || dy->c < 1) return false;
   if ((uintptr_t)dy->data % 4 != 0 || (uintptr_t)w % 16 != 0) return false;
-  if (dbd_lds_bytes(dx->c, dy->c) > 160 * 1024) return false;
+  if (dbd_mrb(dx->c, dy->c) == 0) return false;
   const int64_t ys = (int64_t)dy->c * (dy->halo_lo + dy->d + dy->halo_hi) * dy->h * dy->w * 2;
   const int64_t xs = (int64_t)dx->c * (dx->halo_lo + dx->d + dx->halo_hi) * dx->h * dx->w * 2;
   return ys < ((int64_t)1 << 31) && xs < ((int64_t)1 << 31);
@@ -188,8 +200,8 @@ h3d_status deconv_bd_mfma(void* handle, const h3d_tensor* dy, const void* w, h3d
   a.wblks = (int)cdiv(dx->w, 32);
   a.ncb = (int64_t)dx->n * dx->d * dx->h * a.wblks;
   if (a.ncb == 0) return H3D_OK;
-  const size_t lds_bytes = dbd_lds_bytes(a.cin, a.cout);
-  const int mrb = (int)cdiv(a.cin, 32);
+  const int mrb = dbd_mrb(a.cin, a.cout);
+  const size_t lds_bytes = dbd_lds_bytes(mrb, a.cout);
   const bf16_t* yp = (const bf16_t*)dy->data;
   const bf16_t* wp = (const bf16_t*)w;
   bf16_t* xp = (bf16_t*)dx->data;

@@ -121,6 +121,25 @@ def test_deconv_forward_of_more_than_64_output_channels(N, cin, cout, d, H, W, f
     assert torch.all(buf[:32] == 3.0) and torch.all(buf[32 + n:] == 3.0)
 
 
+@pytest.mark.parametrize("N,cin,cout,d,H,W,blocks", [(1, 129, 5, 2, 3, 8, 3), (2, 128, 78, 1, 5, 40, 4), (2, 128, 79, 1, 5, 40, 2), (1, 97, 110, 2, 3, 33, 2), (1, 70, 156, 2, 2, 34, 2),
+                                                     (1, 40, 159, 3, 2, 31, 1), (1, 33, 310, 1, 2, 5, 1), (1, 20, 311, 1, 2, 5, 0), (1, 300, 17, 1, 4, 9, 4), (1, 1025, 3, 1, 2, 3, 0)])
+def test_deconv_backward_data_in_groups_of_input_channels(N, cin, cout, d, H, W, blocks):
+    """Blocks of 32 input channels that do not fit in one workgroup, the last group with few channels or none of a block; nothing is written around the result."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    b = np.sqrt(3.0 / (8 * cin))
+    w = quantize(synth.flat("uniform", SEED, 6300 + cout, (cin, cout, 2, 2, 2), -b, b), "bf16")
+    dyo, dyg = slab_pair(synth.flat("normal", SEED, 6400 + cout, (N, cout, 2 * d, 2 * H, 2 * W)), "bf16")
+    dxo = orc.deconv2_bwd_data(dyo, w)
+    n = dxo.a.size
+    buf = torch.full((n + 64,), 3.0, dtype=torch.bfloat16, device="cuda")
+    dx = h3d.Slab(buf[32:32 + n].view(dxo.a.shape), 0, 0, dxo.d_offset, dxo.d_global)
+    h3d.deconv2_bwd_data(dyg, to_dev(w, "bf16"), dx)
+    assert h3d.h3d_last_kernel() == (f"deconv_bd_mfma_kernel<{blocks},0>" if blocks else "deconv2_bwd_data"), h3d.h3d_last_kernel()
+    close(from_dev(dx.t), dxo.a, TOL["bf16"])
+    assert torch.all(buf[:32] == 3.0) and torch.all(buf[32 + n:] == 3.0)
+
+
 @pytest.mark.parametrize("case", [(0, 1, 33, 20, 2, 5, 7, 0), (1, 2, 16, 17, 1, 3, 33, 1), (2, 1, 70, 64, 3, 4, 45, 2), (3, 1, 128, 24, 1, 2, 3, 0),
                                   (4, 1, 5, 9, 2, 1, 40, 1), (5, 3, 100, 34, 2, 9, 100, 0), (6, 1, 1, 1, 1, 2, 4, 2)])
 def test_deconv_ragged_rows_bf16(case):
