@@ -5,7 +5,7 @@
 // of them and moves both tensors through memory three times; these kernels execute the 27.
 //
 // 64 -> 128 channels on 64^3 (14.5 GFlop and 42 MB a pass: 6 us of matrix cores, 6 us of memory), all three passes of a masked
-// layer: 818 us by the rewriting, 111 us here (kernels 32 forward, 35 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
+// layer: 818 us by the rewriting, 108 us here (kernels 29 forward, 35 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
 // At that size what bounds them is the serial chain of a workgroup (fetch a tile, transpose it into LDS, multiply): there are
 // one to two workgroups per CU, and every one lives for two to eight stages.
 #include <algorithm>
@@ -52,7 +52,9 @@ __device__ __forceinline__ int xcd_tile(int i, int n) {
 // channels in one wavefront half of the SIMDs would idle), and add their accumulators through LDS at the end, in order.
 //   NCO = 2: two wavefront pairs take 64 channels each (CB = 2 blocks of 32) and all four rows;
 //   NCO = 1: at most 64 output channels (CB = 1: 32): the pairs take two rows each.
-// Weight fragments come from L2 in packed order, one (kd,kw) step ahead.
+// Weight fragments come from L2 in packed order, two (kd,kw) steps ahead, also into the next stage, whose rows are requested behind the last fragments of
+// this one, three steps before they are needed.  us, one step ahead (and loads that the compiler had moved next to their use) and this:
+// 64->128 on 64^3 31.6 and 30.2, 128->256 on 32^3 50 and 42, 256->256 on 16x32x32 88 and 71, 64->64 on 4 x 16x32x32 23.8 and 18.9, 48->40 on 16x40x72 23.4 and 18.4.
 constexpr int SF_PITCH = 66, SF_ROWS = 9, SF_CIG = 3 * SF_ROWS * SF_PITCH, SF_UNITS = 4 * SF_CIG;   // row: 33 odd columns (from 2 w0 - 1), 32 even ones
 constexpr size_t SF_LDS = (size_t)SF_UNITS * 16;
 
@@ -142,44 +144,49 @@ __global__ void __launch_bounds__(256, 1) s2_fwd_kernel(const bf16_t* __restrict
 
   const uint4* wbase[CB];
 #pragma unroll
-  for (int c = 0; c < CB; ++c) wbase[c] = wp + (int64_t)min(blk0 + c, ncoblk - 1) * a.nchunk * 27 * 64 + lane;
+  for (int c = 0; c < CB; ++c)
+    wbase[c] = wp + ((int64_t)min(__builtin_amdgcn_readfirstlane(blk0) + c, ncoblk - 1) * a.nchunk + __builtin_amdgcn_readfirstlane(khalf)) * 27 * 64;
   const uint4* bbase = lds + (2 * khalf + (lane >> 5)) * SF_CIG + (NCO == 2 ? 0 : pair * 2 * R) * SF_PITCH + (lane & 31);
 
   const int nst = a.nchunk / 2;
+  uint4 A[3][3][CB], B[2][2 * R + 1];
+  auto load_a = [&](int st, int step) {
+#pragma unroll
+    for (int c = 0; c < CB; ++c) {
+      const __amdgpu_buffer_rsrc_t rw = row_rsrc(wbase[c] + (int64_t)st * (2 * 27 * 64), 27 * 1024);
+#pragma unroll
+      for (int kh = 0; kh < 3; ++kh)
+        A[step % 3][kh][c] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16, ((step / 3) * 9 + kh * 3 + step % 3) * 1024, 0));
+    }
+  };
+  load_a(0, 0);
+  load_a(0, 1);
   load_stage(0);
   for (int st = 0; st < nst; ++st) {
     if (st) __syncthreads();
     store_stage(st);
     __syncthreads();
-    uint4 A[2][3][CB], B[2][2 * R + 1];
-    const int64_t wchunk = (int64_t)(2 * st + khalf) * 27 * 64;
-    auto load_a = [&](int step) {
-#pragma unroll
-      for (int kh = 0; kh < 3; ++kh)
-#pragma unroll
-        for (int c = 0; c < CB; ++c) A[step & 1][kh][c] = wbase[c][wchunk + ((step / 3) * 9 + kh * 3 + step % 3) * 64];
-    };
     auto load_b = [&](int step) {
       const int kw = step % 3;
 #pragma unroll
       for (int r = 0; r < 2 * R + 1; ++r) B[step & 1][r] = bbase[((step / 3) * SF_ROWS + r) * SF_PITCH + (kw == 1 ? 33 : kw / 2)];
     };
-    load_a(0);
     load_b(0);
 #pragma unroll
     for (int step = 0; step < 9; ++step) {
-      if (step + 1 < 9) {
-        load_a(step + 1);
-        load_b(step + 1);
-      }
-      // requests return in order: the next stage's rows are asked for behind the last weight fragments of this one
-      if (step == 7 && st + 1 < nst) load_stage(st + 1);
+      if (step + 2 < 9) load_a(st, step + 2);
+      if (step + 1 < 9) load_b(step + 1);
+      // Requests return in order: the next stage's rows are asked for behind the last weight fragments of this one, and the next stage's first
+      // fragments behind them.
+      if (step == 6 && st + 1 < nst) load_stage(st + 1);
+      if (step >= 7 && st + 1 < nst) load_a(st + 1, step - 7);
+      __builtin_amdgcn_sched_barrier(0);      // (or the compiler puts the loads next to their use)
 #pragma unroll
       for (int r = 0; r < R; ++r)
 #pragma unroll
         for (int kh = 0; kh < 3; ++kh)
 #pragma unroll
-          for (int c = 0; c < CB; ++c) acc[c][r] = mfma32(A[step & 1][kh][c], B[step & 1][2 * r + kh], acc[c][r]);
+          for (int c = 0; c < CB; ++c) acc[c][r] = mfma32(A[step % 3][kh][c], B[step & 1][2 * r + kh], acc[c][r]);
     }
   }
 
