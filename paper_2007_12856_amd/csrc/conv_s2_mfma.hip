@@ -5,7 +5,7 @@
 // of them and moves both tensors through memory three times; these kernels execute the 27.
 //
 // 64 -> 128 channels on 64^3 (14.5 GFlop and 42 MB a pass: 6 us of matrix cores, 6 us of memory), all three passes of a masked
-// layer: 818 us by the rewriting, 108 us here (kernels 29 forward, 35 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
+// layer: 818 us by the rewriting, 102 us here (kernels 29 forward, 30 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
 // At that size what bounds them is the serial chain of a workgroup (fetch a tile, transpose it into LDS, multiply): there are
 // one to two workgroups per CU, and every one lives for two to eight stages.
 #include <algorithm>
@@ -296,51 +296,44 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
   const int mcs = (int)a.m.cstride, moff = cq * 4 * mcs + (z + pl + a.m.hlo) * (int)a.m.plane + (h0 + row) * W2;
   auto far_row = [&](int co) { return ms + (int64_t)co * a.m.cstride + (int64_t)(z + pl + a.m.hlo) * a.m.plane + (int64_t)(h0 + row) * W2; };
   const int unit = SD_W + (cq >> 1) * SD_CIG + (pl * SD_ROWS + row) * SD_PITCH + 8 * cg;
-  uint4 v[4], mv[4], wv0, wv1, wv2, wv3;
-#pragma unroll
-  for (int e = 0; e < 4; ++e) v[e] = mv[e] = uint4{0u, 0u, 0u, 0u};
+  // The loads of a chunk are the same buffer loads in every thread, without a branch around them: plain loads, and loads under a condition that returns
+  // at their use, the compiler moves behind the products (or issues again there), and the chunk then waits for all of its latency.  us with a mask and without, before
+  // and after: 128 -> 64 channels onto 64^3 34.7, 30.1 and 30.3, 25.4; 256 -> 128 onto 32^3 53, 45 and 46.9, 37.9; 256 -> 256 onto 16x32x32 60.5, 52.7 and 49.8, 40.9;
+  // 64 -> 32 onto 64x64x128 22.7, 20.1 and 21.5, 18.4; 16 -> 16 onto 64x128x128 19.7, 17.4 and 19.6, 17.2.  Rows two chunks ahead (a second set of registers)
+  // are slower: 31.8, 25.9 on the first, 24.8, 20.0 on the last.
+  uint4 v[4], mv[4], wv[4];
   const uint4* wsrc = wp + (int64_t)blockIdx.y * a.nchunk * SD_W;
-  auto load_chunk = [&](int c) {
-    const uint4* wc = wsrc + (int64_t)c * SD_W + tid;
-    wv0 = wc[0];
-    wv1 = wc[512];
-    wv2 = wc[1024];
-    wv3 = wc[min(1536, SD_W - 1 - tid)];
+  const int last_unit = min(1536 + tid, SD_W - 1);      // the threads beyond the filter all take its last unit
+  auto load_weights = [&](int c) {
+    const __amdgpu_buffer_rsrc_t rw = row_rsrc(wsrc + (int64_t)c * SD_W, SD_W * 16);
+#pragma unroll
+    for (int k = 0; k < 4; ++k) wv[k] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(rw, 16 * (k < 3 ? tid + 512 * k : last_unit), 0, 0));
+  };
+  auto load_rows = [&](int c) {
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       const bool ok = ok0 && c * 16 + cq * 4 + e < a.cout;
-      if (full) {
-        v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y), ok);
-        if (MASK == S2_MASK) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m), ok);
-        if (MASK == S2_FAR_MASK) mv[e] = s2_far8(far_row(c * 16 + cq * 4 + e), col, W2, ok);
-      } else if (tail) {
-        v[e].x = row1(rs, off + (c * 16 + e) * cstride, col, W2, ok);
-        if (MASK == S2_MASK) mv[e].x = row1(rm, moff + (c * 16 + e) * mcs, col, W2, ok);
-        if (MASK == S2_FAR_MASK) mv[e].x = s2_far8(far_row(c * 16 + cq * 4 + e), col, min(col + 1, W2), ok).x;
-      }
+      v[e] = row8<V16>(rs, off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y), ok);
+      if (MASK == S2_MASK) mv[e] = row8<V16>(rm, moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m), ok);
+      if (MASK == S2_FAR_MASK) mv[e] = s2_far8(far_row(c * 16 + cq * 4 + e), col, W2, ok);
     }
   };
   auto store_chunk = [&](int c) {
     uint4* dst = lds + (c & 1) * SD_BUF;
-    dst[tid] = wv0;
-    dst[tid + 512] = wv1;
-    dst[tid + 1024] = wv2;
-    if (tid + 1536 < SD_W) dst[tid + 1536] = wv3;
-    uint2* half = reinterpret_cast<uint2*>(dst + unit) + (cq & 1);
-    if (full) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        v[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y));
-        if (MASK) v[e] = mask8(v[e], MASK == S2_MASK ? fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)) : mv[e], a.slope);
-      }
+    for (int k = 0; k < 3; ++k) dst[tid + 512 * k] = wv[k];
+    dst[last_unit] = wv[3];
+    uint4 g[4];
 #pragma unroll
-      for (int k = 0; k < 8; ++k) half[2 * k] = column_half(v, k);
-    } else if (tail) {
-      uint32_t s[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) s[e] = MASK ? mask2(v[e].x, mv[e].x, a.slope) & 0xffffu : v[e].x;
-      *half = uint2{s[0] | (s[1] << 16), s[2] | (s[3] << 16)};
+    for (int e = 0; e < 4; ++e) {
+      g[e] = fix8<V16>(v[e], off + (c * 16 + e) * cstride, col, W2, (int)stored_span(a.y));
+      if (MASK) g[e] = mask8(g[e], MASK == S2_MASK ? fix8<V16>(mv[e], moff + (c * 16 + e) * mcs, col, W2, (int)stored_span(a.m)) : mv[e], a.slope);
     }
+    uint2* half = reinterpret_cast<uint2*>(dst + unit) + (cq & 1);
+    if (full || tail) half[0] = column_half(g, 0);
+    if (full)
+#pragma unroll
+      for (int k = 1; k < 8; ++k) half[2 * k] = column_half(g, k);
   };
 
   f32x16 acc[8];                  // parity (pd, ph, pw)
@@ -349,11 +342,15 @@ __global__ void __launch_bounds__(512) s2_bwd_data_kernel(const bf16_t* __restri
 #pragma unroll
     for (int i = 0; i < 16; ++i) acc[p][i] = 0.f;
 
-  load_chunk(0);
+  load_weights(0);
+  load_rows(0);
   store_chunk(0);
   for (int c = 0; c < a.nchunk; ++c) {
-    __syncthreads();
-    if (c + 1 < a.nchunk) load_chunk(c + 1);
+    asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    if (c + 1 < a.nchunk) {
+      load_weights(c + 1);
+      load_rows(c + 1);
+    }
     const uint4* wl = lds + (c & 1) * SD_BUF + lane;
     const uint4* bl = lds + (c & 1) * SD_BUF + SD_W + (lane >> 5) * SD_CIG + wave * SD_PITCH + (lane & 31);
 #pragma unroll

@@ -197,6 +197,30 @@ def test_stride2_bf16_tile_edges(shape, act):
     close(from_dev(db), dbo, 2e-4, elem=elem_masked_bf("bf16"))
 
 
+@pytest.mark.parametrize("shape", [
+    (1, 20, 16, 4, 16, 32),      # one chunk of 16 output channels: nothing is requested behind it
+    (1, 36, 65, 4, 18, 80),      # five, the last with one channel; two column tiles, a second row tile and channel block
+    (2, 8, 96, 2, 16, 144),      # six, three column tiles
+    (1, 8, 33, 2, 16, 20),       # rows that are no multiple of eight: the column behind a tile by a load that runs on
+])
+def test_stride2_bwd_data_chunks(shape):
+    """Backward-data over one to six chunks of output channels, with and without a mask, against the oracle."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    w, _ = _weights(Ci, Co, "bf16", 350)
+    wd = to_dev(w, "bf16")
+    xo, _ = slab_pair(np.zeros((N, Ci, D, H, W)), "bf16")
+    coarse = (N, Co, D // 2, H // 2, W // 2)
+    so, sg = slab_pair(synth.flat("normal", SEED, 351, coarse), "bf16")
+    dyo, dyg = slab_pair(synth.flat("normal", SEED, 352, coarse), "bf16")
+    for act in (orc.ACT_NONE, orc.ACT_LEAKY):
+        dxo = orc.conv3d_s2_bwd_data(dyo, so, w, xo, act, 0.01)
+        dxg = h3d.conv3d_s2_bwd_data(dyg, sg, wd, dev_like(dxo, "bf16"), act, 0.01)
+        assert h3d.h3d_last_kernel() == f"s2_bwd_data_kernel<{int(act != orc.ACT_NONE)},{int(W // 2 % 8 == 0)}>"
+        close(from_dev(dxg.t), dxo.a, TOL["bf16"])
+
+
 @pytest.mark.parametrize("shape", [(1, 32, 32, 4, 16, 64), (1, 20, 40, 4, 70, 70), (2, 16, 32, 4, 9, 33), (1, 64, 32, 2, 34, 130)])
 def test_stride2_an_infinity_reaches_only_the_taps_that_read_it(shape):
     """bf16 backward-filter: an infinite voxel of x next to the end of a row, column or plane makes the entries of dw infinite whose sums
