@@ -665,8 +665,9 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
   };
 
   // Epilogue of a tile (CB * 128 values per lane): everything that does not depend on the value is taken out of the
-  // per-value path.  Activation as med3(v, slope * v, +inf) (the same bits as "v > 0 ? v : slope * v" for
-  // 0 <= slope <= 1), skipped when there is none.
+  // per-value path.  The activation is skipped when there is none, and max(v, slope * v) where that has the bits of
+  // "v > 0 ? v : slope * v": 0 < slope <= 1.  Any other slope compares: above 1 the larger one is the wrong one, below 0 a zero gets the other
+  // sign, and with slope 0 the maximum loses the NaN of -inf * 0.
   auto epilogue = [&](int tile_) {
     int t = tile_;
     const int tw = t % a.tiles_w; t /= a.tiles_w;
@@ -700,11 +701,18 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
     const int cs2 = 2 * (int)a.out.cstride;
     const int vbase = (row_ch + (odd ? 1 : 0)) * cs2 + 2 * (ps * (int)a.out.plane + h0 * WO + w0 + j - (odd ? 1 : 0));
     const bool w_ok = w0 + j - (odd ? 1 : 0) < WO;
-    const bool act = a.out_slope != 1.f;        // wave-uniform
+    using T_ = std::true_type;
+    using F_ = std::false_type;
     const float slope = a.out_slope;
-    const float inf = __builtin_inff();
-    // ACT / WHOLE are wave-uniform facts: one branch per channel block, not one select per value
-    auto block = [&](int cb, auto act_c, auto whole_c) {
+    const bool act = slope != 1.f, by_max = slope > 0.f && slope <= 1.f;        // wave-uniform
+    auto activate = [&](float v, auto max_c) {
+      const float s = v * slope;
+      if (decltype(max_c)::value) asm("v_max_f32 %0, %1, %2" : "=v"(v) : "v"(v), "v"(s));
+      else v = v > 0.f ? v : s;
+      return v;
+    };
+    // ACT / BY_MAX / WHOLE are wave-uniform facts: one branch per channel block, not one select per value
+    auto block = [&](int cb, auto act_c, auto max_c, auto whole_c) {
       constexpr bool ACT = decltype(act_c)::value, WHOLE = decltype(whole_c)::value;
       const int cblk = co_blk0 + cb;
 #pragma unroll
@@ -715,11 +723,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
 #pragma unroll
         for (int b = 0; b < VB; ++b) {
           float v0 = acc[cb][b][r], v1 = acc[cb][b][r + 1];
-          if (ACT) {      // max(v, slope v): v where v > 0, slope v elsewhere (0 <= slope <= 1)
-            const float s0 = v0 * slope, s1 = v1 * slope;
-            asm("v_max_f32 %0, %1, %2" : "=v"(v0) : "v"(v0), "v"(s0));
-            asm("v_max_f32 %0, %1, %2" : "=v"(v1) : "v"(v1), "v"(s1));
-          }
+          if (ACT) { v0 = activate(v0, max_c); v1 = activate(v1, max_c); }
           const uint32_t own = pack_bf16x2(v0, v1);
           const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
           uint32_t pk = __builtin_amdgcn_perm(nb, own, sel);
@@ -748,7 +752,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
       const int wy = w0 / 2 + (j >> 1) - (second ? 1 : 0), qy = ps / 2 + a.yp.hlo, hy = h0 / 2 + (VR == 4 && second ? 1 : 0);
       const bool y_ok = wy < a.yp.w && hy < a.yp.h;
       const int ybase = 2 * ((row_ch + (odd ? 1 : 0) + (VR == 2 && second ? 2 : 0)) * (int)a.yp.cstride + qy * (int)a.yp.plane + hy * a.yp.w + wy);
-      auto block = [&](auto whole_c) {
+      auto block = [&](auto max_c, auto whole_c) {
         constexpr bool WHOLE = decltype(whole_c)::value;
         uint32_t before = 0;
 #pragma unroll
@@ -758,11 +762,7 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
           uint32_t pk[VB];
 #pragma unroll
           for (int b = 0; b < VB; ++b) {
-            float v0 = acc[0][b][r], v1 = acc[0][b][r + 1];
-            const float s0 = v0 * slope, s1 = v1 * slope;
-            asm("v_max_f32 %0, %1, %2" : "=v"(v0) : "v"(v0), "v"(s0));
-            asm("v_max_f32 %0, %1, %2" : "=v"(v1) : "v"(v1), "v"(s1));
-            const uint32_t own = pack_bf16x2(v0, v1);
+            const uint32_t own = pack_bf16x2(activate(acc[0][b][r], max_c), activate(acc[0][b][r + 1], max_c));
             const uint32_t nb = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xF, 0xF, true);
             pk[b] = __builtin_amdgcn_perm(nb, own, sel);
             const int o = w_ok && h0 + b % VR < H ? vbase + 2 * (b / VR * (int)a.out.plane + b % VR * WO) : BUF_OOB;
@@ -805,22 +805,25 @@ __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const
                                                 __builtin_amdgcn_readfirstlane(2 * co_y * (int)a.yp.cstride), 0);
         }
       };
-      if (co_blk0 * 32 + 32 <= a.cout_k) block(std::true_type{});
-      else block(std::false_type{});
+      const bool whole = co_blk0 * 32 + 32 <= a.cout_k;
+      if (whole && by_max) block(T_{}, T_{});
+      else if (whole) block(F_{}, T_{});
+      else if (by_max) block(T_{}, F_{});
+      else block(F_{}, F_{});
       return;
     }
-    using T_ = std::true_type;
-    using F_ = std::false_type;
 #pragma unroll
     for (int cb = 0; cb < CB; ++cb) {
       const int cblk = co_blk0 + cb;
       if (cblk >= a.ncoblk) continue;
       const bool whole = cblk * 32 + 32 <= a.cout_k && inside;     // the common case
       if (whole) {
-        if (act) block(cb, T_{}, T_{});
-        else block(cb, F_{}, T_{});
-      } else {
-        block(cb, T_{}, F_{});       // (slope 1 leaves the values as they are)
+        if (!act) block(cb, F_{}, F_{}, T_{});
+        else if (by_max) block(cb, T_{}, T_{}, T_{});
+        else block(cb, T_{}, F_{}, T_{});
+      } else {       // (slope 1 leaves the values as they are)
+        if (by_max) block(cb, T_{}, T_{}, F_{});
+        else block(cb, T_{}, F_{}, F_{});
       }
     }
   };

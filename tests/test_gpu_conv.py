@@ -281,6 +281,39 @@ def test_conv3d_wide_kernel_with_half_a_chunk(shape):
         assert torch.equal(got[0], got[1])
 
 
+# (N, channels in, channels out, D, H, W): half a chunk, one block of output channels, two blocks of which the last is cut, odd rows, and enough tiles for
+# two blocks a workgroup
+@pytest.mark.parametrize("shape", [(1, 8, 12, 5, 9, 34), (2, 16, 32, 4, 8, 32), (1, 24, 40, 6, 10, 36), (1, 16, 24, 3, 8, 33), (2, 16, 64, 36, 66, 100)])
+def test_conv3d_wide_kernel_activations(shape):
+    """z = y > 0 ? y : slope * y for any slope (above 1, where the larger of y and slope * y is the wrong one, and below 0) and for infinite sums (-inf * 0 is NaN): the wide kernel stores what the
+    general kernel does, which a result at an odd address gets."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = shape
+    w, bias = _weights(Ci, Co, "bf16", 96)
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    xo, xg = slab_pair(synth.flat("normal", SEED, 97, (N, Ci, D, H, W)), "bf16")
+    xi = h3d.Slab(xg.t.clone())
+    xi.t[0, Ci - 1, D // 2, H // 2, W // 2] = float("inf")
+    n = N * Co * D * H * W
+    for act, alpha, slope in ((h3d.ACT_LEAKY, 2.0, 2.0), (h3d.ACT_LEAKY, -0.5, -0.5), (h3d.ACT_LEAKY, 0.25, 0.25), (h3d.ACT_LEAKY, 1.0, 1.0), (h3d.ACT_RELU, 0.0, 0.0)):
+        for x in (xg, xi):
+            got = []
+            for shift in (0, 1):
+                buf = torch.full((n + 2,), 3.0, dtype=torch.bfloat16, device="cuda")
+                out = h3d.Slab(buf[shift:shift + n].view(N, Co, D, H, W))
+                h3d.conv3d_fwd(x, wd, bd, out, act, alpha)
+                assert ("wide" in h3d.h3d_last_kernel()) == (shift == 0), h3d.h3d_last_kernel()
+                got.append(out.t.clone())
+            assert torch.all((got[0] == got[1]) | (got[0].isnan() & got[1].isnan())), alpha
+            if x is xi:
+                around = got[0][0, :, D // 2 - 1:D // 2 + 2, H // 2 - 1:H // 2 + 2, W // 2 - 1:W // 2 + 2]      # weights of both signs: sums of both signs
+                assert bool((around == float("inf")).any()) and bool(around.isnan().any()) == (slope == 0.0)
+                assert bool((around == float("-inf")).any()) == (slope > 0.0)
+            elif n < 10 ** 5:
+                close(from_dev(got[0]), orc.conv3d_fwd(xo, w, bias, act=orc.ACT_LEAKY, alpha=slope).a, TOL["bf16"])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cin,cout", [(4, 16), (3, 5), (16, 32)])
 def test_conv3d_sharded_matches_oracle_and_unsharded_gpu(dtype, cin, cout):

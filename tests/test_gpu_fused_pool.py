@@ -164,3 +164,30 @@ def test_conv_fwd_maxpool_equals_the_two_calls(case):
             h3d.pool3d_fwd(zs, ys, h3d.POOL_MAX)
         got.append((z.view(torch.int16).clone(), y.view(torch.int16).clone()))
     assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("case", [(1, 16, 32, 4, 8, 32), (2, 24, 40, 6, 10, 36), (2, 16, 64, 36, 66, 100)])
+@pytest.mark.parametrize("act,alpha", [("LEAKY", 2.0), ("LEAKY", -0.5), ("RELU", 0.0)])
+def test_conv_fwd_maxpool_activations(case, act, alpha):
+    """Slopes outside (0, 1], and infinite sums: z and the pooled tensor are those of the general kernel (a result at an odd address) and of a pooling pass
+    over what it stored."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = case
+    g = torch.Generator(device="cuda").manual_seed(D * W + Co)
+    x = torch.randn((N, Ci, D, H, W), generator=g, device="cuda").bfloat16()
+    x[0, 0, 1, 1, 3], x[0, Ci - 1, D // 2, H // 2, W - 2] = float("inf"), float("-inf")
+    w = (torch.rand((Co, Ci, 3, 3, 3), generator=g, device="cuda") - 0.5).bfloat16()
+    b = torch.rand((Co,), generator=g, device="cuda") - 0.5
+    a = getattr(h3d, "ACT_" + act)
+    n = N * Co * D * H * W
+    z = torch.zeros((n + 1,), dtype=torch.bfloat16, device="cuda")[1:].view(N, Co, D, H, W)
+    h3d.conv3d_fwd(h3d.Slab(x), w, b, h3d.Slab(z), a, alpha)
+    assert "wide" not in h3d.h3d_last_kernel()
+    want = z.clone(), torch.empty((N, Co, D // 2, H // 2, W // 2), dtype=torch.bfloat16, device="cuda")
+    h3d.pool3d_fwd(h3d.Slab(want[0]), h3d.Slab(want[1]), h3d.POOL_MAX)
+    got = torch.empty_like(want[0]), torch.empty_like(want[1])
+    h3d.conv3d_fwd_maxpool(h3d.Slab(x), w, b, h3d.Slab(got[0]), h3d.Slab(got[1]), a, alpha)
+    assert h3d.h3d_last_kernel().endswith("(max-pooled)"), h3d.h3d_last_kernel()
+    for t, r in zip(got, want):
+        assert torch.all((t == r) | (t.isnan() & r.isnan()))
