@@ -127,7 +127,10 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   int voff[ROUNDS][NV], moffb[MASKED ? ROUNDS : 1][NV];
   int n_plan = 0;   // sample index of the planned tile (wave-uniform)
   const __amdgpu_buffer_rsrc_t rs_w = make_rsrc(wp, (uint32_t)a.ncoblk * a.nchunks * 27 * 1024);
-  auto plan_tile = [&](int tile) {
+  // (Inlined by force: where the compiler kept one of these as a function, every array and the arguments themselves lay in scratch, 816 to 912 bytes a
+  // lane in five masked forms for odd rows or addresses.  us, so and inlined, without room for the copy: masked 8->8 on 9x30x41 72 and 34, 64->64 on
+  // 2x32x33 167 and 71, 32->32 on 2 x 12x30x15 58 and 35; an odd result, 16->8 on 4 x 16x64x64 80 and 42.)
+  auto plan_tile = [&](int tile) __attribute__((always_inline)) {
     int t = tile;
     const int tw = t % a.tiles_w; t /= a.tiles_w;
     const int th = t % a.tiles_h; t /= a.tiles_h;
@@ -163,7 +166,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
   // `live` = false turns every load into an out-of-range (zero, no traffic) one: the last stage of a
   // workgroup has nothing to prefetch, but keeping the load count identical on every path lets the
   // compiler use exact s_waitcnt counts for the weight fragments instead of waiting for everything.
-  auto load_chunk = [&](int c, bool live) {
+  auto load_chunk = [&](int c, bool live) __attribute__((always_inline)) {
     const bool full = (c + 1) * CI_CHUNK <= a.cin_k;   // uniform: no channel of this chunk is beyond Cin
     const __amdgpu_buffer_rsrc_t rs_in = make_rsrc(in + n_plan * a.in.nstride, (uint32_t)a.in.nstride * 2);
     const __amdgpu_buffer_rsrc_t rs_mask = make_rsrc(MASKED ? mask + n_plan * a.mask.nstride : in, (uint32_t)a.mask.nstride * 2);
@@ -203,7 +206,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
     }
   };
 
-  auto store_chunk = [&](int buf) {
+  auto store_chunk = [&](int buf) __attribute__((always_inline)) {
 #pragma unroll
     for (int r = 0; r < ROUNDS; ++r) {
       if ((item_meta[r] >> 24) >= 2) continue;
@@ -405,7 +408,7 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
       const bool last_chunk = c + 1 == c_end;
       const int next_tile = tile + G;
       const bool more = !last_chunk || next_tile < a.ntiles;
-      auto issue_next = [&]() {
+      auto issue_next = [&]() __attribute__((always_inline)) {
         if (last_chunk && more) plan_tile(next_tile);
         load_chunk(last_chunk ? c_begin : c + 1, more);
       };

@@ -314,6 +314,32 @@ def test_conv3d_wide_kernel_activations(shape):
                 close(from_dev(got[0]), orc.conv3d_fwd(xo, w, bias, act=orc.ACT_LEAKY, alpha=slope).a, TOL["bf16"])
 
 
+@pytest.mark.parametrize("shape,form", [((1, 8, 8, 9, 30, 41), "1,8,32,1,0,0,0"), ((1, 64, 16, 2, 33, 33), "2,4,32,1,0,0,1"), ((1, 40, 16, 2, 33, 13), "2,4,16,1,0,0,1"),
+                                        ((1, 16, 16, 9, 17, 15), "1,8,16,1,0,0,0"), ((1, 24, 40, 9, 17, 15), "1,8,16,1,0,1,0")])
+def test_conv3d_masked_odd_rows_without_room_for_the_copy(shape, form):
+    """Masked backward-data of odd rows in a workspace without room for a prepared copy: the general kernel's masked forms, which have the bits of the
+    call with room."""
+    import torch
+    import paper_2007_12856_amd as h3d
+
+    class Fixed(h3d.Workspace):      # what the packed filter (and the sums of a split) take, whatever the call would like
+        def get(self, nbytes):
+            return super().get(self.size)
+
+    N, Ci, Co, D, H, W = shape
+    w, _ = _weights(Ci, Co, "bf16", 98)
+    dzo, dzg = slab_pair(synth.flat("normal", SEED, 99, (N, Co, D, H, W)), "bf16")
+    zo, zg = slab_pair(synth.flat("normal", SEED, 100, (N, Co, D, H, W)), "bf16")
+    dxo = orc.conv3d_bwd_data(dzo, zo, w, act=orc.ACT_LEAKY, alpha=0.01)
+    wd, ws = to_dev(w, "bf16"), Fixed()
+    even = [h3d.Slab(torch.empty((N, c, D, H, W + 1), dtype=torch.bfloat16, device="cuda")) for c in (Co, Ci)]
+    ws.size = h3d.h3d_conv3d_workspace_bytes(h3d.OP_FWD, *even)
+    got = [h3d.conv3d_bwd_data(dzg, zg, wd, dev_like(dxo, "bf16"), h3d.ACT_LEAKY, 0.01, s).t for s in (h3d.Workspace(), ws)]
+    assert h3d.h3d_last_kernel().startswith(f"conv3d_mfma_kernel<{form},"), h3d.h3d_last_kernel()
+    close(from_dev(got[1]), dxo.a, TOL["bf16"])
+    assert torch.equal(*got)
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cin,cout", [(4, 16), (3, 5), (16, 32)])
 def test_conv3d_sharded_matches_oracle_and_unsharded_gpu(dtype, cin, cout):
