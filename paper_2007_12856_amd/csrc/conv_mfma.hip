@@ -1337,10 +1337,11 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
 }
 
 // Forward and 2x2x2 max pooling in one launch, for what h3d_conv3d_fwd gives to the wide kernel unsplit and without a copy: pairs of planes, rows and
-// columns that begin with the tensor, and whole pairs of pooled voxels in a row.
+// columns that begin with the tensor, and whole pairs of pooled voxels in a row.  The pooled tensor is written through 31-bit byte offsets too, and its
+// halos, which nothing here bounds, can make it larger than z.
 bool wide_pool_supported(void* handle, const h3d_tensor* in, const h3d_tensor* z, const h3d_tensor* y) {
   if (!mfma_fwd_supported(in, z) || y->dtype != H3D_BF16 || conv3d_thin_supported(in, z) || !wide_dims(in, z)) return false;
-  if (z->halo_lo || z->halo_hi || z->d % 2 || z->h % 2 || z->w % 4 || !is_packed(y)) return false;
+  if (z->halo_lo || z->halo_hi || z->d % 2 || z->h % 2 || z->w % 4 || !is_packed(y) || sample_span(y) >= ((int64_t)1 << 30)) return false;
   if ((uintptr_t)in->data % 4 || (uintptr_t)z->data % 4 || (uintptr_t)y->data % 4) return false;
   return z->n > 0 && wide_splits(in, z, static_cast<Handle*>(handle)->num_cu) == 1;
 }

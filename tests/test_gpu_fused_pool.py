@@ -191,3 +191,24 @@ def test_conv_fwd_maxpool_activations(case, act, alpha):
     assert h3d.h3d_last_kernel().endswith("(max-pooled)"), h3d.h3d_last_kernel()
     for t, r in zip(got, want):
         assert torch.all((t == r) | (t.isnan() & r.isnan()))
+
+
+def test_conv_fwd_maxpool_into_a_tensor_of_wide_halos():
+    """A pooled tensor whose halos take a sample past 31-bit byte offsets: the two calls, and nothing of the halos is touched."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    Ci, Co, D, H, W, halo = 16, 32, 4, 4, 20, 838861
+    g = torch.Generator(device="cuda").manual_seed(7)
+    x = h3d.Slab(torch.randn((1, Ci, D, H, W), generator=g, device="cuda").bfloat16())
+    w = (torch.rand((Co, Ci, 3, 3, 3), generator=g, device="cuda") - 0.5).bfloat16()
+    z = [h3d.Slab(torch.empty((1, Co, D, H, W), dtype=torch.bfloat16, device="cuda")) for _ in range(2)]
+    small = h3d.Slab(torch.empty((1, Co, D // 2, H // 2, W // 2), dtype=torch.bfloat16, device="cuda"))
+    h3d.conv3d_fwd_maxpool(x, w, None, z[0], small, h3d.ACT_NONE)
+    assert h3d.h3d_last_kernel().endswith("(max-pooled)")
+    t = torch.full((1, Co, D // 2 + 2 * halo, H // 2, W // 2), 7.0, dtype=torch.bfloat16, device="cuda")
+    assert t.numel() >= 2 ** 30
+    y = h3d.Slab(t, halo, halo, 0, D // 2)
+    h3d.conv3d_fwd_maxpool(x, w, None, z[1], y, h3d.ACT_NONE)
+    assert not h3d.h3d_last_kernel().endswith("(max-pooled)")
+    assert torch.equal(z[0].t, z[1].t) and torch.equal(small.t, y.interior)
+    assert torch.all(t[:, :, :halo] == 7.0) and torch.all(t[:, :, halo + D // 2:] == 7.0)
