@@ -22,6 +22,9 @@ bool rows_v16(const h3d_tensor* t) {
   const Geo g = make_geo(t);
   return t->w % 8 == 0 && (uintptr_t)t->data % 16 == 0 && g.cstride % 8 == 0 && g.nstride % 8 == 0;
 }
+// a sample, with the strides of the tensor that a view is part of, is reached by 31-bit byte offsets: offsets at and past 2 GiB are what the kernels give to
+// lanes that have nothing to load or store
+bool fits31(const h3d_tensor* t) { return sample_span(t) < ((int64_t)1 << 30); }
 // rows read in pieces that may run past their end: a sample holds at least one piece, and 32-bit byte offsets reach all of it
 bool rows_any(const h3d_tensor* t) {
   const int64_t span = stored_span(make_geo(t));
@@ -188,9 +191,7 @@ bool deconv_bd_mfma_supported(const h3d_tensor* dx, const h3d_tensor* dy, const 
   if (dx->dtype != H3D_BF16 || dx->c < 1 || dx->c > 1024 || dy->c < 1) return false;
   if ((uintptr_t)dy->data % 4 != 0 || (uintptr_t)w % 16 != 0) return false;
   if (dbd_mrb(dx->c, dy->c) == 0) return false;
-  const int64_t ys = (int64_t)dy->c * (dy->halo_lo + dy->d + dy->halo_hi) * dy->h * dy->w * 2;
-  const int64_t xs = (int64_t)dx->c * (dx->halo_lo + dx->d + dx->halo_hi) * dx->h * dx->w * 2;
-  return ys < ((int64_t)1 << 31) && xs < ((int64_t)1 << 31);
+  return fits31(dx) && fits31(dy);
 }
 
 h3d_status deconv_bd_mfma(void* handle, const h3d_tensor* dy, const void* w, h3d_tensor* dx, hipStream_t stream) {
@@ -445,10 +446,8 @@ bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
     if (!rows_any(x)) return false;
     if ((int64_t)x->n * x->d * x->h * x->w < 49152 ? x->c < (y->c > 64 ? 17 : 16) : x->c * y->c < 512) return false;
   }
-  const int64_t xs = (int64_t)x->c * (x->halo_lo + x->d + x->halo_hi) * x->h * x->w * 2;
-  const int64_t ys = (int64_t)y->c * (y->halo_lo + y->d + y->halo_hi) * y->h * y->w * 2;
   const int64_t ncb = (int64_t)x->n * x->d * x->h * cdiv(x->w, 32);
-  return xs < ((int64_t)1 << 31) && ys < ((int64_t)1 << 31) && ncb < ((int64_t)1 << 30);
+  return fits31(x) && fits31(y) && ncb < ((int64_t)1 << 30);
 }
 
 size_t deconv_fw_mfma_ws_bytes(const h3d_tensor* x, const h3d_tensor* y) {

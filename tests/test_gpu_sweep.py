@@ -140,6 +140,34 @@ def test_deconv_backward_data_in_groups_of_input_channels(N, cin, cout, d, H, W,
     assert torch.all(buf[:32] == 3.0) and torch.all(buf[32 + n:] == 3.0)
 
 
+@pytest.mark.parametrize("cin,cout", [(17, 66), (20, 40)])
+def test_deconv_on_views_of_tall_tensors(cin, cout):
+    """y (dy) is a run of planes of a tensor whose samples are past 31-bit byte offsets, on which neither matrix-core kernel runs; nothing is written around the run."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    d, H, W = 2, 3, 8
+    g = torch.Generator(device="cuda").manual_seed(cin)
+    x = h3d.Slab(torch.randn((1, cin, d, H, W), generator=g, device="cuda").bfloat16())
+    w = (torch.rand((cin, cout, 2, 2, 2), generator=g, device="cuda") - 0.5).bfloat16()
+    packed = h3d.Slab(torch.empty((1, cout, 2 * d, 2 * H, 2 * W), dtype=torch.bfloat16, device="cuda"))
+    h3d.deconv2_fwd(x, w, None, packed)
+    assert h3d.h3d_last_kernel().startswith("deconv_fw_mfma_kernel")
+    tall = torch.full((1, cout, -(-2 ** 30 // (cout * 4 * H * W)), 2 * H, 2 * W), 3.0, dtype=torch.bfloat16, device="cuda")
+    p0 = tall.shape[2] - 2 * d - 1
+    view = h3d.Slab(tall[:, :, p0:p0 + 2 * d])
+    h3d.deconv2_fwd(x, w, None, view)
+    assert h3d.h3d_last_kernel() == "deconv2_fwd"
+    close(from_dev(view.t), from_dev(packed.t), TOL["bf16"])
+    assert torch.all(tall[:, :, :p0] == 3.0) and torch.all(tall[:, :, p0 + 2 * d:] == 3.0)
+    dx = [h3d.Slab(torch.empty_like(x.t)) for _ in range(2)]
+    h3d.deconv2_bwd_data(packed, w, dx[0])
+    assert h3d.h3d_last_kernel().startswith("deconv_bd_mfma_kernel")
+    view.t.copy_(packed.t)
+    h3d.deconv2_bwd_data(view, w, dx[1])
+    assert h3d.h3d_last_kernel() == "deconv2_bwd_data"
+    close(from_dev(dx[1].t), from_dev(dx[0].t), TOL["bf16"])
+
+
 @pytest.mark.parametrize("case", [(0, 1, 33, 20, 2, 5, 7, 0), (1, 2, 16, 17, 1, 3, 33, 1), (2, 1, 70, 64, 3, 4, 45, 2), (3, 1, 128, 24, 1, 2, 3, 0),
                                   (4, 1, 5, 9, 2, 1, 40, 1), (5, 3, 100, 34, 2, 9, 100, 0), (6, 1, 1, 1, 1, 2, 4, 2)])
 def test_deconv_ragged_rows_bf16(case):
