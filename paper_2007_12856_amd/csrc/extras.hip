@@ -644,7 +644,10 @@ static h3d_status deconv_fwd_t(void* handle, const h3d_tensor* x, const void* w,
   a.pad = (int)cdiv(a.cout, DC_COT) * DC_COT;
   a.total = (int64_t)x->n * x->d * x->h * x->w;
   if (a.total == 0 || a.cout == 0) return H3D_OK;
-  if (deconv_fw_mfma_supported(x, y)) return deconv_fw_mfma(handle, x, w, bias, y, ws, ws_bytes, s);
+  // More than 64 output channels have a kernel for any workspace that holds its own packed filter, at any address of a float: the other one, where there
+  // is no room for fragments or they would not be aligned.
+  const bool fits = ws && ws_bytes >= deconv_fw_mfma_ws_bytes(x, y) && (uintptr_t)ws % 16 == 0;
+  if (deconv_fw_mfma_supported(x, y) && (a.cout <= 64 || fits)) return deconv_fw_mfma(handle, x, w, bias, y, ws, ws_bytes, s);
   size_t need = (size_t)a.cin * a.pad * 8 * 4;
   if (need && (!ws || ws_bytes < need)) return fail(handle, H3D_EWORKSPACE, "deconv2_fwd: workspace too small");
   if (need) hipLaunchKernelGGL((deconv_pack_kernel<T>), dim3((unsigned)cdiv(need / 4, 256)), dim3(256), 0, s, (const T*)w, (float*)ws, a.cin, a.cout, a.pad, 0);

@@ -121,6 +121,39 @@ def test_deconv_forward_of_more_than_64_output_channels(N, cin, cout, d, H, W, f
     assert torch.all(buf[:32] == 3.0) and torch.all(buf[32 + n:] == 3.0)
 
 
+@pytest.mark.parametrize("cin,cout", [(17, 65), (64, 96), (128, 200)])
+def test_deconv_forward_at_scratch_limits(cin, cout):
+    """A workspace at an address of a float only, or with no more room than the direct kernel's filter: such calls run on the direct kernel; with less they are
+    refused, as is a misaligned workspace of at most 64 output channels."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    xo, xg = slab_pair(synth.flat("normal", SEED, 6500 + cout, (1, cin, 2, 3, 8)), "bf16")
+    b = np.sqrt(3.0 / (8 * cin))
+    w = quantize(synth.flat("uniform", SEED, 6600 + cout, (cin, cout, 2, 2, 2), -b, b), "bf16")
+    yo = orc.deconv2_fwd(xo, w, np.zeros(cout))
+    wd, y = to_dev(w, "bf16"), dev_like(yo, "bf16")
+    lib, xd, yd = h3d.lib(), xg.desc(), y.desc()
+    direct, fragments = cin * -(-cout // 8) * 8 * 32, -(-cout // 4) * (8 if cin > 64 else 4) * 1024
+    size = lib.h3d_deconv2_workspace_bytes(h3d.handle(), h3d.OP_FWD, xd, yd)
+    assert size >= max(direct, fragments)
+    buf = torch.empty(size + 16, dtype=torch.uint8, device="cuda")
+
+    def call(shift, nbytes, yd=yd):
+        st = lib.h3d_deconv2_fwd(h3d.handle(), xd, wd.data_ptr(), None, yd, buf.data_ptr() + shift, nbytes, None)
+        torch.cuda.synchronize()
+        return st
+
+    for shift, nbytes in ((0, size), (4, size), (0, direct), (0, fragments)):
+        fast = shift == 0 and nbytes >= fragments
+        y.t.fill_(3.0)
+        assert call(shift, nbytes) == (0 if fast or nbytes >= direct else -3), h3d.h3d_last_error()
+        if fast or nbytes >= direct:
+            assert h3d.h3d_last_kernel().startswith("deconv_fw_mfma_kernel" if fast else "deconv2_fwd"), (shift, nbytes, h3d.h3d_last_kernel())
+            close(from_dev(y.t), yo.a, TOL["bf16"])
+    assert call(0, min(direct, fragments) - 1) == -3
+    assert call(4, size, h3d.Slab(y.t[:, :64].contiguous()).desc()) == -3
+
+
 @pytest.mark.parametrize("N,cin,cout,d,H,W,blocks", [(1, 129, 5, 2, 3, 8, 3), (2, 128, 78, 1, 5, 40, 4), (2, 128, 79, 1, 5, 40, 2), (1, 97, 110, 2, 3, 33, 2), (1, 70, 156, 2, 2, 34, 2),
                                                      (1, 40, 159, 3, 2, 31, 1), (1, 33, 310, 1, 2, 5, 1), (1, 20, 311, 1, 2, 5, 0), (1, 300, 17, 1, 4, 9, 4), (1, 1025, 3, 1, 2, 3, 0)])
 def test_deconv_backward_data_in_groups_of_input_channels(N, cin, cout, d, H, W, blocks):
