@@ -434,17 +434,23 @@ h3d_status dfw_launch(void* handle, const bf16_t* x, const uint4* wp, const floa
 }  // namespace
 
 // Up to 1024 output channels, 64 a workgroup (each group reads x again, less than it writes).  us, direct kernel and here: 128->128 on 32x64x64 545 and 63,
-// 64->96 on 16x48x80 112 and 29, 28->102 on 4 x 26x26x84 219 and 118, 32->128 on 12x16x80 29.7 and 14.5, 24->96 on 4x8x8 14.7 and 11.7.
+// 64->96 on 16x48x80 112 and 29, 28->102 on 4 x 26x26x84 219 and 118, 32->128 on 12x16x80 29.7 and 14.5, 24->96 on 4x8x8 14.7 and 11.7 (few input channels: below).
 constexpr int DF_COUT = 1024;
 bool deconv_fw_mfma_supported(const h3d_tensor* x, const h3d_tensor* y) {
   if (x->dtype != H3D_BF16 || x->c < 1 || x->c > 128 || y->c < 1 || y->c > DF_COUT || (uintptr_t)y->data % 4 != 0) return false;
   if (make_geo(y).cstride % 2 != 0 || make_geo(y).nstride % 2 != 0) return false;      // results leave as pairs in one dword
-  // Ragged rows with few channels stay with the direct kernel, which reads x once per 8 output channels; this one pads the channels of
-  // both sides.  us, direct and here: 8->16 on 8x9x10 8.9 and 10.0, 16->16 there 12.3 and 10.0; 16->16 on 32x62x66 21 and 26, 16->32 there
-  // 33 and 26; 4->4 on 2 x 24x70x90 13 and 37; 16->72 on 8x10x14 12.2 and 12.7.
-  if (!rows_v16(x)) {
-    if (!rows_any(x)) return false;
-    if ((int64_t)x->n * x->d * x->h * x->w < 49152 ? x->c < (y->c > 64 ? 17 : 16) : x->c * y->c < 512) return false;
+  // Few input channels stay with the direct kernel, which reads x once per 8 output channels; this one pads them to 64.  More than 64 output channels
+  // pay from 16 on, in aligned rows of large volumes from 8.  us, direct and here: 2->96 on 16^3 9.6 and 12.3, 8->128 on 8^3 9.6 and 11.8, 12->65 on 8^3
+  // 10.8 and 11.7, 14->192 there 11.7 and 11.9, 16->128 on 16^3 13.1 and 12.8; 8->96 on 16x32x32 13.5 and 14.1, on 32x48x64 43 and 38, 6->65 on 32x64x64 37 and
+  // 33, 4->96 there 44 and 46; ragged 8->65 on 32x64x66 43 and 54, 16->72 on 8x10x14 12.2 and 12.7, 17->1000 on 16x18x22 48 and 33.
+  // Up to 64: 8->16 on 8x9x10 8.9 and 10.0, 16->16 there 12.3 and 10.0; 16->16 on 32x62x66 21 and 26, 16->32 there 33 and 26; 4->4 on 2 x 24x70x90 13 and 37.
+  const int64_t voxels = (int64_t)x->n * x->d * x->h * x->w;
+  const bool v16 = rows_v16(x);
+  if (!v16 && !rows_any(x)) return false;
+  if (y->c > 64) {
+    if (x->c < (v16 && voxels >= 98304 ? 8 : 16)) return false;
+  } else if (!v16 && (voxels < 49152 ? x->c < 16 : x->c * y->c < 512)) {
+    return false;
   }
   const int64_t ncb = (int64_t)x->n * x->d * x->h * cdiv(x->w, 32);
   return fits31(x) && fits31(y) && ncb < ((int64_t)1 << 30);

@@ -102,7 +102,8 @@ def test_deconv_sweep_bf16(case):
 
 
 @pytest.mark.parametrize("N,cin,cout,d,H,W,fast", [(1, 17, 65, 2, 3, 8, True), (2, 64, 96, 1, 5, 40, True), (1, 70, 128, 2, 3, 33, True), (1, 20, 129, 3, 2, 31, True),
-                                                   (1, 9, 200, 2, 4, 16, True), (1, 16, 72, 2, 5, 14, False), (1, 130, 66, 1, 3, 8, False)])
+                                                   (1, 9, 200, 2, 4, 16, False), (1, 15, 66, 2, 4, 16, False), (1, 16, 66, 2, 4, 16, True), (1, 16, 72, 2, 5, 14, True),
+                                                   (1, 15, 72, 2, 5, 14, False), (2, 7, 65, 16, 48, 64, False), (2, 8, 65, 16, 48, 64, True), (1, 130, 66, 1, 3, 8, False)])
 def test_deconv_forward_of_more_than_64_output_channels(N, cin, cout, d, H, W, fast):
     """Groups of 64 output channels, the last one with few of them, whole and ragged rows; nothing is written around the result."""
     import torch
