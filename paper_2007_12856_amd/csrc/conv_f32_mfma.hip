@@ -334,34 +334,44 @@ static F32Plan f32_plan(void* handle, int cin_k, const h3d_tensor* out) {
   p.ncig = (int)cdiv(cin_k, 4);
   const int64_t ds = out->halo_lo + out->d + out->halo_hi, tiles = out->n * cdiv(ds, FT_P) * cdiv(out->w, 16 * p.hv);
   // One or two blocks of 16 output channels, 8 or 2 rows a workgroup (the sums of a voxel are the same in all of them).  A block of 16 channels,
-  // two rows and a group of 4 input channels takes the chip 6.3 to 6.9 ns in each, so what counts is the padding of channels and rows
-  // and how the workgroups divide over the CUs: 8-row tiles come in rounds of two a CU, 2-row ones run four to seven to a CU and follow each
+  // two rows and a group of 4 input channels takes the chip 6.3 to 7.2 ns in each (16 columns: half of that), so what counts is the padding of channels
+  // and rows and how the workgroups divide over the CUs: 8-row tiles come in rounds of two a CU, 2-row ones run four to seven to a CU and follow each
   // other one by one.  us, 8 rows x 2 blocks, 8 x 1, 2 x 2, 2 x 1: 96->48 on 4 x 9x210x32 1199, 636, 761, 569; 16->81 on 2 x 26x18x208 220, 223, 157,
   // 153; 32->64 on 32x128x128 429, 454, 440, 451; 11->64 on 8 x 32x32x48 173, 187, 181, 181; 64->32 on 2 x 16x50x80 231, -, 173, 144; one block only: 64->11
   // on 8 x 32x32x48 -, 218, -, 245; 48->9 on 42x128x60 -, 166, -, 127.  One block where the layer has more of them only from four groups of input channels on
   // (below, staging and results count: 5->177 on 8 x 13x126x32 333 against 329), and where all workgroups run at once only if it saves padding or
-  // there are more than that (whole samples whose channels are split: 96->41 on 18x16x64 70 -> 56).
-  auto wgs_of = [&](int cb, int tr) { return tiles * cdiv(out->h, tr) * cdiv(out->c, 16 * cb); };
-  auto cost = [&](int cb, int tr) {
-    const int64_t round = tr == 8 ? 2 * num_cu : num_cu;
-    return (double)(cdiv(wgs_of(cb, tr), round) * round * cb * tr / 2) * (tr == 8 ? (cb == 2 ? 1.0 : 1.04) : (cb == 2 ? 1.03 : 1.06));
-  };
+  // there are more than that (whole samples whose channels are split: 96->41 on 18x16x64 70 -> 56).  A form whose channels are split is compared by the
+  // rounds of its parts, their sums and their second launch: two blocks split and one whole 147->128 on 16x37x32 184 and 199, 254->71 on 16x54x16 163 and
+  // 177, 150->64 on 4 x 20x16x32 192 and 204; 96->32 on 21x112x13 77 and 73.  The rule's misses among 369 random layers are up to a tenth: 163->96 on
+  // 4 x 3x192x8 takes 342 in 2 rows x 1 block, 308 in 2 x 2.
   const bool may_split = out->d == out->d_global && !out->halo_lo && !out->halo_hi && is_packed(out) && out->c > 4 && p.ncig > 8;
-  const int cb_min = p.ncig >= 4 && (wgs_of(2, 2) >= num_cu || (may_split && cdiv(out->c, 16) % 2)) ? 1 : f32_cb(out->c);
-  p.cb = f32_cb(out->c); p.tr = 8;
-  if (out->c <= 4) {      // (thin: products of its own)
-    if (tiles * cdiv(out->h, 8) < 2 * num_cu && out->h > 2) p.tr = 2;
-  } else {
-    double best = cost(p.cb, 8);
+  auto wgs_of = [&](int cb, int tr) { return tiles * cdiv(out->h, tr) * cdiv(out->c, 16 * cb); };
+  auto split = [&](int cb, int tr, int* per) {
+    int64_t n = 1;
+    if (may_split && tr == 2) n = std::max<int64_t>(1, std::min<int64_t>({4 * num_cu / std::max<int64_t>(1, wgs_of(cb, tr)), (int64_t)p.ncig / 2, (int64_t)8}));
+    *per = (int)cdiv(p.ncig, n);
+    return (int)cdiv(p.ncig, *per);
+  };
+  auto cost = [&](int cb, int tr) {      // ns
+    const int64_t round = tr == 8 ? 2 * num_cu : num_cu;
+    int per;
+    const int n = split(cb, tr, &per);
+    const double sums = n > 1 ? 6200.0 + (n + 1) * (double)(out->n * (int64_t)out->c * out->d * out->h * out->w) * 4 / 3600 : 0.0;
+    return (tr == 8 ? (cb == 2 ? 3.45 : 3.59) : (cb == 2 ? 3.55 : 3.66)) * p.hv * (double)(cdiv(wgs_of(cb, tr) * n, round) * round * cb * tr / 2) * per + sums;
+  };
+  const int cb_max = f32_cb(out->c);
+  const int cb_min = p.ncig >= 4 && (wgs_of(2, 2) >= num_cu || (may_split && cdiv(out->c, 16) % 2)) ? 1 : cb_max;
+  // from the fewest workgroups that fill the chip (8 rows if those make two a CU)
+  p.cb = cb_max;
+  p.tr = wgs_of(cb_max, 8) < 2 * num_cu && out->h > 2 ? 2 : 8;
+  if (out->c > 4) {      // (thin: products of its own)
+    double best = 0.99 * cost(p.cb, p.tr);
     for (const int tr : {8, 2})
-      for (int cb = f32_cb(out->c); cb >= cb_min; --cb)
+      for (int cb = cb_max; cb >= cb_min; --cb)
         if ((tr == 8 || out->h > 2) && cost(cb, tr) < best) { best = cost(cb, tr); p.cb = cb; p.tr = tr; }
   }
   p.ncog = (int)cdiv(out->c, 16 * p.cb);
-  const int64_t wgs = std::max<int64_t>(1, wgs_of(p.cb, p.tr));
-  p.nsplit = may_split && p.tr == 2 ? (int)std::max<int64_t>(1, std::min<int64_t>({4 * num_cu / wgs, (int64_t)p.ncig / 2, (int64_t)8})) : 1;
-  p.per_split = (int)cdiv(p.ncig, p.nsplit);
-  p.nsplit = (int)cdiv(p.ncig, p.per_split);
+  p.nsplit = split(p.cb, p.tr, &p.per_split);
   // (room for the larger blocks whichever are taken: a workspace for one volume does for another of the same channels)
   p.wk_bytes = up256((size_t)cdiv(out->c, 16 * f32_cb(out->c)) * p.ncig * 108 * 16 * f32_cb(out->c) * sizeof(float));
   p.part_bytes = p.nsplit > 1 ? (size_t)p.nsplit * out->n * out->c * out->d * out->h * out->w * sizeof(float) : 0;

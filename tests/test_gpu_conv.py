@@ -509,7 +509,7 @@ F32_SHAPES = [
     (2, 20, 24, 4, 12, 8, 1, 0, 4),
     (1, 3, 6, 5, 9, 12, 0, 0, 5),
     (4, 5, 6, 16, 256, 16, 0, 0, 16),
-    # where the rows or the channels of a workgroup's tile divide evenly over the chip
+    # forms of one block and of 8 rows that the shapes above do not take
     (2, 5, 32, 16, 128, 128, 0, 0, 16),
     (1, 5, 32, 4, 128, 128, 0, 0, 4),
     (4, 5, 32, 16, 32, 16, 0, 0, 16),
@@ -568,6 +568,52 @@ def test_conv3d_fp32_matrix_core_kernels(shape):
     dwo_n, _ = orc.conv3d_bwd_filter(xo, dzo, None, act=orc.ACT_NONE)
     h3d.conv3d_bwd_filter(xg, dzg, None, dw2, None, h3d.ACT_NONE, 0.0)
     close(from_dev(dw2), dwo_n, 1e-5)
+
+
+# (N, channels in, channels out, D, H, W, planes of the volume on either side of the shard, kernel forward, kernel backward-data) on 256 CUs: one block
+# of several a workgroup (whole samples and shards, 2 and 8 rows, 32 and 16 columns, a last block of few channels); shapes where two blocks, split, are faster
+@pytest.mark.parametrize("shape,fwd,bwd", [
+    ((2, 64, 32, 16, 50, 80, 0), "1,2,2", "2,2,2"),
+    ((1, 20, 40, 16, 66, 33, 1), "1,2,2", "1,2,2"),
+    ((1, 24, 48, 16, 66, 12, 2), "1,2,1", "2,2,1"),
+    ((1, 48, 24, 16, 66, 12, 1), "2,2,1", "1,2,1"),
+    ((4, 16, 33, 12, 104, 24, 0), "1,8,2", "1,2,2"),
+    ((1, 147, 128, 16, 37, 32, 0), "2,2,2> (split)", "1,2,2"),
+    ((1, 254, 71, 16, 54, 16, 0), "2,2,1> (split)", "1,2,1"),
+])
+def test_conv3d_fp32_tile_forms(shape, fwd, bwd):
+    """The tile form that the planner takes, by name, and its result (masked in the data gradient) against the tap-by-tap products in 64 bits."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W, beside = shape
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the forms are those of 256 CUs")
+    g = torch.Generator(device="cuda").manual_seed(Ci * Co + W)
+    halo, ends = (1, (beside, D + 2 * beside)) if beside else (0, (0, D))
+    normal = lambda c, p: torch.randn((N, c, D + 2 * p, H, W), generator=g, device="cuda")
+    slab = lambda t, p: h3d.Slab(t, p, p, *ends)
+    x, dz, z = normal(Ci, halo), normal(Co, halo), normal(Co, halo)
+    w = (torch.rand((Co, Ci, 3, 3, 3), generator=g, device="cuda") - 0.5) * 2 * (3.0 / (27 * Ci)) ** 0.5
+    b = torch.rand((Co,), generator=g, device="cuda") - 0.5
+
+    def products(t, w):      # of a tensor with its halo planes, or zeros for them
+        t = torch.nn.functional.pad(t.double(), (1, 1, 1, 1) + ((0, 0) if halo else (1, 1)))
+        out = torch.zeros((N, w.shape[0], D * H * W), dtype=torch.float64, device="cuda")
+        for tap in range(27):
+            i, j, k = tap // 9, tap // 3 % 3, tap % 3
+            for n in range(N):
+                out[n] += w[:, :, i, j, k].double() @ t[n, :, i:i + D, j:j + H, k:k + W].reshape(t.shape[1], -1)
+        return out.view(N, -1, D, H, W)
+
+    y, dx = (torch.empty((N, c, D, H, W), device="cuda") for c in (Co, Ci))
+    h3d.conv3d_fwd(slab(x, halo), w, b, slab(y, 0), h3d.ACT_LEAKY, 0.01)
+    name = lambda form: "conv3d_f32_mfma_kernel<%s%s" % (form, "" if ">" in form else ">")
+    assert h3d.h3d_last_kernel() == name(fwd), h3d.h3d_last_kernel()
+    want = products(x, w) + b.double().view(1, -1, 1, 1, 1)
+    close(from_dev(y), torch.where(want > 0, want, 0.01 * want).cpu().numpy(), 1e-5)
+    h3d.conv3d_bwd_data(slab(dz, halo), slab(z, halo), w, slab(dx, 0), h3d.ACT_LEAKY, 0.01)
+    assert h3d.h3d_last_kernel() == name(bwd), h3d.h3d_last_kernel()
+    close(from_dev(dx), products(torch.where(z > 0, dz, 0.01 * dz), w.transpose(0, 1).flip(2, 3, 4)).cpu().numpy(), 1e-5)
 
 
 def _f32_random_shapes(k=12):
