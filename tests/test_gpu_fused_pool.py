@@ -193,6 +193,65 @@ def test_conv_fwd_maxpool_activations(case, act, alpha):
         assert torch.all((t == r) | (t.isnan() & r.isnan()))
 
 
+# what the test above does not vary: activation, no bias, fp32 and a pooled tensor that is a view (two calls)
+@pytest.mark.parametrize("act,alpha,bias,dtype,view", [("NONE", 0.0, True, "bf16", False), ("LEAKY", 0.01, False, "bf16", False), ("NONE", 0.0, False, "bf16", True),
+                                                       ("LEAKY", 0.01, True, "f32", False)])
+@pytest.mark.parametrize("case", [(1, 16, 32, 4, 8, 32), (1, 33, 70, 10, 18, 68), (2, 16, 64, 36, 66, 100)])
+def test_conv_fwd_maxpool_forms(case, act, alpha, bias, dtype, view):
+    """z and the pooled tensor have the bits of the separate calls, with windows of negative values among them."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = case
+    dt, bits = (torch.bfloat16, torch.int16) if dtype == "bf16" else (torch.float32, torch.int32)
+    g = torch.Generator(device="cuda").manual_seed(D * W + Co)
+    x = h3d.Slab(torch.randn((N, Ci, D, H, W), generator=g, device="cuda").to(dt))
+    w = (torch.rand((Co, Ci, 3, 3, 3), generator=g, device="cuda") - 0.5).to(dt)
+    b = torch.rand((Co,), generator=g, device="cuda") - 0.5 if bias else None
+    a, got = getattr(h3d, "ACT_" + act), []
+    for fused in (True, False):
+        z = torch.full((N, Co, D, H, W), 5.0, dtype=dt, device="cuda")
+        y = torch.full((N, Co + 3 if view else Co, D // 2, H // 2, W // 2), 7.0, dtype=dt, device="cuda")
+        ys = h3d.Slab(y).channels(2, 2 + Co) if view else h3d.Slab(y)
+        if fused:
+            h3d.conv3d_fwd_maxpool(x, w, b, h3d.Slab(z), ys, a, alpha)
+            assert h3d.h3d_last_kernel().endswith("(max-pooled)") == (dtype == "bf16" and not (view and N > 1)), h3d.h3d_last_kernel()
+        else:
+            h3d.conv3d_fwd(x, w, b, h3d.Slab(z), a, alpha)
+            h3d.pool3d_fwd(h3d.Slab(z), ys, h3d.POOL_MAX)
+        got.append((z, y))
+    assert bool((got[0][1] < 0).any())
+    for t, r in zip(*got):
+        assert torch.equal(t.view(bits), r.view(bits))
+
+
+@pytest.mark.parametrize("Co", [32, 64])
+def test_conv_fwd_maxpool_zeros_of_both_signs(Co):
+    """Windows of a negative value, -0 and +0 in every order: the pooled zero is the first of them, as a pass over the window with "if e > m" finds it (a
+    negative value times the slope is -0 where it is too small for the type)."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, D, H, W = 1, 16, 8, 16, 64
+    g = torch.Generator(device="cuda").manual_seed(Co)
+    values = torch.tensor([-1.0, -1.0, -2.0 ** -40, 0.0, 2.0 ** -20], device="cuda")
+    x = values[torch.randint(0, 50, (N, Ci, D, H, W), generator=g, device="cuda").clamp_(max=43) // 11].bfloat16()
+    x[:, :, ::2, ::2, ::2] = -1.0
+    w = torch.zeros((Co, Ci, 3, 3, 3), dtype=torch.bfloat16, device="cuda")
+    w[torch.arange(Co), torch.arange(Co) % Ci, 1, 1, 1] = 1.0
+    z = h3d.Slab(torch.empty((N, Co, D, H, W), dtype=torch.bfloat16, device="cuda"))
+    y = h3d.Slab(torch.empty((N, Co, D // 2, H // 2, W // 2), dtype=torch.bfloat16, device="cuda"))
+    h3d.conv3d_fwd_maxpool(h3d.Slab(x), w, None, z, y, h3d.ACT_LEAKY, 2.0 ** -100)
+    assert h3d.h3d_last_kernel().endswith("(max-pooled)")
+    v = x.repeat(1, Co // Ci, 1, 1, 1).float()
+    want = torch.where(v > 0, v, v * 2.0 ** -100).bfloat16()
+    assert torch.equal(z.t.view(torch.int16), want.view(torch.int16))
+    best = want[:, :, ::2, ::2, ::2].clone()
+    for k in range(1, 8):
+        e = want[:, :, k >> 2::2, k >> 1 & 1::2, k & 1::2]
+        best = torch.where(e > best, e, best)
+    assert all(bool((best.view(torch.int16) == b).any()) for b in (0, -32768)) and bool((best < 0).any())
+    assert torch.equal(y.t.view(torch.int16), best.view(torch.int16))
+
+
 def test_conv_fwd_maxpool_into_a_tensor_of_wide_halos():
     """A pooled tensor whose halos take a sample past 31-bit byte offsets: the two calls, and nothing of the halos is touched."""
     import torch
