@@ -258,9 +258,10 @@ size_t h3d_act_mask_bytes(const h3d_tensor* z);                       /* 0 if w 
 h3d_status h3d_conv3d_fwd_pool(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
                                h3d_tensor* y, void* mask, int act, float alpha,
                                void* ws, size_t ws_bytes, void* stream);
-/* z = act(b + W * x) and y = maxpool(z), for every shape h3d_conv3d_fwd and h3d_pool3d_fwd accept (z and y may be views); one launch for bf16
- * volumes wider than 16 voxels with z without halos and w a multiple of 4, the two calls one after the other otherwise.  Same bits either
- * way; workspace as for H3D_OP_FWD. */
+/* z = act(b + W * x) and y = maxpool(z), for every shape h3d_conv3d_fwd and h3d_pool3d_fwd accept (z and y may be views).  Where a fused kernel
+ * exists the pooling is part of the convolution's pass: bf16, z without halos, at least 4 planes and rows, w a multiple of 4 and more than 16, y
+ * packed, and channels that h3d_conv3d_fwd neither sums in parts nor gives to a kernel of its own for few of them (x at most 4 and z at most 32; x
+ * at most 16 and z at most 8).  The two calls one after the other otherwise.  Same bits either way; workspace as for H3D_OP_FWD. */
 h3d_status h3d_conv3d_fwd_maxpool(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* z,
                                   h3d_tensor* y, int act, float alpha, void* ws, size_t ws_bytes, void* stream);
 /* mask of a stored output z (what the fused call writes by itself). */
@@ -309,7 +310,8 @@ h3d_status h3d_box_unpack(void* handle, const void* buf, void* t, int dtype, int
 
 /* ---- 2x2x2 stride-2 transposed convolution (U-Net up-sampling "deconvolution", Sec. III-A) ----
  * w: [cin][cout][2][2][2]; y[n,co,2q+k] = bias[co] + sum_ci w[ci,co,k] * x[n,ci,q].  Interiors only;
- * y interior extents are twice x's. */
+ * y interior extents are twice x's.  The bf16 forward pass and the filter gradient want a workspace aligned to 16 bytes (H3D_EWORKSPACE);
+ * the forward pass of more than 64 output channels has a slower kernel for any other address of a float. */
 size_t h3d_deconv2_workspace_bytes(void* handle, int op /* h3d_conv_op */, const h3d_tensor* x, const h3d_tensor* y);
 h3d_status h3d_deconv2_fwd(void* handle, const h3d_tensor* x, const void* w, const float* bias, h3d_tensor* y,
                            void* ws, size_t ws_bytes, void* stream);

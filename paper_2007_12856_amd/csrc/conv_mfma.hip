@@ -12,8 +12,8 @@
 //     into LDS: 16-byte units of 8 channels, laid out [ci-group][d][h][w], read back with
 //     conflict-free ds_read_b128 at the 27 shifted offsets;
 //   * weights are pre-packed in exact fragment order ([co-block][ci-chunk][tap][lane][8], taps.h) and go
-//     global -> registers (fully coalesced 1 KB per fragment, L1/L2 resident), prefetched one
-//     (kd,kw) step ahead; they never touch LDS;
+//     global -> registers (fully coalesced 1 KB per fragment, L1/L2 resident), requested several
+//     (kd,kw) steps ahead, partly by the chunk before; they never touch LDS;
 //   * a workgroup is 8 wavefronts: NCB blocks of 32 output channels x ND depth planes; each
 //     wavefront owns 32 channels x 128 voxels (4 MFMA column blocks = 4 groups of h rows).  For a
 //     fixed (kd,kw) the 12 (block, kh) products need only 3*RPB+3 distinct row fragments, so LDS
@@ -460,9 +460,9 @@ __global__ void __launch_bounds__(WG_THREADS) conv3d_mfma_kernel(const bf16_t* _
 // RAGGED: output rows of odd length (the input is then a prepared copy): a row's last voxel is stored on its own.
 // SPLIT: the input chunks are dealt to blockIdx.z; the accumulators leave as they are, [split][tile][channel block][plane][row * 16 + r][lane].
 // POOL: the 2x2x2 max pooling of the result is written beside it.  A wavefront takes half of the rows of two planes, so that a window's eight voxels are
-// in one pair of lanes (12 row fragments a step instead of 10; with whole planes and an exchange through LDS the wavefronts meet between tiles,
-// and nothing hides their stores: 512 us).  us, two calls and one: 32 -> 64 on
-// 64x256x256 544 and 486, on 16x128x128 41.6 and 38.1, 16 -> 32 on 4 x 64^3 54.7 and 46.4, 32 -> 64 on 4 x 32^3 31.3 and 24.8.
+// in one pair of lanes (12 row fragments a step instead of 10; with whole planes and an exchange through LDS the wavefronts meet between tiles: 512 us).
+// The form of two blocks a workgroup keeps 13 registers of its epilogue's addresses and tests in scratch, and waits for its stores where it reads them back.  us,
+// two calls and one: 32 -> 64 on 64x256x256 544 and 486, on 16x128x128 41.6 and 38.1, 16 -> 32 on 4 x 64^3 54.7 and 46.4, 32 -> 64 on 4 x 32^3 31.3 and 24.8.
 template <int CB, int WCB, int RSP = 1, bool RAGGED = false, bool SPLIT = false, bool POOL = false>
 __global__ void __launch_bounds__(256 * WCB * RSP) conv3d_mfma_wide_kernel(const bf16_t* __restrict__ in, const uint4* __restrict__ wp,
                                                                      const float* __restrict__ bias, bf16_t* __restrict__ out, MfmaArgs a) {

@@ -10,7 +10,7 @@
 // price is that 27 of the 216 (parity, tap) products per input channel are non-zero.  This is the route of
 // fp32 tensors, of bf16 samples beyond 32-bit offsets and of large bf16 layers with few input channels (s2_direct); other bf16
 // tensors go to conv_s2_mfma.hip
-// (64 -> 128 channels on 64^3, three passes: 111 us there, 818 us this way).
+// (64 -> 128 channels on 64^3, three passes: 104 us there, 818 us this way).
 //
 // Small element-wise kernels here: the parity split of x, its inverse for dx, the masked copy of dy into
 // a slab with both halo planes, the filter expansion and the extraction of dw from dW'.

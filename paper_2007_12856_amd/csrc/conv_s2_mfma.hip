@@ -5,7 +5,7 @@
 // of them and moves both tensors through memory three times; these kernels execute the 27.
 //
 // 64 -> 128 channels on 64^3 (14.5 GFlop and 42 MB a pass: 6 us of matrix cores, 6 us of memory), all three passes of a masked
-// layer: 818 us by the rewriting, 102 us here (kernels 29 forward, 30 backward-data, 33 + 10 backward-filter, 2 x 4 packing).
+// layer: 818 us by the rewriting, 104 us here (profiled, a few per cent slower: 29 forward, 30 backward-data, 34 + 10 backward-filter, 4 + 3 packing).
 // At that size what bounds them is the serial chain of a workgroup (fetch a tile, transpose it into LDS, multiply): there are
 // one to two workgroups per CU, and every one lives for two to eight stages.
 #include <algorithm>
@@ -55,6 +55,7 @@ __device__ __forceinline__ int xcd_tile(int i, int n) {
 // Weight fragments come from L2 in packed order, two (kd,kw) steps ahead, also into the next stage, whose rows are requested behind the last fragments of
 // this one, three steps before they are needed.  us, one step ahead (and loads that the compiler had moved next to their use) and this:
 // 64->128 on 64^3 31.6 and 30.2, 128->256 on 32^3 50 and 42, 256->256 on 16x32x32 88 and 71, 64->64 on 4 x 16x32x32 23.8 and 18.9, 48->40 on 16x40x72 23.4 and 18.4.
+// The form of more than 64 output channels in aligned rows fills all 512 registers with it and keeps nine in scratch.
 constexpr int SF_PITCH = 66, SF_ROWS = 9, SF_CIG = 3 * SF_ROWS * SF_PITCH, SF_UNITS = 4 * SF_CIG;   // row: 33 odd columns (from 2 w0 - 1), 32 even ones
 constexpr size_t SF_LDS = (size_t)SF_UNITS * 16;
 
