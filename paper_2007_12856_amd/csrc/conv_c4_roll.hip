@@ -387,7 +387,7 @@ bool c4_roll_supported(const h3d_tensor* in, const h3d_tensor* z) {
   if (in->dtype != H3D_BF16 || in->c < 1 || in->c > 4 || z->c < 1 || z->c > 16) return false;
   if (z->halo_lo || z->halo_hi || z->w % 8 || z->h < 8) return false;      // (plane-run views are fine: the kernel uses the strides)
   if ((uintptr_t)in->data % 16 || (z->data && (uintptr_t)z->data % 16)) return false;
-  return sample_span(in) < ((int64_t)1 << 30) && (int64_t)z->c * z->d * z->h * z->w < ((int64_t)1 << 30);
+  return sample_span(in) < ((int64_t)1 << 30) && sample_span(z) < ((int64_t)1 << 30);
 }
 
 size_t c4_roll_ws_bytes() { return 12 * 512 * sizeof(bf16_t); }

@@ -977,6 +977,9 @@ static size_t mfma_wp_bytes(const h3d_tensor* in, const h3d_tensor* out) {
   return ((size_t)ncoblk * nchunks * 27 * 512 * sizeof(bf16_t) + 255) & ~(size_t)255;
 }
 
+template <typename T>
+h3d_status conv3d_direct(void* handle, const h3d_tensor* in, const h3d_tensor* mask, const void* w, const float* bias, h3d_tensor* out, bool transpose,
+                         float out_slope, float mask_slope, void* ws, size_t ws_bytes, hipStream_t stream);
 bool conv3d_thin_supported(const h3d_tensor* in, const h3d_tensor* out);
 h3d_status conv3d_thin(void* handle, const h3d_tensor* in, const void* w, const float* bias, h3d_tensor* out, bool transpose,
                        float out_slope, void* ws, hipStream_t stream);
@@ -1317,6 +1320,8 @@ h3d_status conv3d_mfma(void* handle, const h3d_tensor* in, const h3d_tensor* mas
     a.in.plane = (int64_t)in->h * a.in.w; a.in.cstride = a.in.plane * a.in.ds; a.in.nstride = a.in.cstride * in->c;
     a.pairs = out->w % 2 == 0 && (uintptr_t)out->data % 4 == 0 && a.out.cstride % 2 == 0 && a.out.nstride % 2 == 0;
     st = pick_variant<false, true>(handle, dst, nullptr, wq, bias, op, a, out->n, stream);
+  } else if (mask && sample_span(mask) >= ((int64_t)1 << 30)) {      // (the copies above address it in 64 bits)
+    return conv3d_direct<bf16_t>(handle, in, mask, w, bias, out, transpose, out_slope, mask_slope, ws, ws_bytes, stream);
   } else {
     taps_pack(pack, stream);
     if (mask) st = vec ? pick_variant<true, true>(handle, ip, mp, wq, bias, op, a, out->n, stream)

@@ -340,6 +340,57 @@ def test_conv3d_masked_odd_rows_without_room_for_the_copy(shape, form):
     assert torch.equal(*got)
 
 
+def _in_a_tall_tensor(t):
+    """A copy of t, all of whose planes lie in a bf16 tensor whose samples are past 31-bit byte offsets, next to its end (a Slab), and that tensor."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    n, c, d, h, w = t.shape
+    tall = torch.full((n, c, -(-2 ** 30 // (c * h * w)), h, w), 3.0, dtype=torch.bfloat16, device="cuda")
+    p = tall.shape[2] - d - 1
+    tall[:, :, p:p + d] = t
+    return h3d.Slab(tall[:, :, p:p + d]), tall, p
+
+
+def test_conv3d_first_layer_into_a_view_of_a_tall_tensor():
+    """z is a run of planes of such a tensor: not the row-streaming kernel, which stores through 32-bit offsets; nothing around the run is written."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    Ci, Co, D, H, W = 4, 16, 4, 8, 32
+    w, bias = _weights(Ci, Co, "bf16", 101)
+    xo, xg = slab_pair(synth.flat("normal", SEED, 102, (1, Ci, D, H, W)), "bf16")
+    zo = orc.conv3d_fwd(xo, w, bias, act=orc.ACT_LEAKY, alpha=0.01)
+    wd, bd = to_dev(w, "bf16"), to_dev(bias, "f32")
+    h3d.conv3d_fwd(xg, wd, bd, dev_like(zo, "bf16"), h3d.ACT_LEAKY, 0.01)
+    roll = h3d.h3d_last_kernel()
+    z, tall, p = _in_a_tall_tensor(torch.zeros((1, Co, D, H, W), device="cuda"))
+    h3d.conv3d_fwd(xg, wd, bd, z, h3d.ACT_LEAKY, 0.01)
+    assert "roll" in roll and "roll" not in h3d.h3d_last_kernel(), (roll, h3d.h3d_last_kernel())
+    close(from_dev(z.t), zo.a, TOL["bf16"])
+    assert torch.all(tall[:, :, :p] == 3.0) and torch.all(tall[:, :, p + D:] == 3.0)
+
+
+def test_conv3d_masked_by_a_view_of_a_tall_tensor():
+    """The saved output of a masked data gradient is a run of planes of such a tensor: copied where the workspace has room, on the direct kernel where not."""
+    import torch
+    import paper_2007_12856_amd as h3d
+    N, Ci, Co, D, H, W = 1, 16, 24, 5, 9, 33
+    w, _ = _weights(Ci, Co, "bf16", 103)
+    dzo, dzg = slab_pair(synth.flat("normal", SEED, 104, (N, Co, D, H, W)), "bf16")
+    zo, zg = slab_pair(synth.flat("normal", SEED, 105, (N, Co, D, H, W)), "bf16")
+    dxo = orc.conv3d_bwd_data(dzo, zo, w, act=orc.ACT_LEAKY, alpha=0.01)
+    z, _, _ = _in_a_tall_tensor(zg.t)
+    even = [h3d.Slab(torch.empty((N, c, D, H, W + 1), dtype=torch.bfloat16, device="cuda")) for c in (Co, Ci)]
+
+    class Fixed(h3d.Workspace):
+        def get(self, nbytes):
+            return super().get(h3d.h3d_conv3d_workspace_bytes(h3d.OP_FWD, *even))
+
+    for ws, kernel in ((h3d.Workspace(), "conv3d_mfma_wide"), (Fixed(), "conv3d_direct")):
+        dx = h3d.conv3d_bwd_data(dzg, z, to_dev(w, "bf16"), dev_like(dxo, "bf16"), h3d.ACT_LEAKY, 0.01, ws)
+        assert h3d.h3d_last_kernel().startswith(kernel), h3d.h3d_last_kernel()
+        close(from_dev(dx.t), dxo.a, TOL["bf16"])
+
+
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("cin,cout", [(4, 16), (3, 5), (16, 32)])
 def test_conv3d_sharded_matches_oracle_and_unsharded_gpu(dtype, cin, cout):
